@@ -6,14 +6,21 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-// Value held by lane (lane ^ J) of the same wave, J a power of two below 64.
+// Value held by lane (lane ^ J) of the same wave, J a power of two below 64.  No exchange
+// goes through the LDS crossbar (ds_swizzle): a sort of 64 keys by one wave is a chain of
+// 21 of them, and a crossbar round trip costs about ten times a DPP move.
 template <int J>
 __device__ __forceinline__ uint32_t gd_lane_xor(uint32_t v, uint32_t lane) {
     if constexpr (J == 1) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);
     else if constexpr (J == 2) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);
     else if constexpr (J == 8) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, true);
-    else if constexpr (J == 4 || J == 16)
-        return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x1F | (J << 10));
+    else if constexpr (J == 4) {       // mirrored within 8 lanes (i ^ 7), then within 4 (i ^ 3)
+        const int m = __builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, true);
+        return (uint32_t)__builtin_amdgcn_mov_dpp(m, 0x1B, 0xF, 0xF, true);
+    } else if constexpr (J == 16) {
+        auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return (lane & 16) ? r[0] : r[1];
+    }
     else {
         static_assert(J == 32, "gd_lane_xor");
         auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);

@@ -69,10 +69,6 @@ __device__ __forceinline__ uint32_t sort8(uint32_t v, uint32_t lane) {
     return v;
 }
 
-__device__ __forceinline__ float lane_value(uint32_t v, int src) {
-    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)v, src));
-}
-
 __global__ __launch_bounds__(SWEEP_NT) void sweep_kernel(const gd_sweep_args a) {
     const uint32_t lane = threadIdx.x & (WAVE - 1);
     const uint32_t b = blockIdx.x * (SWEEP_NT / WAVE) + threadIdx.x / WAVE;      // uniform over the wave

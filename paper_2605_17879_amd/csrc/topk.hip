@@ -7,18 +7,27 @@
 // scores.
 //
 // One workgroup builds a unique 64-bit key per node (N <= 8192) and writes the k
-// largest in descending order.
+// largest in descending order.  The launch is one chain of dependent steps over 48 KB
+// of input, so the length of the chain is what counts.
 //
-// k <= 64 (the usual request): no full sort.  Every thread keeps its few keys in
-// registers.  The k-th largest of the per-thread maxima is a threshold that at
-// least k keys reach and, the maxima being the likeliest top keys, few more do.
-// The keys that reach it are compacted into LDS and the k largest of them taken.
-// Both "k largest of a list" steps work on 64-key chunks, one key per lane: each
-// wave sorts a chunk with a bitonic network of lane exchanges, then one wave
-// folds the sorted chunks together, keeping the upper 64 of two chunks at a time
-// (max of chunk A's i-th and chunk B's (63-i)-th key is a bitonic sequence that
-// holds the 64 largest of both; six more exchange stages sort it).
+// k <= 64 (the usual request): nothing is sorted.
+//   1. A thread loads 1, 2, 4 or 8 neighbouring nodes (three vector loads at the most)
+//      and keeps their keys in registers.
+//   2. The largest upper half (count and the leading half of the score) of every group
+//      of up to 8 neighbouring threads goes into LDS: 128 to 255 values.  Each wave ranks
+//      a few of them against all (one value per lane, a compare and a count of the
+//      lanes per 64).  The k-th largest is a threshold that at least k keys reach --
+//      it is the k-th largest of a subset -- and, a group's best being the likeliest of
+//      its members, few more do (about 90 of 8 192 keys in random order for k = 64).
+//   3. The keys that reach it are compacted into LDS and ranked in the same way; a
+//      key's rank is its place in the output.  Where very many reach it (equal scores
+//      throughout), they are sorted instead.
+// Measured (launch time, k = 64): 8 192 nodes 12.5 -> 6.1 us, 8 nodes 7.5 -> 2.0 us.
+// Before, the waves sorted their threads' largest keys and one wave folded the sixteen
+// sorted lists one after another; with that fold replaced by a sort of the waves' best
+// eight it was 10.5 us, a sixth of it waiting for sixteen 2- and 4-byte loads per thread.
 //
+// At most 64 nodes: one wave, one sort by lane exchanges.
 // Larger k: all keys are sorted in LDS with a bitonic network.
 #include "gd_internal.h"
 #include "gd_lanes.h"
@@ -28,8 +37,8 @@ namespace {
 constexpr int WAVE = 64;
 constexpr int TOPK_NT = 1024;
 constexpr int TOPK_MAX = 8192;
-constexpr int KPT = TOPK_MAX / TOPK_NT;     // keys per thread
-constexpr int CHUNKS = TOPK_NT / WAVE;      // 64-key chunks that one folding pass takes
+constexpr int GROUPS = 256;                 // room for the groups' best (128 to 255 of them)
+constexpr uint32_t RANKED = 512;            // most keys that are ranked rather than sorted
 
 __device__ __forceinline__ uint32_t key_of(float f) {
     uint32_t b = __float_as_uint(f);
@@ -42,7 +51,7 @@ template <int J>
 __device__ __forceinline__ uint64_t exchange(uint64_t v, uint32_t lane, bool desc) {
     const uint64_t o = gd_lane_xor64<J>(v, lane);
     const bool keep_max = ((lane & J) == 0) == desc;
-    return keep_max ? (v > o ? v : o) : (v < o ? v : o);
+    return (o > v) == keep_max ? o : v;         // (equal keys: either)
 }
 
 // A bitonic sequence (one key per lane) into descending order.
@@ -76,81 +85,27 @@ __device__ __forceinline__ uint64_t sort_desc(uint64_t v, uint32_t lane) {
     return merge_desc(v, lane);
 }
 
-// The 64 largest of `chunks` sorted 64-key chunks in LDS, descending, one per
-// lane of the calling wave.
-__device__ __forceinline__ uint64_t fold_chunks(const uint64_t* lists, uint32_t chunks, uint32_t lane) {
-    uint64_t best = lists[lane];
-    for (uint32_t c = 1; c < chunks; ++c) {
-        const uint64_t other = lists[c * WAVE + (WAVE - 1 - lane)];
-        best = merge_desc(best > other ? best : other, lane);
-    }
-    return best;
+// The middle field of a node's key.
+__device__ __forceinline__ uint32_t mid_of(const gd_topk_args& a, uint32_t bits) {
+    return a.z_last ? key_of(__uint_as_float(bits) + 0.0f)        // -0 ranks as +0
+                    : bits ^ 0x80000000u;                         // sum + 2^31: signed order as unsigned
+}
+__device__ __forceinline__ uint64_t key_from(uint32_t count, uint32_t mid, uint32_t n) {
+    return ((uint64_t)count << 48) | ((uint64_t)mid << 16) | (uint64_t)(0xFFFFu - n);
+}
+__device__ __forceinline__ uint64_t make_key(const gd_topk_args& a, uint32_t n) {
+    if (n >= a.N) return 0;                     // padding sorts last (no node's key is 0)
+    const uint32_t* mid = a.z_last ? reinterpret_cast<const uint32_t*>(a.z_last)
+                                   : reinterpret_cast<const uint32_t*>(a.score_sum);
+    return key_from(a.count[n], mid_of(a, mid[n]), n);
+}
+__device__ __forceinline__ void write_out(const gd_topk_args& a, uint32_t i, uint64_t k) {
+    a.idx[i] = (int32_t)(0xFFFFu - (uint32_t)(k & 0xFFFFu));
+    if (a.key) a.key[i] = k;
 }
 
-__global__ __launch_bounds__(TOPK_NT) void topk_kernel(const gd_topk_args a) {
-    __shared__ uint64_t keys[TOPK_MAX];
-    __shared__ uint64_t threshold;
-    __shared__ uint32_t n_reach;
-    const uint16_t* nc = a.count;
-    const float* nz = a.z_last;
-    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
-    auto make_key = [&](uint32_t n) -> uint64_t {
-        if (n >= a.N) return 0;                     // padding sorts last
-        uint32_t mid;
-        if (nz) mid = key_of(nz[n] + 0.0f);         // -0 ranks as +0
-        else mid = (uint32_t)a.score_sum[n] ^ 0x80000000u;   // sum + 2^31: signed order as unsigned
-        return ((uint64_t)nc[n] << 48) | ((uint64_t)mid << 16) | (uint64_t)(0xFFFFu - n);
-    };
-    auto write_out = [&](uint32_t i, uint64_t k) {
-        a.idx[i] = (int32_t)(0xFFFFu - (uint32_t)(k & 0xFFFFu));
-        if (a.key) a.key[i] = k;
-    };
-
-    if (a.k <= (uint32_t)WAVE) {
-        uint64_t mine[KPT], top = 0;
-#pragma unroll
-        for (int q = 0; q < KPT; ++q) {
-            mine[q] = make_key(q * TOPK_NT + tid);
-            top = mine[q] > top ? mine[q] : top;
-        }
-        if (tid == 0) n_reach = 0;
-        keys[tid] = sort_desc(top, lane);           // chunk w of the per-thread maxima
-        __syncthreads();
-        if (w == 0) {
-            const uint64_t best = fold_chunks(keys, CHUNKS, lane);
-            if (lane == a.k - 1) threshold = best;  // at least k keys are >= this one
-        }
-        __syncthreads();
-        const uint64_t thr = threshold;
-#pragma unroll
-        for (int q = 0; q < KPT; ++q) {
-            if (mine[q] >= thr && mine[q] != 0) {
-                const uint32_t pos = atomicAdd(&n_reach, 1u);
-                if (pos < (uint32_t)TOPK_NT) keys[pos] = mine[q];
-            }
-        }
-        __syncthreads();
-        // k <= m <= KPT * k: only the k threads with the largest maxima hold such keys
-        const uint32_t m = min(n_reach, (uint32_t)TOPK_NT);
-        const uint32_t chunks = (m + WAVE - 1) / WAVE;
-        if (w < chunks) {
-            const uint32_t i = w * WAVE + lane;
-            const uint64_t sorted = sort_desc(i < m ? keys[i] : 0, lane);
-            keys[i] = sorted;                       // a wave rewrites only its own chunk
-        }
-        __syncthreads();
-        if (w == 0) {
-            const uint64_t best = fold_chunks(keys, chunks, lane);
-            if (lane < a.k) write_out(lane, best);
-        }
-        return;
-    }
-
-    uint32_t P = 64;
-    while (P < a.N) P <<= 1;                       // power of two >= N, <= TOPK_MAX
-    for (uint32_t n = tid; n < P; n += TOPK_NT) keys[n] = make_key(n);
-    __syncthreads();
-    // bitonic sort, descending
+// keys[0 .. P), P a power of two, into descending order (all threads of the workgroup).
+__device__ __forceinline__ void sort_in_lds(uint64_t* keys, uint32_t P, uint32_t tid) {
     for (uint32_t k = 2; k <= P; k <<= 1) {
         for (uint32_t j = k >> 1; j > 0; j >>= 1) {
             for (uint32_t i = tid; i < P / 2; i += TOPK_NT) {
@@ -163,7 +118,132 @@ __global__ __launch_bounds__(TOPK_NT) void topk_kernel(const gd_topk_args a) {
             __syncthreads();
         }
     }
-    for (uint32_t i = tid; i < a.k; i += TOPK_NT) write_out(i, keys[i]);
+}
+
+// At most 64 nodes.
+__global__ __launch_bounds__(WAVE) void topk_wave_kernel(const gd_topk_args a) {
+    const uint32_t lane = threadIdx.x;
+    const uint64_t best = sort_desc(make_key(a, lane), lane);
+    if (lane < a.k) write_out(a, lane, best);
+}
+
+// k <= 64; KPT keys per thread: KPT * TOPK_NT >= N.
+template <int KPT>
+__global__ __launch_bounds__(TOPK_NT) void topk_short_kernel(const gd_topk_args a) {
+    constexpr int ROOM = KPT * TOPK_NT;             // every key may reach the threshold
+    __shared__ uint64_t keys[ROOM];
+    __shared__ uint32_t best_of[GROUPS];
+    __shared__ uint32_t threshold, n_reach;
+    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    constexpr uint32_t WAVES = TOPK_NT / WAVE;
+    // The threads' nodes are neighbours, so that their counts and scores come in one to three
+    // loads (both arrays start at multiples of 256 bytes and their room is rounded up to that:
+    // the last thread may read past node N - 1, and drops what it read there).
+    uint64_t mine[KPT];
+    uint32_t top = 0;
+    const uint32_t n0 = tid * KPT;
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) mine[q] = 0;
+    if (n0 < a.N) {
+        struct alignas(2 * KPT) Counts { uint16_t v[KPT]; };
+        struct alignas(4 * KPT > 16 ? 16 : 4 * KPT) Mids { uint32_t v[KPT]; };
+        const Counts c = *reinterpret_cast<const Counts*>(a.count + n0);
+        const Mids m = a.z_last ? *reinterpret_cast<const Mids*>(a.z_last + n0)
+                                : *reinterpret_cast<const Mids*>(a.score_sum + n0);
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) {
+            if (n0 + q < a.N) mine[q] = key_from(c.v[q], mid_of(a, m.v[q]), n0 + q);
+            top = max(top, (uint32_t)(mine[q] >> 32));
+        }
+    }
+    // groups of g threads, g the largest of 1, 2, 4, 8 that leaves 128 groups with nodes
+    const uint32_t used = (a.N + KPT - 1) / KPT;
+    const uint32_t lg = used >= 1024 ? 3u : used >= 512 ? 2u : used >= 256 ? 1u : 0u;
+    if (lg > 0) top = max(top, gd_lane_xor<1>(top, lane));
+    if (lg > 1) top = max(top, gd_lane_xor<2>(top, lane));
+    if (lg > 2) top = max(top, gd_lane_xor<4>(top, lane));
+    const uint32_t groups = min((used + (1u << lg) - 1) >> lg, (uint32_t)GROUPS);
+    if ((tid & ((1u << lg) - 1)) == 0 && (tid >> lg) < (uint32_t)GROUPS) best_of[tid >> lg] = top;
+    if (tid == 0) { n_reach = 0; threshold = 0; }
+    __syncthreads();
+    if (groups > a.k) {                             // (else every key is ranked)
+        // The largest value that at least k values reach.  Lane j holds values j, 64 + j, ...,
+        // so a value comes out of a register by its lane number: no LDS round trip in the loop.
+        uint32_t v[GROUPS / WAVE], best = 0;
+#pragma unroll
+        for (int c = 0; c < GROUPS / WAVE; ++c) v[c] = c * WAVE + lane < groups ? best_of[c * WAVE + lane] : 0u;
+#pragma unroll
+        for (int c = 0; c < GROUPS / WAVE; ++c) {
+            if ((uint32_t)c * WAVE >= groups) break;
+#pragma unroll
+            for (uint32_t q = 0; q < WAVE / WAVES; ++q) {
+                const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)v[c], (int)(q * WAVES + w));
+                uint32_t reach = 0;
+#pragma unroll
+                for (int d = 0; d < GROUPS / WAVE; ++d) reach += (uint32_t)__popcll(__ballot(v[d] >= x));
+                if (reach >= a.k) best = max(best, x);      // (padding: x = 0 never raises it)
+            }
+        }
+        if (lane == 0) atomicMax(&threshold, best);
+        __syncthreads();
+    }
+    const uint32_t thr = threshold;
+    uint32_t hits = 0;
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) hits += (uint32_t)(mine[q] >> 32) >= thr && mine[q] != 0 ? 1u : 0u;
+    if (hits) {
+        uint32_t pos = atomicAdd(&n_reach, hits);
+#pragma unroll
+        for (int q = 0; q < KPT; ++q)
+            if ((uint32_t)(mine[q] >> 32) >= thr && mine[q] != 0) keys[pos++] = mine[q];
+    }
+    __syncthreads();
+    const uint32_t m = n_reach;                     // at least min(k, N) = k of them
+    if (m <= 2 * WAVE) {                            // the usual case: two keys per lane
+        const uint64_t k0 = lane < m ? keys[lane] : 0, k1 = WAVE + lane < m ? keys[WAVE + lane] : 0;
+#pragma unroll
+        for (uint32_t q = 0; q < 2 * WAVE / WAVES; ++q) {
+            const uint32_t i = q * WAVES + w;
+            if (i >= m) break;
+            const uint64_t src = q < WAVE / WAVES ? k0 : k1;
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)src, (int)(i & (WAVE - 1)));
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(src >> 32), (int)(i & (WAVE - 1)));
+            const uint64_t x = ((uint64_t)hi << 32) | lo;
+            const uint32_t r = (uint32_t)(__popcll(__ballot(k0 > x)) + __popcll(__ballot(k1 > x)));
+            if (r < a.k && lane == 0) write_out(a, r, x);
+        }
+        return;
+    }
+    if (m <= RANKED) {
+        for (uint32_t i = w; i < m; i += WAVES) {
+            const uint64_t x = keys[i];
+            uint32_t r = 0;
+            for (uint32_t j0 = 0; j0 < m; j0 += WAVE) {
+                const uint32_t j = j0 + lane;
+                r += (uint32_t)__popcll(__ballot(j < m && keys[j] > x));
+            }
+            if (r < a.k && lane == 0) write_out(a, r, x);
+        }
+        return;
+    }
+    uint32_t P = 2 * RANKED;
+    while (P < m) P <<= 1;                          // <= ROOM: both are powers of two and m <= N <= ROOM
+    for (uint32_t i = m + tid; i < P; i += TOPK_NT) keys[i] = 0;
+    __syncthreads();
+    sort_in_lds(keys, P, tid);
+    if (tid < a.k) write_out(a, tid, keys[tid]);
+}
+
+// Any k: everything sorted.
+__global__ __launch_bounds__(TOPK_NT) void topk_sort_kernel(const gd_topk_args a) {
+    __shared__ uint64_t keys[TOPK_MAX];
+    const uint32_t tid = threadIdx.x;
+    uint32_t P = 64;
+    while (P < a.N) P <<= 1;                       // power of two >= N, <= TOPK_MAX
+    for (uint32_t n = tid; n < P; n += TOPK_NT) keys[n] = make_key(a, n);
+    __syncthreads();
+    sort_in_lds(keys, P, tid);
+    for (uint32_t i = tid; i < a.k; i += TOPK_NT) write_out(a, i, keys[i]);
 }
 
 }  // namespace
@@ -171,6 +251,12 @@ __global__ __launch_bounds__(TOPK_NT) void topk_kernel(const gd_topk_args a) {
 hipError_t gd_launch_topk(const gd_topk_args& a, hipStream_t s) {
     if (a.k == 0) return hipSuccess;
     if (a.N > TOPK_MAX || a.k > a.N) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(topk_kernel, dim3(1), dim3(TOPK_NT), 0, s, a);
+    // (one wave's sort serves up to 64 nodes whatever k is: k <= N)
+    if (a.N <= (uint32_t)WAVE) hipLaunchKernelGGL(topk_wave_kernel, dim3(1), dim3(WAVE), 0, s, a);
+    else if (a.k > (uint32_t)WAVE) hipLaunchKernelGGL(topk_sort_kernel, dim3(1), dim3(TOPK_NT), 0, s, a);
+    else if (a.N <= 1024) hipLaunchKernelGGL(topk_short_kernel<1>, dim3(1), dim3(TOPK_NT), 0, s, a);
+    else if (a.N <= 2048) hipLaunchKernelGGL(topk_short_kernel<2>, dim3(1), dim3(TOPK_NT), 0, s, a);
+    else if (a.N <= 4096) hipLaunchKernelGGL(topk_short_kernel<4>, dim3(1), dim3(TOPK_NT), 0, s, a);
+    else hipLaunchKernelGGL(topk_short_kernel<8>, dim3(1), dim3(TOPK_NT), 0, s, a);
     return hipGetLastError();
 }
