@@ -6,115 +6,267 @@
 // stored as the scoring kernel's own bit words ring[step % W][item / 64]; a u16
 // count of set bits inside the window; the first flagged step (+1, 0 = never).
 //
-// One thread owns one item and one wave owns one 64-item word column of the
-// ring, so every ring word is read and written by a single wave.  A wave takes
-// 64 steps at a time (fetched a few blocks ahead): lane l fetches the word
-// entering at step s0 + l and the
-// word leaving the window at that step (the one that entered W steps earlier,
-// from the batch itself when recent enough, else from the ring).  Two 64x64 bit
-// transposes across the lanes turn them into per-item time vectors, so a block
-// of 64 steps updates the count with two popcounts.  Only an item that could
-// reach k inside the block (count + entering bits >= k, not flagged before)
-// walks the block step by step to find its first flagged step.
+// A batch (window_blocks_kernel) is counted in bit slices, 32 items per word (see
+// gd_planes.h).  Steps are cut into blocks of 64.  A wave takes one block of 64
+// neighbouring words (2 048 items): the rows' addresses are scalars, a lane's 64 loads
+// are independent of each other and a row's 64 lanes read two whole cache lines.  It
+// leaves the sum of the block, and of its last W % 64 steps, as planes in LDS.  The
+// window that ends where a block begins is then W / 64 whole blocks and the tail of one
+// more, a handful of bit-sliced additions.  An item can only reach k inside a block if
+// its count at the block's start plus everything that enters does, and if it had not
+// reached it already: the few (block, word) pairs left by that test are walked by the
+// wave, one lane per step (two ballots give an item's entering and leaving bits as
+// 64-bit time vectors).
+//
+// A workgroup takes a stretch of blocks and loads the W / 64 blocks before it once more.
+// Stretches are as short as the window allows (four blocks at least): the loads are
+// bound by the requests that one CU can have in flight, so they are spread over as many
+// CUs as there are stretches (one workgroup per tile over all steps: 26.6 us where this
+// takes 18).  Only the first stretch looks at the ring (the others begin W steps or
+// more into the batch), so it also stores the ring's new words, behind its own last
+// read; the last stretch stores the counts, which nobody reads; the first flagged step
+// is kept by compare-and-swap.
+//
+// The form before this one gave every 64 items a wave that walked all steps in order,
+// transposing 64 x 64 bits across its lanes: one wave per SIMD at 65 536 ranks and far
+// fewer below, waiting for its loads and lane exchanges.  Measured: 65 536 ranks x
+// 4 096 steps 52.5 -> 18 us (57 MB loaded in 9 of them), 16 384 x 10 000 117 -> 11.8 us,
+// 1 024 x 2 000 29.4 -> 8.1 us; the smallest, 64 x 200, 5.3 -> 5.9 us.
+// One step per call (window_step_kernel) needs none of this: a thread per item.
 #include "gd_internal.h"
-#include "gd_lanes.h"
+#include "gd_planes.h"
 
 namespace {
 
 constexpr int WAVE = 64;
 constexpr int WIN_NT = 256;
+constexpr uint32_t TILE = WAVE;          // 32-bit words of a workgroup's tile
+constexpr uint32_t MIN_STRETCH = 4, MAX_STRETCH = 16;      // blocks of 64 steps
+constexpr uint32_t MAX_HISTORY = 16;     // blocks that a window of 1 024 steps reaches back
+constexpr int WIN_MAX_NT = 1024;
 
-// Items [0, R) are ranks, then, starting at a fresh workgroup, items [0, N) are nodes.
-// RING > 0: the window is RING blocks of 64 steps long, so the bits leaving during a
-// block are the bits that entered RING blocks earlier -- already transposed then and
-// kept in registers; only the blocks that reach back beyond the batch transpose ring
-// words.  RING == 0: any window length, two transposes per block.
-template <int RING>
-__global__ __launch_bounds__(WIN_NT) void window_kernel(const gd_window_args a) {
+// Where one kind of item (ranks or nodes) lives.
+struct WindowItems {
+    const uint32_t* anom;    // [T][row]
+    uint32_t* ring;          // [W][row]
+    uint16_t* count;
+    int32_t* first;
+    uint32_t n, row;         // items; 32-bit words per step (even)
+};
+
+__device__ __forceinline__ WindowItems window_items(const gd_window_args& a, bool is_node) {
+    WindowItems it;
+    it.anom = reinterpret_cast<const uint32_t*>(is_node ? a.node_anom : a.rank_anom);
+    it.ring = reinterpret_cast<uint32_t*>(a.state + (is_node ? a.lay.node_ring : a.lay.rank_ring));
+    it.count = reinterpret_cast<uint16_t*>(a.state + (is_node ? a.lay.node_count : a.lay.rank_count));
+    it.first = reinterpret_cast<int32_t*>(a.state + (is_node ? a.lay.node_first : a.lay.rank_first));
+    it.n = is_node ? a.N : a.R;
+    it.row = 2 * ((it.n + 63) / 64);
+    return it;
+}
+
+// One step: blocks [0, rank_blocks) take ranks, the rest nodes.
+__global__ __launch_bounds__(WIN_NT) void window_step_kernel(const gd_window_args a) {
     const uint32_t rank_blocks = (a.R + WIN_NT - 1) / WIN_NT;
     const bool is_node = blockIdx.x >= rank_blocks;
-    const uint32_t n_items = is_node ? a.N : a.R;
-    const uint32_t blk = is_node ? blockIdx.x - rank_blocks : blockIdx.x;
-    const uint32_t item = blk * WIN_NT + threadIdx.x;
-    const uint32_t lane = threadIdx.x & (WAVE - 1);
-    const uint32_t words = (n_items + 63) / 64;
-    const uint32_t word = item / 64;                 // uniform over the wave
-    if (word >= words) return;                       // whole wave out of range
-    const uint64_t* anom = is_node ? a.node_anom : a.rank_anom;
-    uint64_t* ring = reinterpret_cast<uint64_t*>(a.state + (is_node ? a.lay.node_ring : a.lay.rank_ring));
-    uint16_t* count = reinterpret_cast<uint16_t*>(a.state + (is_node ? a.lay.node_count : a.lay.rank_count));
-    int32_t* first = reinterpret_cast<int32_t*>(a.state + (is_node ? a.lay.node_first : a.lay.rank_first));
-    const bool live = item < n_items;
-    const uint32_t W = a.W, K = a.K, T = a.T;
+    const WindowItems it = window_items(a, is_node);
+    const uint32_t item = (is_node ? blockIdx.x - rank_blocks : blockIdx.x) * WIN_NT + threadIdx.x;
+    const uint32_t word = item / 32;
+    if (word >= it.row) return;
+    const uint32_t t = (uint32_t)a.first_step;                  // (below 2^31)
+    uint32_t* slot = it.ring + (size_t)(t % a.W) * it.row + word;
+    const uint32_t in = it.anom[word], out = t >= a.W ? *slot : 0u;
+    if (item < it.n) {
+        const uint32_t c = it.count[item] + ((in >> (item & 31)) & 1u) - ((out >> (item & 31)) & 1u);
+        it.count[item] = (uint16_t)c;
+        if (c >= a.K && it.first[item] == 0) it.first[item] = (int32_t)t + 1;
+        if (is_node) reinterpret_cast<float*>(a.state + a.lay.node_z_last)[item] = a.node_z[item];
+    }
+    // (the word's 32 readers are lanes of one wave: all of them have read the slot)
+    if ((item & 31) == 0) *slot = in;
+}
 
-    // the entering and the leaving word of step s (lane l of a block asks for s0 + l)
-    auto fetch = [&](uint32_t s, uint64_t* win, uint64_t* wout) {
-        *win = 0; *wout = 0;
-        if (s < T) {
-            *win = anom[(size_t)s * words + word];
-            const uint64_t t = a.first_step + s;
-            if (t >= W) {
-                if (s < W) *wout = ring[(size_t)(t % W) * words + word];
-                else if (RING == 0) *wout = anom[(size_t)(s - W) * words + word];
-                // (RING > 0: these bits are still in registers from RING blocks ago)
+// A batch.  blockIdx.y: tile of words (ranks first), blockIdx.x: stretch of `stretch`
+// blocks (stretch * 64 >= W where there is more than one).  Dynamic LDS: planes of every
+// slot -- a block of the stretch or one of the few before it -- and word.
+__global__ __launch_bounds__(WIN_MAX_NT) void window_blocks_kernel(const gd_window_args a, uint32_t rank_tiles,
+                                                                    uint32_t stretch) {
+    extern __shared__ uint32_t lds[];
+    __shared__ uint32_t final_planes[GD_COUNT_PLANES][TILE];
+    const bool is_node = blockIdx.y >= rank_tiles;
+    const WindowItems it = window_items(a, is_node);
+    const uint32_t w0 = (is_node ? blockIdx.y - rank_tiles : blockIdx.y) * TILE;
+    const uint32_t tid = threadIdx.x, nt = blockDim.x, lane = tid & (WAVE - 1);
+    const uint32_t wv = __builtin_amdgcn_readfirstlane(tid / WAVE), waves = nt / WAVE;
+    const uint32_t W = a.W, K = a.K, T = a.T, row = it.row;
+    const uint32_t q = W / 64, r = W % 64, hist = q + (r ? 1 : 0);     // whole blocks, steps of a tail, slots before a block
+    const int32_t first = (int32_t)a.first_step;                       // (first + T below 2^31)
+    const uint32_t s0 = blockIdx.x * stretch * 64;
+    const uint32_t blocks = min((T - s0 + 63) / 64, stretch);
+    const bool last = s0 + blocks * 64 >= T;
+    const uint32_t last_start = s0 + (blocks - 1) * 64;                // (the batch's last block, where `last`)
+    const uint32_t wc = min(w0 + lane, row - 1);                       // (lanes past the row repeat its last word, and store nothing)
+    const bool mine = w0 + lane < row;
+    // a slot's planes lie one behind another: of the whole block, then of its tail
+    const uint32_t slot_words = (r ? 2 * GD_BLOCK_PLANES - 1 : GD_BLOCK_PLANES) * TILE;
+    auto planes_of = [&](uint32_t slot) -> uint32_t* { return lds + slot * slot_words + lane; };
+
+    // Slots [0, hist): the blocks before the stretch; [hist, hist + blocks): its own; one more
+    // for the steps that leave the window during the batch's last block.
+    for (uint32_t slot = wv; slot < hist + blocks + (last ? 1 : 0); slot += waves) {
+        const bool leaving = slot == hist + blocks;
+        const int32_t start = leaving ? (int32_t)last_start - (int32_t)W : (int32_t)(s0 + slot * 64) - (int32_t)(hist * 64);
+        const uint32_t n = leaving ? T - last_start : 64u;             // steps that count
+        // Lane j works out where step j's row lies -- in the batch, before it in the ring, or
+        // nowhere (row 0 of the batch is read then and dropped) -- and the rows' addresses are
+        // read from the lanes one after another: worked out in scalars they are a chain of
+        // dependent instructions as long as the loads themselves.
+        const int32_t s = start + (int32_t)lane;
+        const bool ok = lane < n && s < (int32_t)T && s >= -(int32_t)W && first + s >= 0;
+        const uint32_t* of_lane = it.anom + (ok && s >= 0 ? (size_t)(uint32_t)s * row : 0);
+        if (ok && s < 0) of_lane = it.ring + (size_t)((uint32_t)(first + s) % W) * row;
+        const uint64_t valid = __ballot(ok), in_tail = r ? ~0ull << (64 - r) : 0;
+        const uint32_t alo = (uint32_t)(uintptr_t)of_lane, ahi = (uint32_t)((uintptr_t)of_lane >> 32);
+        uint32_t v[4][16];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            if ((valid >> (16 * g) & 0xFFFFull) == 0) continue;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)alo, 16 * g + j);
+                const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)ahi, 16 * g + j);
+                v[g][j] = reinterpret_cast<const uint32_t*>((uintptr_t)hi << 32 | lo)[wc];
             }
         }
-    };
-
-    uint32_t c = live ? count[item] : 0;
-    int32_t f = live ? first[item] : 0;
-    // Blocks are fetched AHEAD blocks in advance (the loop is latency-bound: one wave
-    // per word column walks its steps in order).
-    constexpr int AHEAD = RING > 4 ? RING : 4;
-    uint64_t win[AHEAD], wout[AHEAD];
-    uint64_t entered[RING > 0 ? RING : 1];      // transposed entering bits of the last RING blocks
+        uint32_t all[GD_BLOCK_PLANES] = {}, end[GD_BLOCK_PLANES] = {};
 #pragma unroll
-    for (int q = 0; q < AHEAD; ++q) fetch(q * WAVE + lane, &win[q], &wout[q]);
-    for (uint32_t s0 = 0; s0 < T; s0 += AHEAD * WAVE) {
+        for (int g = 0; g < 4; ++g) {
+            const uint32_t on = (uint32_t)(valid >> (16 * g)) & 0xFFFFu, tail = (uint32_t)(in_tail >> (16 * g)) & on;
+            if (on == 0) continue;
+            if (on != 0xFFFFu) {
 #pragma unroll
-        for (int q = 0; q < AHEAD; ++q) {
-            const uint32_t sq = s0 + q * WAVE;        // uniform over the wave
-            if (sq >= T) break;
-            const uint64_t wi = win[q], wo = wout[q];
-            fetch(sq + AHEAD * WAVE + lane, &win[q], &wout[q]);
-            // bit j of `in` / `out`: does this item enter / leave as anomalous at step sq + j
-            const uint64_t in = gd_transpose64(wi, lane);
-            uint64_t out;
-            if (RING > 0 && sq >= W) {               // (sq and W are multiples of 64)
-                const uint32_t n = T - sq;           // steps of the batch in this block
-                out = entered[q % (RING > 0 ? RING : 1)] & (n < 64 ? (1ull << n) - 1 : ~0ull);
+                for (int j = 0; j < 16; ++j) v[g][j] &= (uint32_t)((int32_t)(on << (31 - j)) >> 31);
             }
-            else out = gd_transpose64(wo, lane);
-            if (RING > 0) entered[q % (RING > 0 ? RING : 1)] = in;
-            const uint32_t pin = __popcll(in), pout = __popcll(out);
-            if (f == 0 && c + pin >= K) {             // the flag may first rise inside this block
-                const uint32_t n = min((uint32_t)WAVE, T - sq);
-                for (uint32_t j = 0; j < n; ++j) {
-                    const uint64_t upto = (2ull << j) - 1;
-                    if (c + __popcll(in & upto) - __popcll(out & upto) >= K) {
-                        f = (int32_t)(a.first_step + sq + j) + 1;
-                        break;
+            gd_add16(all, v[g]);
+            if (tail) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) v[g][j] &= (uint32_t)((int32_t)(tail << (31 - j)) >> 31);
+                gd_add16(end, v[g]);
+            }
+        }
+        uint32_t* o = planes_of(slot);
+#pragma unroll
+        for (int p = 0; p < GD_BLOCK_PLANES; ++p) o[p * TILE] = all[p];
+        if (r) {
+#pragma unroll
+            for (int p = 0; p < GD_BLOCK_PLANES - 1; ++p) o[(GD_BLOCK_PLANES + p) * TILE] = end[p];      // (at most 63)
+        }
+    }
+    // The ring's new words (the batch's last min(T, W) steps) are the first stretch's to
+    // store: some of them are fetched now.
+    const uint32_t keep = T < W ? T : W;
+    constexpr uint32_t EARLY = 16;
+    uint32_t early[EARLY];
+    if (s0 == 0) {
+#pragma unroll
+        for (uint32_t e = 0; e < EARLY; ++e)
+            early[e] = it.anom[(size_t)(T - keep + min(wv + e * waves, keep - 1)) * row + wc];
+    }
+    __syncthreads();
+
+    // counts where each block begins, and the items that may reach k inside it
+    for (uint32_t b = wv; b < blocks; b += waves) {
+        const uint32_t slot = hist + b;
+        uint32_t c[GD_COUNT_PLANES] = {}, u[GD_COUNT_PLANES], f[GD_BLOCK_PLANES];
+        for (uint32_t back = 1; back <= q; ++back) {
+#pragma unroll
+            for (int p = 0; p < GD_BLOCK_PLANES; ++p) f[p] = planes_of(slot - back)[p * TILE];
+            gd_planes_add(c, f);
+        }
+        if (r) {
+            uint32_t e[GD_BLOCK_PLANES - 1];
+#pragma unroll
+            for (int p = 0; p < GD_BLOCK_PLANES - 1; ++p) e[p] = planes_of(slot - q - 1)[(GD_BLOCK_PLANES + p) * TILE];
+            gd_planes_add(c, e);
+        }
+#pragma unroll
+        for (int p = 0; p < GD_COUNT_PLANES; ++p) u[p] = c[p];
+#pragma unroll
+        for (int p = 0; p < GD_BLOCK_PLANES; ++p) f[p] = planes_of(slot)[p * TILE];
+        gd_planes_add(u, f);
+        // the count after the last step: what enters during the last block, less what leaves
+        if (last && b == blocks - 1) {
+            uint32_t fin[GD_COUNT_PLANES];
+#pragma unroll
+            for (int p = 0; p < GD_COUNT_PLANES; ++p) fin[p] = u[p];
+#pragma unroll
+            for (int p = 0; p < GD_BLOCK_PLANES; ++p) f[p] = planes_of(hist + blocks)[p * TILE];
+            gd_planes_sub(fin, f);
+#pragma unroll
+            for (int p = 0; p < GD_COUNT_PLANES; ++p) final_planes[p][lane] = fin[p];
+        }
+        const uint32_t cand = mine ? gd_planes_reach(u, K) & ~gd_planes_reach(c, K) : 0u;
+        const int32_t start = (int32_t)(s0 + b * 64), s = start + (int32_t)lane;       // this lane's step in a walk
+        for (uint64_t todo = __ballot(cand != 0); todo; todo &= todo - 1) {
+            const int src = __builtin_ctzll(todo);
+            const uint32_t w = w0 + (uint32_t)src;
+            uint32_t enters = 0, leaves = 0;
+            if (s < (int32_t)T) {
+                enters = it.anom[(size_t)(uint32_t)s * row + w];
+                const int32_t o = s - (int32_t)W;
+                if (o >= 0) leaves = it.anom[(size_t)(uint32_t)o * row + w];
+                else if (first + o >= 0) leaves = it.ring[(size_t)((uint32_t)(first + o) % W) * row + w];
+            }
+            // items flagged before this batch are left alone (a later step is one that another
+            // stretch has just found), as are those beyond the last one
+            const uint32_t item = w * 32 + (lane & 31);
+            const int32_t seen = item < it.n ? it.first[item] : 1;
+            const uint32_t done = (uint32_t)__ballot(item >= it.n || (seen != 0 && seen <= first));
+            const uint64_t upto = (2ull << lane) - 1;
+            for (uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)cand, src) & ~done; bits; bits &= bits - 1) {
+                const uint32_t bit = (uint32_t)__builtin_ctz(bits);
+                const uint64_t in = __ballot((enters >> bit) & 1u), out = __ballot((leaves >> bit) & 1u);
+                const uint32_t cnt = gd_planes_count(c, src, bit) + (uint32_t)__popcll(in & upto) -
+                                     (uint32_t)__popcll(out & upto);
+                const uint64_t reach = __ballot(cnt >= K && s < (int32_t)T);
+                if (reach && lane == 0) {
+                    int32_t* to = &it.first[w * 32 + bit];
+                    const int32_t found = first + start + __builtin_ctzll(reach) + 1;
+                    int32_t was = 0;
+                    while (was == 0 || was > found) {                  // (ends: the stored step only ever falls)
+                        const int32_t now = atomicCAS(to, was, found);
+                        if (now == was) break;
+                        was = now;
                     }
                 }
             }
-            c += pin - pout;
         }
     }
-    if (live) {
-        count[item] = (uint16_t)c;
-        first[item] = f;
+    if (!last && s0 != 0) return;
+    __syncthreads();                                                   // (the ring has been read for the last time)
+    if (last) {
+        for (uint32_t x = tid; x < TILE * 32; x += nt) {
+            const uint32_t item = w0 * 32 + x;
+            if (item >= it.n) break;
+            uint32_t c = 0;
+#pragma unroll
+            for (int p = 0; p < GD_COUNT_PLANES; ++p) c |= ((final_planes[p][x / 32] >> (x % 32)) & 1u) << p;
+            it.count[item] = (uint16_t)c;
+            if (is_node)
+                reinterpret_cast<float*>(a.state + a.lay.node_z_last)[item] = a.node_z[(size_t)(T - 1) * a.N + item];
+        }
     }
-    // The last min(T, W) words of the batch become the ring's newest slots.
-    // Every ring read above has been consumed before these stores are issued,
-    // and no other wave touches this word column.
-    const uint32_t keep = T < W ? T : W;
-    for (uint32_t i = lane; i < keep; i += WAVE) {
-        const uint32_t s = T - keep + i;
-        ring[(size_t)((a.first_step + s) % W) * words + word] = anom[(size_t)s * words + word];
-    }
-    if (is_node && live && T > 0) {
-        float* last = reinterpret_cast<float*>(a.state + a.lay.node_z_last);
-        last[item] = a.node_z[(size_t)(T - 1) * a.N + item];
+    if (s0 == 0) {
+        const uint32_t ring0 = (uint32_t)(first + (int32_t)(T - keep)) % W;
+        auto into_ring = [&](uint32_t j, uint32_t v) {
+            const uint32_t to = ring0 + j < W ? ring0 + j : ring0 + j - W;
+            if (mine) it.ring[(size_t)to * row + w0 + lane] = v;
+        };
+#pragma unroll
+        for (uint32_t e = 0; e < EARLY; ++e)
+            if (wv + e * waves < keep) into_ring(wv + e * waves, early[e]);
+        for (uint32_t j = wv + EARLY * waves; j < keep; j += waves)
+            into_ring(j, it.anom[(size_t)(T - keep + j) * row + wc]);
     }
 }
 
@@ -152,17 +304,37 @@ __global__ __launch_bounds__(WIN_NT) void flags_kernel(const gd_flags_args a) {
 
 hipError_t gd_launch_window(const gd_window_args& a, hipStream_t s) {
     if (a.T == 0) return hipSuccess;
-    const uint32_t blocks = (a.R + WIN_NT - 1) / WIN_NT + (a.N + WIN_NT - 1) / WIN_NT;
-    // batches longer than the window, whose length is a whole number of 64-step blocks
-    const uint32_t ring = a.W % 64 == 0 && a.T > a.W ? a.W / 64 : 0;
-    switch (ring) {
-        case 1: hipLaunchKernelGGL(window_kernel<1>, dim3(blocks), dim3(WIN_NT), 0, s, a); break;
-        case 2: hipLaunchKernelGGL(window_kernel<2>, dim3(blocks), dim3(WIN_NT), 0, s, a); break;
-        case 4: hipLaunchKernelGGL(window_kernel<4>, dim3(blocks), dim3(WIN_NT), 0, s, a); break;
-        case 8: hipLaunchKernelGGL(window_kernel<8>, dim3(blocks), dim3(WIN_NT), 0, s, a); break;
-        case 16: hipLaunchKernelGGL(window_kernel<16>, dim3(blocks), dim3(WIN_NT), 0, s, a); break;
-        default: hipLaunchKernelGGL(window_kernel<0>, dim3(blocks), dim3(WIN_NT), 0, s, a); break;
+    if (a.T == 1) {
+        const uint32_t blocks = (a.R + WIN_NT - 1) / WIN_NT + (a.N + WIN_NT - 1) / WIN_NT;
+        hipLaunchKernelGGL(window_step_kernel, dim3(blocks), dim3(WIN_NT), 0, s, a);
+        return hipGetLastError();
     }
+    const uint32_t rank_tiles = (2 * ((a.R + 63) / 64) + TILE - 1) / TILE;
+    const uint32_t node_tiles = (2 * ((a.N + 63) / 64) + TILE - 1) / TILE;
+    const uint32_t q = a.W / 64, r = a.W % 64, hist = q + (r ? 1 : 0), blocks = (a.T + 63) / 64;
+    // The shortest stretches that make at most 256 workgroups (one per CU), but of at least
+    // the window (only the first stretch may look at the ring) and four blocks, and no longer
+    // than gives every wave of a 16-wave workgroup one block: 65 536 ranks x 4 096 steps
+    // takes 18 us with 10 or 11 blocks, 21 with 5 (two workgroups after another on most CUs).
+    const uint32_t tiles = rank_tiles + node_tiles;
+    const uint32_t fits = WIN_MAX_NT / WAVE - 1 > hist ? WIN_MAX_NT / WAVE - 1 - hist : 0;
+    uint32_t stretch = hist > MIN_STRETCH ? hist : MIN_STRETCH;
+    while (stretch < fits && (uint64_t)((blocks + stretch - 1) / stretch) * tiles > 256) ++stretch;
+    if (stretch > blocks) stretch = blocks;
+    const uint32_t stretches = (blocks + stretch - 1) / stretch;
+    const uint32_t slots = hist + stretch + 1;
+    const uint32_t nt = (slots < (uint32_t)WIN_MAX_NT / WAVE ? slots : (uint32_t)WIN_MAX_NT / WAVE) * WAVE;
+    const size_t lds = (size_t)(r ? 2 * GD_BLOCK_PLANES - 1 : GD_BLOCK_PLANES) * slots * TILE * 4;
+    static bool configured = false;          // (a repeated set is harmless)
+    if (!configured) {
+        constexpr size_t most = (size_t)(2 * GD_BLOCK_PLANES - 1) * (MAX_HISTORY + MAX_STRETCH + 1) * TILE * 4;
+        static_assert(most + sizeof(uint32_t) * GD_COUNT_PLANES * TILE <= 160 * 1024, "LDS budget of one CU");
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(window_blocks_kernel),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+        if (e != hipSuccess) return e;
+        configured = true;
+    }
+    hipLaunchKernelGGL(window_blocks_kernel, dim3(stretches, tiles), dim3(nt), lds, s, a, rank_tiles, stretch);
     return hipGetLastError();
 }
 
