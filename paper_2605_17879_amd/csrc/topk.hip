@@ -13,8 +13,8 @@
 // k <= 64 (the usual request): nothing is sorted.
 //   1. A thread loads 1, 2, 4 or 8 neighbouring nodes (three vector loads at the most)
 //      and keeps their keys in registers.
-//   2. The largest upper half (count and the leading half of the score) of every group
-//      of up to 8 neighbouring threads goes into LDS: 128 to 255 values.  Each wave ranks
+//   2. The largest digest (see below: the count and the leading bits of the score) of every
+//      group of up to 8 neighbouring threads goes into LDS: 128 to 255 values.  Each wave ranks
 //      a few of them against all (one value per lane, a compare and a count of the
 //      lanes per 64).  The k-th largest is a threshold that at least k keys reach --
 //      it is the k-th largest of a subset -- and, a group's best being the likeliest of
@@ -85,6 +85,20 @@ __device__ __forceinline__ uint64_t sort_desc(uint64_t v, uint32_t lane) {
     return merge_desc(v, lane);
 }
 
+// 32 bits that never decrease with the key: the count (at most 1 024: 11 bits) and the 21
+// leading bits of the middle field that can differ.  A score's are its own; a sum of at most
+// 1 024 values of 16 bits stays within +-2^25, so bits 30 .. 26 of the biased sum say nothing.
+// (The key's upper half, 16 bits of count and 16 of the middle, is one and the same for all
+// sums: every key then reached the threshold and all of them were sorted, 12 us more at 3 230
+// nodes.)  Both fields are clamped, so that a digest is monotone whatever the state holds.
+__device__ __forceinline__ uint32_t digest_of(const gd_topk_args& a, uint32_t count, uint32_t mid) {
+    if (!a.z_last) {
+        constexpr uint32_t lo = 0x80000000u - (1u << 25), hi = 0x80000000u + (1u << 25) - 1;
+        mid = (min(max(mid, lo), hi) - lo) << 6;
+    }
+    return min(count, 2047u) << 21 | mid >> 11;
+}
+
 // The middle field of a node's key.
 __device__ __forceinline__ uint32_t mid_of(const gd_topk_args& a, uint32_t bits) {
     return a.z_last ? key_of(__uint_as_float(bits) + 0.0f)        // -0 ranks as +0
@@ -140,10 +154,10 @@ __global__ __launch_bounds__(TOPK_NT) void topk_short_kernel(const gd_topk_args 
     // loads (both arrays start at multiples of 256 bytes and their room is rounded up to that:
     // the last thread may read past node N - 1, and drops what it read there).
     uint64_t mine[KPT];
-    uint32_t top = 0;
+    uint32_t digest[KPT], top = 0;
     const uint32_t n0 = tid * KPT;
 #pragma unroll
-    for (int q = 0; q < KPT; ++q) mine[q] = 0;
+    for (int q = 0; q < KPT; ++q) { mine[q] = 0; digest[q] = 0; }
     if (n0 < a.N) {
         struct alignas(2 * KPT) Counts { uint16_t v[KPT]; };
         struct alignas(4 * KPT > 16 ? 16 : 4 * KPT) Mids { uint32_t v[KPT]; };
@@ -152,8 +166,12 @@ __global__ __launch_bounds__(TOPK_NT) void topk_short_kernel(const gd_topk_args 
                                 : *reinterpret_cast<const Mids*>(a.score_sum + n0);
 #pragma unroll
         for (int q = 0; q < KPT; ++q) {
-            if (n0 + q < a.N) mine[q] = key_from(c.v[q], mid_of(a, m.v[q]), n0 + q);
-            top = max(top, (uint32_t)(mine[q] >> 32));
+            if (n0 + q < a.N) {
+                const uint32_t mid = mid_of(a, m.v[q]);
+                mine[q] = key_from(c.v[q], mid, n0 + q);
+                digest[q] = digest_of(a, c.v[q], mid);
+            }
+            top = max(top, digest[q]);
         }
     }
     // groups of g threads, g the largest of 1, 2, 4, 8 that leaves 128 groups with nodes
@@ -190,12 +208,12 @@ __global__ __launch_bounds__(TOPK_NT) void topk_short_kernel(const gd_topk_args 
     const uint32_t thr = threshold;
     uint32_t hits = 0;
 #pragma unroll
-    for (int q = 0; q < KPT; ++q) hits += (uint32_t)(mine[q] >> 32) >= thr && mine[q] != 0 ? 1u : 0u;
+    for (int q = 0; q < KPT; ++q) hits += digest[q] >= thr && mine[q] != 0 ? 1u : 0u;
     if (hits) {
         uint32_t pos = atomicAdd(&n_reach, hits);
 #pragma unroll
         for (int q = 0; q < KPT; ++q)
-            if ((uint32_t)(mine[q] >> 32) >= thr && mine[q] != 0) keys[pos++] = mine[q];
+            if (digest[q] >= thr && mine[q] != 0) keys[pos++] = mine[q];
     }
     __syncthreads();
     const uint32_t m = n_reach;                     // at least min(k, N) = k of them

@@ -51,3 +51,28 @@ def test_slowest_nodes_at_the_edges_of_the_dispatch(N, pattern):
         assert np.array_equal(idx, want_idx), (N, pattern, k)
         assert np.array_equal(key, want_key), (N, pattern, k)
     det.close()
+
+
+@pytest.mark.parametrize("spread", ["within 32 of each other", "wide", "at both ends of the range", "equal"])
+@pytest.mark.parametrize("N", [65, 1024, 3230, 8192])
+def test_ranking_by_sums_that_agree_in_their_leading_bits(N, spread):
+    rng = np.random.default_rng(N + len(spread))
+    W = 1024 if spread == "at both ends of the range" else 4
+    det = Detector(Config(n_ranks=8 * N, n_metrics=1, window=W, persist_k=2))
+    q = {"within 32 of each other": rng.integers(-8, 8, (W, N)), "wide": rng.integers(-30000, 30000, (W, N)),
+         "at both ends of the range": np.repeat(rng.choice([-32768, 32767], (1, N)), W, axis=0),
+         "equal": np.full((W, N), 5)}[spread]
+    out = det.alloc_outputs(W)
+    out["exceed_mask"].zero_()
+    node_mask = rng.random((W, N)) < 0.01
+    out["node_mask"].copy_(torch.from_numpy(node_mask.astype(np.uint8)))
+    out["node_z"].copy_(torch.from_numpy((q / 64.0).astype(np.float32)))      # (exact: the default grid is 1/64)
+    det.alloc_ledger(W)
+    det.update_ledger(out, W)
+    for k in (1, 33, 64):
+        want_idx, want_key = oracle.topk_mean(node_mask.sum(0).astype(np.uint16), q.sum(0).astype(np.int32), k)
+        tk = det.alloc_topk(k)
+        det.topk_nodes_mean(k, tk)
+        assert np.array_equal(tk["idx"].cpu().numpy(), want_idx), (N, spread, k)
+        assert np.array_equal(tk["key"].cpu().numpy().view(np.uint64), want_key), (N, spread, k)
+    det.close()
