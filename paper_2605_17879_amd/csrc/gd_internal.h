@@ -151,6 +151,14 @@ struct gd_sweep_args {
 
 hipError_t gd_launch_score(const gd_score_args& a, hipStream_t s);
 hipError_t gd_launch_score_with_z(const gd_score_args& a, hipStream_t s);   // score_z.hip
+// Rank counts that fill no tiling exactly: up to 8 192 ranks, more, and the per-column route
+// of short batches; with and without the z output.
+hipError_t gd_launch_ragged_few(const gd_score_args& a, int n_cu, hipStream_t s);
+hipError_t gd_launch_ragged_many(const gd_score_args& a, int n_cu, hipStream_t s);
+hipError_t gd_launch_ragged_columns(const gd_score_args& a, hipStream_t s);
+hipError_t gd_launch_ragged_few_z(const gd_score_args& a, int n_cu, hipStream_t s);
+hipError_t gd_launch_ragged_many_z(const gd_score_args& a, int n_cu, hipStream_t s);
+hipError_t gd_launch_ragged_columns_z(const gd_score_args& a, hipStream_t s);
 hipError_t gd_launch_sweep(const gd_sweep_args& a, hipStream_t s);
 hipError_t gd_launch_membership(float* d_x, const uint64_t* d_active, uint32_t T, uint32_t R, uint32_t M,
                                 hipStream_t s);

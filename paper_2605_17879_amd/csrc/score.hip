@@ -26,11 +26,15 @@
 
 #include "gd_internal.h"
 
-// This file is compiled twice, side by side: as it is (every launch without the
-// optional z output, and the entry points) and, through score_z.hip, with
-// GD_SCORE_WANT_Z = 1 (the launches that write z as well).
+// This file is compiled several times, side by side: as it is (every launch without the
+// optional z output, and the entry points), through score_z.hip with GD_SCORE_WANT_Z = 1
+// (the launches that write z as well), and through the score_ragged files with
+// GD_SCORE_RAGGED = 1, 2 or 3 (the rank counts that fill no tiling exactly).
 #ifndef GD_SCORE_WANT_Z
 #define GD_SCORE_WANT_Z 0
+#endif
+#ifndef GD_SCORE_RAGGED
+#define GD_SCORE_RAGGED 0
 #endif
 
 namespace {
@@ -662,10 +666,14 @@ struct HintedResult {
     uint32_t q0, q1;            // the two middle distances (bit patterns)
 };
 
-template <int NT, int ROWS, int LOG_NB, typename SH>
-__device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[ROWS][4], uint32_t hint_lo,
-                                                      uint32_t hint_hi, float mad_hint, uint32_t k0,
-                                                      uint32_t k1, uint32_t* umax_slot, uint32_t par) {
+// Padding lanes (of the last rows of a ragged rank count) hold another lane's value until
+// `set_padding(j)` makes them NaN patterns: over the bracket in the count, never within a
+// distance in the gather.
+template <int NT, int ROWS, int LOG_NB, typename SH, typename Pad>
+__device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[ROWS][4], Pad set_padding,
+                                                      uint32_t hint_lo, uint32_t hint_hi, float mad_hint,
+                                                      uint32_t k0, uint32_t k1, uint32_t* umax_slot,
+                                                      uint32_t par) {
     HintedResult out = {0, 0u, 0u, 0u, 0u, 0u};
     constexpr int NB = 1 << LOG_NB;
     constexpr uint32_t KEY_LIMIT = 0x7D000000u;    // beyond it the signed bucket arithmetic could wrap
@@ -691,6 +699,9 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
         for (int j = 0; j < ROWS; ++j) {
             float(&row)[4] = const_cast<float(&)[4]>(v[j]);
             asm volatile("" : "+v"(row[0]), "+v"(row[1]), "+v"(row[2]), "+v"(row[3]));
+            um = max(max(um, __float_as_uint(row[0])), __float_as_uint(row[1]));
+            um = max(max(um, __float_as_uint(row[2])), __float_as_uint(row[3]));
+            set_padding(j);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int q = (int)(__float_as_uint(row[i]) >> sh_s);
@@ -699,8 +710,6 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
                 // counter c - ql + 64, in [63 - lane, 64 + NB + lane]
                 atomicAdd(reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(cnt) + (((uint32_t)c << 2) + kb)), 1u);
             }
-            um = max(max(um, __float_as_uint(row[0])), __float_as_uint(row[1]));
-            um = max(max(um, __float_as_uint(row[2])), __float_as_uint(row[3]));
             asm volatile("" : "+v"(um));
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -882,22 +891,24 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
 // pass of the hinted selection confirms them, so raw bit patterns serve as keys whatever
 // the column holds.  Thread 0 writes the hints of metric m; ends with a barrier, the work
 // area at rest.
+// (valid: this thread's row 0 holds ranks; n: how many values that makes in all)
 template <int NT, int LOG_NB, typename SH>
-__device__ __forceinline__ void sample_hints(SH& sh, const float (&row)[4], uint32_t m) {
+__device__ __forceinline__ void sample_hints(SH& sh, const float (&row)[4], bool valid, uint32_t n, uint32_t m) {
     constexpr int BPT = (1 << LOG_NB) / NT;
-    constexpr uint32_t n = 4u * NT;
     const uint32_t tid = opaque_v(threadIdx.x), lane = tid & (WAVE - 1);
     uint32_t k[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) k[i] = __float_as_uint(row[i]);
-    const uint32_t mn = wave_min_to_last(min(min(k[0], k[1]), min(k[2], k[3])));
-    const uint32_t mx = wave_max_to_last(max(max(k[0], k[1]), max(k[2], k[3])));
+    const uint32_t mn = wave_min_to_last(valid ? min(min(k[0], k[1]), min(k[2], k[3])) : 0xFFFFFFFFu);
+    const uint32_t mx = wave_max_to_last(valid ? max(max(k[0], k[1]), max(k[2], k[3])) : 0u);
     if (lane == WAVE - 1) { atomicMin(&sh.smin, mn); atomicMax(&sh.smax, mx); }
     __syncthreads();
     const uint32_t smin = rfl(sh.smin), smax = rfl(sh.smax);
     const int sshift = shift_for<LOG_NB>(smax - smin);
+    if (valid) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) atomicAdd(&sh.hist[(k[i] - smin) >> sshift], 1u);
+        for (int i = 0; i < 4; ++i) atomicAdd(&sh.hist[(k[i] - smin) >> sshift], 1u);
+    }
     __syncthreads();
     if (tid == 0) { sh.smin = 0xFFFFFFFFu; sh.smax = 0; }
     uint32_t loc[BPT], sum = 0;
@@ -1033,13 +1044,21 @@ __device__ __forceinline__ void score_row_decide(const float (&x)[4], uint32_t x
     *cand = LOWER_IS_WORSE ? sum <= sthr : sum >= sthr;
 }
 
-// FULL: R == NT*4*ROWS exactly, so no lane is padding and no bounds are checked.
+// FULL: R == NT*4*ROWS exactly, so no lane is padding and no bounds are checked.  A ragged
+// rank count takes a tiling of at most two rows too many (NT*4*(ROWS-2) < R): only the
+// last two rows can hold padding lanes and only they are checked, at compile time, so that
+// they take the hinted selection at the cost of an exact fit.  Measured (launch): 40 000
+// ranks x 1 024 steps x 8 metrics 571 us with one tiling up to the next power of two, every
+// row checked and the general selection, 585 us with empty rows passed over at run time
+// (scalars spilled and registers copied at every check), 403 us this way; 5 000 x 1 000 x 2
+// 60 -> 45 us; 65 528 ranks take 600 us where 65 536 take 583.
 // SPLIT (short batches, the streaming case): one workgroup per column instead of
 // per run of steps, so that the M columns of a step are scored side by side.  The
 // exceed bits of a column are then OR-ed into the (zeroed) mask outputs in global
 // memory and combine_kernel applies the multi-signal rule afterwards.
 template <int NT, int ROWS, int LOG_NB, bool FULL, bool SPLIT, bool WANT_Z>
-__global__ __launch_bounds__(NT, 4) void score_kernel(const gd_score_args a) {   // <= 128 VGPRs: 16 waves per CU
+__device__ __forceinline__ void score_columns(const gd_score_args& a) {
+    constexpr int TAIL = FULL ? ROWS : (ROWS > 2 ? ROWS - 2 : 0);     // first row that may hold padding
     constexpr int BLK = NT * 4;               // ranks per register row
     constexpr int MAX_NODES = BLK * ROWS / 8;
     constexpr int NWAVES = NT / WAVE;
@@ -1064,13 +1083,19 @@ __global__ __launch_bounds__(NT, 4) void score_kernel(const gd_score_args a) {  
     const uint32_t m_begin = SPLIT ? blockIdx.x % M : 0u, m_end = SPLIT ? m_begin + 1u : M;
 
     // Row j of wave w covers rank block (j + w) % ROWS, so that the first
-    // registers to arrive (row 0) sample the whole rank range.
+    // registers to arrive (row 0) sample the whole rank range.  (The rows that may hold
+    // padding stay where they are.)
     // The lane part (tid*4) is passed in so that each phase can use its own,
     // optimiser-opaque copy: otherwise every row's store and load address is
     // computed once and kept in registers for the whole kernel.
-    auto rbase = [&](int j, uint32_t tid4) -> uint32_t {
-        return (uint32_t)((j + w) & (ROWS - 1)) * BLK + tid4;
+    const int wrow = FULL ? w : (TAIL > 0 ? w % (TAIL > 0 ? TAIL : 1) : 0);
+    auto block_of = [&](int j) -> uint32_t {
+        if (FULL) return (uint32_t)((j + wrow) & (ROWS - 1));
+        if (j >= TAIL) return (uint32_t)j;
+        return (uint32_t)(j + wrow >= TAIL ? j + wrow - TAIL : j + wrow);
     };
+    auto rbase = [&](int j, uint32_t tid4) -> uint32_t { return block_of(j) * BLK + tid4; };
+    auto holds = [&](int j, uint32_t tid4) -> bool { return j < TAIL || rbase(j, tid4) < R; };
     auto fresh_tid4 = [&]() -> uint32_t { return opaque_v((uint32_t)tid * 4); };
 
     uint32_t NE[(ROWS + 3) / 4]; // node mask byte per row, packed
@@ -1097,18 +1122,8 @@ __global__ __launch_bounds__(NT, 4) void score_kernel(const gd_score_args a) {  
         }
     }
     __syncthreads();
-    // number of threads whose sampled element (row 0) is a real rank
-    uint32_t nsample = NT;
-    if (!FULL) {
-        const uint32_t c = __popcll(__ballot(rbase(0, (uint32_t)tid * 4) < R));
-        if (lane == 0) atomicAdd(&sh.ncand, c);
-        __syncthreads();
-        nsample = rfl(sh.ncand);
-        __syncthreads();
-        if (tid == 0) sh.ncand = 0;
-        __syncthreads();
-    }
-
+    // threads whose row 0, the column's sample, holds ranks
+    const uint32_t nsample = TAIL > 0 ? (uint32_t)NT : min((uint32_t)NT, R / 4);
     const float inv_node_scale = 1.0f / a.node_scale;      // (only used where node_scale > 0)
     uint32_t dir_codes = 0;          // direction + 1 of metric i in bits 2i, 2i + 1
 #pragma unroll
@@ -1118,22 +1133,22 @@ __global__ __launch_bounds__(NT, 4) void score_kernel(const gd_score_args a) {  
     uint32_t colpar = 0;                          // parity of the column count: which umax slot is in use
 
     float v[ROWS][4];
-    // Issue the loads of one register row of a column (padding: a NaN, whose key
-    // lies above every real key).
+    // Issue the loads of one register row of a column.  Padding lanes read the column's last
+    // ranks once more (a load under a condition would be waited for on the spot) and become
+    // NaNs, whose key lies above every real key, when the column is first looked at.
     auto load_row = [&](int j, const float* col, uint32_t tid4) {
+        // (a uniform row pointer plus the lane's 32-bit offset: one address mode, no vector
+        // arithmetic per row)
         float4 q;
-        if (FULL) {
-            // (a uniform row pointer plus the lane's 32-bit offset: one address mode, no vector
-            // arithmetic per row)
-            const float* rowp = col + (uint32_t)((j + w) & (ROWS - 1)) * BLK;
-            q = *reinterpret_cast<const float4*>(rowp + tid4);
-        } else if (rbase(j, tid4) < R) {
-            q = *reinterpret_cast<const float4*>(col + rbase(j, tid4));
-        } else {
-            const float pad = __uint_as_float(0x7FFFFFFFu);
-            q = make_float4(pad, pad, pad, pad);
-        }
+        if (j < TAIL) q = *reinterpret_cast<const float4*>(col + block_of(j) * BLK + tid4);
+        else q = *reinterpret_cast<const float4*>(col + min((uint32_t)j * BLK + tid4, R - 4));
         v[j][0] = q.x; v[j][1] = q.y; v[j][2] = q.z; v[j][3] = q.w;
+    };
+    auto set_padding = [&](int j, uint32_t tid4) {
+        if (j < TAIL) return;
+        const bool pad = (uint32_t)j * BLK + tid4 >= R;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[j][i] = pad ? __uint_as_float(0x7FFFFFFFu) : v[j][i];
     };
     {
         const uint32_t tl = fresh_tid4();
@@ -1159,15 +1174,15 @@ __global__ __launch_bounds__(NT, 4) void score_kernel(const gd_score_args a) {  
         const bool have_next = !SPLIT && (m + 1 < M || t + 1 < t_end);
         const float* next_col = a.x + (t * M + m + (have_next ? 1 : 0)) * (size_t)R;
         const uint32_t tl = fresh_tid4();
-        const bool svalid = FULL || rbase(0, tl) < R;
+        const bool svalid = holds(0, tl);
         // A workgroup scores consecutive steps, and telemetry moves little from one
         // step to the next: the previous step's median of this metric, with the
         // reach its histogram had, brackets this step's counting pass without
         // sampling.  A bracket that misses is noticed and replaced by the sample's.
         // (the first step of a run has no predecessor: a sample of the column stands in)
         bool boot = false;
-        if (FULL && t == t_begin && rfl(sh.hok[m]) == 0) {
-            sample_hints<NT, LOG_NB>(sh, v[0], m);
+        if (t == t_begin && rfl(sh.hok[m]) == 0) {
+            sample_hints<NT, LOG_NB>(sh, v[0], svalid, 4u * nsample, m);
             boot = true;
         }
         bool hinted = rfl(sh.hok[m]) != 0;
@@ -1183,16 +1198,17 @@ __global__ __launch_bounds__(NT, 4) void score_kernel(const gd_score_args a) {  
         uint32_t s0 = 0, s1 = 0;
         float med = 0.0f;
         bool have_mad = false;
-        // The hinted selection (sign-free column, exact-fit tiling, a predecessor's bracket and
-        // MAD): median and MAD in three light passes.  Whatever it does not settle goes
+        // The hinted selection (sign-free column, a predecessor's bracket and MAD): median and
+        // MAD in three light passes.  Whatever it does not settle goes
         // through the general route below.
         int hsel = 0;
         bool tried_fast = false;
-        if (FULL && hinted && rfl(sh.hfast[m]) != 0 && hint_hi < 0x7D000000u - 2u * (hint_hi - hint_lo) &&
+        if (hinted && rfl(sh.hfast[m]) != 0 && hint_hi < 0x7D000000u - 2u * (hint_hi - hint_lo) &&
             hint_hi - hint_lo < 0x20000000u) {
             tried_fast = true;
-            const HintedResult hr = hinted_select<NT, ROWS, LOG_NB>(sh, v, hint_lo, hint_hi, sh.hmad[m], k0_all,
-                                                                    k1_all, umax_slot, colpar);
+            const HintedResult hr = hinted_select<NT, ROWS, LOG_NB>(
+                sh, v, [&](int j) { set_padding(j, tl); }, hint_lo, hint_hi, sh.hmad[m], k0_all, k1_all, umax_slot,
+                colpar);
             hsel = hr.found;
             umax = hr.umax;
             if (hsel == 0) {
@@ -1216,10 +1232,9 @@ __global__ __launch_bounds__(NT, 4) void score_kernel(const gd_score_args a) {  
             uint32_t um = 0;
 #pragma unroll
             for (int j = 0; j < ROWS; ++j) {
-                if (FULL || rbase(j, tl) < R) {
-                    um = max(um, max(__float_as_uint(v[j][0]), __float_as_uint(v[j][1])));
-                    um = max(um, max(__float_as_uint(v[j][2]), __float_as_uint(v[j][3])));
-                }
+                um = max(um, max(__float_as_uint(v[j][0]), __float_as_uint(v[j][1])));
+                um = max(um, max(__float_as_uint(v[j][2]), __float_as_uint(v[j][3])));
+                set_padding(j, tl);
             }
             um = wave_max_to_last(um);
             if (lane == WAVE - 1) atomicMax(umax_slot, um);
@@ -1352,7 +1367,7 @@ __global__ __launch_bounds__(NT, 4) void score_kernel(const gd_score_args a) {  
             };
 #pragma unroll
             for (int j = 0; j < ROWS; ++j) {
-                if (FULL || rbase(j, tz) < R) {
+                if (holds(j, tz)) {
                     float4 q;
                     if (by_recip) {
                         q.x = quotient(v[j][0]); q.y = quotient(v[j][1]);
@@ -1466,7 +1481,7 @@ __global__ __launch_bounds__(NT, 4) void score_kernel(const gd_score_args a) {  
                 eplaced = e << m;
             }
             __hip_atomic_fetch_or(&emask_lane[j * NT], eplaced, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (prim && (FULL || rbase(j, tz) < R) && !(tz & 4)) nzrow[rbase(j, tz) / 8] = nz;
+            if (prim && holds(j, tz) && !(tz & 4)) nzrow[rbase(j, tz) / 8] = nz;
             if (!SPLIT) load_row(j, next_col, tz);   // the row is done: refill it with the next column
             // pin the row's results here, or its scores stay live until the loop ends
             asm volatile("" : "+v"(NE[j / 4]));
@@ -1481,7 +1496,7 @@ __global__ __launch_bounds__(NT, 4) void score_kernel(const gd_score_args a) {  
         // (R and N are multiples of 4 here, the outputs word-aligned: see the launcher)
 #pragma unroll
         for (int j = 0; j < ROWS; ++j) {
-            if (!(FULL || rbase(j, to) < R)) continue;
+            if (!holds(j, to)) continue;
             const uint32_t Ej = emask[j * NT + to / 4];
             if (Ej) atomicOr(reinterpret_cast<uint32_t*>(erow + rbase(j, to)), Ej);
             const uint32_t nb = (NE[j / 4] >> (8 * (j & 3))) & 0xFFu;
@@ -1516,7 +1531,7 @@ __global__ __launch_bounds__(NT, 4) void score_kernel(const gd_score_args a) {  
     };
 #pragma unroll
     for (int j = 0; j < ROWS; ++j) {
-        const bool valid = FULL || rbase(j, to) < R;
+        const bool valid = holds(j, to);
         const uint32_t Ej = emask[j * NT + to / 4];
         if (valid) *reinterpret_cast<uint32_t*>(erow + rbase(j, to)) = Ej;
         uint32_t an = rule4(Ej);
@@ -1534,18 +1549,24 @@ __global__ __launch_bounds__(NT, 4) void score_kernel(const gd_score_args a) {  
         a.rank_anom[t * RW + q] = sh.ranka[q];
         sh.ranka[q] = 0;
     }
-    if (FULL && ROWS == 16) {
-        // N == 8 * NT: eight nodes per thread -- one 8-byte read of the staged bytes and one
-        // 8-byte store; the rule byte-parallel as for the ranks; eight consecutive lanes make
-        // one 64-bit anomaly word
+    if (ROWS >= 10) {
+        // Eight nodes per thread (N <= 8 * NT): one 8-byte read of the staged bytes and, where
+        // the step's bytes begin at a multiple of eight, one 8-byte store; the rule
+        // byte-parallel as for the ranks; eight consecutive lanes make one 64-bit anomaly word
         const uint32_t tq = opaque_v((uint32_t)tid), sl = tq & 7u;
-        const uint2 nb = *reinterpret_cast<const uint2*>(&sh.nodeb[8 * tq]);
+        uint2 nb = *reinterpret_cast<const uint2*>(&sh.nodeb[min(8 * tq, (uint32_t)MAX_NODES - 8)]);
         uint8_t* nm = a.node_mask + t * N + 8 * tq;
-        if (((uintptr_t)a.node_mask & 7u) == 0) {
+        const uint32_t here = FULL ? 8u : (8 * tq < N ? min(N - 8 * tq, 8u) : 0u);      // (nodes of this thread)
+        if (!FULL && here < 8) {                // (bytes beyond the last node were never written)
+            nb.x &= here >= 4 ? 0xFFFFFFFFu : (1u << (8 * here)) - 1u;
+            nb.y &= here <= 4 ? 0u : (1u << (8 * (here - 4))) - 1u;
+        }
+        if (here == 8 && ((uintptr_t)(a.node_mask + t * N) & 7u) == 0) {
             *reinterpret_cast<uint2*>(nm) = nb;
         } else {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) nm[i] = (uint8_t)((i < 4 ? nb.x : nb.y) >> (8 * (i & 3)));
+            for (uint32_t i = 0; i < 8; ++i)
+                if (FULL || i < here) nm[i] = (uint8_t)((i < 4 ? nb.x : nb.y) >> (8 * (i & 3)));
         }
         const uint32_t a0 = rule4(nb.x), a1 = rule4(nb.y);
         const uint32_t ab = ((a0 | (a0 >> 7) | (a0 >> 14) | (a0 >> 21)) & 0xFu) |
@@ -1555,7 +1576,7 @@ __global__ __launch_bounds__(NT, 4) void score_kernel(const gd_score_args a) {  
         wlo |= lane_xor<1>(wlo); whi |= lane_xor<1>(whi);
         wlo |= lane_xor<2>(wlo); whi |= lane_xor<2>(whi);
         wlo |= lane_xor<4>(wlo); whi |= lane_xor<4>(whi);
-        if (sl == 0u) a.node_anom[t * NWD + tq / 8u] = ((uint64_t)whi << 32) | wlo;
+        if (sl == 0u && (FULL || 8 * tq < N)) a.node_anom[t * NWD + tq / 8u] = ((uint64_t)whi << 32) | wlo;
     } else {
         if (FULL) {                             // N == NT * ROWS / 2: a fixed number of rounds
 #pragma unroll
@@ -1578,6 +1599,21 @@ __global__ __launch_bounds__(NT, 4) void score_kernel(const gd_score_args a) {  
         }
     }
     }   // steps of this workgroup
+}
+
+// <= 128 VGPRs: 16 waves per CU
+template <int NT, int ROWS, int LOG_NB, bool FULL, bool SPLIT, bool WANT_Z>
+__global__ __launch_bounds__(NT, 4) void score_kernel(const gd_score_args a) {
+    score_columns<NT, ROWS, LOG_NB, FULL, SPLIT, WANT_Z>(a);
+}
+template <int NT, int ROWS, int LOG_NB, bool SPLIT, bool WANT_Z>
+__global__ __launch_bounds__(NT, 4) void score_ragged_kernel(const gd_score_args a) {
+    score_columns<NT, ROWS, LOG_NB, false, SPLIT, WANT_Z>(a);
+}
+template <int NT, int ROWS, int LOG_NB, bool FULL, bool SPLIT>
+constexpr auto kernel_of() {
+    if constexpr (FULL) return &score_kernel<NT, ROWS, LOG_NB, true, SPLIT, WANT_Z_HERE>;
+    else return &score_ragged_kernel<NT, ROWS, LOG_NB, SPLIT, WANT_Z_HERE>;
 }
 
 // Split route, before the columns are scored: the mask outputs start at zero.
@@ -1682,7 +1718,7 @@ template <int NT, int ROWS, int LOG_NB, bool FULL>
 hipError_t launch_runs(const gd_score_args& a, int n_cu, hipStream_t s) {
     constexpr size_t lds = lds_bytes<NT, ROWS, LOG_NB>();
     static_assert(lds <= 160 * 1024, "LDS budget of one CU");
-    auto kern = score_kernel<NT, ROWS, LOG_NB, FULL, false, WANT_Z_HERE>;
+    auto kern = kernel_of<NT, ROWS, LOG_NB, FULL, false>();
     static bool configured = false;      // a handle is single-threaded; a repeated set is harmless
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -1703,7 +1739,7 @@ template <int NT, int ROWS, int LOG_NB, bool FULL>
 hipError_t launch_columns(const gd_score_args& a, hipStream_t s) {
     constexpr size_t lds = lds_bytes<NT, ROWS, LOG_NB>();
     static_assert(lds <= 160 * 1024, "LDS budget of one CU");
-    auto kern = score_kernel<NT, ROWS, LOG_NB, FULL, true, WANT_Z_HERE>;
+    auto kern = kernel_of<NT, ROWS, LOG_NB, FULL, true>();
     static bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -1720,39 +1756,106 @@ hipError_t launch_columns(const gd_score_args& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// NT x ROWS: the tiling of a batch; CNT x CROWS: that of the per-column route, where a
-// column has the CU to itself and is spread over more threads (fewer rows per lane:
+#if GD_SCORE_RAGGED == 0
+
+// Exact fit.  NT x ROWS: the tiling of a batch; CNT x CROWS: that of the per-column route,
+// where a column has the CU to itself and is spread over more threads (fewer rows per lane:
 // shorter passes between the barriers).
 template <int NT, int ROWS, int LOG_NB, int CNT = NT, int CROWS = ROWS, int CLOG_NB = LOG_NB>
-hipError_t launch(const gd_score_args& a, hipStream_t s) {
+hipError_t launch(const gd_score_args& a, int n_cu, hipStream_t s) {
     static_assert(NT * ROWS == CNT * CROWS, "both tilings hold the same number of ranks");
-    hipError_t cu_err;
-    const int n_cu = compute_units(&cu_err);
-    if (cu_err != hipSuccess) return cu_err;
-    const bool full = a.R == (uint32_t)NT * 4 * ROWS;
-    if (use_split(a, n_cu))
-        return full ? launch_columns<CNT, CROWS, CLOG_NB, true>(a, s) : launch_columns<CNT, CROWS, CLOG_NB, false>(a, s);
-    return full ? launch_runs<NT, ROWS, LOG_NB, true>(a, n_cu, s) : launch_runs<NT, ROWS, LOG_NB, false>(a, n_cu, s);
+    return use_split(a, n_cu) ? launch_columns<CNT, CROWS, CLOG_NB, true>(a, s)
+                              : launch_runs<NT, ROWS, LOG_NB, true>(a, n_cu, s);
 }
 
 // Pick the register tiling for R: NT threads x ROWS float4 rows hold NT*4*ROWS ranks.
 hipError_t pick_tiling(const gd_score_args& a, hipStream_t s) {
-    const uint32_t R = a.R;
-    if (R <= 256) return launch<64, 1, 10>(a, s);
-    if (R <= 1024) return launch<64, 4, 10>(a, s);
+    hipError_t e;
+    const int n_cu = compute_units(&e);
+    if (e != hipSuccess) return e;
     // (the 256-thread tilings take 2048 buckets: four workgroups then share a CU's LDS, and
     // their barrier-bound phases overlap)
-    if (R <= 4096) return launch<256, 4, 11>(a, s);
     static_assert(4 * lds_bytes<256, 16, 11>() <= 160 * 1024, "four workgroups of the 16 384-rank tiling share a CU's LDS");
-    if (R <= 16384) return launch<256, 16, 11, 1024, 4, 12>(a, s);
-    if (R <= 32768) return launch<512, 16, 12, 1024, 8, 12>(a, s);
-    if (R <= 65536) return launch<1024, 16, 12>(a, s);
-    return hipErrorInvalidValue;
+    switch (a.R) {
+        case 256: return launch<64, 1, 10>(a, n_cu, s);
+        case 1024: return launch<64, 4, 10>(a, n_cu, s);
+        case 4096: return launch<256, 4, 11>(a, n_cu, s);
+        case 16384: return launch<256, 16, 11, 1024, 4, 12>(a, n_cu, s);
+        case 32768: return launch<512, 16, 12, 1024, 8, 12>(a, n_cu, s);
+        case 65536: return launch<1024, 16, 12>(a, n_cu, s);
+    }
+    if (a.R > 65536) return hipErrorInvalidValue;
+    constexpr bool z = WANT_Z_HERE;
+    if (use_split(a, n_cu)) return z ? gd_launch_ragged_columns_z(a, s) : gd_launch_ragged_columns(a, s);
+    if (a.R <= 8192) return z ? gd_launch_ragged_few_z(a, n_cu, s) : gd_launch_ragged_few(a, n_cu, s);
+    return z ? gd_launch_ragged_many_z(a, n_cu, s) : gd_launch_ragged_many(a, n_cu, s);
 }
+
+#endif
 
 }  // namespace
 
+#if GD_SCORE_RAGGED == 1 || GD_SCORE_RAGGED == 2 || GD_SCORE_RAGGED == 3
 #if GD_SCORE_WANT_Z
+#define GD_RAGGED(name) name##_z
+#else
+#define GD_RAGGED(name) name
+#endif
+#endif
+
+// Ragged rank counts: the smallest tiling in steps of two rows (of one and two at the
+// smallest), so that no more than the last two rows hold padding.
+#if GD_SCORE_RAGGED == 1
+
+hipError_t GD_RAGGED(gd_launch_ragged_few)(const gd_score_args& a, int n_cu, hipStream_t s) {
+    const uint32_t R = a.R;
+    if (R <= 256) return launch_runs<64, 1, 10, false>(a, n_cu, s);
+    if (R <= 512) return launch_runs<64, 2, 10, false>(a, n_cu, s);
+    if (R <= 1024) return launch_runs<64, 4, 10, false>(a, n_cu, s);
+    if (R <= 2048) return launch_runs<256, 2, 11, false>(a, n_cu, s);
+    if (R <= 4096) return launch_runs<256, 4, 11, false>(a, n_cu, s);
+    if (R <= 6144) return launch_runs<256, 6, 11, false>(a, n_cu, s);
+    return launch_runs<256, 8, 11, false>(a, n_cu, s);
+}
+
+#elif GD_SCORE_RAGGED == 2
+
+hipError_t GD_RAGGED(gd_launch_ragged_many)(const gd_score_args& a, int n_cu, hipStream_t s) {
+    const uint32_t R = a.R;
+    if (R <= 10240) return launch_runs<256, 10, 11, false>(a, n_cu, s);
+    if (R <= 12288) return launch_runs<256, 12, 11, false>(a, n_cu, s);
+    if (R <= 14336) return launch_runs<256, 14, 11, false>(a, n_cu, s);
+    if (R <= 16384) return launch_runs<256, 16, 11, false>(a, n_cu, s);
+    if (R <= 20480) return launch_runs<512, 10, 12, false>(a, n_cu, s);
+    if (R <= 24576) return launch_runs<512, 12, 12, false>(a, n_cu, s);
+    if (R <= 28672) return launch_runs<512, 14, 12, false>(a, n_cu, s);
+    if (R <= 32768) return launch_runs<512, 16, 12, false>(a, n_cu, s);
+    if (R <= 40960) return launch_runs<1024, 10, 12, false>(a, n_cu, s);
+    if (R <= 49152) return launch_runs<1024, 12, 12, false>(a, n_cu, s);
+    if (R <= 57344) return launch_runs<1024, 14, 12, false>(a, n_cu, s);
+    return launch_runs<1024, 16, 12, false>(a, n_cu, s);
+}
+
+#elif GD_SCORE_RAGGED == 3
+
+hipError_t GD_RAGGED(gd_launch_ragged_columns)(const gd_score_args& a, hipStream_t s) {
+    const uint32_t R = a.R;
+    if (R <= 256) return launch_columns<64, 1, 10, false>(a, s);
+    if (R <= 512) return launch_columns<64, 2, 10, false>(a, s);
+    if (R <= 1024) return launch_columns<64, 4, 10, false>(a, s);
+    if (R <= 2048) return launch_columns<256, 2, 11, false>(a, s);
+    if (R <= 4096) return launch_columns<256, 4, 11, false>(a, s);
+    if (R <= 8192) return launch_columns<1024, 2, 12, false>(a, s);
+    if (R <= 16384) return launch_columns<1024, 4, 12, false>(a, s);
+    if (R <= 24576) return launch_columns<1024, 6, 12, false>(a, s);
+    if (R <= 32768) return launch_columns<1024, 8, 12, false>(a, s);
+    if (R <= 40960) return launch_columns<1024, 10, 12, false>(a, s);
+    if (R <= 49152) return launch_columns<1024, 12, 12, false>(a, s);
+    if (R <= 57344) return launch_columns<1024, 14, 12, false>(a, s);
+    return launch_columns<1024, 16, 12, false>(a, s);
+}
+
+#elif GD_SCORE_WANT_Z
 
 hipError_t gd_launch_score_with_z(const gd_score_args& a, hipStream_t s) { return pick_tiling(a, s); }
 
