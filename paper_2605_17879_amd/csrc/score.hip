@@ -25,6 +25,7 @@
 #include <type_traits>
 
 #include "gd_internal.h"
+#include "gd_lanes.h"
 
 // This file is compiled several times, side by side: as it is (every launch without the
 // optional z output, and the entry points), through score_z.hip with GD_SCORE_WANT_Z = 1
@@ -138,10 +139,6 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t tid, ui
                                                     uint32_t* tot) {
     const uint32_t lane = tid & (WAVE - 1), w = tid >> 6;
     const uint32_t inc = wave_incl_scan(v);
-    if (NT == WAVE) {
-        *tot = __builtin_amdgcn_readlane((int)inc, WAVE - 1);
-        return inc - v;
-    }
     if (lane == WAVE - 1) wpart[w] = inc;
     __syncthreads();
     // every wave scans the (at most 16) wave totals itself: one LDS read, a row scan
@@ -727,7 +724,7 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
         d = wave_incl_scan(d);
         if (lane == WAVE - 1) sh.below = d;
     }
-    if (w == (NT > WAVE ? 1u : 0u)) cnt[64 + NB + lane] = 0;
+    if (w == 1u) cnt[64 + NB + lane] = 0;
     uint32_t below;
     const bool bracketed = locate<NT, LOG_NB, true, true>(sh, tid, k0, k1, &below);
     if (umax > KEY_LIMIT || !bracketed || shift < 2) return out;
@@ -1601,14 +1598,20 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     }   // steps of this workgroup
 }
 
-// <= 128 VGPRs: 16 waves per CU
+#include "score_small.h"
+
+// NT threads per column (64: one wave per column, M of them per workgroup; LOG_NB has no
+// meaning there).  <= 128 VGPRs: 16 waves per CU.
+constexpr int block_threads(int NT) { return NT == WAVE ? 8 * WAVE : NT; }
 template <int NT, int ROWS, int LOG_NB, bool FULL, bool SPLIT, bool WANT_Z>
-__global__ __launch_bounds__(NT, 4) void score_kernel(const gd_score_args a) {
-    score_columns<NT, ROWS, LOG_NB, FULL, SPLIT, WANT_Z>(a);
+__global__ __launch_bounds__(block_threads(NT), 4) void score_kernel(const gd_score_args a) {
+    if constexpr (NT == WAVE) score_small<ROWS, FULL, WANT_Z>(a);
+    else score_columns<NT, ROWS, LOG_NB, FULL, SPLIT, WANT_Z>(a);
 }
 template <int NT, int ROWS, int LOG_NB, bool SPLIT, bool WANT_Z>
-__global__ __launch_bounds__(NT, 4) void score_ragged_kernel(const gd_score_args a) {
-    score_columns<NT, ROWS, LOG_NB, false, SPLIT, WANT_Z>(a);
+__global__ __launch_bounds__(block_threads(NT), 4) void score_ragged_kernel(const gd_score_args a) {
+    if constexpr (NT == WAVE) score_small<ROWS, false, WANT_Z>(a);
+    else score_columns<NT, ROWS, LOG_NB, false, SPLIT, WANT_Z>(a);
 }
 template <int NT, int ROWS, int LOG_NB, bool FULL, bool SPLIT>
 constexpr auto kernel_of() {
@@ -1712,10 +1715,33 @@ constexpr size_t lds_bytes() {
     return ((sizeof(SH) + 15) & ~(size_t)15) + (size_t)ROWS * NT * 4;
 }
 
+// Up to 1 024 ranks: a workgroup per step, a wave per column, in short batches and long ones
+// (launched in pieces, because a grid's threads have to fit 32 bits).
+template <int ROWS, bool FULL, bool SPLIT>
+hipError_t launch_small(gd_score_args a, hipStream_t s) {
+    constexpr uint32_t MOST = 1u << 22;
+    static_assert(SmallLds<ROWS>::bytes(8) <= 64 * 1024, "LDS that a launch may ask for without more ado");
+    for (;;) {
+        const uint32_t n = a.T < MOST ? a.T : MOST;
+        hipLaunchKernelGGL((kernel_of<WAVE, ROWS, 10, FULL, SPLIT>()), dim3(n), dim3(WAVE * a.M),
+                           SmallLds<ROWS>::bytes(a.M), s, a);
+        const hipError_t e = hipGetLastError();
+        a.T -= n;
+        if (e != hipSuccess || a.T == 0) return e;
+        const size_t columns = (size_t)n * a.M;
+        a.x += columns * a.R; a.med += columns; a.mad += columns;
+        if (a.z) a.z += columns * a.R;
+        a.exceed_mask += (size_t)n * a.R; a.rank_anom += (size_t)n * ((a.R + 63) / 64);
+        a.node_z += (size_t)n * a.N; a.node_mask += (size_t)n * a.N; a.node_anom += (size_t)n * ((a.N + 63) / 64);
+    }
+}
+
 // A whole batch: enough workgroups to fill every CU once (as many as fit by LDS and
 // wave slots); each takes a contiguous run of ceil(T / grid) steps.
 template <int NT, int ROWS, int LOG_NB, bool FULL>
 hipError_t launch_runs(const gd_score_args& a, int n_cu, hipStream_t s) {
+    if constexpr (NT == WAVE) return launch_small<ROWS, FULL, false>(a, s);
+    else {
     constexpr size_t lds = lds_bytes<NT, ROWS, LOG_NB>();
     static_assert(lds <= 160 * 1024, "LDS budget of one CU");
     auto kern = kernel_of<NT, ROWS, LOG_NB, FULL, false>();
@@ -1732,11 +1758,14 @@ hipError_t launch_runs(const gd_score_args& a, int n_cu, hipStream_t s) {
     const uint32_t grid = (uint32_t)(a.T < cap ? a.T : cap);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, s, a);
     return hipGetLastError();
+    }
 }
 
 // A short batch: one workgroup per column between the fill and the combining kernel.
 template <int NT, int ROWS, int LOG_NB, bool FULL>
 hipError_t launch_columns(const gd_score_args& a, hipStream_t s) {
+    if constexpr (NT == WAVE) return launch_small<ROWS, FULL, true>(a, s);
+    else {
     constexpr size_t lds = lds_bytes<NT, ROWS, LOG_NB>();
     static_assert(lds <= 160 * 1024, "LDS budget of one CU");
     auto kern = kernel_of<NT, ROWS, LOG_NB, FULL, true>();
@@ -1754,6 +1783,7 @@ hipError_t launch_columns(const gd_score_args& a, hipStream_t s) {
     hipLaunchKernelGGL(kern, dim3(a.T * a.M), dim3(NT), lds, s, a);
     hipLaunchKernelGGL(combine_kernel, dim3((a.R / 4 + 255) / 256, a.T), dim3(256), 0, s, a);
     return hipGetLastError();
+    }
 }
 
 #if GD_SCORE_RAGGED == 0

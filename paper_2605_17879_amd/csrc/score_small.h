@@ -1,0 +1,332 @@
+// Scoring of small columns (up to 1 024 ranks): one wave per column, one workgroup of M
+// waves per step.  Included by score.hip, whose row functions it shares.
+//
+// A column of 1 024 values is sixteen registers of one wave.  The histogram route spends
+// its time on fixed costs there (clearing, scanning and searching a thousand buckets, with
+// 64 threads): 112 us for 1 024 ranks x 2 000 steps x 4 metrics, 25 us per step of which
+// hardly anything is arithmetic.  Here the order statistics are found without LDS tables or
+// barriers: the wave counts how many values lie under a pivot (a compare and a count of the
+// lanes that answered, per register), two pivots at a time, first around the middle of a
+// sorted sample of 64 values and then where the counts so far put the wanted rank; when at
+// most 64 values are left between the pivots they are moved to one register and sorted by
+// lane exchanges.  The scalar unit adds up the counts while the vector unit compares.
+// Measured (launch): 1 024 x 2 000 x 4 112 -> 31 us, 1 000 x 1 x 4 (one step) 74 -> 9 us,
+// 64 x 200 x 1 22 -> 4.4 us.  Bound by instruction issue in batches, by the length of the
+// chain (load, median, MAD, scores) in one-step calls.
+#ifndef GD_SCORE_SMALL_H_
+#define GD_SCORE_SMALL_H_
+
+// Rows: register rows of 64 x 4 ranks.  LDS of a workgroup, in this order, for M metrics.
+template <int ROWS>
+struct SmallLds {
+    static constexpr int WORDS = ROWS * WAVE;        // exceed-mask words of a step
+    uint64_t* node;        // [M][ROWS]   lane 2p: node p of the row exceeds
+    uint32_t* exceed;      // [M][WORDS]  bit 0 of each byte: the rank exceeds
+    uint32_t* slots;       // [M][64]     the wave's last candidates
+    __device__ __forceinline__ SmallLds(unsigned char* raw, uint32_t M) {
+        node = reinterpret_cast<uint64_t*>(raw);
+        exceed = reinterpret_cast<uint32_t*>(raw + (size_t)M * ROWS * 8);
+        slots = exceed + (size_t)M * WORDS;
+    }
+    static constexpr size_t bytes(uint32_t M) { return (size_t)M * (ROWS * 8 + WORDS * 4 + WAVE * 4); }
+};
+
+// Which lanes keep the smaller key in the stage of distance J that merges runs of S: a
+// constant, so that it is a scalar literal and no lane works it out (nor keeps it in
+// registers from one sort to the next).
+template <int J, int S>
+constexpr uint64_t keeps_smaller() {
+    uint64_t m = 0;
+    for (int l = 0; l < WAVE; ++l)
+        if (((l & J) == 0) == ((l & S) == 0)) m |= 1ull << l;
+    return m;
+}
+template <int BIT>
+constexpr uint64_t lanes_with() {
+    uint64_t m = 0;
+    for (int l = 0; l < WAVE; ++l)
+        if (l & BIT) m |= 1ull << l;
+    return m;
+}
+
+// One compare-exchange stage across the wave.
+template <int J, int S>
+__device__ __forceinline__ uint32_t small_exchange(uint32_t v) {
+    uint32_t o;
+    if constexpr (J == 16) {
+        auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        o = __builtin_amdgcn_inverse_ballot_w64(lanes_with<16>()) ? r[0] : r[1];
+    } else if constexpr (J == 32) {
+        auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        o = __builtin_amdgcn_inverse_ballot_w64(lanes_with<32>()) ? r[0] : r[1];
+    } else {
+        o = gd_lane_xor<J>(v, 0);
+    }
+    return __builtin_amdgcn_inverse_ballot_w64(keeps_smaller<J, S>()) ? min(v, o) : max(v, o);
+}
+template <int S>
+__device__ __forceinline__ uint32_t small_merge(uint32_t v) {
+    if constexpr (S > 32) v = small_exchange<32, S>(v);
+    if constexpr (S > 16) v = small_exchange<16, S>(v);
+    if constexpr (S > 8) v = small_exchange<8, S>(v);
+    if constexpr (S > 4) v = small_exchange<4, S>(v);
+    if constexpr (S > 2) v = small_exchange<2, S>(v);
+    return small_exchange<1, S>(v);
+}
+
+// 64 keys, one per lane, into ascending order.
+__device__ __forceinline__ uint32_t small_sort64(uint32_t v) {
+    v = small_merge<2>(v);
+    v = small_merge<4>(v);
+    v = small_merge<8>(v);
+    v = small_merge<16>(v);
+    v = small_merge<32>(v);
+    return small_merge<64>(v);
+}
+
+// The order statistics k0 <= k1 <= k0 + 1 of the n keys below `end` among the wave's K
+// (the others, padding and missing samples, are `end` or above).  Throughout, clo keys lie
+// under lo and chi under hi, with clo <= k0 and k1 < chi.  Ends for any contents: a round
+// narrows [lo, hi) to a part of it, from the fourth on to a half.
+template <int V>
+__device__ __forceinline__ void wave_select(const uint32_t (&K)[V], uint32_t sample, uint32_t end, uint32_t n,
+                                            uint32_t k0, uint32_t k1, uint32_t lane, uint32_t* slots, uint32_t* s0,
+                                            uint32_t* s1) {
+    uint32_t lo = 0, hi = end, clo = 0, chi = n;
+    // two pivots, p <= q; true when one of them parts the two statistics (k0 < p <= k1)
+    auto narrow = [&](uint32_t p, uint32_t q) -> bool {
+        uint32_t cp = 0, cq = 0;
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            cp += (uint32_t)__popcll(__ballot(K[i] < p));
+            cq += (uint32_t)__popcll(__ballot(K[i] < q));
+        }
+        uint32_t part = 0;
+        bool parted = false;
+        auto take = [&](uint32_t at, uint32_t c) {
+            const bool up = c <= k0 && at > lo, down = c > k1 && at < hi, splits = c > k0 && c <= k1;
+            lo = up ? at : lo; clo = up ? c : clo;
+            hi = down ? at : hi; chi = down ? c : chi;
+            part = splits ? at : part; parted = parted || splits;
+        };
+        take(p, cp);
+        take(q, cq);
+        if (parted) {
+            uint32_t mx = 0, mn = 0xFFFFFFFFu;
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+                mx = max(mx, K[i] < part ? K[i] : 0u);
+                mn = min(mn, K[i] < part ? 0xFFFFFFFFu : K[i]);
+            }
+            *s0 = (uint32_t)__builtin_amdgcn_readlane((int)wave_max_to_last(mx), WAVE - 1);
+            *s1 = (uint32_t)__builtin_amdgcn_readlane((int)wave_min_to_last(mn), WAVE - 1);
+        }
+        return parted;
+    };
+    if (n > (uint32_t)WAVE) {
+        // around the middle of the sample: two standard deviations of its median's rank
+        const uint32_t ns = (uint32_t)__popcll(__ballot(sample < end));
+        if (ns >= 16) {
+            const uint32_t sorted = small_sort64(sample);
+            const uint32_t reach = 4u + ns / 16u;
+            const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)sorted, (int)(ns / 2 - reach));
+            const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)sorted, (int)min(ns / 2 + reach, ns - 1)) + 1u;
+            if (narrow(p, q)) return;
+        }
+        for (int round = 0; chi - clo > (uint32_t)WAVE; ++round) {
+            const uint32_t span = hi - lo;
+            if (span <= 1) { *s0 = lo; *s1 = lo; return; }             // ties
+            uint32_t p = span / 2, q = p;
+            if (round < 3) {
+                // the values between the pivots taken as evenly spread: the wanted rank's
+                // place, and 2.5 standard deviations of it to either side
+                const float c = (float)(chi - clo), at = (float)(k1 - clo) + 0.5f;
+                const float side = 4.0f + 1.25f * __builtin_sqrtf(c), scale = (float)span / c;
+                p = (uint32_t)fminf(fmaxf((at - side) * scale, 0.0f), 4294967040.0f);
+                q = (uint32_t)fminf(fmaxf((at + side) * scale, 0.0f), 4294967040.0f);
+            }
+            p = rfl(min(max(p, 1u), span - 1u));
+            q = rfl(min(max(q, 1u), span - 1u));
+            if (narrow(lo + p, lo + q)) return;
+        }
+    }
+    // at most 64 keys in [lo, hi)
+    const uint32_t m = chi - clo, width = hi - lo;
+    uint32_t pos = 0;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        const bool hit = K[i] - lo < width;
+        const uint64_t mask = __ballot(hit);
+        if (mask != 0ull) {
+            const uint32_t to = pos + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            if (hit && to < (uint32_t)WAVE) slots[to] = K[i];
+            pos += (uint32_t)__popcll(mask);
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t c = small_sort64(lane < m ? slots[lane] : 0xFFFFFFFFu);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    *s0 = (uint32_t)__builtin_amdgcn_readlane((int)c, (int)((k0 - clo) & (WAVE - 1)));
+    *s1 = (uint32_t)__builtin_amdgcn_readlane((int)c, (int)((k1 - clo) & (WAVE - 1)));
+}
+
+// multi-signal rule on four mask bytes at once: primary bit set and at least min_signals
+// bits in the byte; the answer is bit 0 of each byte
+__device__ __forceinline__ uint32_t small_rule4(uint32_t E, uint32_t primary, uint32_t min_signals) {
+    uint32_t pc = E - ((E >> 1) & 0x55555555u);
+    pc = (pc & 0x33333333u) + ((pc >> 2) & 0x33333333u);
+    pc = (pc + (pc >> 4)) & 0x0F0F0F0Fu;
+    return ((E >> primary) & 0x01010101u) & ((pc + (0x80u - min_signals) * 0x01010101u) >> 7);
+}
+
+// FULL: R == ROWS * 256.  A workgroup for every step (no loop over steps: the compiler
+// would keep the sorts' lane masks in scalar registers across it, and spill them).
+template <int ROWS, bool FULL, bool WANT_Z>
+__device__ __forceinline__ void score_small(const gd_score_args& a) {
+    constexpr int V = ROWS * 4;
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const uint32_t R = a.R, N = a.N, M = a.M, RW = (R + 63) / 64, NWD = (N + 63) / 64;
+    const SmallLds<ROWS> lds(lds_raw, M);
+    const uint32_t lane = threadIdx.x & (WAVE - 1), m = rfl(threadIdx.x / WAVE);
+    const float thr = a.thr;
+    uint32_t dir_codes = 0;          // direction + 1 of metric i in bits 2i, 2i + 1
+#pragma unroll
+    for (int i = 0; i < 8; ++i) dir_codes |= (uint32_t)(a.dir[i] + 1) << (2 * i);
+    const int dir = (int)(rfl(dir_codes) >> (2u * m) & 3u) - 1;
+    const size_t t = blockIdx.x;
+    const size_t column = t * M + m;
+    const float* col = a.x + column * R;
+    auto holds = [&](int j) { return FULL || j * 256 + lane * 4 < R; };
+    float v[ROWS][4];
+#pragma unroll
+    for (int j = 0; j < ROWS; ++j) {
+        float4 q = make_float4(__uint_as_float(0x7FFFFFFFu), __uint_as_float(0x7FFFFFFFu),
+                               __uint_as_float(0x7FFFFFFFu), __uint_as_float(0x7FFFFFFFu));     // padding
+        if (holds(j)) q = *reinterpret_cast<const float4*>(col + j * 256 + lane * 4);
+        v[j][0] = q.x; v[j][1] = q.y; v[j][2] = q.z; v[j][3] = q.w;
+    }
+    // the lane's largest bit pattern: signs, missing samples (NaN) and magnitudes
+    uint32_t um = 0;
+#pragma unroll
+    for (int j = 0; j < ROWS; ++j) {
+        const uint32_t rm = max(max(__float_as_uint(v[j][0]), __float_as_uint(v[j][1])),
+                                max(__float_as_uint(v[j][2]), __float_as_uint(v[j][3])));
+        um = max(um, holds(j) ? rm : 0u);
+    }
+    const bool special = __ballot(um > 0x7F800000u) != 0ull;
+    uint32_t K[V], present = R;
+    if (!special) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) K[i] = __float_as_uint(v[i / 4][i % 4]) | 0x80000000u;
+    } else {
+        present = 0;
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            const float g = v[i / 4][i % 4] + 0.0f;              // -0 reads as +0
+            K[i] = g != g ? 0xFFFFFFFFu : key_of(g);
+            present += (uint32_t)__popcll(__ballot(g == g));
+        }
+    }
+    // one value of every lane, from all rows
+    auto sample_of = [&](const uint32_t (&k)[V]) {
+        if constexpr (ROWS == 1) return k[0];
+        else if constexpr (ROWS == 2) return __builtin_amdgcn_inverse_ballot_w64(lanes_with<32>()) ? k[4] : k[0];
+        else {
+            const bool odd = __builtin_amdgcn_inverse_ballot_w64(lanes_with<16>());
+            const uint32_t lower = odd ? k[4] : k[0], upper = odd ? k[12] : k[8];
+            return __builtin_amdgcn_inverse_ballot_w64(lanes_with<32>()) ? upper : lower;
+        }
+    };
+    float med = __uint_as_float(0x7FC00000u), mad = med;         // nothing to take a median of
+    if (present) {
+        const uint32_t k0 = (present - 1) / 2, k1 = present / 2;
+        uint32_t s0, s1;
+        wave_select<V>(K, sample_of(K), 0xFFFFFFFFu, present, k0, k1, lane, lds.slots + m * WAVE, &s0, &s1);
+        // (an odd count has one middle value: no sum that could overflow)
+        med = k0 == k1 ? float_of_key(s0) : 0.5f * (float_of_key(s0) + float_of_key(s1));
+#pragma unroll
+        for (int i = 0; i < V; ++i) K[i] = __float_as_uint(fabsf(v[i / 4][i % 4] - med));
+        wave_select<V>(K, sample_of(K), 0x7F800001u, present, k0, k1, lane, lds.slots + m * WAVE, &s0, &s1);
+        mad = k0 == k1 ? __uint_as_float(s0) : 0.5f * (__uint_as_float(s0) + __uint_as_float(s1));
+    }
+    if (lane == 0) { a.med[column] = med; a.mad[column] = mad; }
+    float s = 1.4826f * mad;
+    s = fmaxf(s, a.rel_floor * fabsf(med));
+    s = fmaxf(s, a.abs_floor);
+    // (as in score_columns: the quotient by the reciprocal is exact in this range)
+    const bool exact_recip = !special && __ballot(um > 0x5D000000u) == 0ull && med >= 0x1p-34f &&
+                             s >= 0x1p-60f && s <= 0x1p60f;
+    const float r1 = 1.0f / s;
+    if (WANT_Z) {
+        float* zcol = a.z + column * R;
+#pragma unroll
+        for (int j = 0; j < ROWS; ++j) {
+            float q[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float x = v[j][i];
+                if (exact_recip) {
+                    const float d = x - med;
+                    const float q0 = d * r1;
+                    const float e0 = __builtin_fmaf(-q0, s, d);
+                    const float q1 = __builtin_fmaf(e0, r1, q0);
+                    const float e1 = __builtin_fmaf(-q1, s, d);
+                    q[i] = __builtin_fmaf(e1, r1, q1);
+                } else {
+                    q[i] = x == x ? ((x + 0.0f) - med) / s : 0.0f;       // a missing sample scores 0
+                }
+            }
+            if (holds(j)) *reinterpret_cast<float4*>(zcol + j * 256 + lane * 4) = make_float4(q[0], q[1], q[2], q[3]);
+        }
+    }
+    const float ss = dir < 0 ? -s : s, rs = dir < 0 ? -r1 : r1;
+    const uint32_t absmask = dir == 0 ? 0x7FFFFFFFu : 0xFFFFFFFFu, sgnmask = dir < 0 ? 0x80000000u : 0u;
+    const bool fast = exact_recip && a.node_agg == 0;
+    float* nzrow = a.node_z + t * N;
+#pragma unroll
+    for (int j = 0; j < ROWS; ++j) {
+        uint32_t e;
+        float nz;
+        if (fast && dir != 0) score_row_fast<false>(v[j], med, ss, rs, thr, a.node_scale, &e, &nz);
+        else if (fast) score_row_fast<true>(v[j], med, ss, rs, thr, a.node_scale, &e, &nz);
+        else if (a.node_agg == 0) score_row<0>(v[j], med, s, absmask, sgnmask, thr, a.node_scale, &e, &nz);
+        else score_row<1>(v[j], med, s, absmask, sgnmask, thr, a.node_scale, &e, &nz);
+        lds.exceed[m * SmallLds<ROWS>::WORDS + j * WAVE + lane] = e;
+        const uint64_t nb = __ballot(nz > thr);
+        if (lane == 0) lds.node[m * ROWS + j] = nb;
+        if (m == a.primary && holds(j) && !(lane & 1)) nzrow[(j * 256 + lane * 4) / 8] = nz;
+    }
+    __syncthreads();
+    // The step's mask bytes and anomaly words: row c of 64 mask words per wave.
+    for (uint32_t c = m; c < (uint32_t)ROWS; c += M) {
+        const uint32_t q = c * WAVE + lane;
+        const bool valid = q * 4 < R;
+        uint32_t E = 0;
+        for (uint32_t i = 0; i < M; ++i) E |= lds.exceed[i * SmallLds<ROWS>::WORDS + q] << i;
+        if (valid) reinterpret_cast<uint32_t*>(a.exceed_mask + t * R)[q] = E;
+        const uint32_t an = valid ? small_rule4(E, a.primary, a.min_signals) : 0u;
+        const uint32_t nib = (an | (an >> 7) | (an >> 14) | (an >> 21)) & 0xFu;
+        const uint32_t sub = lane & 15;
+        uint32_t wlo = sub < 8 ? nib << (4 * sub) : 0u, whi = sub >= 8 ? nib << (4 * (sub - 8)) : 0u;
+        wlo |= gd_lane_xor<1>(wlo, lane); whi |= gd_lane_xor<1>(whi, lane);
+        wlo |= gd_lane_xor<2>(wlo, lane); whi |= gd_lane_xor<2>(whi, lane);
+        wlo |= gd_lane_xor<4>(wlo, lane); whi |= gd_lane_xor<4>(whi, lane);
+        wlo |= gd_lane_xor<8>(wlo, lane); whi |= gd_lane_xor<8>(whi, lane);
+        if (sub == 0 && valid) a.rank_anom[t * RW + q / 16] = ((uint64_t)whi << 32) | wlo;
+    }
+    for (uint32_t c = M - 1 - m; c < NWD; c += M) {              // (the waves with no row above first)
+        const uint32_t n = c * WAVE + lane;
+        uint32_t b = 0;
+        if (n < N)
+            for (uint32_t i = 0; i < M; ++i)
+                b |= (uint32_t)(lds.node[i * ROWS + n / 32] >> (2 * (n % 32)) & 1ull) << i;
+        if (n < N) a.node_mask[t * N + n] = (uint8_t)b;
+        const uint64_t word = __ballot(((b >> a.primary) & 1u) && (uint32_t)__popc(b) >= a.min_signals);
+        if (lane == 0) a.node_anom[t * NWD + c] = word;
+    }
+}
+
+#endif  // GD_SCORE_SMALL_H_
