@@ -1715,7 +1715,7 @@ constexpr size_t lds_bytes() {
     return ((sizeof(SH) + 15) & ~(size_t)15) + (size_t)ROWS * NT * 4;
 }
 
-// Up to 1 024 ranks: a workgroup per step, a wave per column, in short batches and long ones
+// Few ranks: a workgroup per step, a wave per column, in short batches and long ones
 // (launched in pieces, because a grid's threads have to fit 32 bits).
 template <int ROWS, bool FULL, bool SPLIT>
 hipError_t launch_small(gd_score_args a, hipStream_t s) {
@@ -1809,7 +1809,13 @@ hipError_t pick_tiling(const gd_score_args& a, hipStream_t s) {
     switch (a.R) {
         case 256: return launch<64, 1, 10>(a, n_cu, s);
         case 1024: return launch<64, 4, 10>(a, n_cu, s);
-        case 4096: return launch<256, 4, 11>(a, n_cu, s);
+        case 4096:
+            // One wave per column scores the M columns of a step side by side, 256 threads one
+            // after another: 4 000 ranks x 2 000 steps take 88 us against 118 with four metrics
+            // (64 steps: 35 against 63), with a single one 50 against 40 (64 steps: 34 against
+            // 19; the lines cross at about 8 000 steps).
+            if (a.M > 1 && !use_split(a, n_cu)) break;
+            return launch<256, 4, 11>(a, n_cu, s);
         case 16384: return launch<256, 16, 11, 1024, 4, 12>(a, n_cu, s);
         case 32768: return launch<512, 16, 12, 1024, 8, 12>(a, n_cu, s);
         case 65536: return launch<1024, 16, 12>(a, n_cu, s);
@@ -1833,8 +1839,8 @@ hipError_t pick_tiling(const gd_score_args& a, hipStream_t s) {
 #endif
 #endif
 
-// Ragged rank counts: the smallest tiling in steps of two rows (of one and two at the
-// smallest), so that no more than the last two rows hold padding.
+// Ragged rank counts: the smallest tiling in steps of two rows, so that no more than the
+// last two rows hold padding (one wave per column checks every row).
 #if GD_SCORE_RAGGED == 1
 
 hipError_t GD_RAGGED(gd_launch_ragged_few)(const gd_score_args& a, int n_cu, hipStream_t s) {
@@ -1842,7 +1848,9 @@ hipError_t GD_RAGGED(gd_launch_ragged_few)(const gd_score_args& a, int n_cu, hip
     if (R <= 256) return launch_runs<64, 1, 10, false>(a, n_cu, s);
     if (R <= 512) return launch_runs<64, 2, 10, false>(a, n_cu, s);
     if (R <= 1024) return launch_runs<64, 4, 10, false>(a, n_cu, s);
-    if (R <= 2048) return launch_runs<256, 2, 11, false>(a, n_cu, s);
+    if (R <= 2048) return launch_runs<64, 8, 10, false>(a, n_cu, s);
+    if (a.M > 1 && R <= 3072) return launch_runs<64, 12, 10, false>(a, n_cu, s);
+    if (a.M > 1 && R <= 4096) return launch_runs<64, 16, 10, false>(a, n_cu, s);
     if (R <= 4096) return launch_runs<256, 4, 11, false>(a, n_cu, s);
     if (R <= 6144) return launch_runs<256, 6, 11, false>(a, n_cu, s);
     return launch_runs<256, 8, 11, false>(a, n_cu, s);
@@ -1873,7 +1881,7 @@ hipError_t GD_RAGGED(gd_launch_ragged_columns)(const gd_score_args& a, hipStream
     if (R <= 256) return launch_columns<64, 1, 10, false>(a, s);
     if (R <= 512) return launch_columns<64, 2, 10, false>(a, s);
     if (R <= 1024) return launch_columns<64, 4, 10, false>(a, s);
-    if (R <= 2048) return launch_columns<256, 2, 11, false>(a, s);
+    if (R <= 2048) return launch_columns<64, 8, 10, false>(a, s);
     if (R <= 4096) return launch_columns<256, 4, 11, false>(a, s);
     if (R <= 8192) return launch_columns<1024, 2, 12, false>(a, s);
     if (R <= 16384) return launch_columns<1024, 4, 12, false>(a, s);

@@ -1,5 +1,6 @@
-// Scoring of small columns (up to 1 024 ranks): one wave per column, one workgroup of M
-// waves per step.  Included by score.hip, whose row functions it shares.
+// Scoring of small columns (up to 4 096 ranks): one wave per column, one workgroup of M
+// waves per step.  Included by score.hip, whose row functions it shares and whose launcher
+// draws the line to the histogram route.
 //
 // A column of 1 024 values is sixteen registers of one wave.  The histogram route spends
 // its time on fixed costs there (clearing, scanning and searching a thousand buckets, with
@@ -11,7 +12,8 @@
 // most 64 values are left between the pivots they are moved to one register and sorted by
 // lane exchanges.  The scalar unit adds up the counts while the vector unit compares.
 // Measured (launch): 1 024 x 2 000 x 4 112 -> 31 us, 1 000 x 1 x 4 (one step) 74 -> 9 us,
-// 64 x 200 x 1 22 -> 4.4 us.  Bound by instruction issue in batches, by the length of the
+// 64 x 200 x 1 22 -> 4.4 us; 2 048 x 2 000 x 4 120 -> 49 us, 3 000 x 2 000 x 4 116 -> 66 us,
+// 4 000 x 2 000 x 4 118 -> 88 us.  Bound by instruction issue in batches, by the length of the
 // chain (load, median, MAD, scores) in one-step calls.
 #ifndef GD_SCORE_SMALL_H_
 #define GD_SCORE_SMALL_H_
@@ -84,22 +86,76 @@ __device__ __forceinline__ uint32_t small_sort64(uint32_t v) {
     return small_merge<64>(v);
 }
 
-// The order statistics k0 <= k1 <= k0 + 1 of the n keys below `end` among the wave's K
-// (the others, padding and missing samples, are `end` or above).  Throughout, clo keys lie
+// Keys are worked out from the values whenever they are looked at: a second copy of the
+// column would double its registers, and the optimiser is kept from making one by the
+// token of each pass, a constant that it cannot see through.  Of a column without signs or NaNs: its bits.
+template <int ROWS>
+struct PlainKeys {
+    const float (&v)[ROWS][4];
+    static constexpr uint32_t END = 0x7F800001u;                     // (infinity is the largest key)
+    __device__ __forceinline__ uint32_t token() const { return 0u; }
+    __device__ __forceinline__ uint32_t at(int j, int i, uint32_t) const { return __float_as_uint(v[j][i]); }
+    __device__ __forceinline__ float value(uint32_t k) const { return __uint_as_float(k); }
+};
+// Of any other: an order-preserving image, -0 reading as +0, NaNs above everything.
+template <int ROWS>
+struct MappedKeys {
+    const float (&v)[ROWS][4];
+    static constexpr uint32_t END = 0xFFFFFFFFu;
+    __device__ __forceinline__ uint32_t token() const { return opaque_s(0u); }
+    __device__ __forceinline__ uint32_t at(int j, int i, uint32_t zero) const {
+        const float g = v[j][i] + __uint_as_float(zero);
+        return g != g ? 0xFFFFFFFFu : key_of(g);
+    }
+    __device__ __forceinline__ float value(uint32_t k) const { return float_of_key(k); }
+};
+// Distances from the median.
+template <int ROWS>
+struct DistanceKeys {
+    const float (&v)[ROWS][4];
+    float med;
+    static constexpr uint32_t END = 0x7F800001u;
+    __device__ __forceinline__ uint32_t token() const { return opaque_s(__float_as_uint(med)); }
+    __device__ __forceinline__ uint32_t at(int j, int i, uint32_t med_bits) const {
+        return __float_as_uint(fabsf(v[j][i] - __uint_as_float(med_bits)));
+    }
+    __device__ __forceinline__ float value(uint32_t k) const { return __uint_as_float(k); }
+};
+
+// One key of every lane, from all rows.
+template <int ROWS, typename Keys>
+__device__ __forceinline__ uint32_t small_sample(const Keys& keys) {
+    const uint32_t tok = keys.token();
+    if constexpr (ROWS == 1) return keys.at(0, 0, tok);
+    else if constexpr (ROWS == 2)
+        return __builtin_amdgcn_inverse_ballot_w64(lanes_with<32>()) ? keys.at(1, 0, tok) : keys.at(0, 0, tok);
+    else {
+        constexpr int STEP = ROWS / 4;
+        const bool odd = __builtin_amdgcn_inverse_ballot_w64(lanes_with<16>());
+        const uint32_t lower = odd ? keys.at(STEP, 0, tok) : keys.at(0, 0, tok);
+        const uint32_t upper = odd ? keys.at(3 * STEP, 0, tok) : keys.at(2 * STEP, 0, tok);
+        return __builtin_amdgcn_inverse_ballot_w64(lanes_with<32>()) ? upper : lower;
+    }
+}
+
+// The order statistics k0 <= k1 <= k0 + 1 of the n keys below Keys::END among the wave's
+// (the others, padding and missing samples, are END or above).  Throughout, clo keys lie
 // under lo and chi under hi, with clo <= k0 and k1 < chi.  Ends for any contents: a round
 // narrows [lo, hi) to a part of it, from the fourth on to a half.
-template <int V>
-__device__ __forceinline__ void wave_select(const uint32_t (&K)[V], uint32_t sample, uint32_t end, uint32_t n,
-                                            uint32_t k0, uint32_t k1, uint32_t lane, uint32_t* slots, uint32_t* s0,
-                                            uint32_t* s1) {
-    uint32_t lo = 0, hi = end, clo = 0, chi = n;
+template <int ROWS, typename Keys>
+__device__ __forceinline__ void wave_select(const Keys& keys, uint32_t n, uint32_t k0, uint32_t k1, uint32_t lane,
+                                            uint32_t* slots, uint32_t* s0, uint32_t* s1) {
+    constexpr int V = ROWS * 4;
+    uint32_t lo = 0, hi = Keys::END, clo = 0, chi = n;
     // two pivots, p <= q; true when one of them parts the two statistics (k0 < p <= k1)
     auto narrow = [&](uint32_t p, uint32_t q) -> bool {
         uint32_t cp = 0, cq = 0;
+        const uint32_t tok = keys.token();
 #pragma unroll
         for (int i = 0; i < V; ++i) {
-            cp += (uint32_t)__popcll(__ballot(K[i] < p));
-            cq += (uint32_t)__popcll(__ballot(K[i] < q));
+            const uint32_t k = keys.at(i / 4, i % 4, tok);
+            cp += (uint32_t)__popcll(__ballot(k < p));
+            cq += (uint32_t)__popcll(__ballot(k < q));
         }
         uint32_t part = 0;
         bool parted = false;
@@ -113,10 +169,12 @@ __device__ __forceinline__ void wave_select(const uint32_t (&K)[V], uint32_t sam
         take(q, cq);
         if (parted) {
             uint32_t mx = 0, mn = 0xFFFFFFFFu;
+            const uint32_t again = keys.token();
 #pragma unroll
             for (int i = 0; i < V; ++i) {
-                mx = max(mx, K[i] < part ? K[i] : 0u);
-                mn = min(mn, K[i] < part ? 0xFFFFFFFFu : K[i]);
+                const uint32_t k = keys.at(i / 4, i % 4, again);
+                mx = max(mx, k < part ? k : 0u);
+                mn = min(mn, k < part ? 0xFFFFFFFFu : k);
             }
             *s0 = (uint32_t)__builtin_amdgcn_readlane((int)wave_max_to_last(mx), WAVE - 1);
             *s1 = (uint32_t)__builtin_amdgcn_readlane((int)wave_min_to_last(mn), WAVE - 1);
@@ -125,7 +183,8 @@ __device__ __forceinline__ void wave_select(const uint32_t (&K)[V], uint32_t sam
     };
     if (n > (uint32_t)WAVE) {
         // around the middle of the sample: two standard deviations of its median's rank
-        const uint32_t ns = (uint32_t)__popcll(__ballot(sample < end));
+        const uint32_t sample = small_sample<ROWS>(keys);
+        const uint32_t ns = (uint32_t)__popcll(__ballot(sample < Keys::END));
         if (ns >= 16) {
             const uint32_t sorted = small_sort64(sample);
             const uint32_t reach = 4u + ns / 16u;
@@ -152,15 +211,17 @@ __device__ __forceinline__ void wave_select(const uint32_t (&K)[V], uint32_t sam
     }
     // at most 64 keys in [lo, hi)
     const uint32_t m = chi - clo, width = hi - lo;
+    const uint32_t tok = keys.token();
     uint32_t pos = 0;
 #pragma unroll
     for (int i = 0; i < V; ++i) {
-        const bool hit = K[i] - lo < width;
+        const uint32_t k = keys.at(i / 4, i % 4, tok);
+        const bool hit = k - lo < width;
         const uint64_t mask = __ballot(hit);
         if (mask != 0ull) {
             const uint32_t to = pos + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-            if (hit && to < (uint32_t)WAVE) slots[to] = K[i];
+            if (hit && to < (uint32_t)WAVE) slots[to] = k;
             pos += (uint32_t)__popcll(mask);
         }
     }
@@ -217,40 +278,30 @@ __device__ __forceinline__ void score_small(const gd_score_args& a) {
         um = max(um, holds(j) ? rm : 0u);
     }
     const bool special = __ballot(um > 0x7F800000u) != 0ull;
-    uint32_t K[V], present = R;
-    if (!special) {
-#pragma unroll
-        for (int i = 0; i < V; ++i) K[i] = __float_as_uint(v[i / 4][i % 4]) | 0x80000000u;
-    } else {
+    uint32_t present = R;
+    if (special) {
         present = 0;
 #pragma unroll
-        for (int i = 0; i < V; ++i) {
-            const float g = v[i / 4][i % 4] + 0.0f;              // -0 reads as +0
-            K[i] = g != g ? 0xFFFFFFFFu : key_of(g);
-            present += (uint32_t)__popcll(__ballot(g == g));
-        }
+        for (int i = 0; i < V; ++i) present += (uint32_t)__popcll(__ballot(v[i / 4][i % 4] == v[i / 4][i % 4]));
     }
-    // one value of every lane, from all rows
-    auto sample_of = [&](const uint32_t (&k)[V]) {
-        if constexpr (ROWS == 1) return k[0];
-        else if constexpr (ROWS == 2) return __builtin_amdgcn_inverse_ballot_w64(lanes_with<32>()) ? k[4] : k[0];
-        else {
-            const bool odd = __builtin_amdgcn_inverse_ballot_w64(lanes_with<16>());
-            const uint32_t lower = odd ? k[4] : k[0], upper = odd ? k[12] : k[8];
-            return __builtin_amdgcn_inverse_ballot_w64(lanes_with<32>()) ? upper : lower;
-        }
-    };
-    float med = __uint_as_float(0x7FC00000u), mad = med;         // nothing to take a median of
+    float med = __uint_as_float(0x7FC00000u), mad = med;             // nothing to take a median of
     if (present) {
         const uint32_t k0 = (present - 1) / 2, k1 = present / 2;
+        uint32_t* const slots = lds.slots + m * WAVE;
         uint32_t s0, s1;
-        wave_select<V>(K, sample_of(K), 0xFFFFFFFFu, present, k0, k1, lane, lds.slots + m * WAVE, &s0, &s1);
         // (an odd count has one middle value: no sum that could overflow)
-        med = k0 == k1 ? float_of_key(s0) : 0.5f * (float_of_key(s0) + float_of_key(s1));
-#pragma unroll
-        for (int i = 0; i < V; ++i) K[i] = __float_as_uint(fabsf(v[i / 4][i % 4] - med));
-        wave_select<V>(K, sample_of(K), 0x7F800001u, present, k0, k1, lane, lds.slots + m * WAVE, &s0, &s1);
-        mad = k0 == k1 ? __uint_as_float(s0) : 0.5f * (__uint_as_float(s0) + __uint_as_float(s1));
+        if (!special) {
+            const PlainKeys<ROWS> keys{v};
+            wave_select<ROWS>(keys, present, k0, k1, lane, slots, &s0, &s1);
+            med = 0.5f * (keys.value(s0) + keys.value(s1));          // (R is even)
+        } else {
+            const MappedKeys<ROWS> keys{v};
+            wave_select<ROWS>(keys, present, k0, k1, lane, slots, &s0, &s1);
+            med = k0 == k1 ? keys.value(s0) : 0.5f * (keys.value(s0) + keys.value(s1));
+        }
+        const DistanceKeys<ROWS> keys{v, med};
+        wave_select<ROWS>(keys, present, k0, k1, lane, slots, &s0, &s1);
+        mad = k0 == k1 ? keys.value(s0) : 0.5f * (keys.value(s0) + keys.value(s1));
     }
     if (lane == 0) { a.med[column] = med; a.mad[column] = mad; }
     float s = 1.4826f * mad;
