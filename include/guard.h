@@ -333,8 +333,7 @@ gd_status gd_update_ledger(gd_handle h, const uint8_t* d_exceed_mask, const uint
  * gd_update_ledger for callers that cannot allocate device memory or hand over a work
  * area: code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, same results in the ledger, same two kernels; their work
- * area (the episode-start map and the staged counts) is a static device array inside
- * the library, gd_ledger_static_scratch_bytes() = 8 MiB per GPU, held from the first
+ * area (the episode-start map) is a static device array inside the library, gd_ledger_static_scratch_bytes() = 8 MiB per GPU, held from the first
  * call on that GPU until the process ends.  The call itself allocates nothing, here or
  * in any library it uses.  The ledger may therefore be bound with max_T = 1; T is
  * limited by the array instead: align256(T * ceil(N/64) * 8) + 16 R + 18 N (rounded up

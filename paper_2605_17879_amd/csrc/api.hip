@@ -387,15 +387,9 @@ gd_status ledger_update_args(gd_handle h, const char* who, const uint8_t* d_exce
     gd_ledger_args& a = *out;
     a.led = h->d_led; a.lay = h->llay;
     a.rise = reinterpret_cast<uint64_t*>(h->d_led + h->llay.rise);
-    a.counts_new = h->d_led + h->llay.counts_new;
     a.exceed_mask = d_exceed_mask; a.node_mask = d_node_mask; a.node_z = d_node_z;
     a.T = T; a.R = h->cfg.n_ranks; a.N = h->N; a.W = h->cfg.window; a.K = h->cfg.persist_k;
     a.primary = h->cfg.primary_metric; a.min_signals = h->cfg.min_signals;
-    // A chunk rebuilds its starting counts from the W steps before it.  Chunks as
-    // short as the window double the steps read, but that part only counts (it is
-    // the cheaper half), and a long batch needs the workgroups: measured at 65 536
-    // ranks x 4 096 steps, W = 256: chunks of 2W 0.40 ms, of W 0.29 ms.
-    a.chunk = h->cfg.window < 128 ? 128 : h->cfg.window;
     a.limit = h->lcfg.recur_limit;
     a.quant = h->lcfg.score_quant;
     a.first_step = first_step_index; a.horizon = h->lcfg.recur_horizon;

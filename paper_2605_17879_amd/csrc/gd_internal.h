@@ -84,7 +84,7 @@ struct gd_ledger_layout {
     size_t rank_cnt;     // u16 [8][R]   per-metric window counts             } one span,
     size_t node_cnt;     // u16 [8][N]                                        } counts_bytes
     size_t node_ccnt;    // u16 [N]      window count of the per-step combined node anomaly  } long
-    size_t counts_new;   // the same span again: where a batch cut into chunks leaves its final counts
+    size_t counts_new;   // the same span again, not in use (the parts behind it stay where saved ledgers have them)
     size_t counts_bytes;
     size_t rank_first;   // u32 [R]      0xFFFFFFFF - first flagged step, 0 = never
     size_t node_first;   // u32 [N]
@@ -99,16 +99,14 @@ struct gd_ledger_layout {
 struct gd_ledger_args {
     uint8_t* led;
     gd_ledger_layout lay;
-    // The two spans that only serve the kernels of one call (not part of the ledger's
-    // contents): inside the caller's buffer at lay.rise / lay.counts_new, or in the
-    // library's own static device array for the entry point that may not allocate.
+    // The span that only serves the kernels of one call (not part of the ledger's contents):
+    // inside the caller's buffer at lay.rise, or in the library's own static device array for
+    // the entry point that may not allocate.
     uint64_t* rise;               // [NW][T] episode starts found in the batch
-    uint8_t* counts_new;          // lay.counts_bytes: final counts of a batch cut into chunks
     const uint8_t* exceed_mask;   // [T][R]
     const uint8_t* node_mask;     // [T][N]
     const float* node_z;          // [T][N]
     uint32_t T, R, N, W, K, primary, min_signals;
-    uint32_t chunk;               // steps per workgroup row of the counting kernel
     uint32_t limit;               // episodes that make a node terminal (1..8)
     float quant;
     uint64_t first_step, horizon;

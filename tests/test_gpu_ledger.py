@@ -243,3 +243,28 @@ def test_ledger_at_the_benchmark_size():
         np.bincount(want["episodes"]).tolist(), "terminal nodes", int((want["terminal"] >= 0).sum()))
     assert (want["terminal"] >= 0).any() and (want["ranks"].first >= 0).any()
     det.close()
+
+
+@pytest.mark.parametrize("batches", [[24, 25, 23], [63, 64, 65], [1, 127, 64], [130, 16, 46]])
+@pytest.mark.parametrize("W", [1, 63, 64, 65, 129])
+@pytest.mark.parametrize("N", [1, 3, 5, 64, 259])
+def test_batches_at_the_edges_of_the_step_blocks(N, W, batches):
+    """Batches one step under, at and over what is counted step by step and what fills a block
+    of 64 steps, with windows around whole blocks and node counts that fill no word of four."""
+    R, M, T = 8 * N, 3, sum(batches)
+    k = max(1, W // 2)
+    p = oracle_params(R=R, M=M, W=W, k=k, primary=1, min_signals=2, directions=(1,) * M)
+    seed = 31 * N + 7 * W + batches[0]
+    bursts = (max(1, W // 2), W + 9)
+    exceed = exceed_history(seed, T, R, M, 0.2, burst_items=max(1, R // 4), burst_len=bursts, gap_len=(1, W + 5),
+                            burst_metrics=M)
+    node_mask = exceed_history(seed + 3, T, N, M, 0.2, burst_items=max(1, N // 2), burst_len=bursts,
+                               gap_len=(1, W + 5), burst_metrics=M)
+    node_z = node_score_history(seed, T, N, scale=3.0)
+    node_anom = oracle.combine(node_mask, p.primary, p.min_signals)
+    want = oracle_ledger(p, exceed, node_mask, node_anom, node_z, 64.0, 50, 2, min(8, N))
+    det = detector_for(p)
+    det.alloc_ledger(max(batches), recur_horizon=50, recur_limit=2)
+    feed(det, exceed, node_mask, node_z, batches)
+    compare_ledger(want, read_ledger(det, min(8, N)), f"N{N}-W{W}")
+    det.close()
