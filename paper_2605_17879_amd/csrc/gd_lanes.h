@@ -35,4 +35,57 @@ __device__ __forceinline__ uint64_t gd_lane_xor64(uint64_t v, uint32_t lane) {
     return ((uint64_t)hi << 32) | lo;
 }
 
+// Which lanes keep the smaller key in the stage of distance J that merges runs of S: a
+// constant, so that it is a scalar literal and no lane works it out (nor keeps it in
+// registers from one sort to the next).
+template <int J, int S>
+constexpr uint64_t gd_keeps_smaller() {
+    uint64_t m = 0;
+    for (int l = 0; l < 64; ++l)
+        if (((l & J) == 0) == ((l & S) == 0)) m |= 1ull << l;
+    return m;
+}
+template <int BIT>
+constexpr uint64_t gd_lanes_with() {
+    uint64_t m = 0;
+    for (int l = 0; l < 64; ++l)
+        if (l & BIT) m |= 1ull << l;
+    return m;
+}
+
+// One compare-exchange stage across the wave.
+template <int J, int S>
+__device__ __forceinline__ uint32_t gd_exchange(uint32_t v) {
+    uint32_t o;
+    if constexpr (J == 16) {
+        auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        o = __builtin_amdgcn_inverse_ballot_w64(gd_lanes_with<16>()) ? r[0] : r[1];
+    } else if constexpr (J == 32) {
+        auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        o = __builtin_amdgcn_inverse_ballot_w64(gd_lanes_with<32>()) ? r[0] : r[1];
+    } else {
+        o = gd_lane_xor<J>(v, 0);
+    }
+    return __builtin_amdgcn_inverse_ballot_w64(gd_keeps_smaller<J, S>()) ? min(v, o) : max(v, o);
+}
+template <int S>
+__device__ __forceinline__ uint32_t gd_merge(uint32_t v) {
+    if constexpr (S > 32) v = gd_exchange<32, S>(v);
+    if constexpr (S > 16) v = gd_exchange<16, S>(v);
+    if constexpr (S > 8) v = gd_exchange<8, S>(v);
+    if constexpr (S > 4) v = gd_exchange<4, S>(v);
+    if constexpr (S > 2) v = gd_exchange<2, S>(v);
+    return gd_exchange<1, S>(v);
+}
+
+// 64 keys, one per lane, into ascending order.
+__device__ __forceinline__ uint32_t gd_sort64(uint32_t v) {
+    v = gd_merge<2>(v);
+    v = gd_merge<4>(v);
+    v = gd_merge<8>(v);
+    v = gd_merge<16>(v);
+    v = gd_merge<32>(v);
+    return gd_merge<64>(v);
+}
+
 #endif  // GD_LANES_H_

@@ -33,59 +33,6 @@ struct SmallLds {
     static constexpr size_t bytes(uint32_t M) { return (size_t)M * (ROWS * 8 + WORDS * 4 + WAVE * 4); }
 };
 
-// Which lanes keep the smaller key in the stage of distance J that merges runs of S: a
-// constant, so that it is a scalar literal and no lane works it out (nor keeps it in
-// registers from one sort to the next).
-template <int J, int S>
-constexpr uint64_t keeps_smaller() {
-    uint64_t m = 0;
-    for (int l = 0; l < WAVE; ++l)
-        if (((l & J) == 0) == ((l & S) == 0)) m |= 1ull << l;
-    return m;
-}
-template <int BIT>
-constexpr uint64_t lanes_with() {
-    uint64_t m = 0;
-    for (int l = 0; l < WAVE; ++l)
-        if (l & BIT) m |= 1ull << l;
-    return m;
-}
-
-// One compare-exchange stage across the wave.
-template <int J, int S>
-__device__ __forceinline__ uint32_t small_exchange(uint32_t v) {
-    uint32_t o;
-    if constexpr (J == 16) {
-        auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-        o = __builtin_amdgcn_inverse_ballot_w64(lanes_with<16>()) ? r[0] : r[1];
-    } else if constexpr (J == 32) {
-        auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-        o = __builtin_amdgcn_inverse_ballot_w64(lanes_with<32>()) ? r[0] : r[1];
-    } else {
-        o = gd_lane_xor<J>(v, 0);
-    }
-    return __builtin_amdgcn_inverse_ballot_w64(keeps_smaller<J, S>()) ? min(v, o) : max(v, o);
-}
-template <int S>
-__device__ __forceinline__ uint32_t small_merge(uint32_t v) {
-    if constexpr (S > 32) v = small_exchange<32, S>(v);
-    if constexpr (S > 16) v = small_exchange<16, S>(v);
-    if constexpr (S > 8) v = small_exchange<8, S>(v);
-    if constexpr (S > 4) v = small_exchange<4, S>(v);
-    if constexpr (S > 2) v = small_exchange<2, S>(v);
-    return small_exchange<1, S>(v);
-}
-
-// 64 keys, one per lane, into ascending order.
-__device__ __forceinline__ uint32_t small_sort64(uint32_t v) {
-    v = small_merge<2>(v);
-    v = small_merge<4>(v);
-    v = small_merge<8>(v);
-    v = small_merge<16>(v);
-    v = small_merge<32>(v);
-    return small_merge<64>(v);
-}
-
 // Keys are worked out from the values whenever they are looked at: a second copy of the
 // column would double its registers, and the optimiser is kept from making one by the
 // token of each pass, a constant that it cannot see through.  Of a column without signs or NaNs: its bits.
@@ -128,13 +75,13 @@ __device__ __forceinline__ uint32_t small_sample(const Keys& keys) {
     const uint32_t tok = keys.token();
     if constexpr (ROWS == 1) return keys.at(0, 0, tok);
     else if constexpr (ROWS == 2)
-        return __builtin_amdgcn_inverse_ballot_w64(lanes_with<32>()) ? keys.at(1, 0, tok) : keys.at(0, 0, tok);
+        return __builtin_amdgcn_inverse_ballot_w64(gd_lanes_with<32>()) ? keys.at(1, 0, tok) : keys.at(0, 0, tok);
     else {
         constexpr int STEP = ROWS / 4;
-        const bool odd = __builtin_amdgcn_inverse_ballot_w64(lanes_with<16>());
+        const bool odd = __builtin_amdgcn_inverse_ballot_w64(gd_lanes_with<16>());
         const uint32_t lower = odd ? keys.at(STEP, 0, tok) : keys.at(0, 0, tok);
         const uint32_t upper = odd ? keys.at(3 * STEP, 0, tok) : keys.at(2 * STEP, 0, tok);
-        return __builtin_amdgcn_inverse_ballot_w64(lanes_with<32>()) ? upper : lower;
+        return __builtin_amdgcn_inverse_ballot_w64(gd_lanes_with<32>()) ? upper : lower;
     }
 }
 
@@ -186,7 +133,7 @@ __device__ __forceinline__ void wave_select(const Keys& keys, uint32_t n, uint32
         const uint32_t sample = small_sample<ROWS>(keys);
         const uint32_t ns = (uint32_t)__popcll(__ballot(sample < Keys::END));
         if (ns >= 16) {
-            const uint32_t sorted = small_sort64(sample);
+            const uint32_t sorted = gd_sort64(sample);
             const uint32_t reach = 4u + ns / 16u;
             const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)sorted, (int)(ns / 2 - reach));
             const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)sorted, (int)min(ns / 2 + reach, ns - 1)) + 1u;
@@ -227,7 +174,7 @@ __device__ __forceinline__ void wave_select(const Keys& keys, uint32_t n, uint32
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    const uint32_t c = small_sort64(lane < m ? slots[lane] : 0xFFFFFFFFu);
+    const uint32_t c = gd_sort64(lane < m ? slots[lane] : 0xFFFFFFFFu);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     *s0 = (uint32_t)__builtin_amdgcn_readlane((int)c, (int)((k0 - clo) & (WAVE - 1)));
