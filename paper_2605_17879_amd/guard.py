@@ -174,6 +174,7 @@ class Detector:
             raise GuardError(st, (self.lib.gd_last_error(None) or b"").decode())
         self.h = h
         self.device = torch.device(device)
+        self._raw_stream = torch._C._cuda_getCurrentRawStream
         self.R, self.M = cfg.n_ranks, cfg.n_metrics
         self.N = self.R // cfg.gpus_per_node
         self.RW, self.NW = (self.R + 63) // 64, (self.N + 63) // 64
@@ -197,8 +198,12 @@ class Detector:
             raise GuardError(st, (self.lib.gd_last_error(self.h) or b"").decode())
 
     def _stream(self, stream) -> int:
-        s = stream if stream is not None else self._torch.cuda.current_stream(self.device)
-        return s.cuda_stream
+        if stream is not None:
+            return stream.cuda_stream
+        # The current stream's handle alone: building the Stream object around it took longer
+        # than the rest of a call's marshalling, and a small job's calls are bound by that.
+        index = self.device.index
+        return self._raw_stream(self._torch.cuda.current_device() if index is None else index)
 
     # ---- the C ABI, one method per entry point --------------------------------
     def state_bytes(self) -> int:
