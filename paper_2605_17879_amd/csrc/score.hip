@@ -57,6 +57,9 @@ __device__ __forceinline__ float float_of_key(uint32_t k) {
     return __uint_as_float(b);
 }
 
+// Ranks whose exceed bits one workgroup of combine_kernel puts together.
+constexpr uint32_t PLANE_RANKS = 2048;
+
 template <int NT, int LOG_NB, int MAX_NODES>
 struct Shared {
     static constexpr int NB = 1 << LOG_NB;
@@ -1051,8 +1054,8 @@ __device__ __forceinline__ void score_row_decide(const float (&x)[4], uint32_t x
 // 60 -> 45 us; 65 528 ranks take 600 us where 65 536 take 583.
 // SPLIT (short batches, the streaming case): one workgroup per column instead of
 // per run of steps, so that the M columns of a step are scored side by side.  The
-// exceed bits of a column are then OR-ed into the (zeroed) mask outputs in global
-// memory and combine_kernel applies the multi-signal rule afterwards.
+// exceed bits of a column then go out as bit planes and combine_kernel makes the mask
+// bytes of them and applies the multi-signal rule.
 template <int NT, int ROWS, int LOG_NB, bool FULL, bool SPLIT, bool WANT_Z>
 __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     constexpr int TAIL = FULL ? ROWS : (ROWS > 2 ? ROWS - 2 : 0);     // first row that may hold padding
@@ -1489,19 +1492,24 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     const uint32_t to = fresh_tid4();
     uint8_t* erow = a.exceed_mask + t * R;
     if (SPLIT) {
-        // this column's bits join those of the step's other columns in global memory
-        // (R and N are multiples of 4 here, the outputs word-aligned: see the launcher)
+        // This column's exceed bits go out as bit planes, for combine_kernel to put together:
+        // those of PLANE_RANKS ranks as M planes in the mask bytes of these ranks, those of
+        // their nodes in their anomaly words (eight planes fit either).
+        uint8_t* const wrow8 = reinterpret_cast<uint8_t*>(a.rank_anom + t * RW);
 #pragma unroll
         for (int j = 0; j < ROWS; ++j) {
-            if (!holds(j, to)) continue;
-            const uint32_t Ej = emask[j * NT + to / 4];
-            if (Ej) atomicOr(reinterpret_cast<uint32_t*>(erow + rbase(j, to)), Ej);
-            const uint32_t nb = (NE[j / 4] >> (8 * (j & 3))) & 0xFFu;
-            if (nb && !(to & 4)) {
-                const size_t nidx = t * N + rbase(j, to) / 8;
-                atomicOr(reinterpret_cast<uint32_t*>(a.node_mask + (nidx & ~(size_t)3)),
-                         nb << (8 * (uint32_t)(nidx & 3)));
-            }
+            const bool valid = holds(j, to);
+            const uint32_t r = rbase(j, to), Ej = valid ? (emask[j * NT + to / 4] >> m_begin) & 0x01010101u : 0u;
+            const uint32_t nib = (Ej | (Ej >> 7) | (Ej >> 14) | (Ej >> 21)) & 0xFu;
+            const uint32_t byte = nib | (lane_xor<1>(nib) << 4);              // (lanes 2p and 2p + 1: one node's ranks)
+            const uint32_t r0 = r & ~(PLANE_RANKS - 1u), here = min(PLANE_RANKS, R - r0);
+            if (valid && !(to & 4)) erow[r0 + (m_begin * here + (r - r0)) / 8] = (uint8_t)byte;
+            // eight nodes, the even ones of sixteen lanes, make a byte
+            uint32_t nb = valid && !(to & 4) ? ((NE[j / 4] >> (8 * (j & 3) + m_begin)) & 1u) << ((to >> 3) & 7u) : 0u;
+            nb |= lane_xor<2>(nb);
+            nb |= lane_xor<4>(nb);
+            nb |= lane_xor<8>(nb);
+            if (valid && (to & 63u) == 0) wrow8[r0 / 8 + m_begin * ((here + 63) / 64) + (r - r0) / 64] = (uint8_t)nb;
         }
         return;
     }
@@ -1619,51 +1627,72 @@ constexpr auto kernel_of() {
     else return &score_ragged_kernel<NT, ROWS, LOG_NB, SPLIT, WANT_Z_HERE>;
 }
 
-// Split route, before the columns are scored: the mask outputs start at zero.
-// (A fill kernel rather than a memset, so that a caller may capture the call.)
-__global__ __launch_bounds__(256) void zero_masks_kernel(uint32_t* exceed_words, size_t n_exceed,
-                                                         uint32_t* node_words, size_t n_node) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n_exceed) exceed_words[i] = 0;
-    if (i < n_node) node_words[i] = 0;
+// Eight bytes of eight bits: bit j of byte i becomes bit i of byte j.
+__device__ __forceinline__ uint64_t transpose8x8(uint64_t x) {
+    uint64_t t = (x ^ (x >> 7)) & 0x00AA00AA00AA00AAull;
+    x ^= t ^ (t << 7);
+    t = (x ^ (x >> 14)) & 0x0000CCCC0000CCCCull;
+    x ^= t ^ (t << 14);
+    t = (x ^ (x >> 28)) & 0x00000000F0F0F0F0ull;
+    return x ^ t ^ (t << 28);
 }
 
-// Split route, after the columns: the multi-signal rule (primary bit set and at
-// least min_signals bits) on the finished mask bytes.  blockIdx.y = step; a
-// thread takes four ranks (one mask word), 16 lanes make one 64-bit word.
-__global__ __launch_bounds__(256) void combine_kernel(const gd_score_args a) {
-    const uint32_t t = blockIdx.y, lane = threadIdx.x & (WAVE - 1);
-    const uint32_t R = a.R, N = a.N;
+// Split route, after the columns: mask bytes and anomaly words from the columns' bit planes,
+// which lie where they go (see score_columns): a workgroup has read all the planes of its
+// PLANE_RANKS ranks, a thread those of eight, when it writes the first byte.  Latency-bound
+// (one round of loads, one of stores).  The planes spare the zeroing launch and the atomics
+// that merged the columns' bits before (one step of 32 768 ranks x 8: 2.0 + 14.4 + 4.0 us in
+// three launches, now 15.8 + 4.0 in two), and whole words per step, without which a call took the
+// route of long batches (14 072 x 8: 118 -> 26 us a call).  One workgroup per step, which
+// needs no order of the planes, took 12 us for this.
+__global__ __launch_bounds__(PLANE_RANKS / 8) void combine_kernel(const gd_score_args a) {
+    const uint32_t tid = threadIdx.x, sl = tid & 7u, R = a.R, N = a.N, M = a.M;
     const uint32_t RW = (R + 63) / 64, NWD = (N + 63) / 64;
-    const uint32_t q = blockIdx.x * 256 + threadIdx.x;          // mask word index in the step
-    if ((q & ~63u) * 4 < R) {                                   // some lane of this wave has ranks
-        const bool valid = q * 4 < R;
-        const uint32_t Ej = valid ? reinterpret_cast<const uint32_t*>(a.exceed_mask + (size_t)t * R)[q] : 0u;
-        const uint32_t prim_set = (Ej >> a.primary) & 0x01010101u;
-        uint32_t pc = Ej - ((Ej >> 1) & 0x55555555u);
-        pc = (pc & 0x33333333u) + ((pc >> 2) & 0x33333333u);
-        pc = (pc + (pc >> 4)) & 0x0F0F0F0Fu;
-        const uint32_t enough = ((pc + (0x80u - a.min_signals) * 0x01010101u) >> 7) & 0x01010101u;
-        const uint32_t an = prim_set & enough;
-        const uint32_t nib = (an | (an >> 7) | (an >> 14) | (an >> 21)) & 0xFu;
-        const uint32_t sub = lane & 15;
-        uint32_t wlo = sub < 8 ? nib << (4 * sub) : 0u;
-        uint32_t whi = sub >= 8 ? nib << (4 * (sub - 8)) : 0u;
+    const uint32_t r0 = blockIdx.x * PLANE_RANKS, here = min(PLANE_RANKS, R - r0);
+    const uint32_t groups = here / 8, nbytes = (here + 63) / 64;      // (eight ranks, one node each; bytes of a node plane)
+    const size_t t = blockIdx.y;
+    uint8_t* const mask = a.exceed_mask + t * R + r0;
+    uint64_t* const words = a.rank_anom + t * RW + r0 / 64;
+    uint64_t ranks = 0, nodes = 0;                              // byte m: plane m
+#pragma unroll
+    for (uint32_t m = 0; m < 8; ++m) {
+        if (m < M && tid < groups) ranks |= (uint64_t)mask[m * groups + tid] << (8 * m);
+        if (m < M && tid < nbytes) nodes |= (uint64_t)reinterpret_cast<const uint8_t*>(words)[m * nbytes + tid] << (8 * m);
+    }
+    // (every load has arrived before the first store of any wave)
+    asm volatile("" : "+v"(ranks), "+v"(nodes));
+    __syncthreads();
+    const uint32_t min_signals = a.min_signals, primary = a.primary;
+    // the rule on eight bytes: bit j of the answer for byte j
+    auto rule8 = [&](uint64_t E) -> uint32_t {
+        const uint32_t lo = small_rule4((uint32_t)E, primary, min_signals);
+        const uint32_t hi = small_rule4((uint32_t)(E >> 32), primary, min_signals);
+        return ((lo | (lo >> 7) | (lo >> 14) | (lo >> 21)) & 0xFu) |
+               (((hi | (hi >> 7) | (hi >> 14) | (hi >> 21)) & 0xFu) << 4);
+    };
+    // eight lanes' bytes make a word
+    auto word_of = [&](uint32_t byte) -> uint64_t {
+        uint32_t wlo = sl < 4u ? byte << (8u * sl) : 0u, whi = sl >= 4u ? byte << (8u * (sl - 4u)) : 0u;
         wlo |= lane_xor<1>(wlo); whi |= lane_xor<1>(whi);
         wlo |= lane_xor<2>(wlo); whi |= lane_xor<2>(whi);
         wlo |= lane_xor<4>(wlo); whi |= lane_xor<4>(whi);
-        wlo |= lane_xor<8>(wlo); whi |= lane_xor<8>(whi);
-        if (sub == 0 && valid) a.rank_anom[(size_t)t * RW + q / 16] = ((uint64_t)whi << 32) | wlo;
+        return ((uint64_t)whi << 32) | wlo;
+    };
+    const uint64_t E = transpose8x8(ranks);                     // (0 beyond the last rank)
+    const uint64_t w = word_of(rule8(E));
+    if (tid < groups) {
+        reinterpret_cast<uint32_t*>(mask + 8 * tid)[0] = (uint32_t)E;
+        reinterpret_cast<uint32_t*>(mask + 8 * tid)[1] = (uint32_t)(E >> 32);
+        if (sl == 0) words[tid / 8] = w;
     }
-    const uint32_t n = blockIdx.x * 256 + threadIdx.x;
-    if ((n & ~63u) < N) {
-        bool an = false;
-        if (n < N) {
-            const uint32_t b = a.node_mask[(size_t)t * N + n];
-            an = ((b >> a.primary) & 1u) && (uint32_t)__popc(b) >= a.min_signals;
-        }
-        const uint64_t word = __ballot(an);
-        if (lane == 0) a.node_anom[(size_t)t * NWD + n / 64] = word;
+    const uint64_t F = transpose8x8(nodes);
+    const uint64_t v = word_of(rule8(F));
+    if (tid < nbytes) {
+        uint8_t* const nm = a.node_mask + t * N + r0 / 8 + 8 * tid;      // (at any address)
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i)
+            if (8 * tid + i < groups) nm[i] = (uint8_t)(F >> (8 * i));
+        if (sl == 0) a.node_anom[t * NWD + r0 / 512 + tid / 8] = v;
     }
 }
 
@@ -1702,11 +1731,9 @@ int compute_units(hipError_t* err) {
     return n_cu;
 }
 
-// One workgroup per column needs whole mask words per step (R, N multiples of 4,
-// word-aligned outputs) and pays off while the columns fit the chip side by side.
+// One workgroup per column pays off while the columns fit the chip side by side.
 bool use_split(const gd_score_args& a, int n_cu) {
-    return a.split_steps > 0 && a.T <= a.split_steps && (uint64_t)a.T * a.M <= (uint64_t)n_cu &&
-           a.R % 32 == 0 && ((uintptr_t)a.node_mask & 3) == 0;
+    return a.split_steps > 0 && a.T <= a.split_steps && (uint64_t)a.T * a.M <= (uint64_t)n_cu;
 }
 
 template <int NT, int ROWS, int LOG_NB>
@@ -1761,7 +1788,7 @@ hipError_t launch_runs(const gd_score_args& a, int n_cu, hipStream_t s) {
     }
 }
 
-// A short batch: one workgroup per column between the fill and the combining kernel.
+// A short batch: one workgroup per column, then the combining kernel.
 template <int NT, int ROWS, int LOG_NB, bool FULL>
 hipError_t launch_columns(const gd_score_args& a, hipStream_t s) {
     if constexpr (NT == WAVE) return launch_small<ROWS, FULL, true>(a, s);
@@ -1776,12 +1803,8 @@ hipError_t launch_columns(const gd_score_args& a, hipStream_t s) {
         if (e != hipSuccess) return e;
         configured = true;
     }
-    const size_t n_exceed = (size_t)a.T * a.R / 4, n_node = (size_t)a.T * a.N / 4;
-    hipLaunchKernelGGL(zero_masks_kernel, dim3((uint32_t)((n_exceed + 255) / 256)), dim3(256), 0, s,
-                       reinterpret_cast<uint32_t*>(a.exceed_mask), n_exceed,
-                       reinterpret_cast<uint32_t*>(a.node_mask), n_node);
     hipLaunchKernelGGL(kern, dim3(a.T * a.M), dim3(NT), lds, s, a);
-    hipLaunchKernelGGL(combine_kernel, dim3((a.R / 4 + 255) / 256, a.T), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(combine_kernel, dim3((a.R + PLANE_RANKS - 1) / PLANE_RANKS, a.T), dim3(PLANE_RANKS / 8), 0, s, a);
     return hipGetLastError();
     }
 }
