@@ -664,7 +664,39 @@ struct HintedResult {
     uint32_t umax;              // largest raw bit pattern of the column
     uint32_t m0, m1;            // the two middle keys
     uint32_t q0, q1;            // the two middle distances (bit patterns)
+    uint32_t present;           // samples that arrived, where some did not (0: all did)
 };
+
+// How many of the column's values are no NaNs, and their largest bit pattern (of a column
+// without sign bits).  The work area is at rest before and after; two barriers.
+template <int ROWS, typename SH>
+__device__ __forceinline__ void count_present(SH& sh, const float (&v)[ROWS][4], uint32_t* present, uint32_t* top) {
+    const uint32_t tid = opaque_v(threadIdx.x), lane = tid & (WAVE - 1);
+    // (tested on the bit patterns, against an opaque constant: other tests of the same
+    // registers must not be merged with these and kept for later)
+    const uint32_t absm = opaque_s(0x7FFFFFFFu);
+    uint32_t np = 0, um = 0;
+#pragma unroll
+    for (int j = 0; j < ROWS; ++j) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t b = __float_as_uint(v[j][i]);
+            const bool here = (b & absm) <= 0x7F800000u;
+            np += here ? 1u : 0u;
+            um = max(um, here ? b : 0u);
+        }
+        asm volatile("" : "+v"(np), "+v"(um));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    np = wave_incl_scan(np);
+    um = wave_max_to_last(um);
+    if (lane == WAVE - 1) { atomicAdd(&sh.ncand, np); atomicMax(&sh.smax, um); }
+    __syncthreads();
+    *present = rfl(sh.ncand);
+    *top = rfl(sh.smax);
+    __syncthreads();                    // everyone has read them
+    if (tid == 0) { sh.ncand = 0; sh.smax = 0; }
+}
 
 // Padding lanes (of the last rows of a ragged rank count) hold another lane's value until
 // `set_padding(j)` makes them NaN patterns: over the bracket in the count, never within a
@@ -674,7 +706,7 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
                                                       uint32_t hint_lo, uint32_t hint_hi, float mad_hint,
                                                       uint32_t k0, uint32_t k1, uint32_t* umax_slot,
                                                       uint32_t par) {
-    HintedResult out = {0, 0u, 0u, 0u, 0u, 0u};
+    HintedResult out = {0, 0u, 0u, 0u, 0u, 0u, 0u};
     constexpr int NB = 1 << LOG_NB;
     constexpr uint32_t KEY_LIMIT = 0x7D000000u;    // beyond it the signed bucket arithmetic could wrap
     const uint32_t span0 = hint_hi - hint_lo;
@@ -720,6 +752,14 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
     const uint32_t tid = opaque_v(threadIdx.x), lane = tid & (WAVE - 1), w = rfl(tid >> 6);
     const uint32_t umax = rfl(*umax_slot);
     out.umax = umax;
+    uint32_t top = umax;                   // (of the samples that arrived)
+    if (__builtin_expect(umax > 0x7F800000u && umax < 0x80000000u, 0)) {
+        // missing samples (NaNs): counted over the bracket like any large value, they only
+        // move the ranks asked for
+        count_present(sh, v, &out.present, &top);
+        k0 = out.present ? (out.present - 1) / 2 : 0u;
+        k1 = out.present / 2;
+    }
     // the lane-private words: everything under the bracket is `below`
     if (w == 0) {
         uint32_t d = cnt[lane];
@@ -730,7 +770,7 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
     if (w == 1u) cnt[64 + NB + lane] = 0;
     uint32_t below;
     const bool bracketed = locate<NT, LOG_NB, true, true>(sh, tid, k0, k1, &below);
-    if (umax > KEY_LIMIT || !bracketed || shift < 2) return out;
+    if (top > KEY_LIMIT || !bracketed || shift < 2) return out;
     const uint32_t ba = rfl(sh.res[0]), pa = rfl(sh.res[1]);
     const uint32_t bb = rfl(sh.res[2]), pb = rfl(sh.res[3]);
     if (pb - pa > (uint32_t)CAND_CAP / 2 || bb - ba > 1u) return out;      // crowded (ties): the general route narrows
@@ -765,6 +805,7 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
     const uint32_t s0 = rfl(sh.res[4]), s1 = rfl(sh.res[5]);
     out.m0 = s0; out.m1 = s1;
     out.found = 1;
+    out.umax = top;
     const float med = 0.5f * (__uint_as_float(s0) + __uint_as_float(s1));
     if (!(mad_hint > 0.0f)) return out;
     // ---- MAD: search the prefix sums.  Candidate c is the right edge e_c (a bucket's lower
@@ -891,24 +932,30 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
 // pass of the hinted selection confirms them, so raw bit patterns serve as keys whatever
 // the column holds.  Thread 0 writes the hints of metric m; ends with a barrier, the work
 // area at rest.
-// (valid: this thread's row 0 holds ranks; n: how many values that makes in all)
+// (valid: this thread's row 0 holds ranks; missing samples are left out)
 template <int NT, int LOG_NB, typename SH>
-__device__ __forceinline__ void sample_hints(SH& sh, const float (&row)[4], bool valid, uint32_t n, uint32_t m) {
+__device__ __forceinline__ void sample_hints(SH& sh, const float (&row)[4], bool valid, uint32_t m) {
     constexpr int BPT = (1 << LOG_NB) / NT;
     const uint32_t tid = opaque_v(threadIdx.x), lane = tid & (WAVE - 1);
     uint32_t k[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) k[i] = __float_as_uint(row[i]);
-    const uint32_t mn = wave_min_to_last(valid ? min(min(k[0], k[1]), min(k[2], k[3])) : 0xFFFFFFFFu);
-    const uint32_t mx = wave_max_to_last(valid ? max(max(k[0], k[1]), max(k[2], k[3])) : 0u);
+    uint32_t mn = 0xFFFFFFFFu, mx = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const bool in = valid && (k[i] & 0x7FFFFFFFu) <= 0x7F800000u;
+        mn = in ? min(mn, k[i]) : mn;
+        mx = in ? max(mx, k[i]) : mx;
+    }
+    mn = wave_min_to_last(mn);
+    mx = wave_max_to_last(mx);
     if (lane == WAVE - 1) { atomicMin(&sh.smin, mn); atomicMax(&sh.smax, mx); }
     __syncthreads();
     const uint32_t smin = rfl(sh.smin), smax = rfl(sh.smax);
     const int sshift = shift_for<LOG_NB>(smax - smin);
-    if (valid) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) atomicAdd(&sh.hist[(k[i] - smin) >> sshift], 1u);
-    }
+    for (int i = 0; i < 4; ++i)
+        if (valid && (k[i] & 0x7FFFFFFFu) <= 0x7F800000u) atomicAdd(&sh.hist[(k[i] - smin) >> sshift], 1u);
     __syncthreads();
     if (tid == 0) { sh.smin = 0xFFFFFFFFu; sh.smax = 0; }
     uint32_t loc[BPT], sum = 0;
@@ -916,8 +963,8 @@ __device__ __forceinline__ void sample_hints(SH& sh, const float (&row)[4], bool
     for (int q = 0; q < BPT; ++q) { loc[q] = sh.hist[tid * BPT + q]; sum += loc[q]; }
 #pragma unroll
     for (int q = 0; q < BPT; ++q) sh.hist[tid * BPT + q] = 0;
-    uint32_t total;
-    const uint32_t excl = block_excl_scan<NT>(sum, tid, sh.wpart, &total);
+    uint32_t n;
+    const uint32_t excl = block_excl_scan<NT>(sum, tid, sh.wpart, &n);
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
         const uint32_t want = (uint32_t)(r + 1) * (n / 4) - excl;      // sample ranks n/4, n/2, 3n/4
@@ -932,7 +979,7 @@ __device__ __forceinline__ void sample_hints(SH& sh, const float (&row)[4], bool
         }
     }
     __syncthreads();
-    if (tid == 0) {
+    if (tid == 0 && n != 0) {
         const uint32_t half = (1u << sshift) >> 1;
         const float q25 = __uint_as_float(smin + (sh.res[0] << sshift) + half);
         const float q50 = __uint_as_float(smin + (sh.res[1] << sshift) + half);
@@ -1182,7 +1229,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         // (the first step of a run has no predecessor: a sample of the column stands in)
         bool boot = false;
         if (t == t_begin && rfl(sh.hok[m]) == 0) {
-            sample_hints<NT, LOG_NB>(sh, v[0], svalid, 4u * nsample, m);
+            sample_hints<NT, LOG_NB>(sh, v[0], svalid, m);
             boot = true;
         }
         bool hinted = rfl(sh.hok[m]) != 0;
@@ -1198,6 +1245,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         uint32_t s0 = 0, s1 = 0;
         float med = 0.0f;
         bool have_mad = false;
+        uint32_t missing = 0;                   // the samples that arrived, where some did not (hinted selection)
         // The hinted selection (sign-free column, a predecessor's bracket and MAD): median and
         // MAD in three light passes.  Whatever it does not settle goes
         // through the general route below.
@@ -1219,6 +1267,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
                 med = 0.5f * (__uint_as_float(hr.m0) + __uint_as_float(hr.m1));
                 have_mad = hsel == 2;
                 s0 = hr.q0; s1 = hr.q1;
+                missing = hr.present;
                 if (tid == 0) sh.hmed[m] = med;
             }
         }
@@ -1281,28 +1330,16 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         if (tid == 0) { sh.umax[colpar ^ 1u] = 0; sh.mres[colpar ^ 1u][3] = 0; }
         colpar ^= 1u;
         uint32_t present = R;
+        if (__builtin_expect(missing != 0, 0)) { present = missing; k0 = (present - 1) / 2; k1 = present / 2; }
         if (__builtin_expect(special, 0)) {
             if (tid == 0) sh.hok[m] = 0;
-            __syncthreads();    // (a counting pass given up above has just reset sh.below)
-            // samples present (padding lanes hold NaNs too): median and MAD are taken
-            // over them alone, the middle one(s) of `present`
-            // (tested on the bit patterns, against an opaque constant: the score loop's own
-            // tests of the same registers must not be merged with these and kept for later)
-            uint32_t np = 0;
-            const uint32_t absm = opaque_s(0x7FFFFFFFu);
-#pragma unroll
-            for (int j = 0; j < ROWS; ++j) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) np += (__float_as_uint(v[j][i]) & absm) <= 0x7F800000u ? 1u : 0u;
-                asm volatile("" : "+v"(np));
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            np = wave_incl_scan(np);
-            if (lane == WAVE - 1 && np) atomicAdd(&sh.below, np);
+            __syncthreads();    // (a counting pass given up above has just reset its counters)
+            // median and MAD are taken over the samples present alone (padding lanes hold NaNs
+            // too): the middle one(s) of `present`
+            uint32_t top;
+            count_present(sh, v, &present, &top);
             __syncthreads();
-            present = rfl(sh.below);
-            __syncthreads();                    // everyone has read the count
-            if (tid == 0) sh.below = 0;
+            if (umax < 0x80000000u) { umax = top; missing = present; }      // (no signs)
             k0 = present ? (present - 1) / 2 : 0u;
             k1 = present / 2;
             if (present) {
@@ -1323,6 +1360,12 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
             a.med[t * M + m] = med;
             a.mad[t * M + m] = mad;
             if (hsel) sh.hmad[m] = mad;         // the hinted selection follows median and MAD step by step
+            // a column with missing samples, but no signs, leads the next step's selection too
+            if (hsel == 0 && missing != 0 && med > 0.0f && mad > 0.0f && med < 3.0e38f && mad < 3.0e38f) {
+                sh.hmed[m] = med; sh.hmad[m] = mad;
+                sh.hwl[m] = 1.25f * mad; sh.hwh[m] = 1.25f * mad;
+                sh.hok[m] = 1;
+            }
             // (from here on the reach is the exact MAD's, as after the general route)
             if (boot && hsel == 2) { sh.hwl[m] = 1.25f * mad; sh.hwh[m] = 1.25f * mad; }
         }
@@ -1335,6 +1378,22 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         // would be a load from memory, and a wait for it, in every column)
         const int dir = (int)((dir_codes >> (2u * m)) & 3u) - 1;
         const bool prim = m == a.primary;
+        // Missing samples take the median's place once it is known: their score is then the +0
+        // that a missing sample counts with, and (with a threshold that is not negative) never
+        // exceeds, so that the column is scored like any other.  Of a primary metric that
+        // falls the zero would be negative; signs leave the fast routes anyway.
+        if (__builtin_expect(missing != 0, 0)) {
+          special = !(thr >= 0.0f && a.node_agg == 0 && (!prim || dir >= 0) && med < 3.0e38f);
+          if (!special) {
+            const uint32_t absm = opaque_s(0x7FFFFFFFu);
+#pragma unroll
+            for (int j = 0; j < ROWS; ++j) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[j][i] = (__float_as_uint(v[j][i]) & absm) <= 0x7F800000u ? v[j][i] : med;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+          }
+        }
         const uint32_t tz = fresh_tid4();
         float* nzrow = a.node_z + t * N;
         // The reciprocal route is exact while no intermediate can leave the normal
