@@ -84,6 +84,29 @@ __device__ __forceinline__ uint32_t gd_planes_reach(const uint32_t (&a)[NP], uin
     return c;
 }
 
+// a + (2^NP - K), one plane more: its last plane says which counts have reached K (1 <= K <= 2^NP).
+template <int NP>
+__device__ __forceinline__ void gd_planes_bias(const uint32_t (&a)[NP], uint32_t K, uint32_t (&v)[NP + 1]) {
+    const uint32_t add = (1u << NP) - K;
+    uint32_t c = 0;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) gd_full_add(a[p], (add >> p) & 1u ? 0xFFFFFFFFu : 0u, c, &v[p], &c);
+    v[NP] = c;
+}
+
+// One step of every series: `in` enters its count, `out` leaves it.  Counting down is counting
+// up on the complement, so both are one chain of two instructions a plane.
+template <int NP>
+__device__ __forceinline__ void gd_planes_step(uint32_t (&v)[NP], uint32_t in, uint32_t out) {
+    uint32_t c = in ^ out;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const uint32_t t = c & (v[p] ^ out);
+        v[p] ^= c;
+        c = t;
+    }
+}
+
 // the count of series `bit` in lane `lane`'s planes, for the whole wave
 template <int NP>
 __device__ __forceinline__ uint32_t gd_planes_count(const uint32_t (&a)[NP], int lane, uint32_t bit) {

@@ -14,9 +14,13 @@
 // window that ends where a block begins is then W / 64 whole blocks and the tail of one
 // more, a handful of bit-sliced additions.  An item can only reach k inside a block if
 // its count at the block's start plus everything that enters does, and if it had not
-// reached it already: the few (block, word) pairs left by that test are walked by the
-// wave, one lane per step (two ballots give an item's entering and leaving bits as
-// 64-bit time vectors).
+// reached it already.  Where that test leaves a few words of a block, the wave walks them
+// item by item, one lane per step (two ballots give an item's entering and leaving bits as
+// 64-bit time vectors).  Where it leaves many -- ranks that fall behind together, counts that
+// hover about k -- every lane takes its own word through the 64 steps, all items at once and
+// still in bit slices (walk_all), which costs the same whatever the number of items: 65 536
+// ranks x 1 024 steps, a third of them flagged at one step, 17 us, where the walk
+// by item takes 396 (13 with nothing flagged).
 //
 // A workgroup takes a stretch of blocks and loads the W / 64 blocks before it once more.
 // Stretches are as short as the window allows (four blocks at least): the loads are
@@ -24,8 +28,8 @@
 // CUs as there are stretches (one workgroup per tile over all steps: 26.6 us where this
 // takes 18).  Only the first stretch looks at the ring (the others begin W steps or
 // more into the batch), so it also stores the ring's new words, behind its own last
-// read; the last stretch stores the counts, which nobody reads; the first flagged step
-// is kept by compare-and-swap.
+// read; the last stretch stores the counts, which nobody reads.  The first flagged steps
+// are kept by compare-and-swap (gathered in LDS first where there are many).
 //
 // The form before this one gave every 64 items a wave that walked all steps in order,
 // transposing 64 x 64 bits across its lanes: one wave per SIMD at 65 536 ranks and far
@@ -44,6 +48,11 @@ constexpr uint32_t TILE = WAVE;          // 32-bit words of a workgroup's tile
 constexpr uint32_t MIN_STRETCH = 4, MAX_STRETCH = 16;      // blocks of 64 steps
 constexpr uint32_t MAX_HISTORY = 16;     // blocks that a window of 1 024 steps reaches back
 constexpr int WIN_MAX_NT = 1024;
+// Words of a block, and items of a word, up to which candidates are walked item by item: a
+// word costs about a microsecond that way (its loads) and an item a tenth, walk_all about
+// five in all.
+constexpr int FEW_WORDS = 4, FEW_ITEMS = 8;
+constexpr uint32_t FOUND_PITCH = TILE + 1;                 // (items in order and lanes side by side: no bank conflicts)
 
 // Where one kind of item (ranks or nodes) lives.
 struct WindowItems {
@@ -86,6 +95,73 @@ __global__ __launch_bounds__(WIN_NT) void window_step_kernel(const gd_window_arg
     if ((item & 31) == 0) *slot = in;
 }
 
+// The first flagged step (+1, 0 = never) of an item becomes `step` unless it is an earlier one
+// already, of an earlier batch or another block of this one.
+__device__ __forceinline__ void lower_first(int32_t* to, int32_t step) {
+    int32_t was = 0;
+    while (was == 0 || was > step) {                                   // (ends: the stored step only ever falls)
+        const int32_t now = atomicCAS(to, was, step);
+        if (now == was) break;
+        was = now;
+    }
+}
+
+// The candidates `cand` of one block, all at once: a lane takes its word's 32 items from their
+// counts at the block's start through the 64 steps and notes, in bit slices again, the step at
+// which each reaches K first.  Those steps (of the batch) lower found[item's bit][lane].
+__device__ __forceinline__ void walk_all(const WindowItems& it, const uint32_t (&c)[GD_COUNT_PLANES], uint32_t cand,
+                                         uint32_t start, int32_t first, uint32_t T, uint32_t W, uint32_t K,
+                                         uint32_t wc, uint32_t lane, uint32_t* found) {
+    uint32_t v[GD_COUNT_PLANES + 1];
+    gd_planes_bias(c, K, v);
+    // (lane j works out the rows of step j, as in the counting of the blocks)
+    const uint32_t s = start + lane;
+    const int32_t o = (int32_t)s - (int32_t)W;
+    const bool ok = s < T, old = ok && (o >= 0 || first + o >= 0);
+    const uint32_t* enters = it.anom + (ok ? (size_t)s * it.row : 0);
+    const uint32_t* leaves = it.anom + (old && o >= 0 ? (size_t)(uint32_t)o * it.row : 0);
+    if (old && o < 0) leaves = it.ring + (size_t)((uint32_t)(first + o) % W) * it.row;
+    const uint64_t in_valid = __ballot(ok), out_valid = __ballot(old);
+    const uint32_t elo = (uint32_t)(uintptr_t)enters, ehi = (uint32_t)((uintptr_t)enters >> 32);
+    const uint32_t llo = (uint32_t)(uintptr_t)leaves, lhi = (uint32_t)((uintptr_t)leaves >> 32);
+    uint32_t open = cand, at[6] = {};                // items not found yet; bit slices of the steps
+#pragma unroll 1
+    for (int g = 0; g < 8; ++g) {
+        uint32_t in[8], out[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int l = 8 * g + j;
+            const uint32_t e0 = (uint32_t)__builtin_amdgcn_readlane((int)elo, l), e1 = (uint32_t)__builtin_amdgcn_readlane((int)ehi, l);
+            const uint32_t l0 = (uint32_t)__builtin_amdgcn_readlane((int)llo, l), l1 = (uint32_t)__builtin_amdgcn_readlane((int)lhi, l);
+            in[j] = reinterpret_cast<const uint32_t*>((uintptr_t)e1 << 32 | e0)[wc];
+            out[j] = reinterpret_cast<const uint32_t*>((uintptr_t)l1 << 32 | l0)[wc];
+        }
+        const uint32_t in_on = (uint32_t)(in_valid >> (8 * g)), out_on = (uint32_t)(out_valid >> (8 * g));
+        const uint32_t before = open;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            gd_planes_step(v, in[j] & (uint32_t)((int32_t)(in_on << (31 - j)) >> 31),
+                           out[j] & (uint32_t)((int32_t)(out_on << (31 - j)) >> 31));
+            const uint32_t hit = v[GD_COUNT_PLANES] & open;      // (past the last step nothing changes any more)
+            open &= ~hit;
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+                if ((j >> p) & 1) at[p] |= hit;
+        }
+        const uint32_t hits = before & ~open;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) at[3 + p] |= (g >> p) & 1 ? hits : 0u;
+        if (__ballot(open != 0) == 0) break;
+    }
+    for (uint32_t bits = cand & ~open; bits; bits &= bits - 1) {
+        const uint32_t bit = (uint32_t)__builtin_ctz(bits);
+        uint32_t step = 0;
+#pragma unroll
+        for (int p = 0; p < 6; ++p) step |= ((at[p] >> bit) & 1u) << p;
+        atomicMin(&found[bit * FOUND_PITCH + lane], start + step);
+    }
+}
+
 // A batch.  blockIdx.y: tile of words (ranks first), blockIdx.x: stretch of `stretch`
 // blocks (stretch * 64 >= W where there is more than one).  Dynamic LDS: planes of every
 // slot -- a block of the stretch or one of the few before it -- and word.
@@ -93,6 +169,8 @@ __global__ __launch_bounds__(WIN_MAX_NT) void window_blocks_kernel(const gd_wind
                                                                     uint32_t stretch) {
     extern __shared__ uint32_t lds[];
     __shared__ uint32_t final_planes[GD_COUNT_PLANES][TILE];
+    __shared__ uint32_t found[32 * FOUND_PITCH];       // first flagged step of the tile's items in this stretch
+    __shared__ uint32_t walked;
     const bool is_node = blockIdx.y >= rank_tiles;
     const WindowItems it = window_items(a, is_node);
     const uint32_t w0 = (is_node ? blockIdx.y - rank_tiles : blockIdx.y) * TILE;
@@ -162,6 +240,8 @@ __global__ __launch_bounds__(WIN_MAX_NT) void window_blocks_kernel(const gd_wind
             for (int p = 0; p < GD_BLOCK_PLANES - 1; ++p) o[(GD_BLOCK_PLANES + p) * TILE] = end[p];      // (at most 63)
         }
     }
+    if (tid == 0) walked = 0;
+    for (uint32_t x = tid; x < 32 * FOUND_PITCH; x += nt) found[x] = 0xFFFFFFFFu;
     // The ring's new words (the batch's last min(T, W) steps) are the first stretch's to
     // store: some of them are fetched now.
     const uint32_t keep = T < W ? T : W;
@@ -207,7 +287,13 @@ __global__ __launch_bounds__(WIN_MAX_NT) void window_blocks_kernel(const gd_wind
         }
         const uint32_t cand = mine ? gd_planes_reach(u, K) & ~gd_planes_reach(c, K) : 0u;
         const int32_t start = (int32_t)(s0 + b * 64), s = start + (int32_t)lane;       // this lane's step in a walk
-        for (uint64_t todo = __ballot(cand != 0); todo; todo &= todo - 1) {
+        uint64_t todo = __ballot(cand != 0);
+        if (__builtin_expect(__popcll(todo) > FEW_WORDS || __ballot(__popc(cand) > FEW_ITEMS) != 0, 0)) {
+            walk_all(it, c, cand, (uint32_t)start, first, T, W, K, wc, lane, found);
+            if (lane == 0) walked = 1;
+            todo = 0;
+        }
+        for (; todo; todo &= todo - 1) {
             const int src = __builtin_ctzll(todo);
             const uint32_t w = w0 + (uint32_t)src;
             uint32_t enters = 0, leaves = 0;
@@ -217,8 +303,7 @@ __global__ __launch_bounds__(WIN_MAX_NT) void window_blocks_kernel(const gd_wind
                 if (o >= 0) leaves = it.anom[(size_t)(uint32_t)o * row + w];
                 else if (first + o >= 0) leaves = it.ring[(size_t)((uint32_t)(first + o) % W) * row + w];
             }
-            // items flagged before this batch are left alone (a later step is one that another
-            // stretch has just found), as are those beyond the last one
+            // items flagged before this batch are left alone, as are those beyond the last one
             const uint32_t item = w * 32 + (lane & 31);
             const int32_t seen = item < it.n ? it.first[item] : 1;
             const uint32_t done = (uint32_t)__ballot(item >= it.n || (seen != 0 && seen <= first));
@@ -229,21 +314,17 @@ __global__ __launch_bounds__(WIN_MAX_NT) void window_blocks_kernel(const gd_wind
                 const uint32_t cnt = gd_planes_count(c, src, bit) + (uint32_t)__popcll(in & upto) -
                                      (uint32_t)__popcll(out & upto);
                 const uint64_t reach = __ballot(cnt >= K && s < (int32_t)T);
-                if (reach && lane == 0) {
-                    int32_t* to = &it.first[w * 32 + bit];
-                    const int32_t found = first + start + __builtin_ctzll(reach) + 1;
-                    int32_t was = 0;
-                    while (was == 0 || was > found) {                  // (ends: the stored step only ever falls)
-                        const int32_t now = atomicCAS(to, was, found);
-                        if (now == was) break;
-                        was = now;
-                    }
-                }
+                if (reach && lane == 0) lower_first(&it.first[w * 32 + bit], first + start + __builtin_ctzll(reach) + 1);
             }
         }
     }
+    __syncthreads();                                                   // (and the ring has been read for the last time)
+    for (uint32_t x = walked ? tid : TILE * 32; x < TILE * 32; x += nt) {
+        const uint32_t at = found[(x % 32) * FOUND_PITCH + x / 32], item = w0 * 32 + x;
+        if (at == 0xFFFFFFFFu || item >= it.n) continue;
+        lower_first(&it.first[item], first + (int32_t)at + 1);
+    }
     if (!last && s0 != 0) return;
-    __syncthreads();                                                   // (the ring has been read for the last time)
     if (last) {
         for (uint32_t x = tid; x < TILE * 32; x += nt) {
             const uint32_t item = w0 * 32 + x;
@@ -328,7 +409,8 @@ hipError_t gd_launch_window(const gd_window_args& a, hipStream_t s) {
     static bool configured = false;          // (a repeated set is harmless)
     if (!configured) {
         constexpr size_t most = (size_t)(2 * GD_BLOCK_PLANES - 1) * (MAX_HISTORY + MAX_STRETCH + 1) * TILE * 4;
-        static_assert(most + sizeof(uint32_t) * GD_COUNT_PLANES * TILE <= 160 * 1024, "LDS budget of one CU");
+        static_assert(most + sizeof(uint32_t) * (GD_COUNT_PLANES * TILE + 32 * FOUND_PITCH) <= 160 * 1024,
+                      "LDS budget of one CU");
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(window_blocks_kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
         if (e != hipSuccess) return e;

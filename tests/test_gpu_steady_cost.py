@@ -1,0 +1,53 @@
+"""Inputs whose answers take more looking for must not cost many times what plain ones do:
+both are timed in turn in this process, so that only their ratio counts.  The bounds lie
+far from what either form of a kernel takes, with the ratios measured beside them."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_harness import detector_for, oracle_params
+
+pytestmark = pytest.mark.gpu
+
+
+def device_us(prepare, call, n=7):
+    """The median device time of `call` behind an untimed `prepare`."""
+    got = []
+    for _ in range(n + 2):
+        prepare()
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        ev[0].record()
+        call()
+        ev[1].record()
+        torch.cuda.synchronize()
+        got.append(1e3 * ev[0].elapsed_time(ev[1]))
+    return sorted(got[2:])[n // 2]
+
+
+def packed(bits):
+    T, n = bits.shape
+    padded = np.zeros((T, (n + 63) // 64 * 64), np.uint8)
+    padded[:, :n] = bits
+    words = np.packbits(padded.reshape(T, -1, 64), axis=2, bitorder="little").view(np.int64).reshape(T, -1)
+    return torch.from_numpy(words.copy()).cuda()
+
+
+@pytest.mark.parametrize("kind", ["fall behind together", "come and go", "hover"])
+@pytest.mark.parametrize("R,T,W,k", [(65536, 1024, 256, 200), (16384, 2048, 20, 15), (1024, 2000, 100, 80)])
+def test_window_of_many_items_flagged(R, T, W, k, kind):
+    """Measured, 65 536 ranks: 13 us with nothing flagged; many items at once by the walk of
+    one item after another 396, 733 and 1 179 us, in bit slices 16, 18 and 26 us."""
+    rng = np.random.default_rng(R)
+    quiet = rng.random((T, R), dtype=np.float32) < 0.01
+    sick = rng.random(R) < 0.3
+    t = np.arange(T)[:, None]
+    many = {"fall behind together": quiet | (sick & (t > T // 3)), "come and go": quiet | (sick & (t // W % 2 == 0)),
+            "hover": rng.random((T, R), dtype=np.float32) < k / W}[kind]
+    us = []
+    for bits in (quiet, many):
+        det = detector_for(oracle_params(R=R, M=1, W=W, k=k, min_signals=1))
+        out = dict(rank_anom=packed(bits), node_anom=packed(bits[:, ::8]), node_z=torch.zeros((T, R // 8), device="cuda"))
+        us.append(device_us(det.state.zero_, lambda: det.update_window(out, T, 0)))
+        det.close()
+    print(f"{kind}, {R} ranks: {us[0]:.1f} us quiet, {us[1]:.1f} us many", flush=True)
+    assert us[1] < 8 * us[0]

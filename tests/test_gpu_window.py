@@ -57,3 +57,33 @@ def test_batches_around_blocks_tiles_and_stretches(R, W, k, batches):
         t0 += c
     compare_decision(p, d, det, top, label=f"R={R} W={W} k={k} {batches}")
     det.close()
+
+
+@pytest.mark.parametrize("R,W,k,T", [(2056, 64, 30, 700), (4096, 65, 60, 641), (65536, 256, 200, 900), (1024, 100, 80, 703)])
+@pytest.mark.parametrize("share", [0.002, 0.05, 0.6])
+def test_items_flagged_together(R, W, k, T, share):
+    """Few and many candidates of a block: walked item by item, or all items at once.  Some fall
+    behind at one step, some in the last, partial block, some come and go; a second batch
+    finds most of them flagged already."""
+    print(f"case flagged together R={R} W={W} k={k} T={T} share={share}", flush=True)
+    rng = np.random.default_rng(R + W + int(1000 * share))
+    N, t = R // 8, np.arange(2 * T)[:, None]
+
+    def history(n):
+        kind = rng.permutation(np.where(rng.random(n) < share, rng.integers(1, 5, n), 0))[None]
+        noise = rng.random((2 * T, n), dtype=np.float32) < 0.02
+        return noise | ((kind == 1) & (t > T // 3)) | ((kind == 2) & (t > T - k - 3)) | \
+            ((kind == 3) & (t // W % 2 == 0)) | ((kind == 4) & (rng.random((2 * T, n), dtype=np.float32) < k / W))
+
+    ra, na = _words(history(R)), _words(history(N))
+    p = oracle_params(R=R, M=1, W=W, k=k, min_signals=1)
+    pr, pn = oracle.window(R, ra, W, k), oracle.window(N, na, W, k)
+    node_z = rng.standard_normal((2 * T, N)).astype(np.float32)
+    d = dict(ranks=pr, nodes=pn, node_flag_byte=oracle.node_flag_byte(8, pn.flag, pr.flag))
+    d["topk_idx"], d["topk_key"] = oracle.topk(pn.count, node_z[-1], min(N, 64))
+    det = detector_for(p, topk=min(N, 64))
+    for a in (0, T):
+        det.update_window({name: torch.from_numpy(v[a:a + T]).cuda() for name, v in
+                           (("rank_anom", ra.view(np.int64)), ("node_anom", na.view(np.int64)), ("node_z", node_z))}, T)
+    compare_decision(p, d, det, min(N, 64), label=f"together-{R}-{share}")
+    det.close()
