@@ -88,4 +88,34 @@ __device__ __forceinline__ uint32_t gd_sort64(uint32_t v) {
     return gd_merge<64>(v);
 }
 
+// Transpose of the 64x64 bit matrix whose row i is the word held by lane i:
+// afterwards bit j of lane i is what bit i of lane j was.  For every index bit
+// K the rows and columns exchange that bit (a butterfly with the lane i ^ K).
+template <int K>
+__device__ __forceinline__ uint64_t gd_transpose_stage(uint64_t x, uint32_t lane) {
+    constexpr uint64_t m = K == 32 ? 0x00000000FFFFFFFFull
+                         : K == 16 ? 0x0000FFFF0000FFFFull
+                         : K == 8  ? 0x00FF00FF00FF00FFull
+                         : K == 4  ? 0x0F0F0F0F0F0F0F0Full
+                         : K == 2  ? 0x3333333333333333ull
+                                   : 0x5555555555555555ull;
+    const uint64_t p = gd_lane_xor64<K>(x, lane);
+    if ((lane & K) == 0) {
+        const uint64_t t = ((x >> K) ^ p) & m;
+        return x ^ (t << K);
+    }
+    const uint64_t t = ((p >> K) ^ x) & m;
+    return x ^ t;
+}
+
+__device__ __forceinline__ uint64_t gd_transpose64(uint64_t x, uint32_t lane) {
+    x = gd_transpose_stage<32>(x, lane);
+    x = gd_transpose_stage<16>(x, lane);
+    x = gd_transpose_stage<8>(x, lane);
+    x = gd_transpose_stage<4>(x, lane);
+    x = gd_transpose_stage<2>(x, lane);
+    x = gd_transpose_stage<1>(x, lane);
+    return x;
+}
+
 #endif  // GD_LANES_H_

@@ -31,13 +31,16 @@
 // read; the last stretch stores the counts, which nobody reads.  The first flagged steps
 // are kept by compare-and-swap (gathered in LDS first where there are many).
 //
-// The form before this one gave every 64 items a wave that walked all steps in order,
-// transposing 64 x 64 bits across its lanes: one wave per SIMD at 65 536 ranks and far
-// fewer below, waiting for its loads and lane exchanges.  Measured: 65 536 ranks x
-// 4 096 steps 52.5 -> 18 us (57 MB loaded in 9 of them), 16 384 x 10 000 117 -> 11.8 us,
-// 1 024 x 2 000 29.4 -> 8.1 us; the smallest, 64 x 200, 5.3 -> 5.9 us.
+// Measured against the kernel of short batches: 65 536 ranks x 4 096 steps 52.5 -> 18 us
+// (57 MB loaded in 9 of them), 16 384 x 10 000 117 -> 11.8 us, 1 024 x 2 000 29.4 -> 8.1 us.
+//
+// Short batches (window_short_kernel) start from the stored counts instead of the whole
+// window: every 64 items have a wave that walks the batch in order, 64 steps at a time,
+// transposing 64 x 64 bits across its lanes (one wave per SIMD at 65 536 ranks and fewer
+// below, waiting for its loads and lane exchanges).
 // One step per call (window_step_kernel) needs none of this: a thread per item.
 #include "gd_internal.h"
+#include "gd_lanes.h"
 #include "gd_planes.h"
 
 namespace {
@@ -48,6 +51,7 @@ constexpr uint32_t TILE = WAVE;          // 32-bit words of a workgroup's tile
 constexpr uint32_t MIN_STRETCH = 4, MAX_STRETCH = 16;      // blocks of 64 steps
 constexpr uint32_t MAX_HISTORY = 16;     // blocks that a window of 1 024 steps reaches back
 constexpr int WIN_MAX_NT = 1024;
+constexpr uint32_t SHORT_BATCH = 256;    // steps up to which a batch is walked in order, whatever the window
 // Words of a block, and items of a word, up to which candidates are walked item by item: a
 // word costs about a microsecond that way (its loads) and an item a tenth, walk_all about
 // five in all.
@@ -159,6 +163,74 @@ __device__ __forceinline__ void walk_all(const WindowItems& it, const uint32_t (
 #pragma unroll
         for (int p = 0; p < 6; ++p) step |= ((at[p] >> bit) & 1u) << p;
         atomicMin(&found[bit * FOUND_PITCH + lane], start + step);
+    }
+}
+
+// A short batch.  A thread owns one item and a wave one 64-item word of the rows, so every
+// ring word is read and written by a single wave.  Lane l of a block of 64 steps fetches the
+// word that enters at the block's step l and the word that leaves the window then; two bit
+// transposes across the lanes make them the item's own time vectors, so that the count takes
+// two popcounts a block, and only an item that may reach k inside the block walks its steps.
+__global__ __launch_bounds__(WIN_NT) void window_short_kernel(const gd_window_args a) {
+    const uint32_t rank_blocks = (a.R + WIN_NT - 1) / WIN_NT;
+    const bool is_node = blockIdx.x >= rank_blocks;
+    const WindowItems it = window_items(a, is_node);
+    const uint32_t item = (is_node ? blockIdx.x - rank_blocks : blockIdx.x) * WIN_NT + threadIdx.x;
+    const uint32_t lane = threadIdx.x & (WAVE - 1), words = it.row / 2, word = item / 64;
+    if (word >= words) return;                                  // the whole wave
+    const uint64_t* anom = reinterpret_cast<const uint64_t*>(it.anom);
+    uint64_t* ring = reinterpret_cast<uint64_t*>(it.ring);
+    const bool live = item < it.n;
+    const uint32_t W = a.W, K = a.K, T = a.T, first = (uint32_t)a.first_step;      // (first + T below 2^31)
+
+    // the entering and the leaving word of step s
+    auto fetch = [&](uint32_t s, uint64_t* win, uint64_t* wout) {
+        *win = 0; *wout = 0;
+        if (s >= T) return;
+        *win = anom[(size_t)s * words + word];
+        if (s >= W) *wout = anom[(size_t)(s - W) * words + word];
+        else if (first + s >= W) *wout = ring[(size_t)((first + s) % W) * words + word];
+    };
+
+    uint32_t c = live ? it.count[item] : 0;
+    int32_t f = live ? it.first[item] : 0;
+    constexpr uint32_t AHEAD = 4;                               // blocks fetched in advance
+    uint64_t win[AHEAD], wout[AHEAD];
+#pragma unroll
+    for (uint32_t q = 0; q < AHEAD; ++q) fetch(q * WAVE + lane, &win[q], &wout[q]);
+    for (uint32_t s0 = 0; s0 < T; s0 += AHEAD * WAVE) {
+#pragma unroll
+        for (uint32_t q = 0; q < AHEAD; ++q) {
+            const uint32_t sq = s0 + q * WAVE;                  // uniform over the wave
+            if (sq >= T) break;
+            // bit j: does this item enter / leave as anomalous at step sq + j
+            const uint64_t in = gd_transpose64(win[q], lane), out = gd_transpose64(wout[q], lane);
+            fetch(sq + AHEAD * WAVE + lane, &win[q], &wout[q]);
+            const uint32_t enters = (uint32_t)__popcll(in);
+            if (f == 0 && c + enters >= K) {                    // the flag may first rise inside this block
+                const uint32_t n = min((uint32_t)WAVE, T - sq);
+                for (uint32_t j = 0; j < n; ++j) {
+                    const uint64_t upto = (2ull << j) - 1;
+                    if (c + __popcll(in & upto) - __popcll(out & upto) >= K) {
+                        f = (int32_t)(first + sq + j) + 1;
+                        break;
+                    }
+                }
+            }
+            c += enters - (uint32_t)__popcll(out);
+        }
+    }
+    if (live) {
+        it.count[item] = (uint16_t)c;
+        it.first[item] = f;
+        if (is_node) reinterpret_cast<float*>(a.state + a.lay.node_z_last)[item] = a.node_z[(size_t)(T - 1) * a.N + item];
+    }
+    // The batch's last min(T, W) words become the ring's newest slots: every ring word has
+    // been read by now, and by this wave alone.
+    const uint32_t keep = T < W ? T : W;
+    for (uint32_t i = lane; i < keep; i += WAVE) {
+        const uint32_t s = T - keep + i;
+        ring[(size_t)((first + s) % W) * words + word] = anom[(size_t)s * words + word];
     }
 }
 
@@ -388,6 +460,18 @@ hipError_t gd_launch_window(const gd_window_args& a, hipStream_t s) {
     if (a.T == 1) {
         const uint32_t blocks = (a.R + WIN_NT - 1) / WIN_NT + (a.N + WIN_NT - 1) / WIN_NT;
         hipLaunchKernelGGL(window_step_kernel, dim3(blocks), dim3(WIN_NT), 0, s, a);
+        return hipGetLastError();
+    }
+    // Walking the steps costs by the step, and the more the more waves share a SIMD; the blocks
+    // load the whole window whatever the batch.  us by steps / by blocks, 65 536 ranks: window
+    // 1 024, 64 steps 5.2 / 13.5, 256 13.1 / 15.1, 512 22 / 20; window 256, 256 steps 12.9 / 12.0,
+    // 300 13.8 / 10.0; 16 384 ranks: window 512, 300 steps 9.9 / 12.7, 512 15.0 / 16.0, 700 18.2 /
+    // 14.9; window 1 024, 512 steps 14.8 / 19.5, 1 024 27 / 30; 64 ranks: window 256, 300 steps
+    // 6.8 / 9.7; window 511, 511 steps 9.9 / 18.5.
+    const uint32_t walked = a.W > SHORT_BATCH && a.R <= 32768 ? a.W : SHORT_BATCH;
+    if (a.T <= walked) {
+        const uint32_t blocks = (a.R + WIN_NT - 1) / WIN_NT + (a.N + WIN_NT - 1) / WIN_NT;
+        hipLaunchKernelGGL(window_short_kernel, dim3(blocks), dim3(WIN_NT), 0, s, a);
         return hipGetLastError();
     }
     const uint32_t rank_tiles = (2 * ((a.R + 63) / 64) + TILE - 1) / TILE;

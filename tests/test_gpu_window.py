@@ -22,6 +22,12 @@ CASES = [  # ranks, window, persist, batches
     (4104, 1024, 300, [1000, 24, 1, 2100, 64]),
     (520, 1023, 1023, [1100, 1, 1500]),
     (65536, 20, 15, [350, 1]),
+    # around the longest batch that is walked step by step, and whole blocks behind it
+    (64, 1, 1, [255, 256, 257, 320, 321]),
+    (2056, 63, 20, [257, 383, 256, 384, 2]),
+    (2040, 511, 100, [511, 512, 3, 576]),
+    (4104, 1024, 300, [1023, 1024, 1025, 64, 1]),
+    (32776, 300, 100, [256, 257, 300]),
 ]
 
 
