@@ -16,8 +16,12 @@
 // window of the default rule, a wave takes 64 steps of 64 neighbouring words and leaves
 // their sums as planes in LDS; the window that ends where a block of 64 steps begins is W /
 // 64 whole blocks and the tail of one more.  Per block the words tell which items may come
-// to satisfy the rule inside it (their counts at its start plus everything that enters);
-// those few are walked, one lane per step.  A third kind of tile follows the default rule's
+// to satisfy the rule inside it (their counts at its start plus everything that enters).
+// A few such words are walked one after another, one lane per step; where there are many --
+// ranks that fall behind together, counts that hover about k -- every lane takes its own word
+// through the 64 steps, still in bit slices (walk_all): 65 536 ranks x 512 steps, window 100, a
+// third of the ranks coming and going 173 -> 59 us, all hovering about k 497 -> 163 (35 with
+// nothing flagged).  A third kind of tile follows the default rule's
 // own count of the nodes (the rule applied to each step's bytes before they are summed) and
 // leaves one bit per (step, node) where an episode starts.  Every workgroup takes a stretch
 // of blocks and loads the few before it once more (from the ring at the batch's start), so
@@ -34,6 +38,7 @@
 // score sums are brought up to date, and a lane per node walks the episode starts in step
 // order.
 #include "gd_internal.h"
+#include "gd_lanes.h"
 #include "gd_planes.h"
 
 namespace {
@@ -242,6 +247,110 @@ struct WordPlace {
     }
 };
 
+// Words of a block up to which candidates are walked one after another: a word costs about a
+// microsecond that way (its loads), and a tenth for every item and metric; walk_all about seven
+// in all.
+constexpr int FEW_WORDS = 5;
+
+// A block's candidates, all at once: a lane takes its word's 32 series from their counts at the
+// block's start (c) through the 64 steps.  Per metric: the first step at which the rule holds
+// for an item of `cand` goes to first_of.  Default rule: where a node's count comes to reach K
+// its bit in this lane's step's word of `rise` is set.
+template <Tiles KIND>
+__device__ __forceinline__ void walk_all(const gd_ledger_args& a, const uint8_t* ring, const WordPlace& place,
+                                         const uint32_t (&c)[GD_COUNT_PLANES], uint32_t cand, uint32_t before,
+                                         uint32_t start, uint32_t w0, uint32_t wc, bool mine, uint32_t lane,
+                                         uint32_t* first_of, uint64_t (&rise)[4]) {
+    constexpr bool RANKS = KIND == RANK_METRICS, RULE = KIND == NODE_RULE;
+    const uint8_t* mask = RANKS ? a.exceed_mask : a.node_mask;
+    const uint32_t n_items = RANKS ? a.R : a.N, primary = a.primary, min_signals = a.min_signals;
+    const int32_t first = (int32_t)a.first_step, W = (int32_t)a.W;
+    uint32_t v[GD_COUNT_PLANES + 1];
+    gd_planes_bias(c, a.K, v);
+    // lane j works out the rows of step j (nowhere: row 0 of the batch, dropped)
+    const int32_t s = (int32_t)(start + lane), o = s - W;
+    const bool ok = s < (int32_t)a.T, old = ok && first + o >= 0;
+    auto is_early = [&](int32_t t) { return !RANKS && (uint64_t)(uint32_t)t * n_items < place.back; };
+    const bool in_early = ok && is_early(s), out_early = old && o >= 0 && is_early(o);
+    const uint8_t *enters = mask, *leaves = mask;
+    if (ok) enters = mask + (size_t)(uint32_t)s * n_items - (in_early ? 0 : place.back);
+    if (old && o >= 0) leaves = mask + (size_t)(uint32_t)o * n_items - (out_early ? 0 : place.back);
+    if (old && o < 0) leaves = ring + (size_t)((uint32_t)(first + o) % (uint32_t)W) * n_items - place.back;
+    const uint64_t in_valid = __ballot(ok), out_valid = __ballot(old);
+    const uint64_t in_up = RANKS ? 0ull : __ballot(in_early), out_up = RANKS ? 0ull : __ballot(out_early);
+    const uint32_t elo = (uint32_t)(uintptr_t)enters, ehi = (uint32_t)((uintptr_t)enters >> 32);
+    const uint32_t llo = (uint32_t)(uintptr_t)leaves, lhi = (uint32_t)((uintptr_t)leaves >> 32);
+    auto row_of = [&](uint32_t lo, uint32_t hi, int l) {
+        return reinterpret_cast<gd_row>((uintptr_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, l) << 32 |
+                                        (uint32_t)__builtin_amdgcn_readlane((int)lo, l));
+    };
+    auto load = [&](gd_row row) -> uint32_t {
+        return RANKS ? reinterpret_cast<const __attribute__((address_space(1))) uint32_t*>(row)[wc] : word_at(row + place.at);
+    };
+    auto settle = [&](uint32_t x, bool up, bool on) -> uint32_t {       // (up, on: uniform)
+        if (!RANKS) x = (up ? x << place.shift : x) >> place.shift;
+        if (RULE) x = combine4(x, primary, min_signals);
+        return on ? x : 0u;
+    };
+    uint32_t open = cand, prev = before, at[6] = {};
+#pragma unroll 1
+    for (int g = 0; g < 8; ++g) {
+        uint32_t in[8], out[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            in[j] = load(row_of(elo, ehi, 8 * g + j));
+            out[j] = load(row_of(llo, lhi, 8 * g + j));
+        }
+        const uint32_t was_open = open;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int l = 8 * g + j;
+            gd_planes_step(v, settle(in[j], (in_up >> l) & 1ull, (in_valid >> l) & 1ull),
+                           settle(out[j], (out_up >> l) & 1ull, (out_valid >> l) & 1ull));
+            const uint32_t reach = v[GD_COUNT_PLANES];
+            if (RULE) {
+                const uint32_t starts = mine ? reach & ~prev & 0x01010101u : 0u;      // (past the last step nothing changes)
+                prev = reach;
+                if (__ballot(starts != 0) == 0) continue;
+                // sixteen lanes' nodes make a word, the words of a step go to the step's lane
+                const uint32_t nib = (starts | (starts >> 7) | (starts >> 14) | (starts >> 21)) & 0xFu;
+                uint32_t lo = lane & 8u ? 0u : nib << (4 * (lane & 7u)), hi = lane & 8u ? nib << (4 * (lane & 7u)) : 0u;
+                lo |= gd_lane_xor<1>(lo, lane); hi |= gd_lane_xor<1>(hi, lane);
+                lo |= gd_lane_xor<2>(lo, lane); hi |= gd_lane_xor<2>(hi, lane);
+                lo |= gd_lane_xor<4>(lo, lane); hi |= gd_lane_xor<4>(hi, lane);
+                lo |= gd_lane_xor<8>(lo, lane); hi |= gd_lane_xor<8>(hi, lane);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const uint64_t word = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, 16 * q) << 32 |
+                                          (uint32_t)__builtin_amdgcn_readlane((int)lo, 16 * q);
+                    rise[q] = (int)lane == l ? word : rise[q];
+                }
+            } else {
+                const uint32_t hit = combine4(reach, primary, min_signals) & open;
+                open &= ~hit;
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    if ((j >> p) & 1) at[p] |= hit;
+            }
+        }
+        if (!RULE) {
+            const uint32_t hits = was_open & ~open;
+#pragma unroll
+            for (int p = 0; p < 3; ++p) at[3 + p] |= (g >> p) & 1 ? hits : 0u;
+            if (__ballot(open != 0) == 0) break;
+        }
+    }
+    if (RULE) return;
+    for (uint32_t bits = cand & ~open; bits; bits &= bits - 1) {
+        const uint32_t bit = (uint32_t)__builtin_ctz(bits), item = 4 * (w0 + lane) + bit / 8;
+        uint32_t step = start;
+#pragma unroll
+        for (int p = 0; p < 6; ++p) step += ((at[p] >> bit) & 1u) << p;
+        // (an item flagged earlier keeps its earlier step)
+        if (item < n_items) atomicMax(&first_of[item], 0xFFFFFFFFu - ((uint32_t)first + step));
+    }
+}
+
 // blockIdx.x: a stretch of `stretch` blocks of 64 steps; w0: the tile's first word.
 template <Tiles KIND>
 __device__ __forceinline__ void count_blocks(const gd_ledger_args& a, uint32_t w0, uint32_t stretch, uint32_t* lds,
@@ -387,7 +496,12 @@ __device__ __forceinline__ void count_blocks(const gd_ledger_args& a, uint32_t w
         const int32_t start = (int32_t)(s0 + b * 64), s = start + (int32_t)lane;       // this lane's step in a walk
         const uint64_t upto = (2ull << lane) - 1;
         uint64_t rise[4] = {};                                         // this step's episode starts, 64 nodes a word
-        for (uint64_t todo = __ballot(cand != 0); todo; todo &= todo - 1) {
+        uint64_t todo = __ballot(cand != 0);
+        if (__builtin_expect(__popcll(todo) > FEW_WORDS, 0)) {
+            walk_all<KIND>(a, ring, place, c, cand, before, (uint32_t)start, w0, wc, mine, lane, first_of, rise);
+            todo = 0;
+        }
+        for (; todo; todo &= todo - 1) {
             const int src = __builtin_ctzll(todo);
             const uint32_t w = w0 + (uint32_t)src;
             uint32_t enters = 0, leaves = 0;

@@ -268,3 +268,38 @@ def test_batches_at_the_edges_of_the_step_blocks(N, W, batches):
     feed(det, exceed, node_mask, node_z, batches)
     compare_ledger(want, read_ledger(det, min(8, N)), f"N{N}-W{W}")
     det.close()
+
+
+@pytest.mark.parametrize("N,W,k,batches", [(1, 3, 2, [40, 70]), (3, 65, 50, [333, 300]), (130, 64, 40, [320, 257]),
+                                           (511, 100, 80, [450, 403]), (2048, 20, 15, [200, 131])])
+@pytest.mark.parametrize("share", [0.01, 0.5])
+def test_many_items_flagged_together(N, W, k, batches, share):
+    """Few and many candidates of a block: walked one after another, or all at once.  Some items
+    fall behind at one step, some in the last, partial block of the first batch, some come and
+    go, some hover about k; metrics differ."""
+    say(f"case ledger together N={N} W={W} batches={batches} share={share}")
+    M, T = 3, sum(batches)
+    rng = np.random.default_rng(N + W)
+    t = np.arange(T)[:, None]
+
+    def history(n):
+        kind = rng.permutation(np.where(rng.random(n) < share, rng.integers(1, 5, n), 0))[None]
+        mask = np.zeros((T, n), np.uint8)
+        for m in range(M):
+            on = rng.random((T, n), dtype=np.float32) < 0.03
+            late = m * 2 * (rng.random(n) < 0.5)[None]
+            on |= ((kind == 1) & (t > T // 4 + late)) | ((kind == 2) & (t > batches[0] - k - 3 + late)) | \
+                ((kind == 3) & (t // W % 2 == 0)) | ((kind == 4) & (rng.random((T, n), dtype=np.float32) < k / W))
+            mask |= on.astype(np.uint8) << m
+        return mask
+
+    exceed, node_mask = history(8 * N), history(N)
+    p = oracle_params(R=8 * N, M=M, W=W, k=k, primary=1, min_signals=2, directions=(1,) * M)
+    node_anom = oracle.combine(node_mask, p.primary, p.min_signals)
+    node_z = node_score_history(N, T, N, scale=3.0)
+    want = oracle_ledger(p, exceed, node_mask, node_anom, node_z, 64.0, 200, 2, min(8, N))
+    det = detector_for(p)
+    det.alloc_ledger(max(batches), recur_horizon=200, recur_limit=2)
+    feed(det, exceed, node_mask, node_z, batches)
+    compare_ledger(want, read_ledger(det, min(8, N)), f"together-N{N}-W{W}")
+    det.close()
