@@ -773,7 +773,12 @@ __global__ __launch_bounds__(LED_NT) void ledger_flags_kernel(const gd_ledger_fl
 hipError_t gd_launch_ledger(const gd_ledger_args& a, hipStream_t s) {
     if (a.T == 0) return hipSuccess;
     if (a.limit < 1 || a.limit > (uint32_t)MAX_STARTS) return hipErrorInvalidValue;
-    if (a.T <= SHORT_BATCH) {
+    // The line moves up where the window's rows alone take long to load.  us by steps / by
+    // blocks, window 1 024: 65 536 ranks, 25 steps 20 / 38, 32 23 / 38, 48 32 / 40, 56 36 / 41;
+    // 49 152 ranks, 25 steps 19 / 25, 36 25 / 26; 32 768 ranks, 24 steps 19 / 22, 32 22 / 23.
+    const uint64_t window_bytes = (uint64_t)a.W * a.R;
+    const uint32_t by_step = SHORT_BATCH + (window_bytes > 1u << 25 ? (uint32_t)((window_bytes - (1u << 25)) >> 20) : 0u);
+    if (a.T <= by_step) {
         const uint32_t item_blocks = (a.R / RANK_IPT + LED_NT - 1) / LED_NT + (a.N + LED_NT - 1) / LED_NT;
         hipLaunchKernelGGL(ledger_steps_kernel, dim3(item_blocks), dim3(LED_NT), 0, s, a);
     } else {

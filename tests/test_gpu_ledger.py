@@ -270,6 +270,25 @@ def test_batches_at_the_edges_of_the_step_blocks(N, W, batches):
     det.close()
 
 
+@pytest.mark.parametrize("batches", [[56, 57, 25], [24, 40, 56, 58]])
+def test_batches_around_the_line_of_a_wide_window(batches):
+    """65 536 ranks, window 1 024: counted step by step up to 56 steps, in blocks from there on."""
+    say(f"case ledger wide window {batches}")
+    R, M, W, k, T = 65536, 2, 1024, 30, sum(batches)
+    N = R // 8
+    p = oracle_params(R=R, M=M, W=W, k=k, primary=0, min_signals=2, directions=(1,) * M)
+    exceed = exceed_history(5, T, R, M, 0.1, burst_items=R // 50, burst_len=(20, 90), gap_len=(1, 9), burst_metrics=M)
+    node_mask = exceed_history(6, T, N, M, 0.1, burst_items=N // 50, burst_len=(20, 90), gap_len=(1, 9), burst_metrics=M)
+    node_z = node_score_history(7, T, N, scale=3.0)
+    want = oracle_ledger(p, exceed, node_mask, oracle.combine(node_mask, p.primary, p.min_signals), node_z, 64.0, 50, 2, 64)
+    det = detector_for(p)
+    det.alloc_ledger(max(batches), recur_horizon=50, recur_limit=2)
+    feed(det, exceed, node_mask, node_z, batches)
+    compare_ledger(want, read_ledger(det, 64), f"wide window {batches}")
+    assert (want["ranks"].first >= 0).any()
+    det.close()
+
+
 @pytest.mark.parametrize("N,W,k,batches", [(1, 3, 2, [40, 70]), (3, 65, 50, [333, 300]), (130, 64, 40, [320, 257]),
                                            (511, 100, 80, [450, 403]), (2048, 20, 15, [200, 131])])
 @pytest.mark.parametrize("share", [0.01, 0.5])
