@@ -21,7 +21,8 @@
 //      its members, few more do (about 90 of 8 192 keys in random order for k = 64).
 //   3. The keys that reach it are compacted into LDS and ranked in the same way; a
 //      key's rank is its place in the output.  Where very many reach it (equal scores
-//      throughout), they are sorted instead.
+//      throughout), the k-th largest of the threads' best whole keys is the threshold instead,
+//      which at most 8 k keys reach: 8 192 equal scores take 11 us, 70 where they were sorted.
 // Measured (launch time, k = 64): 8 192 nodes 12.5 -> 6.1 us, 8 nodes 7.5 -> 2.0 us.
 // Before, the waves sorted their threads' largest keys and one wave folded the sixteen
 // sorted lists one after another; with that fold replaced by a sort of the waves' best
@@ -38,7 +39,7 @@ constexpr int WAVE = 64;
 constexpr int TOPK_NT = 1024;
 constexpr int TOPK_MAX = 8192;
 constexpr int GROUPS = 256;                 // room for the groups' best (128 to 255 of them)
-constexpr uint32_t RANKED = 512;            // most keys that are ranked rather than sorted
+constexpr uint32_t RANKED = 512;            // most keys that are ranked: 8 of 64 threads
 
 __device__ __forceinline__ uint32_t key_of(float f) {
     uint32_t b = __float_as_uint(f);
@@ -141,11 +142,35 @@ __global__ __launch_bounds__(WAVE) void topk_wave_kernel(const gd_topk_args a) {
     if (lane < a.k) write_out(a, lane, best);
 }
 
+// The a.k largest of keys[0 .. m), m at most CHUNKS * 64, to their places in the output: lane j
+// of every wave holds keys j, 64 + j, ..., a wave ranks every sixteenth of them.
+template <int CHUNKS>
+__device__ __forceinline__ void rank_keys(const gd_topk_args& a, const uint64_t* keys, uint32_t m, uint32_t lane, uint32_t w) {
+    constexpr uint32_t WAVES = TOPK_NT / WAVE;
+    uint64_t k[CHUNKS];
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) k[c] = c * WAVE + lane < m ? keys[c * WAVE + lane] : 0;
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) {
+#pragma unroll
+        for (uint32_t q = 0; q < WAVE / WAVES; ++q) {
+            const uint32_t at = q * WAVES + w;
+            if (c * WAVE + at >= m) return;
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)k[c], (int)at);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(k[c] >> 32), (int)at);
+            const uint64_t x = ((uint64_t)hi << 32) | lo;
+            uint32_t r = 0;
+#pragma unroll
+            for (int d = 0; d < CHUNKS; ++d) r += (uint32_t)__popcll(__ballot(k[d] > x));
+            if (r < a.k && lane == 0) write_out(a, r, x);
+        }
+    }
+}
+
 // k <= 64; KPT keys per thread: KPT * TOPK_NT >= N.
 template <int KPT>
 __global__ __launch_bounds__(TOPK_NT) void topk_short_kernel(const gd_topk_args a) {
-    constexpr int ROOM = KPT * TOPK_NT;             // every key may reach the threshold
-    __shared__ uint64_t keys[ROOM];
+    __shared__ uint64_t keys[TOPK_NT];
     __shared__ uint32_t best_of[GROUPS];
     __shared__ uint32_t threshold, n_reach;
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(tid / WAVE);
@@ -184,6 +209,7 @@ __global__ __launch_bounds__(TOPK_NT) void topk_short_kernel(const gd_topk_args 
     if ((tid & ((1u << lg) - 1)) == 0 && (tid >> lg) < (uint32_t)GROUPS) best_of[tid >> lg] = top;
     if (tid == 0) { n_reach = 0; threshold = 0; }
     __syncthreads();
+    uint32_t alike = 0;                             // groups whose best reaches the threshold
     if (groups > a.k) {                             // (else every key is ranked)
         // The largest value that at least k values reach.  Lane j holds values j, 64 + j, ...,
         // so a value comes out of a register by its lane number: no LDS round trip in the loop.
@@ -204,52 +230,68 @@ __global__ __launch_bounds__(TOPK_NT) void topk_short_kernel(const gd_topk_args 
         }
         if (lane == 0) atomicMax(&threshold, best);
         __syncthreads();
+#pragma unroll
+        for (int c = 0; c < GROUPS / WAVE; ++c) alike += (uint32_t)__popcll(__ballot(v[c] >= threshold));
     }
     const uint32_t thr = threshold;
     uint32_t hits = 0;
+    // (many more groups than were asked for: surely more keys than are ranked -- none are gathered)
+    const bool crowded = KPT > 1 && alike > a.k + WAVE / 2;
+    if (!crowded) {
 #pragma unroll
-    for (int q = 0; q < KPT; ++q) hits += digest[q] >= thr && mine[q] != 0 ? 1u : 0u;
+        for (int q = 0; q < KPT; ++q) hits += digest[q] >= thr && mine[q] != 0 ? 1u : 0u;
+    }
     if (hits) {
         uint32_t pos = atomicAdd(&n_reach, hits);
 #pragma unroll
         for (int q = 0; q < KPT; ++q)
-            if (digest[q] >= thr && mine[q] != 0) keys[pos++] = mine[q];
-    }
-    __syncthreads();
-    const uint32_t m = n_reach;                     // at least min(k, N) = k of them
-    if (m <= 2 * WAVE) {                            // the usual case: two keys per lane
-        const uint64_t k0 = lane < m ? keys[lane] : 0, k1 = WAVE + lane < m ? keys[WAVE + lane] : 0;
-#pragma unroll
-        for (uint32_t q = 0; q < 2 * WAVE / WAVES; ++q) {
-            const uint32_t i = q * WAVES + w;
-            if (i >= m) break;
-            const uint64_t src = q < WAVE / WAVES ? k0 : k1;
-            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)src, (int)(i & (WAVE - 1)));
-            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(src >> 32), (int)(i & (WAVE - 1)));
-            const uint64_t x = ((uint64_t)hi << 32) | lo;
-            const uint32_t r = (uint32_t)(__popcll(__ballot(k0 > x)) + __popcll(__ballot(k1 > x)));
-            if (r < a.k && lane == 0) write_out(a, r, x);
-        }
-        return;
-    }
-    if (m <= RANKED) {
-        for (uint32_t i = w; i < m; i += WAVES) {
-            const uint64_t x = keys[i];
-            uint32_t r = 0;
-            for (uint32_t j0 = 0; j0 < m; j0 += WAVE) {
-                const uint32_t j = j0 + lane;
-                r += (uint32_t)__popcll(__ballot(j < m && keys[j] > x));
+            if (digest[q] >= thr && mine[q] != 0) {
+                if (pos < RANKED) keys[pos] = mine[q];
+                ++pos;
             }
-            if (r < a.k && lane == 0) write_out(a, r, x);
-        }
-        return;
     }
-    uint32_t P = 2 * RANKED;
-    while (P < m) P <<= 1;                          // <= ROOM: both are powers of two and m <= N <= ROOM
-    for (uint32_t i = m + tid; i < P; i += TOPK_NT) keys[i] = 0;
     __syncthreads();
-    sort_in_lds(keys, P, tid);
-    if (tid < a.k) write_out(a, tid, keys[tid]);
+    uint32_t m = n_reach;                           // at least min(k, N) = k of them
+    if (__builtin_expect(crowded || m > RANKED, 0)) {
+        // Digests that are alike throughout.  The k-th largest of the threads' best keys: only
+        // the k threads whose best is among those hold keys that reach it, KPT * k at the most.
+        // (Threads take every 1 024th node here: equal scores leave the lowest indices, which
+        // are neighbours, and one of them per thread is what a threshold of best keys needs.)
+        uint64_t best = 0;
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) mine[q] = make_key(a, q * TOPK_NT + tid);
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) best = mine[q] > best ? mine[q] : best;
+        best = sort_desc(best, lane);
+        __syncthreads();                            // (everyone has read the count and is done with the keys)
+        keys[tid] = best;
+        if (tid == 0) n_reach = 0;
+        for (uint32_t half = WAVES / 2; half > 0; half /= 2) {
+            // the upper 64 of two sorted lists are a bitonic sequence
+            __syncthreads();
+            if (w < half) {
+                const uint64_t x = keys[w * WAVE + lane], y = keys[(w + half) * WAVE + (WAVE - 1 - lane)];
+                keys[w * WAVE + lane] = merge_desc(x > y ? x : y, lane);
+            }
+        }
+        __syncthreads();
+        const uint64_t least = keys[a.k - 1];
+        __syncthreads();
+        hits = 0;
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) hits += mine[q] >= least && mine[q] != 0 ? 1u : 0u;
+        if (hits) {
+            uint32_t pos = atomicAdd(&n_reach, hits);
+#pragma unroll
+            for (int q = 0; q < KPT; ++q)
+                if (mine[q] >= least && mine[q] != 0 && pos < RANKED) keys[pos++] = mine[q];
+        }
+        __syncthreads();
+        m = min(n_reach, RANKED);
+    }
+    if (m <= 2 * WAVE) rank_keys<2>(a, keys, m, lane, w);                  // the usual case
+    else if (m <= 4 * WAVE) rank_keys<4>(a, keys, m, lane, w);
+    else rank_keys<8>(a, keys, m, lane, w);
 }
 
 // Any k: everything sorted.
