@@ -2,8 +2,10 @@
 // tiered response -- no observable impact, a moderate sustained slowdown of
 // about 10%, a severe one of 20% or more).
 //
-// A workgroup looks at eight neighbouring nodes.  One that is not flagged (its own window
-// count and those of its 8 ranks all below k) reports tier 0.  For a flagged node, a few
+// A workgroup looks at up to eight nodes, every gridDim.x-th one: neighbours, which often fall
+// behind together (a rack, a switch), are different workgroups' and worked on side by side.  A
+// node that is not flagged (its own window count and those of its 8 ranks all below k) reports
+// tier 0.  For a flagged node, a few
 // dozen of thousands, the workgroup forms the quotient of each of the node's 8
 // primary-metric samples of the last min(T, W) steps by that step's cross-rank median and
 // takes the median of the at most 8192 quotients minus one.  Missing samples (NaN) are left
@@ -16,6 +18,8 @@
 // Bound by the length of that chain (loads, divisions, four or five counts, a barrier each).
 // Measured (launch, 8 192 nodes, 48 of them flagged, 2 048 quotients each): 42 us with a
 // workgroup per node sorting all quotients in LDS (66 stages with a barrier each), 11.8 us.
+// Eight neighbours flagged, a call in a row of them: 37 us that way, 10.2 (128 quotients 6.9 and
+// 5.5), where one workgroup took the neighbours one after another 48 (17).
 #include "gd_internal.h"
 #include "gd_lanes.h"
 
@@ -23,8 +27,9 @@ namespace {
 
 constexpr int WAVE = 64;
 constexpr int SEV_NT = 512;
-constexpr int WAVES = SEV_NT / WAVE;
-constexpr uint32_t GROUP = 8;     // nodes of a workgroup
+constexpr int FEW_NT = 128;       // threads for up to twice as many quotients
+constexpr uint32_t GROUP = 8;     // most nodes of a workgroup
+constexpr uint32_t GROUPS = 1024; // workgroups: as many as fit the chip at once (four a CU)
 constexpr int SEV_MAX = 8192;     // 8 GPUs x the longest window
 constexpr uint32_t MISSING = 0xFFFFFFFFu;      // above every key
 
@@ -39,12 +44,13 @@ __device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgc
 
 struct Shared {
     uint32_t q[SEV_MAX];
-    uint32_t count[2][WAVES];     // two 16-bit counts of each wave, written in turn
+    uint32_t count[2][SEV_NT / WAVE];     // two 16-bit counts of each wave, written in turn
     uint32_t slots[WAVE];         // the last candidates
     uint32_t n_slots, below, above;
 };
 
-// Sum over the workgroup of a value below 2^32 / SEV_NT per thread (turn: alternates).
+// Sum over the workgroup of values whose sum fits 32 bits (turn: alternates).
+template <int NT>
 __device__ __forceinline__ uint32_t block_sum(Shared& sh, uint32_t v, uint32_t turn) {
     const uint32_t lane = threadIdx.x & (WAVE - 1);
     v += gd_lane_xor<1>(v, lane); v += gd_lane_xor<2>(v, lane); v += gd_lane_xor<4>(v, lane);
@@ -53,25 +59,26 @@ __device__ __forceinline__ uint32_t block_sum(Shared& sh, uint32_t v, uint32_t t
     __syncthreads();
     uint32_t s = 0;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) s += sh.count[turn & 1][w];
+    for (int w = 0; w < NT / WAVE; ++w) s += sh.count[turn & 1][w];
     return uniform(s);
 }
 
 // The order statistics k0 <= k1 <= k0 + 1 of the n keys below MISSING among sh.q[0 .. cnt).
 // Throughout, clo keys lie under lo and chi under hi, with clo <= k0 and k1 < chi.  Ends for
 // any contents: a round narrows [lo, hi) to a part of it, from the fourth on to a half.
+template <int NT>
 __device__ __forceinline__ void select(Shared& sh, uint32_t cnt, uint32_t n, uint32_t k0, uint32_t k1, uint32_t turn,
                                        uint32_t* s0, uint32_t* s1) {
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1);
     uint32_t lo = 0, hi = MISSING, clo = 0, chi = n, part = 0;
     // true when one of the pivots p <= q parts the two statistics (k0 < part <= k1)
     auto narrow = [&](uint32_t p, uint32_t q) -> bool {
-        uint32_t c = 0;                                    // (at most 16 per thread: no carry between the halves)
-        for (uint32_t i = tid; i < cnt; i += SEV_NT) {
+        uint32_t c = 0;                                    // (at most SEV_MAX in all: no carry between the halves)
+        for (uint32_t i = tid; i < cnt; i += NT) {
             const uint32_t k = sh.q[i];
             c += (k < p ? 1u : 0u) + (k < q ? 0x10000u : 0u);
         }
-        c = block_sum(sh, c, turn++);
+        c = block_sum<NT>(sh, c, turn++);
         bool parted = false;
         auto take = [&](uint32_t at, uint32_t under) {
             const bool up = under <= k0 && at > lo, down = under > k1 && at < hi, splits = under > k0 && under <= k1;
@@ -114,7 +121,7 @@ __device__ __forceinline__ void select(Shared& sh, uint32_t cnt, uint32_t n, uin
     }
     if (parted) {
         uint32_t mx = 0, mn = MISSING;
-        for (uint32_t i = tid; i < cnt; i += SEV_NT) {
+        for (uint32_t i = tid; i < cnt; i += NT) {
             const uint32_t k = sh.q[i];
             if (k < part) mx = max(mx, k);
             else mn = min(mn, k);
@@ -126,7 +133,7 @@ __device__ __forceinline__ void select(Shared& sh, uint32_t cnt, uint32_t n, uin
         return;
     }
     // at most 64 keys in [lo, hi)
-    for (uint32_t i = tid; i < cnt; i += SEV_NT) {
+    for (uint32_t i = tid; i < cnt; i += NT) {
         const uint32_t k = sh.q[i];
         if (k - lo < hi - lo) {
             const uint32_t to = atomicAdd(&sh.n_slots, 1u);
@@ -139,27 +146,28 @@ __device__ __forceinline__ void select(Shared& sh, uint32_t cnt, uint32_t n, uin
     *s1 = (uint32_t)__builtin_amdgcn_readlane((int)c, (int)((k1 - clo) & (WAVE - 1)));
 }
 
-__global__ __launch_bounds__(SEV_NT) void severity_kernel(const gd_severity_args a) {
+template <int NT>
+__global__ __launch_bounds__(NT) void severity_kernel(const gd_severity_args a) {
     __shared__ Shared sh;
-    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), n0 = blockIdx.x * GROUP;
+    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), groups = gridDim.x;
     const uint16_t* rc = reinterpret_cast<const uint16_t*>(a.state + a.lay.rank_count);
     const uint16_t* nc = reinterpret_cast<const uint16_t*>(a.state + a.lay.node_count);
     const uint32_t ws = a.T < a.W ? a.T : a.W, cnt = ws * 8;
     // every wave finds the group's flagged nodes for itself: lane 8 * i + g looks at GPU g of node i
-    const uint32_t node = n0 + lane / 8;
-    const bool high = node < a.N && (rc[(size_t)n0 * 8 + lane] >= a.K || nc[node] >= a.K);
+    const uint32_t node = blockIdx.x + (lane / 8) * groups;
+    const bool high = node < a.N && (rc[(size_t)node * 8 + (lane & 7)] >= a.K || nc[node] >= a.K);
     const uint64_t flags = ws == 0 ? 0ull : __ballot(high);
-    if (tid < GROUP && n0 + tid < a.N && ((flags >> (8 * tid)) & 0xFFull) == 0) {
-        a.slowdown[n0 + tid] = 0.0f;
-        a.tier[n0 + tid] = 0;
+    if (tid < WAVE && (lane & 7) == 0 && node < a.N && ((flags >> lane) & 0xFFull) == 0) {
+        a.slowdown[node] = 0.0f;
+        a.tier[node] = 0;
     }
     for (uint32_t g = 0; g < GROUP; ++g) {
         if (((flags >> (8 * g)) & 0xFFull) == 0) continue;
-        const uint32_t n = n0 + g;
+        const uint32_t n = blockIdx.x + g * groups;
         __syncthreads();                               // (the node before this one is done with the work area)
         if (tid == 0) { sh.n_slots = 0; sh.below = 0; sh.above = MISSING; }
         uint32_t present = 0;
-        for (uint32_t i = tid; i < cnt; i += SEV_NT) {
+        for (uint32_t i = tid; i < cnt; i += NT) {
             uint32_t k = MISSING;
             const size_t t = a.T - ws + i / 8;
             const float m = a.med[t * a.M + a.primary];
@@ -176,13 +184,13 @@ __global__ __launch_bounds__(SEV_NT) void severity_kernel(const gd_severity_args
             sh.q[i] = k;
         }
         uint32_t turn = 0;
-        const uint32_t np = block_sum(sh, present, turn++);
+        const uint32_t np = block_sum<NT>(sh, present, turn++);
         if (np == 0) {                                 // flagged, but nothing arrived inside the window
             if (tid == 0) { a.slowdown[n] = 0.0f; a.tier[n] = 1; }
             continue;
         }
         uint32_t s0, s1;
-        select(sh, cnt, np, (np - 1) / 2, np / 2, turn, &s0, &s1);
+        select<NT>(sh, cnt, np, (np - 1) / 2, np / 2, turn, &s0, &s1);
         if (tid == 0) {
             // the middle quotient, or the two middle ones added, then halved
             const float mid = (np & 1) ? float_of_key(s1) : 0.5f * (float_of_key(s0) + float_of_key(s1));
@@ -197,6 +205,11 @@ __global__ __launch_bounds__(SEV_NT) void severity_kernel(const gd_severity_args
 
 hipError_t gd_launch_severity(const gd_severity_args& a, hipStream_t s) {
     if (a.N == 0) return hipSuccess;
-    hipLaunchKernelGGL(severity_kernel, dim3((a.N + GROUP - 1) / GROUP), dim3(SEV_NT), 0, s, a);
+    if (a.N > GROUP * GROUPS) return hipErrorInvalidValue;
+    // Few quotients leave most of 512 threads idle, who then only add to the barriers: all of
+    // 8 192 nodes flagged, 128 quotients each, 46.7 us with them, 25.0 with 128 (half of them flagged 26.9 and 16.8).
+    const dim3 grid(a.N < GROUPS ? a.N : GROUPS);
+    if (8 * (a.T < a.W ? a.T : a.W) <= 2 * FEW_NT) hipLaunchKernelGGL(severity_kernel<FEW_NT>, grid, dim3(FEW_NT), 0, s, a);
+    else hipLaunchKernelGGL(severity_kernel<SEV_NT>, grid, dim3(SEV_NT), 0, s, a);
     return hipGetLastError();
 }
