@@ -241,7 +241,7 @@ __global__ __launch_bounds__(WIN_MAX_NT) void window_blocks_kernel(const gd_wind
                                                                     uint32_t stretch) {
     extern __shared__ uint32_t lds[];
     __shared__ uint32_t final_planes[GD_COUNT_PLANES][TILE];
-    __shared__ uint32_t found[32 * FOUND_PITCH];       // first flagged step of the tile's items in this stretch
+    __shared__ __align__(16) uint32_t found[32 * FOUND_PITCH];       // first flagged step of the tile's items in this stretch
     __shared__ uint32_t walked;
     const bool is_node = blockIdx.y >= rank_tiles;
     const WindowItems it = window_items(a, is_node);
@@ -313,7 +313,8 @@ __global__ __launch_bounds__(WIN_MAX_NT) void window_blocks_kernel(const gd_wind
         }
     }
     if (tid == 0) walked = 0;
-    for (uint32_t x = tid; x < 32 * FOUND_PITCH; x += nt) found[x] = 0xFFFFFFFFu;
+    for (uint32_t x = tid; x < 8 * FOUND_PITCH; x += nt)
+        reinterpret_cast<uint4*>(found)[x] = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
     // The ring's new words (the batch's last min(T, W) steps) are the first stretch's to
     // store: some of them are fetched now.
     const uint32_t keep = T < W ? T : W;
