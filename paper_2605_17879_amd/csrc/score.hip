@@ -1227,8 +1227,10 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         // reach its histogram had, brackets this step's counting pass without
         // sampling.  A bracket that misses is noticed and replaced by the sample's.
         // (the first step of a run has no predecessor: a sample of the column stands in)
+        // (a batch's ragged tiling of up to four rows is through the general route sooner: 4 000
+        // ranks x 256 steps, one metric, 16.7 us that way, 19.5 with the sample's hints)
         bool boot = false;
-        if (t == t_begin && rfl(sh.hok[m]) == 0) {
+        if ((FULL || SPLIT || ROWS > 4) && t == t_begin && rfl(sh.hok[m]) == 0) {
             sample_hints<NT, LOG_NB>(sh, v[0], svalid, m);
             boot = true;
         }
@@ -1795,6 +1797,26 @@ bool use_split(const gd_score_args& a, int n_cu) {
     return a.split_steps > 0 && a.T <= a.split_steps && (uint64_t)a.T * a.M <= (uint64_t)n_cu;
 }
 
+// Up to 4 096 ranks: one wave per column scores the M columns of a step side by side, 256 threads
+// one after another but each column faster.  Measured (us by 256 threads / by waves):
+//   1 025 to 2 048 ranks, one metric: 256 steps 18 / 21 (missing samples 16 / 22, both signs 16 / 28,
+//     whole degrees 17..165 / 24), 1 500 steps 37 / 25; two metrics: 256 steps 31 / 20
+//   2 049 to 3 072 ranks, two metrics: 256 steps 29 / 33 (missing 26 / 35, signs 26 / 41, equal values
+//     50 / 15, values over decades 170 / 50), 1 500 steps 60 / 43; three: 256 steps 42 / 34
+//   3 073 to 4 096 ranks, two metrics: 500 steps 36 / 43 (missing 35 / 43, signs 32 / 62, few distinct
+//     values 68 / 15, decades 180 / 55), 3 000 steps 91 / 82; four: 256 steps 50 / 39, 3 000 155 / 124;
+//     one: 2 000 steps 42 / 56 (the lines cross at about 8 000 steps)
+// Two metrics and more go to the waves, whose time the contents change least, and one metric up to
+// 2 048 ranks.  Of a five- or six-wave workgroup only two fit a CU above 3 072 ranks, where four of
+// four waves do: long batches are the 256 threads' there (five metrics, 1 500 steps 135 / 126,
+// 3 000 187 / 229; six, 1 500 160 / 132).
+bool one_wave_per_column(const gd_score_args& a) {
+    if (a.R <= 2048) return true;
+    if (a.R > 4096) return false;
+    if (a.R > 3072 && (a.M == 5 || a.M == 6)) return a.T <= 1536;
+    return a.M > 1;
+}
+
 template <int NT, int ROWS, int LOG_NB>
 constexpr size_t lds_bytes() {
     using SH = Shared<NT, LOG_NB, NT * 4 * ROWS / 8>;
@@ -1892,11 +1914,7 @@ hipError_t pick_tiling(const gd_score_args& a, hipStream_t s) {
         case 256: return launch<64, 1, 10>(a, n_cu, s);
         case 1024: return launch<64, 4, 10>(a, n_cu, s);
         case 4096:
-            // One wave per column scores the M columns of a step side by side, 256 threads one
-            // after another: 4 000 ranks x 2 000 steps take 88 us against 118 with four metrics
-            // (64 steps: 35 against 63), with a single one 50 against 40 (64 steps: 34 against
-            // 19; the lines cross at about 8 000 steps).
-            if (a.M > 1 && !use_split(a, n_cu)) break;
+            if (one_wave_per_column(a) && !use_split(a, n_cu)) break;
             return launch<256, 4, 11>(a, n_cu, s);
         case 16384: return launch<256, 16, 11, 1024, 4, 12>(a, n_cu, s);
         case 32768: return launch<512, 16, 12, 1024, 8, 12>(a, n_cu, s);
@@ -1930,9 +1948,11 @@ hipError_t GD_RAGGED(gd_launch_ragged_few)(const gd_score_args& a, int n_cu, hip
     if (R <= 256) return launch_runs<64, 1, 10, false>(a, n_cu, s);
     if (R <= 512) return launch_runs<64, 2, 10, false>(a, n_cu, s);
     if (R <= 1024) return launch_runs<64, 4, 10, false>(a, n_cu, s);
-    if (R <= 2048) return launch_runs<64, 8, 10, false>(a, n_cu, s);
-    if (a.M > 1 && R <= 3072) return launch_runs<64, 12, 10, false>(a, n_cu, s);
-    if (a.M > 1 && R <= 4096) return launch_runs<64, 16, 10, false>(a, n_cu, s);
+    if (one_wave_per_column(a)) {
+        if (R <= 2048) return launch_runs<64, 8, 10, false>(a, n_cu, s);
+        if (R <= 3072) return launch_runs<64, 12, 10, false>(a, n_cu, s);
+        return launch_runs<64, 16, 10, false>(a, n_cu, s);
+    }
     if (R <= 4096) return launch_runs<256, 4, 11, false>(a, n_cu, s);
     if (R <= 6144) return launch_runs<256, 6, 11, false>(a, n_cu, s);
     return launch_runs<256, 8, 11, false>(a, n_cu, s);

@@ -35,11 +35,12 @@ struct SmallLds {
 
 // Keys are worked out from the values whenever they are looked at: a second copy of the
 // column would double its registers, and the optimiser is kept from making one by the
-// token of each pass, a constant that it cannot see through.  Of a column without signs or NaNs: its bits.
+// token of each pass, a constant that it cannot see through.  Of a column without signs: its
+// bits (missing samples, NaNs, lie above infinity, the largest key).
 template <int ROWS>
 struct PlainKeys {
     const float (&v)[ROWS][4];
-    static constexpr uint32_t END = 0x7F800001u;                     // (infinity is the largest key)
+    static constexpr uint32_t END = 0x7F800001u;
     __device__ __forceinline__ uint32_t token() const { return 0u; }
     __device__ __forceinline__ uint32_t at(int j, int i, uint32_t) const { return __float_as_uint(v[j][i]); }
     __device__ __forceinline__ float value(uint32_t k) const { return __uint_as_float(k); }
@@ -130,6 +131,9 @@ __device__ __forceinline__ void wave_select(const Keys& keys, uint32_t n, uint32
     };
     if (n > (uint32_t)WAVE) {
         // around the middle of the sample: two standard deviations of its median's rank
+        // (and its middle value alone, where an eighth of the sample is that value: of few distinct
+        // ones -- whole degrees -- it is mostly the one wanted)
+        uint32_t mid = 0xFFFFFFFFu;
         const uint32_t sample = small_sample<ROWS>(keys);
         const uint32_t ns = (uint32_t)__popcll(__ballot(sample < Keys::END));
         if (ns >= 16) {
@@ -137,13 +141,20 @@ __device__ __forceinline__ void wave_select(const Keys& keys, uint32_t n, uint32
             const uint32_t reach = 4u + ns / 16u;
             const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)sorted, (int)(ns / 2 - reach));
             const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)sorted, (int)min(ns / 2 + reach, ns - 1)) + 1u;
+            const uint32_t m0 = (uint32_t)__builtin_amdgcn_readlane((int)sorted, (int)(ns / 2 - 4));
+            const uint32_t m1 = (uint32_t)__builtin_amdgcn_readlane((int)sorted, (int)(ns / 2 + 3));
+            mid = m0 == m1 ? m0 : mid;
             if (narrow(p, q)) return;
         }
         for (int round = 0; chi - clo > (uint32_t)WAVE; ++round) {
             const uint32_t span = hi - lo;
             if (span <= 1) { *s0 = lo; *s1 = lo; return; }             // ties
             uint32_t p = span / 2, q = p;
-            if (round < 3) {
+            if (mid != 0xFFFFFFFFu) {
+                p = mid > lo ? mid - lo : 0u;
+                q = p + 1u;
+                mid = 0xFFFFFFFFu;
+            } else if (round < 3) {
                 // the values between the pivots taken as evenly spread: the wanted rank's
                 // place, and 2.5 standard deviations of it to either side
                 const float c = (float)(chi - clo), at = (float)(k1 - clo) + 0.5f;
@@ -224,7 +235,7 @@ __device__ __forceinline__ void score_small(const gd_score_args& a) {
                                 max(__float_as_uint(v[j][2]), __float_as_uint(v[j][3])));
         um = max(um, holds(j) ? rm : 0u);
     }
-    const bool special = __ballot(um > 0x7F800000u) != 0ull;
+    const bool special = __ballot(um > 0x7F800000u) != 0ull, signs = __ballot(um >= 0x80000000u) != 0ull;
     uint32_t present = R;
     if (special) {
         present = 0;
@@ -237,10 +248,10 @@ __device__ __forceinline__ void score_small(const gd_score_args& a) {
         uint32_t* const slots = lds.slots + m * WAVE;
         uint32_t s0, s1;
         // (an odd count has one middle value: no sum that could overflow)
-        if (!special) {
+        if (!signs) {
             const PlainKeys<ROWS> keys{v};
             wave_select<ROWS>(keys, present, k0, k1, lane, slots, &s0, &s1);
-            med = 0.5f * (keys.value(s0) + keys.value(s1));          // (R is even)
+            med = k0 == k1 ? keys.value(s0) : 0.5f * (keys.value(s0) + keys.value(s1));
         } else {
             const MappedKeys<ROWS> keys{v};
             wave_select<ROWS>(keys, present, k0, k1, lane, slots, &s0, &s1);

@@ -1,0 +1,80 @@
+"""Columns that one wave scores (up to 4 096 ranks): few distinct values, missing samples, signs,
+and a sample that misleads -- its 64 ranks made far off, too tight, missing, negative or the
+lowest -- against the oracle, one step and several, at the register rows' edges."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_harness import oracle_params, run_and_compare
+
+pytestmark = pytest.mark.gpu
+
+ROWS = (1, 2, 4, 8, 12, 16)
+
+
+def sampled_ranks(R):
+    """The ranks of a column's sample: lane l looks at element 4 * l of one register row of 256
+    ranks, the row by the lane's group."""
+    rows = next(r for r in ROWS if R <= 256 * r)
+    lane = np.arange(64)
+    if rows == 1:
+        row = np.zeros(64, int)
+    elif rows == 2:
+        row = lane // 32
+    else:
+        row = lane // 16 * (rows // 4)
+    rank = 256 * row + 4 * lane
+    return rank[rank < R]
+
+
+def column(kind, T, M, R, g):
+    x = torch.exp(0.02 * torch.randn((T, M, R), generator=g, dtype=torch.float64))
+    at = torch.from_numpy(sampled_ranks(R))
+    if kind == "whole degrees":
+        x = torch.round(65 * x)
+    elif kind == "tenths":
+        x = torch.round(10 * x) / 10
+    elif kind == "two values":
+        x = torch.where(torch.rand(x.shape, generator=g) < 0.5, 1.0, 2.0).to(x.dtype)
+    elif kind == "equal":
+        x = torch.ones_like(x)
+    elif kind == "missing":
+        x[torch.rand(x.shape, generator=g) < 0.2] = float("nan")
+    elif kind == "missing degrees":
+        x = torch.round(65 * x)
+        x[torch.rand(x.shape, generator=g) < 0.3] = float("nan")
+    elif kind == "signs":
+        x = x - 1
+        x[:, :, ::7] = -0.0
+    elif kind == "signs and missing":
+        x = torch.round(100 * (x - 1))
+        x[torch.rand(x.shape, generator=g) < 0.1] = float("nan")
+    elif kind == "sample far above":
+        x[:, :, at] *= 1e6
+    elif kind == "sample far below":
+        x[:, :, at] *= 1e-6
+    elif kind == "sample too tight":
+        x[:, :, at] = 1.3
+    elif kind == "sample missing":
+        x[:, :, at] = float("nan")
+    elif kind == "sample negative":
+        x[:, :, at] *= -1
+    elif kind == "sample on two values":
+        x[:, :, at] = torch.where(torch.arange(len(at)) % 2 == 0, 0.5, 1.7).to(x.dtype)
+    x[:, 0, -8:] *= 1.3
+    return x.to(torch.float32)
+
+
+KINDS = ("whole degrees", "tenths", "two values", "equal", "missing", "missing degrees", "signs", "signs and missing",
+         "sample far above", "sample far below", "sample too tight", "sample missing", "sample negative",
+         "sample on two values")
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("R", [64, 72, 248, 256, 264, 512, 520, 800, 1024, 1032, 2048, 2056, 3072, 3080, 4088, 4096])
+def test_awkward_columns(R, kind):
+    print(f"case small columns R={R} {kind}", flush=True)
+    g = torch.Generator().manual_seed(R + len(kind))
+    x = column(kind, 6, 2, R, g)
+    p = oracle_params(R=R, M=2, W=3, k=2, thr=2.5, directions=(1, 0), min_signals=1)
+    run_and_compare(p, x, topk_k=min(8, R // 8), chunks=[5, 1], label=f"small-{R}-{kind}")

@@ -158,3 +158,22 @@ def test_severity_of_neighbouring_nodes(nodes, W):
     det.close()
     print(f"severity, {nodes} nodes, window {W}: {us[0]:.1f} us apart, {us[1]:.1f} us side by side", flush=True)
     assert us[1] < 1.8 * us[0]
+
+
+@pytest.mark.parametrize("kind,bound", [("missing", 1.25), ("whole degrees", 2.0)])
+def test_scoring_of_small_awkward_columns(kind, bound):
+    """4 000 ranks x 2 metrics x 256 steps.  Measured: 40 us for plain values; one sample in a
+    hundred missing 57 where their keys were mapped like those of signs, 43; whole degrees 90
+    before their sample's middle value was tried alone, 66."""
+    R, M, T, us = 4000, 2, 256, []
+    det = detector_for(oracle_params(R=R, M=M, W=4, k=2))
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.exp(0.02 * torch.randn((T, M, R), device="cuda", generator=g))
+    other = torch.round(65 * x) if kind == "whole degrees" else \
+        torch.where(torch.rand(x.shape, device="cuda", generator=g) < 0.01, float("nan"), x)
+    out = det.alloc_outputs(T)
+    for v in (x, other):
+        us.append(device_us(lambda: None, lambda: [det.score_batch(v, out) for _ in range(10)]) / 10)
+    det.close()
+    print(f"{kind}, {R} ranks: {us[0]:.1f} us plain, {us[1]:.1f} us", flush=True)
+    assert us[1] < bound * us[0]
