@@ -973,13 +973,18 @@ __device__ __forceinline__ void sample_hints(SH& sh, const float (&row)[4], bool
             bool done = false;
 #pragma unroll
             for (int q = 0; q < BPT; ++q) {
-                if (!done && want - p < loc[q]) { sh.res[r] = tid * BPT + q; done = true; }
+                if (!done && want - p < loc[q]) {
+                    sh.res[r] = r == 1 && loc[q] > n / 8 ? 0xFFFFFFFFu : tid * BPT + q;
+                    done = true;
+                }
                 p += loc[q];
             }
         }
     }
     __syncthreads();
-    if (tid == 0 && n != 0) {
+    // (more than an eighth of the sample in the middle's bucket: few distinct values, whose buckets
+    // the hinted selection would find crowded and give up after its counting pass)
+    if (tid == 0 && n != 0 && sh.res[1] != 0xFFFFFFFFu) {
         const uint32_t half = (1u << sshift) >> 1;
         const float q25 = __uint_as_float(smin + (sh.res[0] << sshift) + half);
         const float q50 = __uint_as_float(smin + (sh.res[1] << sshift) + half);
