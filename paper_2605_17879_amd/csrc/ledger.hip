@@ -265,8 +265,10 @@ __device__ __forceinline__ void walk_all(const gd_ledger_args& a, const uint8_t*
     const uint8_t* mask = RANKS ? a.exceed_mask : a.node_mask;
     const uint32_t n_items = RANKS ? a.R : a.N, primary = a.primary, min_signals = a.min_signals;
     const int32_t first = (int32_t)a.first_step, W = (int32_t)a.W;
-    uint32_t v[GD_COUNT_PLANES + 1];
-    gd_planes_bias(c, a.K, v);
+    uint32_t v[GD_COUNT_PLANES + 1], K = a.K;
+    // (opaque: K's bits, a mask each, are otherwise worked out and spilled before every block)
+    asm volatile("" : "+s"(K));
+    gd_planes_bias(c, K, v);
     // lane j works out the rows of step j (nowhere: row 0 of the batch, dropped)
     const int32_t s = (int32_t)(start + lane), o = s - W;
     const bool ok = s < (int32_t)a.T, old = ok && first + o >= 0;

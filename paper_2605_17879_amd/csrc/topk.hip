@@ -170,7 +170,8 @@ __device__ __forceinline__ void rank_keys(const gd_topk_args& a, const uint64_t*
 // k <= 64; KPT keys per thread: KPT * TOPK_NT >= N.
 template <int KPT>
 __global__ __launch_bounds__(TOPK_NT) void topk_short_kernel(const gd_topk_args a) {
-    __shared__ uint64_t keys[TOPK_NT];
+    constexpr int ROOM = KPT * TOPK_NT;             // every key may reach the first threshold
+    __shared__ uint64_t keys[ROOM];
     __shared__ uint32_t best_of[GROUPS];
     __shared__ uint32_t threshold, n_reach;
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), w = __builtin_amdgcn_readfirstlane(tid / WAVE);
@@ -245,10 +246,7 @@ __global__ __launch_bounds__(TOPK_NT) void topk_short_kernel(const gd_topk_args 
         uint32_t pos = atomicAdd(&n_reach, hits);
 #pragma unroll
         for (int q = 0; q < KPT; ++q)
-            if (digest[q] >= thr && mine[q] != 0) {
-                if (pos < RANKED) keys[pos] = mine[q];
-                ++pos;
-            }
+            if (digest[q] >= thr && mine[q] != 0) keys[pos++] = mine[q];
     }
     __syncthreads();
     uint32_t m = n_reach;                           // at least min(k, N) = k of them

@@ -117,6 +117,8 @@ __device__ __forceinline__ void walk_all(const WindowItems& it, const uint32_t (
                                          uint32_t start, int32_t first, uint32_t T, uint32_t W, uint32_t K,
                                          uint32_t wc, uint32_t lane, uint32_t* found) {
     uint32_t v[GD_COUNT_PLANES + 1];
+    // (opaque: K's bits, a mask each, are otherwise worked out and spilled before every block)
+    asm volatile("" : "+s"(K));
     gd_planes_bias(c, K, v);
     // (lane j works out the rows of step j, as in the counting of the blocks)
     const uint32_t s = start + lane;
