@@ -37,6 +37,7 @@
 // ledger_finish_kernel, launched behind either: the rings take the batch's last steps, the
 // score sums are brought up to date, and a lane per node walks the episode starts in step
 // order.
+#include "gd_grant.h"
 #include "gd_internal.h"
 #include "gd_lanes.h"
 #include "gd_planes.h"
@@ -797,15 +798,11 @@ hipError_t gd_launch_ledger(const gd_ledger_args& a, hipStream_t s) {
         if (stretches > 0x7FFFFFFFu / 1024 || tiles > 65535u) return hipErrorInvalidValue;
         const uint32_t nt = (slots < (uint32_t)BLOCKS_NT / WAVE ? slots : (uint32_t)BLOCKS_NT / WAVE) * WAVE;
         const size_t lds = (size_t)(r ? 2 * GD_BLOCK_PLANES - 1 : GD_BLOCK_PLANES) * slots * TILE * 4;
-        static bool configured = false;      // (a repeated set is harmless)
-        if (!configured) {
-            constexpr size_t most = (size_t)(2 * GD_BLOCK_PLANES - 1) * MAX_SLOTS * TILE * 4;
-            static_assert(most + sizeof(uint32_t) * GD_COUNT_PLANES * TILE <= 160 * 1024, "LDS budget of one CU");
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ledger_blocks_kernel),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
-            if (e != hipSuccess) return e;
-            configured = true;
-        }
+        constexpr size_t most = (size_t)(2 * GD_BLOCK_PLANES - 1) * MAX_SLOTS * TILE * 4;
+        static_assert(most + sizeof(uint32_t) * GD_COUNT_PLANES * TILE <= 160 * 1024, "LDS budget of one CU");
+        static std::atomic<uint64_t> granted{0};
+        const hipError_t e = gd_grant_lds(granted, reinterpret_cast<const void*>(ledger_blocks_kernel), most);
+        if (e != hipSuccess) return e;
         hipLaunchKernelGGL(ledger_blocks_kernel, dim3(stretches, tiles), dim3(nt), lds, s, a, rank_tiles, node_tiles,
                            stretch);
     }

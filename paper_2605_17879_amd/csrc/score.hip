@@ -24,6 +24,7 @@
 // rank and step of outputs.
 #include <type_traits>
 
+#include "gd_grant.h"
 #include "gd_internal.h"
 #include "gd_lanes.h"
 
@@ -1810,14 +1811,16 @@ __global__ __launch_bounds__(1024) void read_probe_kernel(const float* x, uint64
 }
 
 int compute_units(hipError_t* err) {
-    static int n_cu = 0;
+    static std::atomic<int> known{0};        // (several threads may ask at once)
     *err = hipSuccess;
+    int n_cu = known.load(std::memory_order_relaxed);
     if (n_cu == 0) {
         int dev = 0;
         hipError_t e = hipGetDevice(&dev);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
         if (e != hipSuccess) { *err = e; return 0; }
         if (n_cu <= 0) n_cu = 256;
+        known.store(n_cu, std::memory_order_relaxed);
     }
     return n_cu;
 }
@@ -1883,13 +1886,9 @@ hipError_t launch_runs(const gd_score_args& a, int n_cu, hipStream_t s) {
     constexpr size_t lds = lds_bytes<NT, ROWS, LOG_NB>();
     static_assert(lds <= 160 * 1024, "LDS budget of one CU");
     auto kern = kernel_of<NT, ROWS, LOG_NB, FULL, false>();
-    static bool configured = false;      // a handle is single-threaded; a repeated set is harmless
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        configured = true;
-    }
+    static std::atomic<uint64_t> granted{0};
+    const hipError_t e = gd_grant_lds(granted, reinterpret_cast<const void*>(kern), lds);
+    if (e != hipSuccess) return e;
     const size_t by_lds = (size_t)160 * 1024 / lds, by_waves = (size_t)16 / (NT / WAVE);
     const size_t per_cu = by_lds < by_waves ? (by_lds ? by_lds : 1) : by_waves;
     const size_t cap = (size_t)n_cu * per_cu;
@@ -1907,13 +1906,9 @@ hipError_t launch_columns(const gd_score_args& a, hipStream_t s) {
     constexpr size_t lds = lds_bytes<NT, ROWS, LOG_NB>();
     static_assert(lds <= 160 * 1024, "LDS budget of one CU");
     auto kern = kernel_of<NT, ROWS, LOG_NB, FULL, true>();
-    static bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        configured = true;
-    }
+    static std::atomic<uint64_t> granted{0};
+    const hipError_t e = gd_grant_lds(granted, reinterpret_cast<const void*>(kern), lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(a.T * a.M), dim3(NT), lds, s, a);
     hipLaunchKernelGGL(combine_kernel, dim3((a.R + PLANE_RANKS - 1) / PLANE_RANKS, a.T), dim3(PLANE_RANKS / 8), 0, s, a);
     return hipGetLastError();

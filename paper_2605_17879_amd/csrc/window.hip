@@ -39,6 +39,7 @@
 // transposing 64 x 64 bits across its lanes (one wave per SIMD at 65 536 ranks and fewer
 // below, waiting for its loads and lane exchanges).
 // One step per call (window_step_kernel) needs none of this: a thread per item.
+#include "gd_grant.h"
 #include "gd_internal.h"
 #include "gd_lanes.h"
 #include "gd_planes.h"
@@ -493,16 +494,12 @@ hipError_t gd_launch_window(const gd_window_args& a, hipStream_t s) {
     const uint32_t slots = hist + stretch + 1;
     const uint32_t nt = (slots < (uint32_t)WIN_MAX_NT / WAVE ? slots : (uint32_t)WIN_MAX_NT / WAVE) * WAVE;
     const size_t lds = (size_t)(r ? 2 * GD_BLOCK_PLANES - 1 : GD_BLOCK_PLANES) * slots * TILE * 4;
-    static bool configured = false;          // (a repeated set is harmless)
-    if (!configured) {
-        constexpr size_t most = (size_t)(2 * GD_BLOCK_PLANES - 1) * (MAX_HISTORY + MAX_STRETCH + 1) * TILE * 4;
-        static_assert(most + sizeof(uint32_t) * (GD_COUNT_PLANES * TILE + 32 * FOUND_PITCH) <= 160 * 1024,
-                      "LDS budget of one CU");
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(window_blocks_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
-        if (e != hipSuccess) return e;
-        configured = true;
-    }
+    constexpr size_t most = (size_t)(2 * GD_BLOCK_PLANES - 1) * (MAX_HISTORY + MAX_STRETCH + 1) * TILE * 4;
+    static_assert(most + sizeof(uint32_t) * (GD_COUNT_PLANES * TILE + 32 * FOUND_PITCH) <= 160 * 1024,
+                  "LDS budget of one CU");
+    static std::atomic<uint64_t> granted{0};
+    const hipError_t e = gd_grant_lds(granted, reinterpret_cast<const void*>(window_blocks_kernel), most);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(window_blocks_kernel, dim3(stretches, tiles), dim3(nt), lds, s, a, rank_tiles, stretch);
     return hipGetLastError();
 }
