@@ -933,9 +933,9 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
 // pass of the hinted selection confirms them, so raw bit patterns serve as keys whatever
 // the column holds.  Thread 0 writes the hints of metric m; ends with a barrier, the work
 // area at rest.
-// (valid: this thread's row 0 holds ranks; missing samples are left out)
+// (missing samples are left out)
 template <int NT, int LOG_NB, typename SH>
-__device__ __forceinline__ void sample_hints(SH& sh, const float (&row)[4], bool valid, uint32_t m) {
+__device__ __forceinline__ void sample_hints(SH& sh, const float (&row)[4], uint32_t m) {
     constexpr int BPT = (1 << LOG_NB) / NT;
     const uint32_t tid = opaque_v(threadIdx.x), lane = tid & (WAVE - 1);
     uint32_t k[4];
@@ -944,7 +944,7 @@ __device__ __forceinline__ void sample_hints(SH& sh, const float (&row)[4], bool
     uint32_t mn = 0xFFFFFFFFu, mx = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const bool in = valid && (k[i] & 0x7FFFFFFFu) <= 0x7F800000u;
+        const bool in = (k[i] & 0x7FFFFFFFu) <= 0x7F800000u;
         mn = in ? min(mn, k[i]) : mn;
         mx = in ? max(mx, k[i]) : mx;
     }
@@ -956,7 +956,7 @@ __device__ __forceinline__ void sample_hints(SH& sh, const float (&row)[4], bool
     const int sshift = shift_for<LOG_NB>(smax - smin);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-        if (valid && (k[i] & 0x7FFFFFFFu) <= 0x7F800000u) atomicAdd(&sh.hist[(k[i] - smin) >> sshift], 1u);
+        if ((k[i] & 0x7FFFFFFFu) <= 0x7F800000u) atomicAdd(&sh.hist[(k[i] - smin) >> sshift], 1u);
     __syncthreads();
     if (tid == 0) { sh.smin = 0xFFFFFFFFu; sh.smax = 0; }
     uint32_t loc[BPT], sum = 0;
@@ -1175,8 +1175,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         }
     }
     __syncthreads();
-    // threads whose row 0, the column's sample, holds ranks
-    const uint32_t nsample = TAIL > 0 ? (uint32_t)NT : min((uint32_t)NT, R / 4);
+    constexpr uint32_t nsample = NT;          // (row 0, the column's sample, holds ranks throughout)
     const float inv_node_scale = 1.0f / a.node_scale;      // (only used where node_scale > 0)
     uint32_t dir_codes = 0;          // direction + 1 of metric i in bits 2i, 2i + 1
 #pragma unroll
@@ -1227,7 +1226,6 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         const bool have_next = !SPLIT && (m + 1 < M || t + 1 < t_end);
         const float* next_col = a.x + (t * M + m + (have_next ? 1 : 0)) * (size_t)R;
         const uint32_t tl = fresh_tid4();
-        const bool svalid = holds(0, tl);
         // A workgroup scores consecutive steps, and telemetry moves little from one
         // step to the next: the previous step's median of this metric, with the
         // reach its histogram had, brackets this step's counting pass without
@@ -1237,7 +1235,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         // ranks x 256 steps, one metric, 16.7 us that way, 19.5 with the sample's hints)
         bool boot = false;
         if ((FULL || SPLIT || ROWS > 4) && t == t_begin && rfl(sh.hok[m]) == 0) {
-            sample_hints<NT, LOG_NB>(sh, v[0], svalid, m);
+            sample_hints<NT, LOG_NB>(sh, v[0], m);
             boot = true;
         }
         bool hinted = rfl(sh.hok[m]) != 0;
@@ -1307,7 +1305,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
             uint32_t hlo = 0, hhi = 0;
             int hshift = 0;
             const bool one_round = block_select<NT, ROWS, LOG_NB, true>(
-                sh, XKeys<ROWS, true>{v}, __float_as_uint(v[0][0]), svalid, nsample, k0_all, k1_all, &s0,
+                sh, XKeys<ROWS, true>{v}, __float_as_uint(v[0][0]), true, nsample, k0_all, k1_all, &s0,
                 &s1, &hlo, &hhi, &hshift, hinted, hint_lo, hint_hi, fused_umax ? umax_slot : nullptr, &umax);
             special = umax > 0x7F800000u;      // (only the fused pass can find this out here)
         if (!special) {
@@ -1351,7 +1349,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
             k0 = present ? (present - 1) / 2 : 0u;
             k1 = present / 2;
             if (present) {
-                const bool sv = svalid && v[0][0] == v[0][0];
+                const bool sv = v[0][0] == v[0][0];
                 block_select<NT, ROWS, LOG_NB, false>(sh, XKeys<ROWS, false>{v}, key_of(v[0][0] + 0.0f),
                                                       sv, nsample, k0, k1, &s0, &s1);
                 // (an odd count has one middle value: no sum that could overflow)
@@ -1361,7 +1359,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         if (__builtin_expect(!have_mad && present, 0))
             block_select<NT, ROWS, LOG_NB, false>(sh, DKeys<ROWS>{v, med},
                                                   __float_as_uint(fabsf(v[0][0] - med)),
-                                                  svalid && v[0][0] == v[0][0], nsample, k0, k1, &s0, &s1);
+                                                  v[0][0] == v[0][0], nsample, k0, k1, &s0, &s1);
         float mad = k0 == k1 ? __uint_as_float(s0) : 0.5f * (__uint_as_float(s0) + __uint_as_float(s1));
         if (!present) med = mad = __uint_as_float(0x7FC00000u);      // nothing to take a median of
         if (tid == 0) {
@@ -1883,6 +1881,7 @@ template <int NT, int ROWS, int LOG_NB, bool FULL>
 hipError_t launch_runs(const gd_score_args& a, int n_cu, hipStream_t s) {
     if constexpr (NT == WAVE) return launch_small<ROWS, FULL, false>(a, s);
     else {
+    if (a.R < (uint32_t)NT * 4) return hipErrorInvalidValue;      // (row 0 holds ranks throughout)
     constexpr size_t lds = lds_bytes<NT, ROWS, LOG_NB>();
     static_assert(lds <= 160 * 1024, "LDS budget of one CU");
     auto kern = kernel_of<NT, ROWS, LOG_NB, FULL, false>();
@@ -1903,6 +1902,7 @@ template <int NT, int ROWS, int LOG_NB, bool FULL>
 hipError_t launch_columns(const gd_score_args& a, hipStream_t s) {
     if constexpr (NT == WAVE) return launch_small<ROWS, FULL, true>(a, s);
     else {
+    if (a.R < (uint32_t)NT * 4) return hipErrorInvalidValue;      // (row 0 holds ranks throughout)
     constexpr size_t lds = lds_bytes<NT, ROWS, LOG_NB>();
     static_assert(lds <= 160 * 1024, "LDS budget of one CU");
     auto kern = kernel_of<NT, ROWS, LOG_NB, FULL, true>();
@@ -1947,7 +1947,8 @@ hipError_t pick_tiling(const gd_score_args& a, hipStream_t s) {
     }
     if (a.R > 65536) return hipErrorInvalidValue;
     constexpr bool z = WANT_Z_HERE;
-    if (use_split(a, n_cu)) return z ? gd_launch_ragged_columns_z(a, s) : gd_launch_ragged_columns(a, s);
+    // (up to 2 048 ranks a column is one wave's on either route)
+    if (a.R > 2048 && use_split(a, n_cu)) return z ? gd_launch_ragged_columns_z(a, s) : gd_launch_ragged_columns(a, s);
     if (a.R <= 8192) return z ? gd_launch_ragged_few_z(a, n_cu, s) : gd_launch_ragged_few(a, n_cu, s);
     return z ? gd_launch_ragged_many_z(a, n_cu, s) : gd_launch_ragged_many(a, n_cu, s);
 }
@@ -2005,10 +2006,6 @@ hipError_t GD_RAGGED(gd_launch_ragged_many)(const gd_score_args& a, int n_cu, hi
 
 hipError_t GD_RAGGED(gd_launch_ragged_columns)(const gd_score_args& a, hipStream_t s) {
     const uint32_t R = a.R;
-    if (R <= 256) return launch_columns<64, 1, 10, false>(a, s);
-    if (R <= 512) return launch_columns<64, 2, 10, false>(a, s);
-    if (R <= 1024) return launch_columns<64, 4, 10, false>(a, s);
-    if (R <= 2048) return launch_columns<64, 8, 10, false>(a, s);
     if (R <= 4096) return launch_columns<256, 4, 11, false>(a, s);
     if (R <= 8192) return launch_columns<1024, 2, 12, false>(a, s);
     if (R <= 16384) return launch_columns<1024, 4, 12, false>(a, s);
