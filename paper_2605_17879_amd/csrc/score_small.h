@@ -168,7 +168,7 @@ __device__ __forceinline__ void wave_select(const Keys& keys, uint32_t n, uint32
         }
     }
     // at most 64 keys in [lo, hi)
-    const uint32_t m = chi - clo, width = hi - lo;
+    const uint32_t width = hi - lo;
     const uint32_t tok = keys.token();
     uint32_t pos = 0;
 #pragma unroll
@@ -185,7 +185,8 @@ __device__ __forceinline__ void wave_select(const Keys& keys, uint32_t n, uint32
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    const uint32_t c = gd_sort64(lane < m ? slots[lane] : 0xFFFFFFFFu);
+    // (an infinite median leaves fewer distances than n: slots that no lane wrote are not read)
+    const uint32_t c = gd_sort64(lane < pos ? slots[lane] : 0xFFFFFFFFu);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     *s0 = (uint32_t)__builtin_amdgcn_readlane((int)c, (int)((k0 - clo) & (WAVE - 1)));

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_harness import oracle_params, run_and_compare
+from gpu_harness import bits32, detector_for, oracle_params, run_and_compare
 
 pytestmark = pytest.mark.gpu
 
@@ -78,3 +78,24 @@ def test_awkward_columns(R, kind):
     x = column(kind, 6, 2, R, g)
     p = oracle_params(R=R, M=2, W=3, k=2, thr=2.5, directions=(1, 0), min_signals=1)
     run_and_compare(p, x, topk_k=min(8, R // 8), chunks=[5, 1], label=f"small-{R}-{kind}")
+
+
+@pytest.mark.parametrize("R", [8, 56, 64, 512, 1024, 2048])
+def test_infinite_medians_repeat(R):
+    """Infinities are unsupported input, but one call gives what another gives: nothing that an
+    earlier launch left in the work area is read."""
+    print(f"case infinite medians R={R}", flush=True)
+    det = detector_for(oracle_params(R=R, M=2, W=3, k=2))
+    g = torch.Generator().manual_seed(R)
+    x = torch.exp(0.02 * torch.randn((1, 2, R), generator=g))
+    x[0, 0, : 5 * R // 8] = float("inf")
+    x[0, 1, : 3 * R // 4] = float("-inf")
+    seen = set()
+    for i in range(6):
+        other = det.alloc_outputs(64)
+        det.score_batch(torch.exp((1 + i) * torch.randn((64, 2, R), generator=g)).cuda(), other)
+        out = det.alloc_outputs(1)
+        det.score_batch(x.cuda(), out)
+        seen.add(bits32(out["med"].cpu()).tobytes() + bits32(out["mad"].cpu()).tobytes())
+    det.close()
+    assert len(seen) == 1
