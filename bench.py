@@ -34,9 +34,21 @@ def algorithmic_bytes_per_launch(R: int, M: int, T: int) -> int:
 
 
 def _score_source_hash() -> str:
+    """Of the scoring kernel's source and every file of its own folder that it includes."""
     import hashlib
-    src = os.path.join(ROOT, "paper_2605_17879_amd", "csrc", "score.hip")
-    return hashlib.sha256(open(src, "rb").read()).hexdigest()
+    import re
+    folder = os.path.join(ROOT, "paper_2605_17879_amd", "csrc")
+    names, todo = [], ["score.hip"]
+    while todo:
+        name = todo.pop()
+        if name not in names:
+            names.append(name)
+            text = open(os.path.join(folder, name)).read()
+            todo += [n for n in re.findall(r'#include "([^"]+)"', text) if os.path.exists(os.path.join(folder, n))]
+    h = hashlib.sha256()
+    for name in sorted(names):
+        h.update(name.encode() + b"\0" + open(os.path.join(folder, name), "rb").read() + b"\0")
+    return h.hexdigest()
 
 
 def _profile_record(name: str):
@@ -44,7 +56,7 @@ def _profile_record(name: str):
     changed since it was taken (the figures would no longer describe this kernel)."""
     try:
         rec = json.load(open(os.path.join(ROOT, "profiles", name)))
-        if rec.get("score_hip_sha256") == _score_source_hash():
+        if rec.get("score_sources_sha256") == _score_source_hash():
             return rec
     except (OSError, ValueError, KeyError):
         pass

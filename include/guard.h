@@ -203,8 +203,8 @@ gd_status gd_flags(gd_handle h, uint8_t* d_rank_flag, uint16_t* d_rank_count,
 
 /*
  * The k slowest nodes.  The paper ranks nothing (a flagged node is simply handed to
- * mitigation, Section 4.2); the order is this library's: all N nodes ordered by (window count, high first; latest
- * primary node score, high first, -0 == +0; node index, low first).
+ * mitigation, Section 4.2); the order is this library's: all N nodes ordered by (window
+ * count, high first; latest primary node score, high first, -0 == +0; node index, low first).
  *   d_idx [k] i32  node indices in that order
  *   d_key [k] u64  count << 48 | order_key(score) << 16 | (0xFFFF - index), where
  *                  order_key maps fp32 to u32 preserving order; may be NULL
@@ -214,8 +214,9 @@ gd_status gd_topk_nodes(gd_handle h, uint32_t k, int32_t* d_idx, uint64_t* d_key
 
 /*
  * Elastic membership (the paper is silent on ranks that join or leave a job; this is
- * the missing-sample rule of gd_score_batch applied to whole ranks): marks the ranks that take no part in a step as missing samples
- * of that step, in place, before gd_score_batch sees the batch.
+ * the missing-sample rule of gd_score_batch applied to whole ranks): marks the ranks that
+ * take no part in a step as missing samples of that step, in place, before gd_score_batch
+ * sees the batch.
  *   d_x      in/out [T][M][R] f32 device, 16-byte aligned
  *   d_active in     [T][ceil(R/64)] u64 device: bit r%64 of word r/64 set = rank r takes
  *                   part in step t
@@ -333,7 +334,8 @@ gd_status gd_update_ledger(gd_handle h, const uint8_t* d_exceed_mask, const uint
  * gd_update_ledger for callers that cannot allocate device memory or hand over a work
  * area: code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, same results in the ledger, same two kernels; their work
- * area (the episode-start map) is a static device array inside the library, gd_ledger_static_scratch_bytes() = 8 MiB per GPU, held from the first
+ * area (the episode-start map) is a static device array inside the library,
+ * gd_ledger_static_scratch_bytes() = 8 MiB per GPU, held from the first
  * call on that GPU until the process ends.  The call itself allocates nothing, here or
  * in any library it uses.  The ledger may therefore be bound with max_T = 1; T is
  * limited by the array instead: align256(T * ceil(N/64) * 8) + 16 R + 18 N (rounded up
@@ -375,8 +377,8 @@ gd_status gd_topk_nodes_mean(gd_handle h, uint32_t k, int32_t* d_idx, uint64_t* 
 
 /*
  * NOT part of the detector's contract -- a diagnostic for benchmarks, exported so that
- * the benchmark can time it through the same library: reads the first n_bytes (rounded down to a multiple of
- * 256 KiB) of d_x with the scoring kernel's own load pattern and does nothing else,
+ * the benchmark can time it through the same library: reads the first n_bytes (rounded
+ * down to a multiple of 256 KiB) of d_x with the scoring kernel's own load pattern and does nothing else,
  * so that its duration next to gd_score_batch's gives the ceiling of a single pass
  * over the data on this chip.  d_x 16-byte aligned device memory; d_sink one u32 of
  * device memory that the call may write.

@@ -835,6 +835,8 @@ hipError_t gd_launch_ledger_static(gd_ledger_args a, hipStream_t s, bool* fits) 
     if (a.T == 0) return hipSuccess;
     const size_t NW = ((size_t)a.N + 63) / 64;
     const size_t rise_bytes = ((size_t)a.T * NW * 8 + 255) & ~(size_t)255;
+    // (counts_bytes: nothing is kept there any more, but the bound is the one that guard.h states,
+    // and a batch that was refused stays refused)
     if (rise_bytes + a.lay.counts_bytes > LEDGER_SCRATCH_BYTES) { *fits = false; return hipSuccess; }
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
