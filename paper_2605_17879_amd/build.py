@@ -63,7 +63,7 @@ def is_ragged(symbol: str) -> bool:
 
 
 # Ragged tilings (rank counts that do not fill the register tile: bounds checks on the last
-# rows), the one-wave tilings of up to 1 024 ranks (launch-bound) and the per-column route
+# rows), the one-wave tilings of up to 4 096 ranks and the per-column route
 # of short batches (latency-bound: one column per workgroup) may keep a few registers in
 # scratch memory; the exact-fit batch tilings of 256 threads and more may not.
 RAGGED_SCRATCH_LIMIT = 128     # bytes per lane

@@ -7,6 +7,7 @@ import torch
 import oracle
 from gpu_harness import (compare_decision, compare_scores, compare_severity, detector_for, gpu_flags, gpu_score, gpu_topk,
                          oracle_params, run_and_compare)
+from test_gpu_small_columns import sampled_ranks
 from workloads import adversarial, generate, workload
 from workloads.telemetry import ADVERSARIAL_KINDS
 
@@ -801,19 +802,21 @@ def test_window_random_long_batches(seed):
     _random_window_case(seed, long_batches=True)
 
 
-@pytest.mark.parametrize("R,T", [(256, 9000), (1024, 9000), (4096, 2400), (16384, 2400), (65536, 800)])
-def test_hinted_runs_under_regime_changes(R, T):
-    _regime_case(R, T, R // 7 + T)
+# (up to 2 048 ranks, and up to 4 096 of two metrics, one wave scores a column and nothing is
+# carried over; 5 000, 10 248 and 40 000 ranks are ragged tilings of 256 and of 1 024 threads)
+@pytest.mark.parametrize("R,T,M", [(256, 9000, 2), (1024, 9000, 2), (4096, 2400, 2), (16384, 2400, 2), (65536, 800, 2),
+                                   (4096, 3100, 1), (3000, 3100, 1), (5000, 2200, 2), (10248, 2200, 2), (40000, 700, 2)])
+def test_hinted_runs_under_regime_changes(R, T, M):
+    _regime_case(R, T, R // 7 + T, M)
 
 
-def _regime_case(R, T, seed):
-    """Long enough batches that every workgroup scores several consecutive steps and
-    carries the previous step's median, reach and MAD over as hints -- on data whose
+def _regime_case(R, T, seed, M=2):
+    """Long enough batches that every workgroup of the tilings of 256 threads and more scores
+    several consecutive steps and carries the previous step's median, reach and MAD over as hints -- on data whose
     level, spread and character keep changing from one step to the next: level jumps,
     spread collapsing to ties or exploding, two-valued and constant columns, signs,
     missing samples, then calm again."""
-    say(f"case regime changes R={R} T={T} seed={seed}")
-    M = 2
+    say(f"case regime changes R={R} T={T} M={M} seed={seed}")
     g = torch.Generator().manual_seed(seed)
     level = torch.ones(T, dtype=torch.float64)
     spread = torch.full((T,), 0.02, dtype=torch.float64)
@@ -830,7 +833,7 @@ def _regime_case(R, T, seed):
         t += run
     x = level[:, None, None] * torch.exp(spread[:, None, None] *
                                          torch.randn((T, M, R), generator=g, dtype=torch.float64))
-    x[:, 1] = 300.0 / x[:, 1]
+    x[:, 1:] = 300.0 / x[:, 1:]
     for t in range(T):
         k = int(kind[t])
         if k == 5:                                   # two values
@@ -839,10 +842,10 @@ def _regime_case(R, T, seed):
             x[t, 0, ::3] = -x[t, 0, ::3]
         elif k == 7:                                 # missing samples
             x[t, 0, torch.randperm(R, generator=g)[: max(1, R // 9)]] = NAN
-            x[t, 1, int(torch.randint(0, R, (1,), generator=g))] = NAN
+            x[t, M - 1, int(torch.randint(0, R, (1,), generator=g))] = NAN
     x[:, :, 8:16] *= 1.15
     x = x.to(torch.float32)
-    p = oracle_params(R=R, M=M, W=8, k=4, directions=(1, -1), min_signals=1)
+    p = oracle_params(R=R, M=M, W=8, k=4, directions=(1, -1)[:M], min_signals=1)
     det = detector_for(p)
     det.set_streaming_steps(0)
     out = gpu_score(det, x, want_z=False)
@@ -856,18 +859,21 @@ HINTED_KINDS = ["binade", "huge", "integers", "tied_centre", "denormal", "ramp",
                 "narrowing"]
 
 
-@pytest.mark.parametrize("R", [1024, 4096, 65536])
+@pytest.mark.parametrize("R,M", [(1024, 3), (4096, 3), (65536, 3), (4096, 1), (5000, 3), (40000, 3)])
 @pytest.mark.parametrize("kind", HINTED_KINDS)
-def test_hinted_selection_on_stationary_runs_of_awkward_columns(kind, R):
-    """Several consecutive steps of the same kind of column in exact-fit tilings, so that from
-    the second step on the hinted selection runs (bracket, median and MAD carried over): columns
+def test_hinted_selection_on_stationary_runs_of_awkward_columns(kind, R, M):
+    """Several consecutive steps of the same kind of column, so that in the tilings of 256 threads
+    and more (of 4 096 ranks with a single metric, and from 5 000 up; the others are scored by one
+    wave per column, without hints) the hinted selection runs from
+    the second step on (bracket, median and MAD carried over): columns
     centred on a power of two, magnitudes beyond its key limit, integer sensors, a third of the
     ranks tied at the centre, denormals, sorted ranks (every candidate in one wave), one-sided
     and bimodal distributions (the two distance ranges far from symmetric, or falling into a
     gap), and a spread that shrinks a hundredfold from one step to the next."""
     # (a batch is dealt out in runs of ceil(T / workgroups) consecutive steps: three steps per run here)
-    T, M = {1024: 12300, 4096: 3080, 65536: 772}[R], 3
-    say(f"case hinted selection kind={kind} R={R} T={T}")
+    T = {1024: 12300, 4096: 3080, 65536: 772, 5000: 2060, 40000: 520}[R]
+    say(f"case hinted selection kind={kind} R={R} M={M} T={T}")
+    single, M = M == 1, 3                                       # (a single metric: each of the three by itself)
     g = torch.Generator().manual_seed(len(kind) * 1000 + R)
     n = torch.randn((T, M, R), generator=g, dtype=torch.float32).to(torch.float64)
     u = torch.rand((T, M, R), generator=g, dtype=torch.float32).to(torch.float64).clamp_(1e-7, 1.0)
@@ -901,44 +907,55 @@ def test_hinted_selection_on_stationary_runs_of_awkward_columns(kind, R):
     x = x.to(torch.float32)
     x[:, :, 8:16] *= 1.2 if kind != "huge" else 1.0           # one slow node
     dirs = (1, -1, 1)
-    p = oracle_params(R=R, M=M, W=4, k=2, directions=dirs)
     import gpu_harness
     gpu_harness.STREAMING_STEPS = 0                             # whole-run route: hints carried from step to step
     try:
-        rep = run_and_compare(p, x, topk_k=min(8, R // 8), chunks=[T], label=f"{kind}-R{R}")
+        for metrics in ([0], [1], [2]) if single else ([0, 1, 2],):
+            p = oracle_params(R=R, M=len(metrics), W=4, k=2, directions=tuple(dirs[m] for m in metrics))
+            rep = run_and_compare(p, x[:, metrics].contiguous(), topk_k=min(8, R // 8), chunks=[T], label=f"{kind}-R{R}")
+            say("  report", rep)
+            assert rep["z_bit_exact"]
     finally:
         gpu_harness.STREAMING_STEPS = None
-    say("  report", rep)
-    assert rep["z_bit_exact"]
 
 
-# (threads, float4 rows) of the exact-fit tiling of a rank count: the sample behind a run's
-# first hints is register row 0, i.e. ranks (w % rows) * threads * 4 + thread * 4 + 0..3 of
-# thread (w * 64 + lane)
-_SAMPLE_TILING = {1024: (64, 4), 4096: (256, 4), 16384: (256, 16), 65536: (1024, 16)}
+# (threads, float4 rows, rows that hold no padding) of a rank count's tiling: the sample behind a
+# run's first hints is register row 0, i.e. ranks (w % full) * threads * 4 + thread * 4 + 0..3 of
+# thread (w * 64 + lane).  One wave per column (up to 2 048 ranks, and to 4 096 of several metrics)
+# has a sample of its own in every step.
+_SAMPLE_TILING = {4096: (256, 4, 4), 16384: (256, 16, 16), 65536: (1024, 16, 16), 5000: (256, 6, 4), 40000: (1024, 10, 8)}
+
+
+def _sampled_ranks(R, M):
+    if R <= 2048 or (R <= 4096 and M > 1):
+        return torch.from_numpy(sampled_ranks(R))
+    nt, rows, full = _SAMPLE_TILING[R]
+    thread = torch.arange(nt)
+    first = ((thread // 64) % full) * nt * 4 + thread * 4
+    sampled = (first[:, None] + torch.arange(4)[None, :]).reshape(-1)
+    assert int(sampled.max()) < R and len(set(sampled.tolist())) == 4 * nt
+    return sampled
+
+
 SAMPLE_KINDS = ["far_above", "other_scale", "too_tight", "missing", "negative", "constant", "lowest_values"]
 
 
-@pytest.mark.parametrize("R", sorted(_SAMPLE_TILING))
+@pytest.mark.parametrize("R,M", [(1024, 3), (4096, 3), (16384, 3), (65536, 3), (4096, 1), (5000, 3), (40000, 3)])
 @pytest.mark.parametrize("kind", SAMPLE_KINDS)
-def test_first_step_hints_from_unrepresentative_samples(kind, R):
+def test_first_step_hints_from_unrepresentative_samples(kind, R, M):
     """The first step of a run takes its hints from a sample of the column (one register row
-    per thread).  Here exactly the sampled ranks are made misleading -- far above the rest, on
+    per thread; of a column that one wave scores, its first pivots, from 64 ranks).  Here exactly the sampled ranks are made misleading -- far above the rest, on
     another scale, squeezed around the centre, missing, negative, constant, or the lowest
     values of the column -- so that the sampled median, quartiles or both point the wrong way;
     the selection must notice and still return the exact statistics.  Every step of these short
     batches is a first step."""
-    nt, rows = _SAMPLE_TILING[R]
-    T, M = 5, 3
-    say(f"case sampled hints kind={kind} R={R}")
+    say(f"case sampled hints kind={kind} R={R} M={M}")
+    sampled = _sampled_ranks(R, M)
+    T, single, M = 5, M == 1, 3                                 # (a single metric: each of the three by itself)
     g = torch.Generator().manual_seed(len(kind) * 77 + R)
     n = torch.randn((T, M, R), generator=g, dtype=torch.float64)
     x = torch.exp(0.02 * n)
     x[:, 1] = 400.0 / x[:, 1]
-    thread = torch.arange(nt)
-    first = ((thread // 64) % rows) * nt * 4 + thread * 4
-    sampled = (first[:, None] + torch.arange(4)[None, :]).reshape(-1)
-    assert int(sampled.max()) < R and len(set(sampled.tolist())) == 4 * nt
     s = x[:, :, sampled]
     if kind == "far_above":
         s = s * 50.0
@@ -960,18 +977,20 @@ def test_first_step_hints_from_unrepresentative_samples(kind, R):
         srt = torch.sort(x, dim=-1).values                  # the sample holds the lowest values,
         rest = torch.ones(R, dtype=torch.bool)              # the other ranks the rest in order
         rest[sampled] = False
-        x[:, :, rest] = srt[:, :, 4 * nt:]
-        s = srt[:, :, : 4 * nt]
+        x[:, :, rest] = srt[:, :, len(sampled):]
+        s = srt[:, :, : len(sampled)]
     x[:, :, sampled] = s
     x = x.to(torch.float32)
-    p = oracle_params(R=R, M=M, W=4, k=2, directions=(1, -1, 0))
     import gpu_harness
     gpu_harness.STREAMING_STEPS = 0                             # whole-run route
     try:
-        rep = run_and_compare(p, x, topk_k=min(8, R // 8), chunks=[T], label=f"sample-{kind}-R{R}")
+        for metrics in ([0], [1], [2]) if single else ([0, 1, 2],):
+            p = oracle_params(R=R, M=len(metrics), W=4, k=2, directions=tuple((1, -1, 0)[m] for m in metrics))
+            rep = run_and_compare(p, x[:, metrics].contiguous(), topk_k=min(8, R // 8), chunks=[T],
+                                  label=f"sample-{kind}-R{R}")
+            say("  report", rep)
     finally:
         gpu_harness.STREAMING_STEPS = None
-    say("  report", rep)
 
 
 @pytest.mark.parametrize("R", [16384, 65536])

@@ -3,6 +3,7 @@ per compute unit: at most 128 vector registers per lane and nothing spilled.  Th
 compiler's own resource report (-Rpass-analysis=kernel-resource-usage, written beside the
 objects by the build) is parsed here; no GPU is needed."""
 import os
+import re
 
 import pytest
 
@@ -25,7 +26,7 @@ def test_every_scoring_instantiation_is_within_the_register_budget(src):
     res = _report(src)
     tilings = {k: hip_build.tiling_of(k) for k in res if hip_build.tiling_of(k)}
     want_z = 1 if src == "score_z.hip" else 0
-    # six tilings of whole batches (exact fit and ragged) and those of the per-column route
+    # the exact-fit tilings of whole batches and those of the per-column route
     batch = {(64, 1, 10), (64, 4, 10), (256, 4, 11), (256, 16, 11), (512, 16, 12), (1024, 16, 12)}
     column = {(64, 1, 10), (64, 4, 10), (256, 4, 11), (1024, 4, 12), (1024, 8, 12), (1024, 16, 12)}
     seen_batch = {t[:3] for t in tilings.values() if t[4] == 0 and t[5] == want_z}
@@ -39,6 +40,23 @@ def test_every_scoring_instantiation_is_within_the_register_budget(src):
         assert r["LDS Size [bytes/block]"] == 0, name          # all of its LDS is dynamic (sized by the launcher)
         if t[3] and t[0] >= 256 and not t[4]:                  # exact-fit batch tilings: nothing in scratch memory
             assert r["VGPRs Spill"] == 0 and r["ScratchSize [bytes/lane]"] == 0, (name, r)
+
+
+RAGGED = {"few": {(64, 1, 10), (64, 2, 10), (64, 4, 10), (64, 8, 10), (64, 12, 10), (64, 16, 10), (256, 4, 11),
+                  (256, 6, 11), (256, 8, 11)},
+          "many": {(nt, rows, log) for nt, log in ((256, 11), (512, 12), (1024, 12)) for rows in (10, 12, 14, 16)},
+          "columns": {(256, 4, 11)} | {(1024, rows, 12) for rows in (2, 4, 6, 8, 10, 12, 14, 16)}}
+
+
+@pytest.mark.parametrize("src", hip_build.RAGGED_SOURCES)
+def test_every_ragged_instantiation_is_within_the_register_budget(src):
+    res = {k: r for k, r in _report(src).items() if hip_build.is_ragged(k)}
+    seen = {tuple(int(g) for g in re.search(r"score_ragged_kernelILi(\d+)ELi(\d+)ELi(\d+)E", k).groups()) for k in res}
+    kind = re.match(r"score_ragged_([a-z]+?)(_z)?\.hip", src).group(1)
+    assert seen == RAGGED[kind], seen
+    assert hip_build.check_register_budget(res) == []
+    for name, r in res.items():
+        assert r["VGPRs"] + r["AGPRs"] <= hip_build.VGPR_BUDGET and r["Occupancy [waves/SIMD]"] >= 4, name
 
 
 def test_the_parser_reads_the_compiler_remarks():
