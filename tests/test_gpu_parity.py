@@ -805,7 +805,7 @@ def test_window_random_long_batches(seed):
 # (up to 2 048 ranks, and up to 4 096 of two metrics, one wave scores a column and nothing is
 # carried over; 5 000, 10 248 and 40 000 ranks are ragged tilings of 256 and of 1 024 threads)
 @pytest.mark.parametrize("R,T,M", [(256, 9000, 2), (1024, 9000, 2), (4096, 2400, 2), (16384, 2400, 2), (65536, 800, 2),
-                                   (4096, 3100, 1), (3000, 3100, 1), (5000, 2200, 2), (10248, 2200, 2), (40000, 700, 2)])
+                                   (4096, 3100, 1), (3000, 3100, 1), (3080, 1700, 5), (4096, 1700, 6), (5000, 2200, 2), (10248, 2200, 2), (40000, 700, 2)])
 def test_hinted_runs_under_regime_changes(R, T, M):
     _regime_case(R, T, R // 7 + T, M)
 
@@ -845,7 +845,7 @@ def _regime_case(R, T, seed, M=2):
             x[t, M - 1, int(torch.randint(0, R, (1,), generator=g))] = NAN
     x[:, :, 8:16] *= 1.15
     x = x.to(torch.float32)
-    p = oracle_params(R=R, M=M, W=8, k=4, directions=(1, -1)[:M], min_signals=1)
+    p = oracle_params(R=R, M=M, W=8, k=4, directions=(1,) + (-1,) * (M - 1), min_signals=1)
     det = detector_for(p)
     det.set_streaming_steps(0)
     out = gpu_score(det, x, want_z=False)
