@@ -1831,7 +1831,7 @@ bool use_split(const gd_score_args& a, int n_cu) {
 // Up to 4 096 ranks: one wave per column scores the M columns of a step side by side, 256 threads
 // one after another but each column faster.  Measured (us by 256 threads / by waves):
 //   1 025 to 2 048 ranks, one metric: 256 steps 18 / 21 (missing samples 16 / 22, both signs 16 / 28,
-//     whole degrees 17..165 / 24), 1 500 steps 37 / 25; two metrics: 256 steps 31 / 20
+//     whole degrees 17..165 / 25..52), 1 500 steps 37 / 25; two metrics: 256 steps 31 / 20
 //   2 049 to 3 072 ranks, two metrics: 256 steps 29 / 33 (missing 26 / 35, signs 26 / 41, equal values
 //     50 / 15, values over decades 170 / 50), 1 500 steps 60 / 43; three: 256 steps 42 / 34
 //   3 073 to 4 096 ranks, two metrics: 500 steps 36 / 43 (missing 35 / 43, signs 32 / 62, few distinct
