@@ -21,6 +21,9 @@ FLAGS = [
     "-ffp-contract=off", "-fno-fast-math", "-fhip-fp32-correctly-rounded-divide-sqrt",
     "-fno-gpu-flush-denormals-to-zero",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # atomics on LDS and memory as they are written: the kernels have one lane of a wave make
+    # them, which the optimiser would still wrap into a loop over the active lanes
+    "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
     "-Wall", "-Wno-unused-command-line-argument",
     # the compiler's own account of registers, spills and LDS per kernel (kept as text
     # beside the objects and checked below)

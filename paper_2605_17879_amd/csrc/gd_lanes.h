@@ -53,39 +53,51 @@ constexpr uint64_t gd_lanes_with() {
     return m;
 }
 
+// The lanes of a constant mask.  INLOOP: made where it is used, from words that the optimiser
+// cannot see through -- in a kernel that sorts inside a loop it would otherwise keep all of a
+// sort's masks in scalar registers across the loop, and spill them.
+template <uint64_t MASK, bool INLOOP>
+__device__ __forceinline__ bool gd_lane_in() {
+    if constexpr (!INLOOP) return __builtin_amdgcn_inverse_ballot_w64(MASK);
+    uint32_t lo = (uint32_t)MASK, hi = (uint32_t)(MASK >> 32);
+    asm volatile("" : "+s"(lo), "+s"(hi));
+    return __builtin_amdgcn_inverse_ballot_w64((uint64_t)hi << 32 | lo);
+}
+
 // One compare-exchange stage across the wave.
-template <int J, int S>
+template <int J, int S, bool INLOOP>
 __device__ __forceinline__ uint32_t gd_exchange(uint32_t v) {
     uint32_t o;
     if constexpr (J == 16) {
         auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-        o = __builtin_amdgcn_inverse_ballot_w64(gd_lanes_with<16>()) ? r[0] : r[1];
+        o = gd_lane_in<gd_lanes_with<16>(), INLOOP>() ? r[0] : r[1];
     } else if constexpr (J == 32) {
         auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-        o = __builtin_amdgcn_inverse_ballot_w64(gd_lanes_with<32>()) ? r[0] : r[1];
+        o = gd_lane_in<gd_lanes_with<32>(), INLOOP>() ? r[0] : r[1];
     } else {
         o = gd_lane_xor<J>(v, 0);
     }
-    return __builtin_amdgcn_inverse_ballot_w64(gd_keeps_smaller<J, S>()) ? min(v, o) : max(v, o);
+    return gd_lane_in<gd_keeps_smaller<J, S>(), INLOOP>() ? min(v, o) : max(v, o);
 }
-template <int S>
+template <int S, bool INLOOP>
 __device__ __forceinline__ uint32_t gd_merge(uint32_t v) {
-    if constexpr (S > 32) v = gd_exchange<32, S>(v);
-    if constexpr (S > 16) v = gd_exchange<16, S>(v);
-    if constexpr (S > 8) v = gd_exchange<8, S>(v);
-    if constexpr (S > 4) v = gd_exchange<4, S>(v);
-    if constexpr (S > 2) v = gd_exchange<2, S>(v);
-    return gd_exchange<1, S>(v);
+    if constexpr (S > 32) v = gd_exchange<32, S, INLOOP>(v);
+    if constexpr (S > 16) v = gd_exchange<16, S, INLOOP>(v);
+    if constexpr (S > 8) v = gd_exchange<8, S, INLOOP>(v);
+    if constexpr (S > 4) v = gd_exchange<4, S, INLOOP>(v);
+    if constexpr (S > 2) v = gd_exchange<2, S, INLOOP>(v);
+    return gd_exchange<1, S, INLOOP>(v);
 }
 
 // 64 keys, one per lane, into ascending order.
+template <bool INLOOP = false>
 __device__ __forceinline__ uint32_t gd_sort64(uint32_t v) {
-    v = gd_merge<2>(v);
-    v = gd_merge<4>(v);
-    v = gd_merge<8>(v);
-    v = gd_merge<16>(v);
-    v = gd_merge<32>(v);
-    return gd_merge<64>(v);
+    v = gd_merge<2, INLOOP>(v);
+    v = gd_merge<4, INLOOP>(v);
+    v = gd_merge<8, INLOOP>(v);
+    v = gd_merge<16, INLOOP>(v);
+    v = gd_merge<32, INLOOP>(v);
+    return gd_merge<64, INLOOP>(v);
 }
 
 // Transpose of the 64x64 bit matrix whose row i is the word held by lane i:

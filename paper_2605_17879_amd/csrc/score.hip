@@ -47,6 +47,7 @@ constexpr int WAVE = 64;
 constexpr int CAND_CAP = 512;  // values ranked exactly in LDS per selection
 
 __device__ __forceinline__ uint32_t rfl(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ float uniform(float v) { return __uint_as_float(rfl(__float_as_uint(v))); }
 
 // Order-preserving map fp32 -> u32 and back.
 __device__ __forceinline__ uint32_t key_of(float f) {
@@ -61,6 +62,13 @@ __device__ __forceinline__ float float_of_key(uint32_t k) {
 // Ranks whose exceed bits one workgroup of combine_kernel puts together.
 constexpr uint32_t PLANE_RANKS = 2048;
 
+// What the score loop needs to know of a column (worked out by one wave).
+struct alignas(16) ScoreParams {
+    float s, ss, rs;           // scale, its signed form and the reciprocal of that
+    float cc, kk, margin, sthr;    // node estimate of the decision-only route
+    uint32_t xcut, route, exact_recip;
+};
+
 template <int NT, int LOG_NB, int MAX_NODES>
 struct Shared {
     static constexpr int NB = 1 << LOG_NB;
@@ -73,9 +81,7 @@ struct Shared {
     uint32_t cand[CAND_CAP + 4];   // 16-byte aligned; read four at a time when ranking
     uint32_t wpart[16];
     uint32_t below, ncand;
-    uint32_t nkept;            // hinted MAD: candidates kept after the exact test
-    uint32_t wcnt[16];         // hinted MAD: values gathered by each wave
-    uint32_t mres[2][4];       // hinted MAD: edge indices found by the search and a found flag (two slots, used in turn)
+    uint32_t nkept, nnear;     // hinted MAD: candidates kept after the exact test, and those found nearer
     uint32_t smin, smax;       // extremes of the sample keys
     uint32_t d1, d2;           // MAD shortcut: distance interval holding the wanted ranks
     uint32_t umax[2];          // largest raw bit pattern of the column (double-buffered)
@@ -85,6 +91,7 @@ struct Shared {
     float hmed[8], hwl[8], hwh[8], hmad[8];
     uint32_t hok[8];
     uint32_t hfast[8];         // the hinted selection below has not failed for this metric yet
+    ScoreParams par;
     alignas(8) uint8_t nodeb[MAX_NODES];        // the step's node mask bytes, read eight at a time
     uint64_t ranka[MAX_NODES / 8 > 0 ? MAX_NODES / 8 : 1];     // the step's rank anomaly words (zero between steps)
 };
@@ -96,8 +103,8 @@ __device__ __forceinline__ uint32_t dpp0(uint32_t v) {   // lanes without a sour
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xF, true);
 }
 template <int CTRL, int ROW_MASK = 0xF>
-__device__ __forceinline__ uint32_t dpp_keep(uint32_t v) {   // lanes without a source keep v
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROW_MASK, 0xF, false);
+__device__ __forceinline__ uint32_t dpp1(uint32_t v) {   // lanes without a source read all ones
+    return (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, CTRL, ROW_MASK, 0xF, false);
 }
 template <int J>
 __device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
@@ -123,17 +130,18 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
     v += dpp0<0x143, 0xC>(v);     // row_bcast:31 into rows 2 and 3
     return v;
 }
-// Minimum / maximum over the wave, valid in lane 63.
+// Minimum / maximum over the wave, valid in lane 63 (lanes without a source read what changes
+// nothing, so that a step is one instruction).
 __device__ __forceinline__ uint32_t wave_min_to_last(uint32_t v) {
-    v = min(v, dpp_keep<0x111>(v)); v = min(v, dpp_keep<0x112>(v));
-    v = min(v, dpp_keep<0x114>(v)); v = min(v, dpp_keep<0x118>(v));
-    v = min(v, dpp_keep<0x142, 0xA>(v)); v = min(v, dpp_keep<0x143, 0xC>(v));
+    v = min(v, dpp1<0x111>(v)); v = min(v, dpp1<0x112>(v));
+    v = min(v, dpp1<0x114>(v)); v = min(v, dpp1<0x118>(v));
+    v = min(v, dpp1<0x142, 0xA>(v)); v = min(v, dpp1<0x143, 0xC>(v));
     return v;
 }
 __device__ __forceinline__ uint32_t wave_max_to_last(uint32_t v) {
-    v = max(v, dpp_keep<0x111>(v)); v = max(v, dpp_keep<0x112>(v));
-    v = max(v, dpp_keep<0x114>(v)); v = max(v, dpp_keep<0x118>(v));
-    v = max(v, dpp_keep<0x142, 0xA>(v)); v = max(v, dpp_keep<0x143, 0xC>(v));
+    v = max(v, dpp0<0x111>(v)); v = max(v, dpp0<0x112>(v));
+    v = max(v, dpp0<0x114>(v)); v = max(v, dpp0<0x118>(v));
+    v = max(v, dpp0<0x142, 0xA>(v)); v = max(v, dpp0<0x143, 0xC>(v));
     return v;
 }
 
@@ -254,6 +262,59 @@ __device__ __forceinline__ bool locate(SH& sh, uint32_t tid, uint32_t ka, uint32
     if (USE_BELOW && tid == 0) sh.below = 0;
     *below_out = rfl(below);
     return rfl(ka >= below && rb < total) != 0;
+}
+
+// A wave's own list of register rows (four values of a lane) that hold a value somebody looks
+// for.  Rows instead of values, at a position made of a count in a scalar register and the
+// lanes' ballot: six instructions for the rows with a hit, and no round trip to LDS; which of
+// the four values it was is found out afterwards, by drain(), a value per lane.  The list lies in
+// the counters, which are at rest between two counting passes, and leaves them at rest.
+template <typename SH>
+struct RowList {
+    static constexpr uint32_t MOST = 64;           // rows of a wave
+    uint32_t* const words;
+    uint32_t n = 0;                                // (wave-uniform)
+    __device__ __forceinline__ RowList(SH& sh, uint32_t w) : words(sh.hist + w * (MOST * 4u)) {}
+    __device__ __forceinline__ bool overflow() const { return n > MOST; }
+    __device__ __forceinline__ void add(bool hit, const float (&row)[4]) {
+        const uint64_t hm = __ballot(hit);
+        if (__builtin_expect(hm != 0ull, 0)) {
+            const uint32_t pos = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(hm >> 32),
+                                                               __builtin_amdgcn_mbcnt_lo((uint32_t)hm, 0u));
+            if (hit && pos < MOST) {
+                // (word by word: a store of all four ties the row's registers together, and the
+                // column is then copied between passes)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    __hip_atomic_store(&words[4 * pos + i], __float_as_uint(row[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            }
+            n += (uint32_t)__popcll(hm);
+        }
+    }
+    // use(value, valid) for every value listed, by whole waves
+    template <typename Use>
+    __device__ __forceinline__ void drain(uint32_t lane, Use use) {
+        const uint32_t end = 4u * min(n, MOST);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        for (uint32_t at = 0; at < end; at += WAVE) {
+            const bool valid = at + lane < end;
+            uint32_t x = 0;
+            if (valid) { x = words[at + lane]; words[at + lane] = 0; }
+            use(x, valid);
+        }
+        n = 0;
+    }
+};
+
+// The lanes with a hit append their value to a list shared by the workgroup (whole waves call).
+__device__ __forceinline__ void append(uint32_t* list, uint32_t* count, bool hit, uint32_t value) {
+    const uint64_t hm = __ballot(hit);
+    if (hm == 0ull) return;
+    uint32_t base = 0;
+    const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(hm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hm, 0u));
+    if (hit && before == 0) base = atomicAdd(count, (uint32_t)__popcll(hm));
+    base = (uint32_t)__builtin_amdgcn_readlane((int)base, __builtin_ctzll(hm));
+    if (hit && base + before < (uint32_t)CAND_CAP) list[base + before] = value;
 }
 
 // Exact ranking of the cnt gathered candidates in sh.cand (ties broken by
@@ -434,40 +495,41 @@ __device__ __forceinline__ bool block_select(SH& sh, const Keys& keys, uint32_t 
         }
         const uint32_t ba = rfl(sh.res[0]), pa = rfl(sh.res[1]);
         const uint32_t bb = rfl(sh.res[2]), pb = rfl(sh.res[3]);
-        uint32_t va, vb;
-        if (shift == 0) {               // one key per bucket: the bucket is the answer
-            va = lo + ba; vb = lo + bb;
-        } else if (pb - pa <= (uint32_t)CAND_CAP) {
+        uint32_t va = lo + ba, vb = lo + bb;            // shift == 0: one key per bucket, the answer
+        bool settled = shift == 0;
+        if (!settled && pb - pa <= (uint32_t)CAND_CAP) {
             // gather the values of buckets ba..bb and rank them exactly
             const uint32_t clo = lo + (ba << shift);
             const uint64_t cend = (uint64_t)lo + ((uint64_t)(bb + 1) << shift) - 1;
             const uint32_t chi = cend > hi ? hi : (uint32_t)cend;
             const uint32_t cspan = chi - clo;
             const uint32_t tok = keys.token();
+            RowList<SH> rows(sh, rfl(tid >> 6));
 #pragma unroll
             for (int j = 0; j < ROWS; ++j) {
                 // one test per register row (hits are rare): the smallest offset decides
                 uint32_t off[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) off[i] = keys.at(j, i, tok) - clo;
-                if (min(min(off[0], off[1]), min(off[2], off[3])) <= cspan) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        if (off[i] <= cspan) {
-                            uint32_t pos = atomicAdd(&sh.ncand, 1u);
-                            if (pos < (uint32_t)CAND_CAP) sh.cand[pos] = off[i] + clo;
-                        }
-                    }
-                }
+                rows.add(min(min(off[0], off[1]), min(off[2], off[3])) <= cspan, keys.v[j]);
                 __builtin_amdgcn_sched_barrier(0);
             }
+            rows.drain(lane, [&](uint32_t x, bool valid) {
+                const uint32_t kk = keys.key(__uint_as_float(x), tok);
+                append(sh.cand, &sh.ncand, valid && kk - clo <= cspan, kk);
+            });
             __syncthreads();
-            const uint32_t cnt = min(sh.ncand, (uint32_t)CAND_CAP);
-            const uint32_t wa = ka - below - pa, wb = kb - below - pa;
-            rank_candidates<NT>(sh, tid, cnt, wa, wb);
+            const uint32_t cnt = rfl(sh.ncand);
+            settled = cnt == pb - pa;                   // (else a wave's list overflowed)
+            if (settled) {
+                rank_candidates<NT>(sh, tid, cnt, ka - below - pa, kb - below - pa);
+                va = rfl(sh.res[4]); vb = rfl(sh.res[5]);
+            } else {
+                __syncthreads();
+            }
             if (tid == 0) sh.ncand = 0;
-            va = rfl(sh.res[4]); vb = rfl(sh.res[5]);
-        } else {
+        }
+        if (!settled) {
             // crowded (ties): look inside bucket ba; if the two statistics sit in
             // different crowded buckets, finish k0 first, then k1 on its own
             if (ba != bb) { mode = 1; kb = ka; }
@@ -597,6 +659,7 @@ __device__ __forceinline__ bool mad_from_histogram(SH& sh, const float (&v)[ROWS
     uint32_t nbelow = 0;
     {
         const uint32_t tok = opaque_s(__float_as_uint(med));
+        RowList<SH> rows(sh, rfl(tid >> 6));
 #pragma unroll
         for (int j = 0; j < ROWS; ++j) {
             uint32_t off[4];
@@ -607,18 +670,15 @@ __device__ __forceinline__ bool mad_from_histogram(SH& sh, const float (&v)[ROWS
                 off[i] = kk - d1;
             }
             // one test per register row (hits are rare): the smallest offset decides
-            if (min(min(off[0], off[1]), min(off[2], off[3])) <= span) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if (off[i] <= span) {
-                        uint32_t pos = atomicAdd(&sh.ncand, 1u);
-                        if (pos < (uint32_t)CAND_CAP) sh.cand[pos] = off[i] + d1;
-                    }
-                }
-            }
+            rows.add(min(min(off[0], off[1]), min(off[2], off[3])) <= span, v[j]);
             asm volatile("" : "+v"(nbelow));
             __builtin_amdgcn_sched_barrier(0);
         }
+        if (rows.overflow() && lane == 0) atomicAdd(&sh.ncand, (uint32_t)CAND_CAP + 1u);
+        rows.drain(lane, [&](uint32_t x, bool valid) {
+            const uint32_t kk = __float_as_uint(fabsf(__uint_as_float(x) - __uint_as_float(tok)));
+            append(sh.cand, &sh.ncand, valid && kk - d1 <= span, kk);
+        });
     }
     nbelow = wave_incl_scan(nbelow);
     if (lane == WAVE - 1 && nbelow) atomicAdd(&sh.below, nbelow);
@@ -664,7 +724,8 @@ struct HintedResult {
     int found;                  // 2: median and MAD, 1: median alone, 0: neither
     uint32_t umax;              // largest raw bit pattern of the column
     uint32_t m0, m1;            // the two middle keys
-    uint32_t q0, q1;            // the two middle distances (bit patterns)
+    uint32_t q0, q1;            // the two middle distances (bit patterns), or, of `listed` ones in
+    uint32_t listed;            // sh.cand (at most 64), their ranks: for the first wave to sort
     uint32_t present;           // samples that arrived, where some did not (0: all did)
 };
 
@@ -705,9 +766,8 @@ __device__ __forceinline__ void count_present(SH& sh, const float (&v)[ROWS][4],
 template <int NT, int ROWS, int LOG_NB, typename SH, typename Pad>
 __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[ROWS][4], Pad set_padding,
                                                       uint32_t hint_lo, uint32_t hint_hi, float mad_hint,
-                                                      uint32_t k0, uint32_t k1, uint32_t* umax_slot,
-                                                      uint32_t par) {
-    HintedResult out = {0, 0u, 0u, 0u, 0u, 0u, 0u};
+                                                      uint32_t k0, uint32_t k1, uint32_t* umax_slot) {
+    HintedResult out = {0, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
     constexpr int NB = 1 << LOG_NB;
     constexpr uint32_t KEY_LIMIT = 0x7D000000u;    // beyond it the signed bucket arithmetic could wrap
     const uint32_t span0 = hint_hi - hint_lo;
@@ -776,6 +836,7 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
     const uint32_t bb = rfl(sh.res[2]), pb = rfl(sh.res[3]);
     if (pb - pa > (uint32_t)CAND_CAP / 2 || bb - ba > 1u) return out;      // crowded (ties): the general route narrows
     // ---- pass 2: the median's bucket(s)
+    RowList<SH> rows(sh, w);
     {
         const uint32_t clo = lo + (ba << shift);
         const uint32_t cspan = ((bb - ba + 1u) << shift) - 1u;
@@ -785,142 +846,115 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
             uint32_t off[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) off[i] = __float_as_uint(v[j][i]) - tok;
-            if (min(min(off[0], off[1]), min(off[2], off[3])) <= cspan) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if (off[i] <= cspan) {
-                        uint32_t pos = atomicAdd(&sh.ncand, 1u);
-                        if (pos < (uint32_t)CAND_CAP) sh.cand[pos] = off[i] + tok;
-                    }
-                }
-            }
+            rows.add(min(min(off[0], off[1]), min(off[2], off[3])) <= cspan, v[j]);
             __builtin_amdgcn_sched_barrier(0);
         }
+        rows.drain(lane, [&](uint32_t x, bool valid) {
+            const bool hit = valid && x - tok <= cspan;
+            append(sh.cand, &sh.ncand, hit, x);
+        });
     }
     __syncthreads();
-    {
-        const uint32_t ncnt = min(sh.ncand, (uint32_t)CAND_CAP);
-        rank_candidates<NT>(sh, tid, ncnt, k0 - below - pa, k1 - below - pa);
-        if (tid == 0) sh.ncand = 0;
-    }
+    const uint32_t ncnt = rfl(sh.ncand);
+    rank_candidates<NT>(sh, tid, min(ncnt, (uint32_t)CAND_CAP), k0 - below - pa, k1 - below - pa);
+    if (tid == 0) sh.ncand = 0;
+    if (ncnt != pb - pa) return out;               // (a wave's list overflowed)
     const uint32_t s0 = rfl(sh.res[4]), s1 = rfl(sh.res[5]);
     out.m0 = s0; out.m1 = s1;
     out.found = 1;
     out.umax = top;
     const float med = 0.5f * (__uint_as_float(s0) + __uint_as_float(s1));
     if (!(mad_hint > 0.0f)) return out;
-    // ---- MAD: search the prefix sums.  Candidate c is the right edge e_c (a bucket's lower
-    // edge, e_c > bb); its distance from the median mirrored to the left gives the edge
-    // f_c, the first one above the mirror point.  F_c = #[f_c, e_c) never decreases with c;
-    // the thread that sees F_c <= k0 < F_{c+1} reports e_c, f_c, f_{c+1}.
+    // ---- MAD: search the prefix sums.  Candidate e is a right edge (a bucket's lower
+    // edge, e > bb); its distance from the median mirrored to the left gives the edge
+    // f, the first one above the mirror point.  F = #[f, e) never decreases with e.  Every wave
+    // looks at 64 edges around the one that the hint points at (and, should they not hold the
+    // answer, at the 64 beside them), one a lane, for itself: no barrier.
     auto edge = [&](uint32_t e) { return __uint_as_float(lo + (e << shift)); };
-    struct Inner { uint32_t count, f; };                 // count ~0u: not a candidate
-    auto inner_count = [&](uint32_t e) -> Inner {
-        if (e <= bb || e > bmax + 1u) return Inner{0xFFFFFFFFu, 0u};
-        const float d = edge(e) - med;
-        const uint32_t kl = __float_as_uint(med - d);
-        if (!(d > 0.0f) || kl < lo || kl > hi) return Inner{0xFFFFFFFFu, 0u};
-        const uint32_t f = ((kl - lo) >> shift) + 1u;
-        return Inner{f <= e ? sh.pref[e] - sh.pref[f] : 0xFFFFFFFFu, f};
-    };
-    {
-        const uint32_t kr = __float_as_uint(med + mad_hint);
-        const uint32_t eh = kr >= lo && kr <= hi ? (kr - lo) >> shift : bmax;   // the edge the hint points at
-        constexpr int CPT = NT >= 512 ? 1 : 512 / NT;          // candidates per thread: at least 512 in all
-#pragma unroll
-        for (int c = 0; c < CPT; ++c) {
-            const uint32_t e = eh - (uint32_t)(NT * CPT / 2) + tid * CPT + c;     // (wraps below 0: rejected as > bmax + 1)
-            const Inner A = inner_count(e), B = inner_count(e + 1u);
-            if (A.count != 0xFFFFFFFFu && B.count != 0xFFFFFFFFu && A.count <= k0 && B.count > k0) {
-                sh.mres[par][0] = e; sh.mres[par][1] = A.f; sh.mres[par][2] = B.f; sh.mres[par][3] = 1;
-            }
+    const uint32_t kr = __float_as_uint(med + mad_hint);
+    uint32_t e0 = (kr >= lo && kr <= hi ? (kr - lo) >> shift : bmax) - 32u;     // the first lane's edge (mod 2^32)
+    uint32_t Rb0 = 0, Rb1 = 0, Lb0 = 0, Lb1 = 0;
+    bool found = false;
+    for (int round = 0; round < 8 && !found; ++round) {
+        const uint32_t e = e0 + lane;
+        uint32_t f = 0, F = 0;
+        bool valid = e > bb && e <= bmax + 1u;                    // (wraps below 0: beyond bmax)
+        if (valid) {
+            const float d = edge(e) - med;
+            const uint32_t kl = __float_as_uint(med - d);
+            f = ((kl - lo) >> shift) + 1u;
+            valid = d > 0.0f && kl >= lo && kl <= hi && f <= e;
+            if (valid) F = sh.pref[e] - sh.pref[f];
         }
+        const uint64_t under = __ballot(valid && F <= k0), over = __ballot(valid && F > k1);
+        if (over == 0ull && under == 0ull) break;                  // no edge here has a mirror image
+        if (over == 0ull) { e0 += 32u; continue; }
+        // the last edge with at most k0 values inside, and the last one before it whose mirror
+        // image is a bucket further in: at most k0 values are closer than that one
+        const uint32_t c = under ? 63u - (uint32_t)__builtin_clzll(under) : 0u;
+        const uint32_t fc = (uint32_t)__builtin_amdgcn_readlane((int)f, (int)c);
+        const uint64_t inner = __ballot(valid && f > fc);
+        if (under == 0ull || inner == 0ull) { e0 -= 32u; continue; }
+        const uint32_t la = 63u - (uint32_t)__builtin_clzll(inner), lb = (uint32_t)__builtin_ctzll(over);
+        Rb0 = rfl(e0 + la);
+        Rb1 = rfl(e0 + lb - 1u);
+        Lb1 = (uint32_t)__builtin_amdgcn_readlane((int)f, (int)la) - 1u;
+        Lb0 = (uint32_t)__builtin_amdgcn_readlane((int)f, (int)lb) - 1u;
+        found = true;
     }
-    __syncthreads();
-    // (the caller clears the other slot's flag, which every thread read a column ago)
-    const uint32_t found = rfl(sh.mres[par][3]);
-    const uint32_t e_star = rfl(sh.mres[par][0]), f_star = rfl(sh.mres[par][1]), f_next = rfl(sh.mres[par][2]);
-    if (!found) return out;
-    // bucket ranges around the edges (one bucket of margin each side)
-    const uint32_t Rb0 = e_star - 1u, Rb1 = min(e_star + 1u, bmax);
-    const uint32_t Lb1 = f_star, Lb0 = f_next >= 2u ? f_next - 2u : 0u;
-    if (Rb0 <= bb || Lb1 >= ba || Lb0 > Lb1) return out;          // ranges reach the median's buckets: general route
+    // Bucket ranges: the distances wanted end in the buckets Rb0..Rb1 on the right of the
+    // median, Lb0..Lb1 on its left.
+    if (!found || Rb0 <= bb || Rb1 > bmax || Rb0 > Rb1 || Lb1 >= ba || Lb0 > Lb1) return out;
     const float dLi = med - edge(Lb1 + 1u), dLo = med - edge(Lb0);
     const float dRi = edge(Rb0) - med, dRo = edge(Rb1 + 1u) - med;
     const float DI = fmaxf(dLi, dRi), DO = fminf(dLo, dRo);
     const float Da = fminf(dLi, dRi), Db = fmaxf(dLo, dRo);
     const uint32_t n_in = rfl(sh.pref[Rb0] - sh.pref[Lb1 + 1u]);
     if (!(Da > 0.0f) || !(DO >= DI)) return out;
-    // ---- pass 3: gather the values whose distance from the median lies in [Da, Db].  No
-    // round trips: each wave appends to a list of its own inside sh.cand (free at this point),
-    // at a position made of a count kept in a scalar register and the lanes' ballot.
-    constexpr uint32_t NWAVES = NT / WAVE, SUB = (uint32_t)CAND_CAP / NWAVES;
+    // ---- pass 3: gather the rows that hold a value whose distance from the median lies in
+    // [Da, Db], and classify their values exactly
     {
         const float tokm = __uint_as_float(opaque_s(__float_as_uint(med)));
         const float toka = __uint_as_float(opaque_s(__float_as_uint(Da)));
         const uint32_t wspan = __float_as_uint(Db - Da);
-        uint32_t* const mine = sh.cand + w * SUB;
-        uint32_t n = 0;                            // (wave-uniform)
 #pragma unroll
         for (int j = 0; j < ROWS; ++j) {
             uint32_t off[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) off[i] = __float_as_uint(fabsf(v[j][i] - tokm) - toka);   // negative: a large pattern
-            // one test per register row (hits are rare): the smallest offset decides
-            if (__builtin_expect(__ballot(min(min(off[0], off[1]), min(off[2], off[3])) <= wspan) != 0ull, 0)) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const bool hit = off[i] <= wspan;
-                    const uint64_t hm = __ballot(hit);
-                    if (hm != 0ull) {
-                        const uint32_t pos = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(hm >> 32),
-                                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)hm, 0u));
-                        if (hit && pos < SUB) mine[pos] = __float_as_uint(v[j][i]);
-                        n += (uint32_t)__popcll(hm);
-                    }
-                }
-            }
+            rows.add(min(min(off[0], off[1]), min(off[2], off[3])) <= wspan, v[j]);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (lane == 0) sh.wcnt[w] = n;
+        if (rows.overflow() && lane == 0) atomicAdd(&sh.nkept, (uint32_t)CAND_CAP + 1u);
+        rows.drain(lane, [&](uint32_t x, bool valid) {
+            const uint32_t b = (x - lo) >> shift;              // (values outside the bracket: b is huge)
+            const bool in = valid && x >= lo && ((b >= Lb0 && b <= Lb1) || (b >= Rb0 && b <= Rb1));
+            const float d = fabsf(__uint_as_float(x) - med);
+            const uint32_t nlt = (uint32_t)__popcll(__ballot(in && d < DI));
+            if (nlt != 0 && lane == 0) atomicAdd(&sh.nnear, nlt);
+            append(sh.cand, &sh.nkept, in && d >= DI && d <= DO, __float_as_uint(d));
+        });
     }
     __syncthreads();
-    // classify the gathered values exactly; those kept go to a second list, which takes the
-    // place of the prefix sums (read for the last time above).  A wave whose list overflowed
-    // fails the selection for everybody.
-    static_assert(NB + 4 >= CAND_CAP + 4, "the prefix array holds the second list");
-    uint32_t* const kept_list = sh.pref;
-    const bool fits = __ballot(lane < NWAVES && sh.wcnt[lane < NWAVES ? lane : 0u] > SUB) == 0ull;
-    if (fits) {
-        uint32_t nlt = 0;
-#pragma unroll
-        for (int q = 0; q < (CAND_CAP + NT - 1) / NT; ++q) {
-            const uint32_t slot = tid + q * NT;
-            if (slot < (uint32_t)CAND_CAP && slot % SUB < sh.wcnt[slot / SUB]) {
-                const uint32_t x = sh.cand[slot];
-                const uint32_t b = (x - lo) >> shift;          // (values outside the bracket: b is huge)
-                const bool in_l = x >= lo && b >= Lb0 && b <= Lb1, in_r = x >= lo && b >= Rb0 && b <= Rb1;
-                const float d = fabsf(__uint_as_float(x) - med);
-                if (in_l || in_r) {
-                    if (d < DI) nlt += 1u;
-                    else if (d <= DO) kept_list[atomicAdd(&sh.nkept, 1u)] = __float_as_uint(d);
-                }
-            }
+    const uint32_t c_in = n_in + rfl(sh.nnear), kept = rfl(sh.nkept);
+    const bool ok = kept <= (uint32_t)CAND_CAP && c_in <= k0 && k1 < c_in + kept;
+    out.q0 = k0 - c_in; out.q1 = k1 - c_in;
+    out.listed = kept;
+    if (__builtin_expect(!ok || kept > (uint32_t)WAVE, 0)) {
+        if (ok) {
+            rank_candidates<NT>(sh, tid, kept, k0 - c_in, k1 - c_in);
+            out.q0 = rfl(sh.res[4]);
+            out.q1 = rfl(sh.res[5]);
+            out.listed = 0;
+        } else {
+            __syncthreads();
         }
-        if (nlt) atomicAdd(&sh.below, nlt);
+        if (tid == 0) {          // (a zero made here: kept in registers for the whole kernel it ends up spilled)
+            const uint32_t zero = opaque_v(0u);
+            sh.nkept = zero; sh.nnear = zero;
+        }
+        if (!ok) return out;
     }
-    __syncthreads();
-    const uint32_t c_in = n_in + rfl(sh.below), kept = rfl(sh.nkept);
-    const bool ok = fits && c_in <= k0 && k1 < c_in + kept;
-    if (ok) rank_candidates<NT>(sh, tid, kept, k0 - c_in, k1 - c_in, kept_list);
-    else __syncthreads();
-    if (tid == 0) {          // (a zero made here: kept in registers for the whole kernel it ends up spilled)
-        const uint32_t zero = opaque_v(0u);
-        sh.nkept = zero; sh.below = zero;
-    }
-    if (!ok) return out;
-    out.q0 = rfl(sh.res[4]);
-    out.q1 = rfl(sh.res[5]);
     out.found = 2;
     return out;
 }
@@ -1002,11 +1036,17 @@ __device__ __forceinline__ void sample_hints(SH& sh, const float (&row)[4], uint
     __syncthreads();
 }
 
+// The top bytes of four words, in order.
+__device__ __forceinline__ uint32_t sign_bytes(uint32_t d0, uint32_t d1, uint32_t d2, uint32_t d3) {
+    const uint32_t lo2 = __builtin_amdgcn_perm(d1, d0, 0x0C0C0703u);         // bytes: d0.b3, d1.b3, 0, 0
+    const uint32_t hi2 = __builtin_amdgcn_perm(d3, d2, 0x07030C0Cu);         // bytes: 0, 0, d2.b3, d3.b3
+    return lo2 | hi2;
+}
+
 // Signed score and node score of one register row, dividing with the IEEE
-// operator.  AGG 0 = scaled pairwise sum, 1 = max.  This is the route of every
+// operator.  agg 0 = scaled pairwise sum, 1 = max (uniform).  This is the route of every
 // column that holds a missing sample.
-template <int AGG>
-__device__ __forceinline__ void score_row(const float (&x)[4], float med, float s, uint32_t absmask,
+__device__ __forceinline__ void score_row(uint32_t agg, const float (&x)[4], float med, float s, uint32_t absmask,
                                           uint32_t sgnmask, float thr, float node_scale,
                                           uint32_t* e, float* nz) {
     float zs[4];
@@ -1022,7 +1062,7 @@ __device__ __forceinline__ void score_row(const float (&x)[4], float med, float 
     }
     *e = bits;
     // lanes 2p and 2p+1 hold GPUs 0-3 and 4-7 of one node
-    if (AGG == 0) {
+    if (agg == 0) {
         const float half = (zs[0] + zs[1]) + (zs[2] + zs[3]);
         const float other = lane_xor1(half);
         *nz = node_scale * (half + other);
@@ -1055,10 +1095,9 @@ __device__ __forceinline__ void score_row_fast(const float (&x)[4], float med, f
         const float q2 = __builtin_fmaf(e1, rs, q1);
         zs[i] = TWO_SIDED ? fabsf(q2) : q2;
     }
-    uint32_t bits = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) bits |= (zs[i] > thr ? 1u : 0u) << (8 * i);
-    *e = bits;
+    // (finite numbers: a score exceeds iff thr less it is negative, denormals being kept)
+    *e = (sign_bytes(__float_as_uint(thr - zs[0]), __float_as_uint(thr - zs[1]), __float_as_uint(thr - zs[2]),
+                     __float_as_uint(thr - zs[3])) >> 7) & 0x01010101u;
     const float half = (zs[0] + zs[1]) + (zs[2] + zs[3]);
     const float other = lane_xor1(half);
     *nz = node_scale * (half + other);
@@ -1089,9 +1128,7 @@ __device__ __forceinline__ void score_row_decide(const float (&x)[4], uint32_t x
 #pragma unroll
     for (int i = 0; i < 4; ++i)
         d[i] = LOWER_IS_WORSE ? __float_as_uint(x[i]) - xcut : xcut - __float_as_uint(x[i]);
-    const uint32_t lo2 = __builtin_amdgcn_perm(d[1], d[0], 0x0C0C0703u);     // bytes: d0.b3, d1.b3, 0, 0
-    const uint32_t hi2 = __builtin_amdgcn_perm(d[3], d[2], 0x07030C0Cu);     // bytes: 0, 0, d2.b3, d3.b3
-    *e = ((lo2 | hi2) >> shift_m) & mask_m;                  // (already in place for metric m)
+    *e = (sign_bytes(d[0], d[1], d[2], d[3]) >> shift_m) & mask_m;      // (already in place for metric m)
     const float half = (x[0] + x[1]) + (x[2] + x[3]);
     const float sum = half + lane_xor1(half);
     *cand = LOWER_IS_WORSE ? sum <= sthr : sum >= sthr;
@@ -1109,6 +1146,15 @@ __device__ __forceinline__ void score_row_decide(const float (&x)[4], uint32_t x
 // per run of steps, so that the M columns of a step are scored side by side.  The
 // exceed bits of a column then go out as bit planes and combine_kernel makes the mask
 // bytes of them and applies the multi-signal rule.
+// The kernel's arguments, read from its argument segment where they are used: kept in scalar
+// registers across the column loop they are most of what the compiler has to spill there.
+typedef const __attribute__((address_space(4))) gd_score_args* gd_args_ptr;
+__device__ __forceinline__ gd_args_ptr args_here() {
+    gd_args_ptr p = (gd_args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 template <int NT, int ROWS, int LOG_NB, bool FULL, bool SPLIT, bool WANT_Z>
 __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     constexpr int TAIL = FULL ? ROWS : (ROWS > 2 ? ROWS - 2 : 0);     // first row that may hold padding
@@ -1124,9 +1170,9 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
 
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int w = rfl(tid >> 6);
-    const uint32_t R = a.R, N = a.N, M = a.M;
+    // (opaque: four words of a tuple otherwise, which is spilled as a whole)
+    const uint32_t R = opaque_s(a.R), N = opaque_s(a.N), M = opaque_s(a.M);
     const uint32_t RW = (R + 63) / 64, NWD = (N + 63) / 64;
-    const float thr = a.thr;
     // Each workgroup scores a contiguous run of steps, column after column, and
     // loads the next column while it scores the current one.
     const uint32_t spw = SPLIT ? 1u : (a.T + gridDim.x - 1) / gridDim.x;
@@ -1156,7 +1202,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     for (int i = tid; i < SH::NB + 128; i += NT) sh.dlo[i] = 0;      // dlo, hist, dhi
     for (int i = tid; i < (MAX_NODES / 8 > 0 ? MAX_NODES / 8 : 1); i += NT) sh.ranka[i] = 0;
     if (tid == 0) {
-        sh.umax[0] = 0; sh.umax[1] = 0; sh.ncand = 0; sh.below = 0; sh.nkept = 0; sh.mres[0][3] = 0; sh.mres[1][3] = 0;
+        sh.umax[0] = 0; sh.umax[1] = 0; sh.ncand = 0; sh.below = 0; sh.nkept = 0; sh.nnear = 0;
         sh.smin = 0xFFFFFFFFu; sh.smax = 0; sh.d1 = 0; sh.d2 = 0xFFFFFFFFu;
         for (int m = 0; m < 8; ++m) { sh.hok[m] = 0; sh.hfast[m] = 1; }
         // A one-step call may be told the medians and MADs of a recent step (usually the
@@ -1176,7 +1222,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     }
     __syncthreads();
     constexpr uint32_t nsample = NT;          // (row 0, the column's sample, holds ranks throughout)
-    const float inv_node_scale = 1.0f / a.node_scale;      // (only used where node_scale > 0)
+    const float inv_node_scale = uniform(1.0f / a.node_scale);      // (only used where node_scale > 0)
     uint32_t dir_codes = 0;          // direction + 1 of metric i in bits 2i, 2i + 1
 #pragma unroll
     for (int i = 0; i < 8; ++i) dir_codes |= (uint32_t)(a.dir[i] + 1) << (2 * i);
@@ -1224,7 +1270,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         // (after the very last column the current one is simply read again: a
         // branch-free refill keeps the register allocation of the score loops simple)
         const bool have_next = !SPLIT && (m + 1 < M || t + 1 < t_end);
-        const float* next_col = a.x + (t * M + m + (have_next ? 1 : 0)) * (size_t)R;
+        const float* next_col = args_here()->x + (t * M + m + (have_next ? 1 : 0)) * (size_t)R;
         const uint32_t tl = fresh_tid4();
         // A workgroup scores consecutive steps, and telemetry moves little from one
         // step to the next: the previous step's median of this metric, with the
@@ -1256,13 +1302,13 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         // MAD in three light passes.  Whatever it does not settle goes
         // through the general route below.
         int hsel = 0;
+        uint32_t listed = 0;                    // distances still to be sorted by the first wave
         bool tried_fast = false;
         if (hinted && rfl(sh.hfast[m]) != 0 && hint_hi < 0x7D000000u - 2u * (hint_hi - hint_lo) &&
             hint_hi - hint_lo < 0x20000000u) {
             tried_fast = true;
             const HintedResult hr = hinted_select<NT, ROWS, LOG_NB>(
-                sh, v, [&](int j) { set_padding(j, tl); }, hint_lo, hint_hi, sh.hmad[m], k0_all, k1_all, umax_slot,
-                colpar);
+                sh, v, [&](int j) { set_padding(j, tl); }, hint_lo, hint_hi, sh.hmad[m], k0_all, k1_all, umax_slot);
             hsel = hr.found;
             umax = hr.umax;
             if (hsel == 0) {
@@ -1273,6 +1319,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
                 med = 0.5f * (__uint_as_float(hr.m0) + __uint_as_float(hr.m1));
                 have_mad = hsel == 2;
                 s0 = hr.q0; s1 = hr.q1;
+                if (have_mad) listed = hr.listed;
                 missing = hr.present;
                 if (tid == 0) sh.hmed[m] = med;
             }
@@ -1333,7 +1380,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         }
         }
         // the other slot is free again: every thread read it a column ago
-        if (tid == 0) { sh.umax[colpar ^ 1u] = 0; sh.mres[colpar ^ 1u][3] = 0; }
+        if (tid == 0) sh.umax[colpar ^ 1u] = 0;
         colpar ^= 1u;
         uint32_t present = R;
         if (__builtin_expect(missing != 0, 0)) { present = missing; k0 = (present - 1) / 2; k1 = present / 2; }
@@ -1360,26 +1407,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
             block_select<NT, ROWS, LOG_NB, false>(sh, DKeys<ROWS>{v, med},
                                                   __float_as_uint(fabsf(v[0][0] - med)),
                                                   v[0][0] == v[0][0], nsample, k0, k1, &s0, &s1);
-        float mad = k0 == k1 ? __uint_as_float(s0) : 0.5f * (__uint_as_float(s0) + __uint_as_float(s1));
-        if (!present) med = mad = __uint_as_float(0x7FC00000u);      // nothing to take a median of
-        if (tid == 0) {
-            a.med[t * M + m] = med;
-            a.mad[t * M + m] = mad;
-            if (hsel) sh.hmad[m] = mad;         // the hinted selection follows median and MAD step by step
-            // a column with missing samples, but no signs, leads the next step's selection too
-            if (hsel == 0 && missing != 0 && med > 0.0f && mad > 0.0f && med < 3.0e38f && mad < 3.0e38f) {
-                sh.hmed[m] = med; sh.hmad[m] = mad;
-                sh.hwl[m] = 1.25f * mad; sh.hwh[m] = 1.25f * mad;
-                sh.hok[m] = 1;
-            }
-            // (from here on the reach is the exact MAD's, as after the general route)
-            if (boot && hsel == 2) { sh.hwl[m] = 1.25f * mad; sh.hwh[m] = 1.25f * mad; }
-        }
-        float s = 1.4826f * mad;
-        s = fmaxf(s, a.rel_floor * fabsf(med));
-        s = fmaxf(s, a.abs_floor);
-
-        // z, exceedance and node scores
+        if (!present) med = __uint_as_float(opaque_s(0x7FC00000u));  // nothing to take a median of
         // (all eight directions in one scalar word: indexing the argument array by m
         // would be a load from memory, and a wait for it, in every column)
         const int dir = (int)((dir_codes >> (2u * m)) & 3u) - 1;
@@ -1389,7 +1417,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         // exceeds, so that the column is scored like any other.  Of a primary metric that
         // falls the zero would be negative; signs leave the fast routes anyway.
         if (__builtin_expect(missing != 0, 0)) {
-          special = !(thr >= 0.0f && a.node_agg == 0 && (!prim || dir >= 0) && med < 3.0e38f);
+          special = !(a.thr >= 0.0f && a.node_agg == 0 && (!prim || dir >= 0) && med < 3.0e38f);
           if (!special) {
             const uint32_t absm = opaque_s(0x7FFFFFFFu);
 #pragma unroll
@@ -1400,28 +1428,127 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
             }
           }
         }
+        // The first wave alone sorts the last distances and works out the column's scoring
+        // parameters: done by every wave, the same hundred and thirty instructions kept all four
+        // waves of a SIMD busy one after another (2 100 of 41 000 cycles a column at 65 536 ranks),
+        // and the sort's result would cost one more barrier.
+        if (w == 0) {
+            const gd_args_ptr here = args_here();
+            const float thr = here->thr, node_scale = here->node_scale;
+            if (listed != 0) {
+                const uint32_t key = sh.cand[lane];
+                const uint32_t sorted = gd_sort64<true>((uint32_t)lane < listed ? key : 0xFFFFFFFFu);
+                s0 = (uint32_t)__builtin_amdgcn_readlane((int)sorted, (int)(s0 & (WAVE - 1)));
+                s1 = (uint32_t)__builtin_amdgcn_readlane((int)sorted, (int)(s1 & (WAVE - 1)));
+            }
+            float mad = k0 == k1 ? __uint_as_float(s0) : 0.5f * (__uint_as_float(s0) + __uint_as_float(s1));
+            if (!present) mad = __uint_as_float(opaque_s(0x7FC00000u));      // nothing to take a median of
+            if (tid == 0) {
+                here->med[t * M + m] = med;
+                here->mad[t * M + m] = mad;
+                if (hsel) sh.hmad[m] = mad;         // the hinted selection follows median and MAD step by step
+                // a column with missing samples, but no signs, leads the next step's selection too
+                if (hsel == 0 && missing != 0 && med > 0.0f && mad > 0.0f && med < 3.0e38f && mad < 3.0e38f) {
+                    sh.hmed[m] = med; sh.hmad[m] = mad;
+                    sh.hwl[m] = 1.25f * mad; sh.hwh[m] = 1.25f * mad;
+                    sh.hok[m] = 1;
+                }
+                // (from here on the reach is the exact MAD's, as after the general route)
+                if (boot && hsel == 2) { sh.hwl[m] = 1.25f * mad; sh.hwh[m] = 1.25f * mad; }
+            }
+            float s = 1.4826f * mad;
+            s = fmaxf(s, here->rel_floor * fabsf(med));
+            s = fmaxf(s, here->abs_floor);
+
+            // The reciprocal route is exact while no intermediate can leave the normal
+            // range: all x in [0, 2^59], 2^-34 <= med, 2^-60 <= s <= 2^60 (then every
+            // non-zero |x - med| lies in [2^-59, 2^59]).
+            const bool exact_recip = !special && umax <= 0x5D000000u && med >= 0x1p-34f && s >= 0x1p-60f &&
+                                     s <= 0x1p60f;
+            const bool fast = exact_recip && here->node_agg == 0;
+            // Decision-only route for supporting one-sided metrics: find the exact boundary
+            // xstar of "this rank exceeds" by probing 64 consecutive floats around
+            // med +- thr*s with the defining operations (IEEE subtract and divide).
+            bool decide = fast && !prim && dir != 0 && node_scale > 0.0f;
+            float xstar = 0.0f;
+            // One vector division serves both: lanes 0..62 probe 63 consecutive floats around
+            // med +- thr*s, lane 63 divides 1 by s (the reciprocal every exact route needs).
+            const float ss = dir < 0 ? -s : s;
+            float rs;
+            {
+                const float xc = dir > 0 ? med + thr * s : med - thr * s;
+                const uint32_t kc = key_of(xc);
+                decide = decide && kc >= 64u && kc <= 0xFF800000u - 64u;
+                const float xl = float_of_key(kc + (uint32_t)lane - 31u);
+                const float num = lane == WAVE - 1 ? 1.0f : (dir > 0 ? xl - med : med - xl);
+                const float q = num / s;
+                const float r1 = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(q), WAVE - 1));
+                rs = dir < 0 ? -r1 : r1;                         // 1/(-s) = -(1/s) exactly
+                if (decide) {
+                    const uint64_t probes = ~(1ull << (WAVE - 1));
+                    const uint64_t mk = __ballot(q > thr) & probes;
+                    // higher is worse: lanes f..62 true; lower is worse: lanes 0..f-1 true
+                    const uint64_t want = dir > 0 ? mk : ~mk & probes;
+                    const int f = want ? __builtin_ctzll(want) : 64;
+                    decide = f >= 1 && f <= 62 && want == ((~0ull << f) & probes);
+                    if (decide) xstar = __uint_as_float((uint32_t)__builtin_amdgcn_readlane(
+                                    (int)__float_as_uint(xl), dir > 0 ? f : f - 1));
+                    decide = decide && xstar > 0.0f;             // (the bit-pattern comparison needs a positive boundary)
+                }
+            }
+            // decision-only route:
+            // |estimate - exact node score| < |cc| * (sum(x) + 8*med) * 2^-20 + |thr| * 2^-23
+            // and sum(x) + 8*med <= 16 * max(x):
+            const float cc = node_scale * rs;
+            const float kk = (8.0f * med) * cc;
+            const float margin = __builtin_fmaf(fabsf(cc) * __uint_as_float(umax), 0x1.01p-16f,
+                                                fabsf(thr) * 0x1p-22f);
+            // The bound on sum(x) beyond which the estimate stays under thr - margin: solved
+            // from the estimate's formula (1/cc = ss / node_scale, closely enough) with a little
+            // slack and then checked with the formula itself (the estimate rises with the sum when
+            // higher is worse, cc > 0, and falls with it otherwise).  Without a bound that passes
+            // the check every row is a candidate.
+            float sthr = __uint_as_float(opaque_s(dir > 0 ? 0xFF800000u : 0x7F800000u));
+            if (decide) {
+                const float tl = (thr - margin) - fabsf(thr) * 0x1p-20f;
+                const float s0 = (tl + kk) * (ss * inv_node_scale);
+                const float slack = fabsf(s0) * 0x1p-18f + 0x1p-100f;
+                const float sb = dir > 0 ? s0 - slack : s0 + slack;
+                if (__builtin_fmaf(sb, cc, -kk) < tl) sthr = sb;
+            }
+            const uint32_t xcut = dir > 0 ? __float_as_uint(xstar) - 1u : __float_as_uint(xstar) + 1u;
+            // 0/1 decision-only (higher / lower is worse), 2/3 exact by reciprocal
+            // (one- / two-sided), 4/5 IEEE division (scaled sum / max)
+            const uint32_t route = fast ? (decide ? (dir > 0 ? 0u : 1u) : (dir != 0 ? 2u : 3u))
+                                        : (here->node_agg == 0 ? 4u : 5u);
+            if (lane == 0) {
+                ScoreParams& p = sh.par;
+                p.s = s; p.ss = ss; p.rs = rs; p.cc = cc;
+                p.kk = kk; p.margin = margin; p.sthr = sthr; p.xcut = xcut;
+                p.route = route; p.exact_recip = exact_recip ? 1u : 0u;
+            }
+        }
+        __syncthreads();
+        if (tid == 0) {          // (a zero made here: kept in registers for the whole kernel it ends up spilled)
+            const uint32_t zero = opaque_v(0u);
+            sh.nkept = zero; sh.nnear = zero;
+        }
+        // z, exceedance and node scores
         const uint32_t tz = fresh_tid4();
-        float* nzrow = a.node_z + t * N;
-        // The reciprocal route is exact while no intermediate can leave the normal
-        // range: all x in [0, 2^59], 2^-34 <= med, 2^-60 <= s <= 2^60 (then every
-        // non-zero |x - med| lies in [2^-59, 2^59]).
-        const bool exact_recip = !special && umax <= 0x5D000000u && med >= 0x1p-34f && s >= 0x1p-60f &&
-                                 s <= 0x1p60f;
-        const bool fast = exact_recip && a.node_agg == 0;
         // (the run-time test that is always true keeps the block a region of its own for the
         // register allocator, as it was when the output pointer decided: without it this
         // instantiation spills)
         if (WANT_Z && opaque_s(1u) != 0u) {   // optional full z output, recomputed so that the loops below stay lean
                      // (it must come first: they refill the registers with the next column)
-            float* zcol = a.z + (t * M + m) * (size_t)R;
+            float* zcol = args_here()->z + (t * M + m) * (size_t)R;
             // the quotient by the column's reciprocal and two residual corrections where that
             // is exact (see score_row_fast; no sign bits there, so no -0 to read as +0)
-            const bool by_recip = opaque_s(exact_recip ? 1u : 0u) != 0u;
+            const bool by_recip = opaque_s(sh.par.exact_recip) != 0u;
             // (optimiser-opaque copies of the median and the scale: the differences x - med of
             // this loop must not be kept for the score loop below, 64 registers' worth)
             const float medz = __uint_as_float(opaque_s(__float_as_uint(med)));
-            const float sz = __uint_as_float(opaque_s(__float_as_uint(s)));
-            const float rz = 1.0f / sz;
+            const float sz = __uint_as_float(opaque_s(__float_as_uint(sh.par.s)));
+            const float rz = __uint_as_float(opaque_s(__float_as_uint(dir < 0 ? -sh.par.rs : sh.par.rs)));      // 1 / s
             auto quotient = [&](float x) -> float {
                 const float d = x - medz;
                 const float q0 = d * rz;
@@ -1453,64 +1580,16 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
                 __builtin_amdgcn_sched_barrier(0);      // row by row: nothing of a later row starts early
             }
         }
-        // Decision-only route for supporting one-sided metrics: find the exact boundary
-        // xstar of "this rank exceeds" by probing 64 consecutive floats around
-        // med +- thr*s with the defining operations (IEEE subtract and divide).
-        bool decide = fast && !prim && dir != 0 && a.node_scale > 0.0f;
-        float xstar = 0.0f;
-        // One vector division serves both: lanes 0..62 probe 63 consecutive floats around
-        // med +- thr*s, lane 63 divides 1 by s (the reciprocal every exact route needs).
-        const float ss = dir < 0 ? -s : s;
-        float rs;
-        {
-            const float xc = dir > 0 ? med + thr * s : med - thr * s;
-            const uint32_t kc = key_of(xc);
-            decide = decide && kc >= 64u && kc <= 0xFF800000u - 64u;
-            const float xl = float_of_key(kc + (uint32_t)lane - 31u);
-            const float num = lane == WAVE - 1 ? 1.0f : (dir > 0 ? xl - med : med - xl);
-            const float q = num / s;
-            const float r1 = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(q), WAVE - 1));
-            rs = dir < 0 ? -r1 : r1;                         // 1/(-s) = -(1/s) exactly
-            if (decide) {
-                const uint64_t probes = ~(1ull << (WAVE - 1));
-                const uint64_t mk = __ballot(q > thr) & probes;
-                // higher is worse: lanes f..62 true; lower is worse: lanes 0..f-1 true
-                const uint64_t want = dir > 0 ? mk : ~mk & probes;
-                const int f = want ? __builtin_ctzll(want) : 64;
-                decide = f >= 1 && f <= 62 && want == ((~0ull << f) & probes);
-                if (decide) xstar = __uint_as_float((uint32_t)__builtin_amdgcn_readlane(
-                                (int)__float_as_uint(xl), dir > 0 ? f : f - 1));
-                decide = decide && xstar > 0.0f;             // (the bit-pattern comparison needs a positive boundary)
-            }
-        }
-        // decision-only route:
-        // |estimate - exact node score| < |cc| * (sum(x) + 8*med) * 2^-20 + |thr| * 2^-23
-        // and sum(x) + 8*med <= 16 * max(x):
-        const float cc = a.node_scale * rs;
-        const float kk = (8.0f * med) * cc;
-        const float margin = __builtin_fmaf(fabsf(cc) * __uint_as_float(umax), 0x1.01p-16f,
-                                            fabsf(thr) * 0x1p-22f);
-        // The bound on sum(x) beyond which the estimate stays under thr - margin: solved
-        // from the estimate's formula (1/cc = ss / node_scale, closely enough) with a little
-        // slack and then checked with the formula itself (the estimate rises with the sum when
-        // higher is worse, cc > 0, and falls with it otherwise).  Without a bound that passes
-        // the check every row is a candidate.
-        float sthr = dir > 0 ? -__builtin_inff() : __builtin_inff();
-        if (decide) {
-            const float tl = (thr - margin) - fabsf(thr) * 0x1p-20f;
-            const float s0 = (tl + kk) * (ss * inv_node_scale);
-            const float slack = fabsf(s0) * 0x1p-18f + 0x1p-100f;
-            const float sb = dir > 0 ? s0 - slack : s0 + slack;
-            if (__builtin_fmaf(sb, cc, -kk) < tl) sthr = sb;
-        }
-        const uint32_t xcut = dir > 0 ? __float_as_uint(xstar) - 1u : __float_as_uint(xstar) + 1u;
+        const gd_args_ptr here = args_here();
+        const float thr = here->thr, node_scale = here->node_scale;
+        float* nzrow = here->node_z + t * N;
+        const ScoreParams& par = sh.par;
+        const float s = uniform(par.s), ss = uniform(par.ss), rs = uniform(par.rs);
+        const float cc = uniform(par.cc), kk = uniform(par.kk), margin = uniform(par.margin), sthr = uniform(par.sthr);
+        const uint32_t xcut = rfl(par.xcut), route = rfl(par.route);
         const uint32_t shift_m = 7u - m, mask_m = 0x01010101u << m;
         const uint32_t absmask = dir == 0 ? 0x7FFFFFFFu : 0xFFFFFFFFu;
         const uint32_t sgnmask = dir < 0 ? 0x80000000u : 0u;
-        // 0/1 decision-only (higher / lower is worse), 2/3 exact by reciprocal
-        // (one- / two-sided), 4/5 IEEE division (scaled sum / max)
-        const uint32_t route = fast ? (decide ? (dir > 0 ? 0u : 1u) : (dir != 0 ? 2u : 3u))
-                                    : (a.node_agg == 0 ? 4u : 5u);
         uint32_t* const emask_lane = emask + opaque_v((uint32_t)tid);      // (row j: a constant offset from here)
 #pragma unroll
         for (int j = 0; j < ROWS; ++j) {
@@ -1528,19 +1607,17 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
                     nz = __builtin_fmaf(half + lane_xor1(half), cc, -kk);
                     if (__builtin_expect(__ballot(fabsf(nz - thr) <= margin) != 0, 0)) {
                         uint32_t e2;
-                        score_row_fast<false>(v[j], med, ss, rs, thr, a.node_scale, &e2, &nz);
+                        score_row_fast<false>(v[j], med, ss, rs, thr, node_scale, &e2, &nz);
                     }
                     NE[j / 4] |= (nz > thr ? 1u : 0u) << (8 * (j & 3) + m);
                 }
             } else {
                 if (rt == 2u) {
-                    score_row_fast<false>(v[j], med, ss, rs, thr, a.node_scale, &e, &nz);
+                    score_row_fast<false>(v[j], med, ss, rs, thr, node_scale, &e, &nz);
                 } else if (rt == 3u) {
-                    score_row_fast<true>(v[j], med, ss, rs, thr, a.node_scale, &e, &nz);
-                } else if (__builtin_expect(rt == 4u, 0)) {
-                    score_row<0>(v[j], med, s, absmask, sgnmask, thr, a.node_scale, &e, &nz);
+                    score_row_fast<true>(v[j], med, ss, rs, thr, node_scale, &e, &nz);
                 } else {
-                    score_row<1>(v[j], med, s, absmask, sgnmask, thr, a.node_scale, &e, &nz);
+                    score_row(rt - 4u, v[j], med, s, absmask, sgnmask, thr, node_scale, &e, &nz);
                 }
                 NE[j / 4] |= (nz > thr ? 1u : 0u) << (8 * (j & 3) + m);
                 eplaced = e << m;
@@ -1555,7 +1632,9 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     }
 
     const uint32_t to = fresh_tid4();
-    uint8_t* erow = a.exceed_mask + t * R;
+    const gd_args_ptr out = args_here();
+    const uint32_t primary = out->primary;
+    uint8_t* erow = out->exceed_mask + t * R;
     if (SPLIT) {
         // This column's exceed bits go out as bit planes, for combine_kernel to put together:
         // those of PLANE_RANKS ranks as M planes in the mask bytes of these ranks, those of
@@ -1564,7 +1643,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         // the lanes and by one in sixteen, one step of 65 536 ranks x 8 took 29.3 us (now 27.3; 26.1
         // with the atomics that needed the masks cleared first), of 16 384 x 8 16.1 (15.6).
         static_assert(!SPLIT || ROWS % 2 == 0, "rows in pairs");
-        uint8_t* const wrow8 = reinterpret_cast<uint8_t*>(a.rank_anom + t * RW);
+        uint8_t* const wrow8 = reinterpret_cast<uint8_t*>(out->rank_anom + t * RW);
         const bool odd = (to & 4u) != 0;                 // (lanes 2p and 2p + 1: one node's ranks)
         auto nibble_bits = [&](int j) {                  // bit 0 of each byte: the rank exceeds
             return holds(j, to) ? (emask[j * NT + to / 4] >> m_begin) & 0x01010101u : 0u;
@@ -1606,11 +1685,11 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     // per-rank mask bytes and anomaly bits.  Anomalous ranks are rare: their bits are OR-ed
     // into the step's bit words in LDS (all zero between steps) only by the waves that
     // hold one, and the finished words are copied out below.
-    const uint32_t min_signals = rfl(a.min_signals), others_mask = ~(0x01010101u << a.primary);
+    const uint32_t min_signals = rfl(out->min_signals), others_mask = ~(0x01010101u << primary);
     // multi-signal rule on four mask bytes at once: primary bit set and at least min_signals
     // bits in the byte; the answer is bit 0 of each byte
     auto rule4 = [&](uint32_t E) -> uint32_t {
-        const uint32_t prim_set = (E >> a.primary) & 0x01010101u;
+        const uint32_t prim_set = (E >> primary) & 0x01010101u;
         if (min_signals <= 2u) {
             // (two signals: the primary's and any other -- bit 7 of "low seven bits + 0x7F",
             // or bit 7 itself, says that a byte is not zero)
@@ -1641,7 +1720,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     }
     __syncthreads();
     for (uint32_t q = tid; q < RW; q += NT) {       // (one round at most in the exact-fit tilings)
-        a.rank_anom[t * RW + q] = sh.ranka[q];
+        out->rank_anom[t * RW + q] = sh.ranka[q];
         sh.ranka[q] = 0;
     }
     if (ROWS >= 10) {
@@ -1650,13 +1729,13 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         // byte-parallel as for the ranks; eight consecutive lanes make one 64-bit anomaly word
         const uint32_t tq = opaque_v((uint32_t)tid), sl = tq & 7u;
         uint2 nb = *reinterpret_cast<const uint2*>(&sh.nodeb[min(8 * tq, (uint32_t)MAX_NODES - 8)]);
-        uint8_t* nm = a.node_mask + t * N + 8 * tq;
+        uint8_t* nm = out->node_mask + t * N + 8 * tq;
         const uint32_t here = FULL ? 8u : (8 * tq < N ? min(N - 8 * tq, 8u) : 0u);      // (nodes of this thread)
         if (!FULL && here < 8) {                // (bytes beyond the last node were never written)
             nb.x &= here >= 4 ? 0xFFFFFFFFu : (1u << (8 * here)) - 1u;
             nb.y &= here <= 4 ? 0u : (1u << (8 * (here - 4))) - 1u;
         }
-        if (here == 8 && ((uintptr_t)(a.node_mask + t * N) & 7u) == 0) {
+        if (here == 8 && ((uintptr_t)(out->node_mask + t * N) & 7u) == 0) {
             *reinterpret_cast<uint2*>(nm) = nb;
         } else {
 #pragma unroll
@@ -1671,26 +1750,26 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         wlo |= lane_xor<1>(wlo); whi |= lane_xor<1>(whi);
         wlo |= lane_xor<2>(wlo); whi |= lane_xor<2>(whi);
         wlo |= lane_xor<4>(wlo); whi |= lane_xor<4>(whi);
-        if (sl == 0u && (FULL || 8 * tq < N)) a.node_anom[t * NWD + tq / 8u] = ((uint64_t)whi << 32) | wlo;
+        if (sl == 0u && (FULL || 8 * tq < N)) out->node_anom[t * NWD + tq / 8u] = ((uint64_t)whi << 32) | wlo;
     } else {
         if (FULL) {                             // N == NT * ROWS / 2: a fixed number of rounds
 #pragma unroll
             for (int q = 0; q < (ROWS + 1) / 2; ++q) {
                 const uint32_t n = opaque_v((uint32_t)tid) + (uint32_t)q * NT;
-                if (ROWS % 2 == 0 || n < N) a.node_mask[t * N + n] = sh.nodeb[n];
+                if (ROWS % 2 == 0 || n < N) out->node_mask[t * N + n] = sh.nodeb[n];
             }
         } else {
-            for (uint32_t n = tid; n < N; n += NT) a.node_mask[t * N + n] = sh.nodeb[n];
+            for (uint32_t n = tid; n < N; n += NT) out->node_mask[t * N + n] = sh.nodeb[n];
         }
         for (uint32_t wd = w; wd < NWD; wd += NWAVES) {
             const uint32_t n = wd * 64 + lane;
             bool an = false;
             if (n < N) {
                 const uint32_t b = sh.nodeb[n];
-                an = ((b >> a.primary) & 1u) && (uint32_t)__popc(b) >= a.min_signals;
+                an = ((b >> primary) & 1u) && (uint32_t)__popc(b) >= out->min_signals;
             }
             const uint64_t word = __ballot(an);
-            if (lane == 0) a.node_anom[t * NWD + wd] = word;
+            if (lane == 0) out->node_anom[t * NWD + wd] = word;
         }
     }
     }   // steps of this workgroup

@@ -302,8 +302,7 @@ __device__ __forceinline__ void score_small(const gd_score_args& a) {
         float nz;
         if (fast && dir != 0) score_row_fast<false>(v[j], med, ss, rs, thr, a.node_scale, &e, &nz);
         else if (fast) score_row_fast<true>(v[j], med, ss, rs, thr, a.node_scale, &e, &nz);
-        else if (a.node_agg == 0) score_row<0>(v[j], med, s, absmask, sgnmask, thr, a.node_scale, &e, &nz);
-        else score_row<1>(v[j], med, s, absmask, sgnmask, thr, a.node_scale, &e, &nz);
+        else score_row(a.node_agg, v[j], med, s, absmask, sgnmask, thr, a.node_scale, &e, &nz);
         lds.exceed[m * SmallLds<ROWS>::WORDS + j * WAVE + lane] = e;
         const uint64_t nb = __ballot(nz > thr);
         if (lane == 0) lds.node[m * ROWS + j] = nb;
