@@ -46,6 +46,8 @@ constexpr bool WANT_Z_HERE = GD_SCORE_WANT_Z != 0;
 constexpr int WAVE = 64;
 constexpr int CAND_CAP = 512;  // values ranked exactly in LDS per selection
 
+// (of a condition as it is: __ballot takes an integer, and makes one first)
+__device__ __forceinline__ uint64_t gd_ballot(bool c) { return __builtin_amdgcn_ballot_w64(c); }
 __device__ __forceinline__ uint32_t rfl(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ float uniform(float v) { return __uint_as_float(rfl(__float_as_uint(v))); }
 
@@ -277,16 +279,16 @@ struct RowList {
     __device__ __forceinline__ RowList(SH& sh, uint32_t w) : words(sh.hist + w * (MOST * 4u)) {}
     __device__ __forceinline__ bool overflow() const { return n > MOST; }
     __device__ __forceinline__ void add(bool hit, const float (&row)[4]) {
-        const uint64_t hm = __ballot(hit);
+        const uint64_t hm = gd_ballot(hit);
         if (__builtin_expect(hm != 0ull, 0)) {
-            const uint32_t pos = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(hm >> 32),
-                                                               __builtin_amdgcn_mbcnt_lo((uint32_t)hm, 0u));
-            if (hit && pos < MOST) {
-                // (word by word: a store of all four ties the row's registers together, and the
-                // column is then copied between passes)
+            const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(hm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hm, n));
+            if (hit) {
+                // (two words at a time: a store of all four ties the row's registers together, and the
+                // column is then copied between passes; a list that is full overwrites itself)
+                uint32_t* const to = words + 4 * (pos & (MOST - 1));
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    __hip_atomic_store(&words[4 * pos + i], __float_as_uint(row[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                for (int i = 0; i < 4; i += 2)
+                    __hip_atomic_store(reinterpret_cast<uint64_t*>(to + i), (uint64_t)__float_as_uint(row[i + 1]) << 32 | __float_as_uint(row[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
             }
             n += (uint32_t)__popcll(hm);
         }
@@ -307,14 +309,14 @@ struct RowList {
 };
 
 // The lanes with a hit append their value to a list shared by the workgroup (whole waves call).
-__device__ __forceinline__ void append(uint32_t* list, uint32_t* count, bool hit, uint32_t value) {
-    const uint64_t hm = __ballot(hit);
+__device__ __forceinline__ void append(uint32_t lane, uint32_t* list, uint32_t* count, bool hit, uint32_t value) {
+    const uint64_t hm = gd_ballot(hit);
     if (hm == 0ull) return;
     uint32_t base = 0;
-    const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(hm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hm, 0u));
-    if (hit && before == 0) base = atomicAdd(count, (uint32_t)__popcll(hm));
-    base = (uint32_t)__builtin_amdgcn_readlane((int)base, __builtin_ctzll(hm));
-    if (hit && base + before < (uint32_t)CAND_CAP) list[base + before] = value;
+    if (lane == 0) base = atomicAdd(count, (uint32_t)__popcll(hm));
+    base = rfl(base);
+    const uint32_t to = __builtin_amdgcn_mbcnt_hi((uint32_t)(hm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hm, base));
+    if (hit && to < (uint32_t)CAND_CAP) list[to] = value;
 }
 
 // Exact ranking of the cnt gathered candidates in sh.cand (ties broken by
@@ -332,7 +334,7 @@ __device__ __forceinline__ void rank_candidates(SH& sh, uint32_t tid, uint32_t c
         const uint32_t cj = list[lane];
         for (uint32_t i = w; i < cnt; i += NT / WAVE) {
             const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)cj, (int)i);
-            const uint32_t r = (uint32_t)__popcll(__ballot(lane < cnt && (cj < c || (cj == c && lane < i))));
+            const uint32_t r = (uint32_t)__popcll(gd_ballot(lane < cnt && (cj < c || (cj == c && lane < i))));
             if (lane == 0) {
                 if (r == wa) sh.res[4] = c;
                 if (r == wb) sh.res[5] = c;
@@ -345,7 +347,7 @@ __device__ __forceinline__ void rank_candidates(SH& sh, uint32_t tid, uint32_t c
             for (uint32_t j0 = 0; j0 < cnt; j0 += WAVE) {
                 const uint32_t j = j0 + lane;
                 const uint32_t cj = j < cnt ? list[j] : 0xFFFFFFFFu;
-                r += (uint32_t)__popcll(__ballot(j < cnt && (cj < c || (cj == c && j < i))));
+                r += (uint32_t)__popcll(gd_ballot(j < cnt && (cj < c || (cj == c && j < i))));
             }
             if (lane == 0) {
                 if (r == wa) sh.res[4] = c;
@@ -516,7 +518,7 @@ __device__ __forceinline__ bool block_select(SH& sh, const Keys& keys, uint32_t 
             }
             rows.drain(lane, [&](uint32_t x, bool valid) {
                 const uint32_t kk = keys.key(__uint_as_float(x), tok);
-                append(sh.cand, &sh.ncand, valid && kk - clo <= cspan, kk);
+                append(lane, sh.cand, &sh.ncand, valid && kk - clo <= cspan, kk);
             });
             __syncthreads();
             const uint32_t cnt = rfl(sh.ncand);
@@ -677,7 +679,7 @@ __device__ __forceinline__ bool mad_from_histogram(SH& sh, const float (&v)[ROWS
         if (rows.overflow() && lane == 0) atomicAdd(&sh.ncand, (uint32_t)CAND_CAP + 1u);
         rows.drain(lane, [&](uint32_t x, bool valid) {
             const uint32_t kk = __float_as_uint(fabsf(__uint_as_float(x) - __uint_as_float(tok)));
-            append(sh.cand, &sh.ncand, valid && kk - d1 <= span, kk);
+            append(lane, sh.cand, &sh.ncand, valid && kk - d1 <= span, kk);
         });
     }
     nbelow = wave_incl_scan(nbelow);
@@ -788,6 +790,7 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
         const uint32_t kb = opaque_s((uint32_t)(64 - ql) * 4u);  // counter 64 is bucket 0 (bytes, mod 2^32)
         const uint32_t sh_s = opaque_s((uint32_t)shift);
         uint32_t um = 0;
+        __builtin_amdgcn_s_setprio(2);
 #pragma unroll
         for (int j = 0; j < ROWS; ++j) {
             float(&row)[4] = const_cast<float(&)[4]>(v[j]);
@@ -809,6 +812,11 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
         um = wave_max_to_last(um);
         if (lane == WAVE - 1) atomicMax(umax_slot, um);
     }
+    // Waves of other workgroups of the CU may be anywhere in their columns: the short phases, whose
+    // length is a chain of latencies, go before the counting pass (bound by LDS), that before the
+    // gathers and these before the scores, which are bound by issue (launch: 32 768 ranks x 4 096 x 8
+    // 1 027 us with no priorities, 990 with the short phases' alone, 976 so; 16 384 x 10 000 x 4 741, 724, 721).
+    __builtin_amdgcn_s_setprio(3);
     __syncthreads();
     const uint32_t tid = opaque_v(threadIdx.x), lane = tid & (WAVE - 1), w = rfl(tid >> 6);
     const uint32_t umax = rfl(*umax_slot);
@@ -841,6 +849,7 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
         const uint32_t clo = lo + (ba << shift);
         const uint32_t cspan = ((bb - ba + 1u) << shift) - 1u;
         const uint32_t tok = opaque_s(clo);
+        __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int j = 0; j < ROWS; ++j) {
             uint32_t off[4];
@@ -849,9 +858,10 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
             rows.add(min(min(off[0], off[1]), min(off[2], off[3])) <= cspan, v[j]);
             __builtin_amdgcn_sched_barrier(0);
         }
+        __builtin_amdgcn_s_setprio(3);
         rows.drain(lane, [&](uint32_t x, bool valid) {
             const bool hit = valid && x - tok <= cspan;
-            append(sh.cand, &sh.ncand, hit, x);
+            append(lane, sh.cand, &sh.ncand, hit, x);
         });
     }
     __syncthreads();
@@ -886,14 +896,14 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
             valid = d > 0.0f && kl >= lo && kl <= hi && f <= e;
             if (valid) F = sh.pref[e] - sh.pref[f];
         }
-        const uint64_t under = __ballot(valid && F <= k0), over = __ballot(valid && F > k1);
+        const uint64_t under = gd_ballot(valid && F <= k0), over = gd_ballot(valid && F > k1);
         if (over == 0ull && under == 0ull) break;                  // no edge here has a mirror image
         if (over == 0ull) { e0 += 32u; continue; }
         // the last edge with at most k0 values inside, and the last one before it whose mirror
         // image is a bucket further in: at most k0 values are closer than that one
         const uint32_t c = under ? 63u - (uint32_t)__builtin_clzll(under) : 0u;
         const uint32_t fc = (uint32_t)__builtin_amdgcn_readlane((int)f, (int)c);
-        const uint64_t inner = __ballot(valid && f > fc);
+        const uint64_t inner = gd_ballot(valid && f > fc);
         if (under == 0ull || inner == 0ull) { e0 -= 32u; continue; }
         const uint32_t la = 63u - (uint32_t)__builtin_clzll(inner), lb = (uint32_t)__builtin_ctzll(over);
         Rb0 = rfl(e0 + la);
@@ -911,12 +921,12 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
     const float Da = fminf(dLi, dRi), Db = fmaxf(dLo, dRo);
     const uint32_t n_in = rfl(sh.pref[Rb0] - sh.pref[Lb1 + 1u]);
     if (!(Da > 0.0f) || !(DO >= DI)) return out;
-    // ---- pass 3: gather the rows that hold a value whose distance from the median lies in
-    // [Da, Db], and classify their values exactly
+    // ---- pass 3: gather the rows that hold a value of these buckets, and classify their values exactly
     {
         const float tokm = __uint_as_float(opaque_s(__float_as_uint(med)));
         const float toka = __uint_as_float(opaque_s(__float_as_uint(Da)));
         const uint32_t wspan = __float_as_uint(Db - Da);
+        __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int j = 0; j < ROWS; ++j) {
             uint32_t off[4];
@@ -925,14 +935,16 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
             rows.add(min(min(off[0], off[1]), min(off[2], off[3])) <= wspan, v[j]);
             __builtin_amdgcn_sched_barrier(0);
         }
+        __builtin_amdgcn_s_setprio(3);
         if (rows.overflow() && lane == 0) atomicAdd(&sh.nkept, (uint32_t)CAND_CAP + 1u);
         rows.drain(lane, [&](uint32_t x, bool valid) {
-            const uint32_t b = (x - lo) >> shift;              // (values outside the bracket: b is huge)
-            const bool in = valid && x >= lo && ((b >= Lb0 && b <= Lb1) || (b >= Rb0 && b <= Rb1));
+            // (values under the bracket wrap round: (x - lo) >> shift is beyond every bucket)
+            const uint32_t b = (x - lo) >> shift;
+            const bool in = valid && (b - Lb0 <= Lb1 - Lb0 || b - Rb0 <= Rb1 - Rb0);
             const float d = fabsf(__uint_as_float(x) - med);
-            const uint32_t nlt = (uint32_t)__popcll(__ballot(in && d < DI));
+            const uint32_t nlt = (uint32_t)__popcll(gd_ballot(in && d < DI));
             if (nlt != 0 && lane == 0) atomicAdd(&sh.nnear, nlt);
-            append(sh.cand, &sh.nkept, in && d >= DI && d <= DO, __float_as_uint(d));
+            append(lane, sh.cand, &sh.nkept, in && d >= DI && d <= DO, __float_as_uint(d));
         });
     }
     __syncthreads();
@@ -1230,6 +1242,13 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     const uint32_t k0_all = R / 2 - 1, k1_all = R / 2;   // the middle ranks when nothing is missing (R is even)
     uint32_t colpar = 0;                          // parity of the column count: which umax slot is in use
 
+    // Rows of the next column that the score loop asks for as it is done with each; the others
+    // follow behind the loop.  Asked for row by row to the end, the loads fill the memory
+    // pipeline and the loop's last rows wait for room in it (launch, 65 536 ranks x 4 096 x 8:
+    // 2 115 us all in the loop, 2 081 with a quarter behind it, 2 045 half, 2 085 three quarters;
+    // asked for by the next column's count, which is bound by LDS, 2 033, but then a column that
+    // takes the general way waits for half of its values).
+    constexpr int EARLY = SPLIT ? ROWS : (ROWS + 1) / 2;
     float v[ROWS][4];
     // Issue the loads of one register row of a column.  Padding lanes read the column's last
     // ranks once more (a load under a condition would be waited for on the spot) and become
@@ -1238,8 +1257,9 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         // (a uniform row pointer plus the lane's 32-bit offset: one address mode, no vector
         // arithmetic per row)
         float4 q;
-        if (j < TAIL) q = *reinterpret_cast<const float4*>(col + block_of(j) * BLK + tid4);
-        else q = *reinterpret_cast<const float4*>(col + min((uint32_t)j * BLK + tid4, R - 4));
+        // (offsets in bytes, 32 bits wide: widened before the shift they are 64-bit sums)
+        if (j < TAIL) q = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(col + block_of(j) * BLK) + tid4 * 4u);
+        else q = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(col) + min((uint32_t)j * BLK + tid4, R - 4) * 4u);
         v[j][0] = q.x; v[j][1] = q.y; v[j][2] = q.z; v[j][3] = q.w;
     };
     auto set_padding = [&](int j, uint32_t tid4) {
@@ -1270,7 +1290,8 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         // (after the very last column the current one is simply read again: a
         // branch-free refill keeps the register allocation of the score loops simple)
         const bool have_next = !SPLIT && (m + 1 < M || t + 1 < t_end);
-        const float* next_col = args_here()->x + (t * M + m + (have_next ? 1 : 0)) * (size_t)R;
+        const float* this_col = args_here()->x + (t * M + m) * (size_t)R;
+        const float* next_col = this_col + (have_next ? (size_t)R : 0);
         const uint32_t tl = fresh_tid4();
         // A workgroup scores consecutive steps, and telemetry moves little from one
         // step to the next: the previous step's median of this metric, with the
@@ -1486,7 +1507,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
                 rs = dir < 0 ? -r1 : r1;                         // 1/(-s) = -(1/s) exactly
                 if (decide) {
                     const uint64_t probes = ~(1ull << (WAVE - 1));
-                    const uint64_t mk = __ballot(q > thr) & probes;
+                    const uint64_t mk = gd_ballot(q > thr) & probes;
                     // higher is worse: lanes f..62 true; lower is worse: lanes 0..f-1 true
                     const uint64_t want = dir > 0 ? mk : ~mk & probes;
                     const int f = want ? __builtin_ctzll(want) : 64;
@@ -1590,6 +1611,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         const uint32_t shift_m = 7u - m, mask_m = 0x01010101u << m;
         const uint32_t absmask = dir == 0 ? 0x7FFFFFFFu : 0xFFFFFFFFu;
         const uint32_t sgnmask = dir < 0 ? 0x80000000u : 0u;
+        __builtin_amdgcn_s_setprio(0);
         uint32_t* const emask_lane = emask + opaque_v((uint32_t)tid);      // (row j: a constant offset from here)
 #pragma unroll
         for (int j = 0; j < ROWS; ++j) {
@@ -1602,10 +1624,10 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
                 else score_row_decide<true>(v[j], xcut, shift_m, mask_m, sthr, &e, &cand);
                 eplaced = e;                                // (its bits are on metric m already)
                 nz = thr;                                   // (not above the threshold: no node bit)
-                if (__builtin_expect(__ballot(cand) != 0, 0)) {       // some node may exceed: the estimate decides,
+                if (__builtin_expect(gd_ballot(cand) != 0, 0)) {       // some node may exceed: the estimate decides,
                     const float half = (v[j][0] + v[j][1]) + (v[j][2] + v[j][3]);     // or, too close, the exact chain
                     nz = __builtin_fmaf(half + lane_xor1(half), cc, -kk);
-                    if (__builtin_expect(__ballot(fabsf(nz - thr) <= margin) != 0, 0)) {
+                    if (__builtin_expect(gd_ballot(fabsf(nz - thr) <= margin) != 0, 0)) {
                         uint32_t e2;
                         score_row_fast<false>(v[j], med, ss, rs, thr, node_scale, &e2, &nz);
                     }
@@ -1624,11 +1646,13 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
             }
             __hip_atomic_fetch_or(&emask_lane[j * NT], eplaced, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             if (prim && holds(j, tz) && !(tz & 4)) nzrow[rbase(j, tz) / 8] = nz;
-            if (!SPLIT) load_row(j, next_col, tz);   // the row is done: refill it with the next column
+            if (!SPLIT && j < EARLY) load_row(j, next_col, tz);   // the row is done: refill it with the next column
             // pin the row's results here, or its scores stay live until the loop ends
             asm volatile("" : "+v"(NE[j / 4]));
             __builtin_amdgcn_sched_barrier(0);
         }
+#pragma unroll
+        for (int j = EARLY; j < ROWS; ++j) load_row(j, next_col, tz);
     }
 
     const uint32_t to = fresh_tid4();
@@ -1710,7 +1734,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         if (valid) *reinterpret_cast<uint32_t*>(erow + rbase(j, to)) = Ej;
         uint32_t an = rule4(Ej);
         if (!valid) an = 0u;
-        if (__builtin_expect(__ballot(an != 0u) != 0ull, 0)) {
+        if (__builtin_expect(gd_ballot(an != 0u) != 0ull, 0)) {
             // the lane's four ranks are bits rbase % 32 .. + 3 of 32-bit word rbase / 32
             const uint32_t nib = (an | (an >> 7) | (an >> 14) | (an >> 21)) & 0xFu;
             const uint32_t r0 = rbase(j, to);
@@ -1768,7 +1792,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
                 const uint32_t b = sh.nodeb[n];
                 an = ((b >> primary) & 1u) && (uint32_t)__popc(b) >= out->min_signals;
             }
-            const uint64_t word = __ballot(an);
+            const uint64_t word = gd_ballot(an);
             if (lane == 0) out->node_anom[t * NWD + wd] = word;
         }
     }

@@ -102,8 +102,8 @@ __device__ __forceinline__ void wave_select(const Keys& keys, uint32_t n, uint32
 #pragma unroll
         for (int i = 0; i < V; ++i) {
             const uint32_t k = keys.at(i / 4, i % 4, tok);
-            cp += (uint32_t)__popcll(__ballot(k < p));
-            cq += (uint32_t)__popcll(__ballot(k < q));
+            cp += (uint32_t)__popcll(gd_ballot(k < p));
+            cq += (uint32_t)__popcll(gd_ballot(k < q));
         }
         uint32_t part = 0;
         bool parted = false;
@@ -135,7 +135,7 @@ __device__ __forceinline__ void wave_select(const Keys& keys, uint32_t n, uint32
         // ones -- whole degrees -- it is mostly the one wanted)
         uint32_t mid = 0xFFFFFFFFu;
         const uint32_t sample = small_sample<ROWS>(keys);
-        const uint32_t ns = (uint32_t)__popcll(__ballot(sample < Keys::END));
+        const uint32_t ns = (uint32_t)__popcll(gd_ballot(sample < Keys::END));
         if (ns >= 16) {
             const uint32_t sorted = gd_sort64(sample);
             const uint32_t reach = 4u + ns / 16u;
@@ -175,7 +175,7 @@ __device__ __forceinline__ void wave_select(const Keys& keys, uint32_t n, uint32
     for (int i = 0; i < V; ++i) {
         const uint32_t k = keys.at(i / 4, i % 4, tok);
         const bool hit = k - lo < width;
-        const uint64_t mask = __ballot(hit);
+        const uint64_t mask = gd_ballot(hit);
         if (mask != 0ull) {
             const uint32_t to = pos + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
@@ -236,12 +236,12 @@ __device__ __forceinline__ void score_small(const gd_score_args& a) {
                                 max(__float_as_uint(v[j][2]), __float_as_uint(v[j][3])));
         um = max(um, holds(j) ? rm : 0u);
     }
-    const bool special = __ballot(um > 0x7F800000u) != 0ull, signs = __ballot(um >= 0x80000000u) != 0ull;
+    const bool special = gd_ballot(um > 0x7F800000u) != 0ull, signs = gd_ballot(um >= 0x80000000u) != 0ull;
     uint32_t present = R;
     if (special) {
         present = 0;
 #pragma unroll
-        for (int i = 0; i < V; ++i) present += (uint32_t)__popcll(__ballot(v[i / 4][i % 4] == v[i / 4][i % 4]));
+        for (int i = 0; i < V; ++i) present += (uint32_t)__popcll(gd_ballot(v[i / 4][i % 4] == v[i / 4][i % 4]));
     }
     float med = __uint_as_float(0x7FC00000u), mad = med;             // nothing to take a median of
     if (present) {
@@ -267,7 +267,7 @@ __device__ __forceinline__ void score_small(const gd_score_args& a) {
     s = fmaxf(s, a.rel_floor * fabsf(med));
     s = fmaxf(s, a.abs_floor);
     // (as in score_columns: the quotient by the reciprocal is exact in this range)
-    const bool exact_recip = !special && __ballot(um > 0x5D000000u) == 0ull && med >= 0x1p-34f &&
+    const bool exact_recip = !special && gd_ballot(um > 0x5D000000u) == 0ull && med >= 0x1p-34f &&
                              s >= 0x1p-60f && s <= 0x1p60f;
     const float r1 = 1.0f / s;
     if (WANT_Z) {
@@ -304,7 +304,7 @@ __device__ __forceinline__ void score_small(const gd_score_args& a) {
         else if (fast) score_row_fast<true>(v[j], med, ss, rs, thr, a.node_scale, &e, &nz);
         else score_row(a.node_agg, v[j], med, s, absmask, sgnmask, thr, a.node_scale, &e, &nz);
         lds.exceed[m * SmallLds<ROWS>::WORDS + j * WAVE + lane] = e;
-        const uint64_t nb = __ballot(nz > thr);
+        const uint64_t nb = gd_ballot(nz > thr);
         if (lane == 0) lds.node[m * ROWS + j] = nb;
         if (m == a.primary && holds(j) && !(lane & 1)) nzrow[(j * 256 + lane * 4) / 8] = nz;
     }
@@ -333,7 +333,7 @@ __device__ __forceinline__ void score_small(const gd_score_args& a) {
             for (uint32_t i = 0; i < M; ++i)
                 b |= (uint32_t)(lds.node[i * ROWS + n / 32] >> (2 * (n % 32)) & 1ull) << i;
         if (n < N) a.node_mask[t * N + n] = (uint8_t)b;
-        const uint64_t word = __ballot(((b >> a.primary) & 1u) && (uint32_t)__popc(b) >= a.min_signals);
+        const uint64_t word = gd_ballot(((b >> a.primary) & 1u) && (uint32_t)__popc(b) >= a.min_signals);
         if (lane == 0) a.node_anom[t * NWD + c] = word;
     }
 }
