@@ -782,8 +782,9 @@ __device__ __forceinline__ void count_present(SH& sh, const float (&v)[ROWS][4],
 // Padding lanes (of the last rows of a ragged rank count) hold another lane's value until
 // `set_padding(j)` makes them NaN patterns: over the bracket in the count, never within a
 // distance in the gather.
-template <int NT, int ROWS, int LOG_NB, typename SH, typename Pad>
-__device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[ROWS][4], Pad set_padding,
+// `counted` is called by every wave as it is done with the counting pass.
+template <int NT, int ROWS, int LOG_NB, typename SH, typename Pad, typename Counted>
+__device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[ROWS][4], Pad set_padding, Counted counted,
                                                       uint32_t hint_lo, uint32_t hint_hi, float mad_hint,
                                                       uint32_t k0, uint32_t k1, uint32_t* umax_slot) {
     HintedResult out = {0, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
@@ -834,6 +835,7 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
     // gathers and these before the scores, which are bound by issue (launch: 32 768 ranks x 4 096 x 8
     // 1 027 us with no priorities, 990 with the short phases' alone, 976 so; 16 384 x 10 000 x 4 741, 724, 721).
     __builtin_amdgcn_s_setprio(3);
+    counted();
     __syncthreads();
     const uint32_t tid = opaque_v(threadIdx.x), lane = tid & (WAVE - 1), w = rfl(tid >> 6);
     const uint32_t umax = rfl(*umax_slot);
@@ -1184,6 +1186,17 @@ __device__ __forceinline__ gd_args_ptr args_here() {
     return p;
 }
 
+// Rows of the next column that the 1 024-thread tilings have registers to spare for (128 a lane).
+// They are asked for as soon as the current column is counted: a workgroup has its CU to itself
+// there, and from the count to the scores the memory has nothing to do.  Measured: ten rows, 40 000
+// ranks x 1 024 steps x 8: none 399 us, three 391, five 383, six 382, seven 390; twelve, 48 000 x
+// 2 048 x 4: none 471, two 471, three 465, four 460, five 456; fourteen, 56 000 x 2 048 x 4: none
+// 532, two 538, three 532.  With fewer threads other workgroups of the CU fill the gap (up to eight
+// rows kept this way: 5 000 to 24 000 ranks within 1 %).
+constexpr int rows_ahead(int nt, int rows) {
+    return nt < 1024 ? 0 : rows == 10 ? 6 : rows == 12 ? 5 : 0;
+}
+
 template <int NT, int ROWS, int LOG_NB, bool FULL, bool SPLIT, bool WANT_Z>
 __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     constexpr int TAIL = FULL ? ROWS : (ROWS > 2 ? ROWS - 2 : 0);     // first row that may hold padding
@@ -1265,23 +1278,32 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     // 2 115 us all in the loop, 2 081 with a quarter behind it, 2 045 half, 2 085 three quarters;
     // asked for by the next column's count, which is bound by LDS, 2 033, but then a column that
     // takes the general way waits for half of its values).
-    constexpr int EARLY = SPLIT ? ROWS : (ROWS + 1) / 2;
-    float v[ROWS][4];
+    constexpr int EARLY = SPLIT || rows_ahead(NT, ROWS) > 0 ? ROWS : (ROWS + 1) / 2;
+    constexpr int AHEAD = SPLIT ? 0 : rows_ahead(NT, ROWS);
+    float v[ROWS][4], ahead[AHEAD > 0 ? AHEAD : 1][4];
     // Issue the loads of one register row of a column.  Padding lanes read the column's last
     // ranks once more (a load under a condition would be waited for on the spot) and become
     // NaNs, whose key lies above every real key, when the column is first looked at.
-    auto load_row = [&](int j, const float* col, uint32_t tid4) {
+    auto load_row_to = [&](float (&row)[4], int j, const float* col, uint32_t tid4) {
         // (a uniform row pointer plus the lane's 32-bit offset: one address mode, no vector
         // arithmetic per row)
         // (offsets in bytes, 32 bits wide: widened before the shift they are 64-bit sums)
         const char* p = j < TAIL ? reinterpret_cast<const char*>(col + block_of(j) * BLK) + tid4 * 4u
                                  : reinterpret_cast<const char*>(col) + min((uint32_t)j * BLK + tid4, R - 4) * 4u;
         // (a single step, just arrived, may still lie in the caches)
-        if (!SPLIT) load_once(reinterpret_cast<const float*>(p), v[j]);
+        if (!SPLIT) load_once(reinterpret_cast<const float*>(p), row);
         else {
             const float4 q = *reinterpret_cast<const float4*>(p);
-            v[j][0] = q.x; v[j][1] = q.y; v[j][2] = q.z; v[j][3] = q.w;
+            row[0] = q.x; row[1] = q.y; row[2] = q.z; row[3] = q.w;
         }
+    };
+    auto load_row = [&](int j, const float* col, uint32_t tid4) { load_row_to(v[j], j, col, tid4); };
+    auto load_ahead = [&](const float* col) {
+        if (AHEAD == 0) return;
+        const uint32_t ta = fresh_tid4();
+#pragma unroll
+        for (int j = 0; j < AHEAD; ++j) load_row_to(ahead[j], j, col, ta);
+        __builtin_amdgcn_sched_barrier(0);
     };
     auto set_padding = [&](int j, uint32_t tid4) {
         if (j < TAIL) return;
@@ -1350,7 +1372,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
             hint_hi - hint_lo < 0x20000000u) {
             tried_fast = true;
             const HintedResult hr = hinted_select<NT, ROWS, LOG_NB>(
-                sh, v, [&](int j) { set_padding(j, tl); }, hint_lo, hint_hi, sh.hmad[m], k0_all, k1_all, umax_slot);
+                sh, v, [&](int j) { set_padding(j, tl); }, [&]() { load_ahead(next_col); }, hint_lo, hint_hi, sh.hmad[m], k0_all, k1_all, umax_slot);
             hsel = hr.found;
             umax = hr.umax;
             if (hsel == 0) {
@@ -1385,6 +1407,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
             __syncthreads();
             umax = rfl(*umax_slot);
         }
+        if (!tried_fast) load_ahead(next_col);
         // special: some value carries a sign bit or is a NaN.  The raw bits are then no
         // keys to select by, and a NaN is a missing sample that the ranks must not count.
         bool special = umax > 0x7F800000u;
@@ -1667,7 +1690,11 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
             }
             __hip_atomic_fetch_or(&emask_lane[j * NT], eplaced, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             if (prim && holds(j, tz) && !(tz & 4)) nzrow[rbase(j, tz) / 8] = nz;
-            if (!SPLIT && j < EARLY) load_row(j, next_col, tz);   // the row is done: refill it with the next column
+            // the row is done: refill it with the next column
+            if (j < AHEAD) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[j][i] = ahead[j < AHEAD ? j : 0][i];
+            } else if (!SPLIT && j < EARLY) load_row(j, next_col, tz);
             // pin the row's results here, or its scores stay live until the loop ends
             asm volatile("" : "+v"(NE[j / 4]));
             __builtin_amdgcn_sched_barrier(0);
