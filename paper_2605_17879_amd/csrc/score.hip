@@ -1852,13 +1852,18 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
 // NT threads per column (64: one wave per column, M of them per workgroup; LOG_NB has no
 // meaning there).  <= 128 VGPRs: 16 waves per CU.
 constexpr int block_threads(int NT) { return NT == WAVE ? 8 * WAVE : NT; }
+// Waves per SIMD.  Up to eight rows of 256 threads fit 96 VGPRs, and five such workgroups a CU's
+// LDS: their time is mostly that of the short phases, which overlap (10 000
+// steps, four / five: 4 096 ranks x 1 141 / 127 us, 5 000 x 8 784 / 677, 6 000 x 4 456 / 399, 8 000 x 4
+// 491 / 440; up to 1 024 steps there is no fifth to run).
+constexpr int waves_of(int nt, int rows, bool want_z) { return nt == 256 && rows <= 8 && !want_z ? 5 : 4; }
 template <int NT, int ROWS, int LOG_NB, bool FULL, bool SPLIT, bool WANT_Z>
-__global__ __launch_bounds__(block_threads(NT), 4) void score_kernel(const gd_score_args a) {
+__global__ __launch_bounds__(block_threads(NT), waves_of(NT, ROWS, WANT_Z)) void score_kernel(const gd_score_args a) {
     if constexpr (NT == WAVE) score_small<ROWS, FULL, WANT_Z>(a);
     else score_columns<NT, ROWS, LOG_NB, FULL, SPLIT, WANT_Z>(a);
 }
 template <int NT, int ROWS, int LOG_NB, bool SPLIT, bool WANT_Z>
-__global__ __launch_bounds__(block_threads(NT), 4) void score_ragged_kernel(const gd_score_args a) {
+__global__ __launch_bounds__(block_threads(NT), waves_of(NT, ROWS, WANT_Z)) void score_ragged_kernel(const gd_score_args a) {
     if constexpr (NT == WAVE) score_small<ROWS, false, WANT_Z>(a);
     else score_columns<NT, ROWS, LOG_NB, false, SPLIT, WANT_Z>(a);
 }
@@ -2039,7 +2044,7 @@ hipError_t launch_runs(const gd_score_args& a, int n_cu, hipStream_t s) {
     static std::atomic<uint64_t> granted{0};
     const hipError_t e = gd_grant_lds(granted, reinterpret_cast<const void*>(kern), lds);
     if (e != hipSuccess) return e;
-    const size_t by_lds = (size_t)160 * 1024 / lds, by_waves = (size_t)16 / (NT / WAVE);
+    const size_t by_lds = (size_t)160 * 1024 / lds, by_waves = (size_t)(4 * waves_of(NT, ROWS, WANT_Z_HERE)) / (NT / WAVE);
     const size_t per_cu = by_lds < by_waves ? (by_lds ? by_lds : 1) : by_waves;
     const size_t cap = (size_t)n_cu * per_cu;
     const uint32_t grid = (uint32_t)(a.T < cap ? a.T : cap);
