@@ -354,9 +354,9 @@ __device__ __forceinline__ void walk_all(const gd_ledger_args& a, const uint8_t*
     }
 }
 
-// blockIdx.x: a stretch of `stretch` blocks of 64 steps; w0: the tile's first word.
+// run: which stretch of `stretch` blocks of 64 steps; w0: the tile's first word.
 template <Tiles KIND>
-__device__ __forceinline__ void count_blocks(const gd_ledger_args& a, uint32_t w0, uint32_t stretch, uint32_t* lds,
+__device__ __forceinline__ void count_blocks(const gd_ledger_args& a, uint32_t w0, uint32_t run, uint32_t stretch, uint32_t* lds,
                                              uint32_t (&final_planes)[GD_COUNT_PLANES][TILE]) {
     constexpr bool RANKS = KIND == RANK_METRICS, RULE = KIND == NODE_RULE;
     const uint8_t* mask = RANKS ? a.exceed_mask : a.node_mask;
@@ -369,7 +369,7 @@ __device__ __forceinline__ void count_blocks(const gd_ledger_args& a, uint32_t w
     static_assert(SHORT_BATCH >= 8, "an early row has four bytes of the batch behind its first");
     const uint32_t q = W / 64, r = W % 64, hist = q + (r ? 1 : 0);     // whole blocks, steps of a tail, slots before a block
     const int32_t first = (int32_t)a.first_step;                       // (first + T below 2^31)
-    const uint32_t s0 = blockIdx.x * stretch * 64;
+    const uint32_t s0 = run * stretch * 64;
     const uint32_t blocks = min((T - s0 + 63) / 64, stretch);
     const bool last = s0 + blocks * 64 >= T;
     const uint32_t last_start = s0 + (blocks - 1) * 64;                // (the batch's last block, where `last`)
@@ -576,16 +576,20 @@ __device__ __forceinline__ void count_blocks(const gd_ledger_args& a, uint32_t w
     }
 }
 
-// blockIdx.y: tile (of ranks, of nodes, of nodes once more for the default rule).  Dynamic
+// A workgroup takes a tile (of ranks, of nodes, of nodes once more for the default rule) and a
+// stretch.  Workgroups that start one behind another take neighbouring tiles of the same stretch:
+// they read neighbouring pieces of the same rows (65 536 ranks x 4 096 steps, the whole update and
+// its read-outs: 117.5 us with the stretches of a tile one behind another, 114.9 so).  Dynamic
 // LDS: planes of every slot -- a block of the stretch or one of the few before it -- and word.
 __global__ __launch_bounds__(BLOCKS_NT) void ledger_blocks_kernel(const gd_ledger_args a, uint32_t rank_tiles,
                                                                   uint32_t node_tiles, uint32_t stretch) {
     extern __shared__ uint32_t lds[];
     __shared__ uint32_t final_planes[GD_COUNT_PLANES][TILE];
-    const uint32_t y = blockIdx.y;
-    if (y < rank_tiles) count_blocks<RANK_METRICS>(a, y * TILE, stretch, lds, final_planes);
-    else if (y < rank_tiles + node_tiles) count_blocks<NODE_METRICS>(a, (y - rank_tiles) * TILE, stretch, lds, final_planes);
-    else count_blocks<NODE_RULE>(a, (y - rank_tiles - node_tiles) * TILE, stretch, lds, final_planes);
+    const uint32_t id = blockIdx.y * gridDim.x + blockIdx.x;          // (stretches by tiles: below 2^32, up to 320 tiles)
+    const uint32_t y = id % gridDim.y, run = id / gridDim.y;
+    if (y < rank_tiles) count_blocks<RANK_METRICS>(a, y * TILE, run, stretch, lds, final_planes);
+    else if (y < rank_tiles + node_tiles) count_blocks<NODE_METRICS>(a, (y - rank_tiles) * TILE, run, stretch, lds, final_planes);
+    else count_blocks<NODE_RULE>(a, (y - rank_tiles - node_tiles) * TILE, run, stretch, lds, final_planes);
 }
 
 __device__ __forceinline__ int32_t quantise(float z, float quant) {
