@@ -212,7 +212,8 @@ gd_status gd_score_batch(gd_handle h, const float* d_x, uint32_t T, float* d_med
     a.node_agg = h->cfg.node_agg;
     a.split_steps = h->split_steps;
     a.hint_med = h->hint_med; a.hint_mad = h->hint_mad;
-    a.thr = h->cfg.z_threshold; a.node_scale = h->cfg.node_scale;
+    // (a threshold of -0 is one of +0: the kernels tell "greater" by the sign of thr less the score)
+    a.thr = h->cfg.z_threshold + 0.0f; a.node_scale = h->cfg.node_scale;
     a.rel_floor = h->cfg.rel_floor; a.abs_floor = h->cfg.abs_floor;
     memcpy(a.dir, h->cfg.direction, 8);
     hipError_t e = gd_launch_score(a, static_cast<hipStream_t>(stream));

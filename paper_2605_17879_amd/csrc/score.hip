@@ -1126,7 +1126,8 @@ __device__ __forceinline__ void score_row_fast(const float (&x)[4], float med, f
         const float q2 = __builtin_fmaf(e1, rs, q1);
         zs[i] = TWO_SIDED ? fabsf(q2) : q2;
     }
-    // (finite numbers: a score exceeds iff thr less it is negative, denormals being kept)
+    // (finite numbers and a threshold that is not -0, which less a score of +0 would be negative: a
+    // score exceeds iff thr less it is negative, denormals being kept)
     *e = (sign_bytes(__float_as_uint(thr - zs[0]), __float_as_uint(thr - zs[1]), __float_as_uint(thr - zs[2]),
                      __float_as_uint(thr - zs[3])) >> 7) & 0x01010101u;
     const float half = (zs[0] + zs[1]) + (zs[2] + zs[3]);
