@@ -73,7 +73,7 @@ struct alignas(16) ScoreParams {
 
 template <int NT, int LOG_NB, int MAX_NODES>
 struct Shared {
-    static constexpr int NB = 1 << LOG_NB;
+    static constexpr int NB = 1 << LOG_NB, WAVES = NT / WAVE;
     // dlo, hist, dhi are one array of 64 + NB + 64 counters for the hinted counting pass
     // (keys under / inside / over the bracket); the other passes use hist alone.
     uint32_t dlo[64];
@@ -287,10 +287,15 @@ __device__ __forceinline__ bool locate(SH& sh, uint32_t tid, uint32_t ka, uint32
 // for.  Rows instead of values, at a position made of a count in a scalar register and the
 // lanes' ballot: six instructions for the rows with a hit, and no round trip to LDS; which of
 // the four values it was is found out afterwards, by drain(), a value per lane.  The list lies in
-// the counters, which are at rest between two counting passes, and leaves them at rest.
+// the counters, which are at rest between two counting passes, and leaves them at rest.  Room for
+// more rows, or a second walk for those that did not fit, is no gain: crowded buckets are ranked
+// then instead of narrowed, and to rank a few hundred candidates takes longer (16 384 ranks x 2 048 x
+// 2, 400 equal values about the median: 189 us; 866 with a second walk, which costs plain columns
+// 1 to 2 % too).
 template <typename SH>
 struct RowList {
     static constexpr uint32_t MOST = 64;           // rows of a wave
+    static_assert(MOST * 4 * SH::WAVES <= SH::NB, "the waves' lists lie in the counters");
     uint32_t* const words;
     uint32_t n = 0;                                // (wave-uniform)
     __device__ __forceinline__ RowList(SH& sh, uint32_t w) : words(sh.hist + w * (MOST * 4u)) {}
@@ -334,6 +339,34 @@ __device__ __forceinline__ void append(uint32_t lane, uint32_t* list, uint32_t* 
     base = rfl(base);
     const uint32_t to = __builtin_amdgcn_mbcnt_hi((uint32_t)(hm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hm, base));
     if (hit && to < (uint32_t)CAND_CAP) list[to] = value;
+}
+
+// The keys in [clo, clo + cspan], no more than CAND_CAP, one by one into sh.cand: where a wave's list
+// of rows was too short for them (buckets of few candidates, most of them one wave's: 200 of 48 000
+// ranks x 1 024 steps 155 us where the whole column was selected anew, 104 so).  Begins and ends
+// with a barrier.
+template <int ROWS, typename SH, typename Keys>
+__device__ __forceinline__ void gather_singly(SH& sh, const Keys& keys, uint32_t clo, uint32_t cspan) {
+    __syncthreads();                        // everyone has read the lists' count
+    if (threadIdx.x == 0) sh.ncand = 0;
+    __syncthreads();
+    const uint32_t tok = keys.token(), from = opaque_s(clo);
+#pragma unroll
+    for (int j = 0; j < ROWS; ++j) {
+        uint32_t off[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) off[i] = keys.at(j, i, tok) - from;
+        if (min(min(off[0], off[1]), min(off[2], off[3])) <= cspan) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (off[i] <= cspan) {
+                    const uint32_t pos = atomicAdd(&sh.ncand, 1u);
+                    if (pos < (uint32_t)CAND_CAP) sh.cand[pos] = off[i] + from;
+                }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
 }
 
 // Exact ranking of the cnt gathered candidates in sh.cand (ties broken by
@@ -416,6 +449,10 @@ __device__ __forceinline__ bool block_select(SH& sh, const Keys& keys, uint32_t 
     constexpr int NB = 1 << LOG_NB;
     constexpr int BPT = NB / NT;
     static_assert(BPT >= 1 && (BPT % 4 == 0 || BPT < 4), "bucket split");
+    // What is gathered singly where the lists are too short: as much as sixteen waves rank sooner than
+    // the next round of counting would narrow; four or eight waves rank little (12 000 ranks x 1 000
+    // x 2, 150 equal values about the median: 162 us narrowed, 201 ranked).
+    constexpr uint32_t MOST_SINGLY = NT >= 1024 ? CAND_CAP : 2 * RowList<SH>::MOST;
     uint32_t lo = hint_lo, hi = hint_hi;
     // Bracket from the sample (skipped while a bracket handed in by the caller holds).
     auto sample_bracket = [&]() {
@@ -538,8 +575,12 @@ __device__ __forceinline__ bool block_select(SH& sh, const Keys& keys, uint32_t 
                 append(lane, sh.cand, &sh.ncand, valid && kk - clo <= cspan, kk);
             });
             __syncthreads();
-            const uint32_t cnt = rfl(sh.ncand);
-            settled = cnt == pb - pa;                   // (else a wave's list overflowed)
+            const uint32_t cnt = pb - pa;
+            settled = rfl(sh.ncand) == cnt;             // (else a wave's list was too short)
+            if (!settled && cnt <= MOST_SINGLY) {
+                gather_singly<ROWS>(sh, keys, clo, cspan);
+                settled = true;
+            }
             if (settled) {
                 rank_candidates<NT>(sh, tid, cnt, ka - below - pa, kb - below - pa);
                 va = rfl(sh.res[4]); vb = rfl(sh.res[5]);
@@ -884,10 +925,10 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
         });
     }
     __syncthreads();
-    const uint32_t ncnt = rfl(sh.ncand);
-    rank_candidates<NT>(sh, tid, min(ncnt, (uint32_t)CAND_CAP), k0 - below - pa, k1 - below - pa);
+    if (__builtin_expect(rfl(sh.ncand) != pb - pa, 0))           // (a wave's list was too short)
+        gather_singly<ROWS>(sh, XKeys<ROWS, true>{v}, lo + (ba << shift), ((bb - ba + 1u) << shift) - 1u);
+    rank_candidates<NT>(sh, tid, pb - pa, k0 - below - pa, k1 - below - pa);
     if (tid == 0) sh.ncand = 0;
-    if (ncnt != pb - pa) return out;               // (a wave's list overflowed)
     const uint32_t s0 = rfl(sh.res[4]), s1 = rfl(sh.res[5]);
     out.m0 = s0; out.m1 = s1;
     out.found = 1;

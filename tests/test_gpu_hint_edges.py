@@ -1,13 +1,14 @@
-"""The hinted selection's lists and its search for the MAD's edges, where they change course:
-lists of up to 64, 512 and more values about the median and about median -+ MAD (a wave's list of
-rows that overflows among them), and hints of the MAD that put the search 64 edges off or more on
-either side, or off the histogram.  One step per call, hinted; bit for bit against the oracle."""
+"""The selection's lists and its search for the MAD's edges, where they change course: up to 64,
+512 and more values about the median and about median -+ MAD, spread over all waves, and hints of the
+MAD that put the search 64 edges off or more on either side, or off the histogram (one step per
+call, hinted); buckets of values that are too many for the lists of rows of one wave or of all of
+them (runs of steps in every width of workgroup).  Bit for bit against the oracle."""
 import numpy as np
 import pytest
 import torch
 
 import oracle
-from gpu_harness import compare_scores, detector_for, oracle_params
+from gpu_harness import compare_scores, detector_for, oracle_params, run_and_compare
 
 pytestmark = pytest.mark.gpu
 
@@ -53,3 +54,42 @@ def test_lists_and_edges_of_the_hinted_selection(R, mad_factor):
     assert compare_scores(o, out, f"R={R} x{mad_factor}")["z_bit_exact"]
     det.set_streaming_hints(None, None)
     det.close()
+
+
+def _ranks_of_one_wave(R, threads, n):
+    """n ranks that one wave of a column's `threads` holds, each in a register row of its own."""
+    i = np.arange(n)
+    blocks = R // (4 * threads)                             # whole register rows
+    assert n <= 64 * blocks
+    return (i % blocks) * 4 * threads + 256 + 4 * (i // blocks)
+
+
+# (40 and more rows of a wave, none of the others; shares of all waves; from 300 values on in one
+# bucket for the general way, which counts them once more)
+CROWDS = [("wave", 60), ("wave", 70), ("wave", 128), ("wave", 200), ("wave", 250), ("all", 130), ("all", 240),
+          ("all", 330), ("all", 450), ("all", 700), None]
+
+
+@pytest.mark.parametrize("signs", [False, True])
+@pytest.mark.parametrize("R,T,threads", [(5000, 2600, 256), (8184, 2600, 256), (16384, 2060, 256), (20000, 1030, 512),
+                                         (32768, 1030, 512), (40000, 520, 1024), (65536, 520, 1024), (16384, 12, 1024),
+                                         (65536, 12, 1024)])
+def test_buckets_too_crowded_for_the_lists(R, T, threads, signs):
+    """Two steps a run and more, so that each kind of column is followed by another (T = 12: one
+    workgroup per column).  Some lists hold the bucket, some are a row too short, some overflow in
+    one wave alone, and some buckets hold more than is ranked at all."""
+    print(f"case crowded buckets R={R} T={T} signs={signs}", flush=True)
+    rng = np.random.default_rng(R + T)
+    x = np.exp(0.02 * rng.standard_normal((T, 1, R), dtype=np.float32))
+    for t in range(T):
+        kind = CROWDS[int(rng.integers(len(CROWDS)))]
+        if kind is None:
+            continue
+        where, n = kind
+        n = min(n, 64 * (R // (4 * threads)))
+        at = _ranks_of_one_wave(R, threads, n) if where == "wave" else rng.permutation(R)[:n]
+        x[t, 0, at] = 1.0 + 2e-6 * rng.standard_normal(n)              # about the median, within a bucket or two
+    if signs:
+        x -= np.float32(1.0)
+    p = oracle_params(R=R, M=1, W=8, k=4, directions=(1,), min_signals=1)
+    run_and_compare(p, torch.from_numpy(x), topk_k=8, label=f"crowded buckets R{R}", want_z=False)
