@@ -242,7 +242,18 @@ __global__ __launch_bounds__(TOPK_NT) void topk_short_kernel(const gd_topk_args 
 #pragma unroll
         for (int q = 0; q < KPT; ++q) hits += digest[q] >= thr && mine[q] != 0 ? 1u : 0u;
     }
-    if (hits) {
+    if (KPT == 1) {
+        // (many threads may hold a hit here, one each: a wave's places in one addition.  1 000 equal
+        // scores, k = 64: 8.1 us with an addition a thread, 7.3 so)
+        const uint64_t with = __ballot(hits != 0);
+        if (with != 0ull) {
+            uint32_t base = 0;
+            if (lane == 0) base = atomicAdd(&n_reach, (uint32_t)__popcll(with));
+            base = __builtin_amdgcn_readfirstlane(base);
+            const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(with >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)with, base));
+            if (hits) keys[pos] = mine[0];
+        }
+    } else if (hits) {
         uint32_t pos = atomicAdd(&n_reach, hits);
 #pragma unroll
         for (int q = 0; q < KPT; ++q)
