@@ -1906,10 +1906,12 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
 // NT threads per column (64: one wave per column, M of them per workgroup; LOG_NB has no
 // meaning there).  <= 128 VGPRs: 16 waves per CU.
 constexpr int block_threads(int NT) { return NT == WAVE ? 8 * WAVE : NT; }
-// Waves per SIMD.  Up to eight rows of 256 threads fit 96 VGPRs, and five such workgroups a CU's
-// LDS: their time is mostly that of the short phases, which overlap (10 000
-// steps, four / five: 4 096 ranks x 1 141 / 127 us, 5 000 x 8 784 / 677, 6 000 x 4 456 / 399, 8 000 x 4
-// 491 / 440; up to 1 024 steps there is no fifth to run).
+// Waves per SIMD.  Up to eight rows of 256 threads are kept to 96 VGPRs, and five such workgroups fit
+// a CU's LDS: their time is mostly that of the short phases, which overlap (four / five: 10 000
+// steps, 4 096 ranks x 1 141 / 127 us, 5 000 x 8 784 / 677, 6 000 x 4 456 / 399, 8 000 x 4 491 / 440;
+// 1 200 steps, which four to a CU take in two rounds, 8 000 x 4 94 / 68).  The ragged tiling of eight
+// rows has two registers too many for that and keeps them in scratch memory, 12 bytes a lane: up to
+// 1 024 steps, where there is no fifth to run, 8 000 ranks take 1 % longer so (x 8 102.5 / 103.8).
 constexpr int waves_of(int nt, int rows, bool want_z) { return nt == 256 && rows <= 8 && !want_z ? 5 : 4; }
 template <int NT, int ROWS, int LOG_NB, bool FULL, bool SPLIT, bool WANT_Z>
 __global__ __launch_bounds__(block_threads(NT), waves_of(NT, ROWS, WANT_Z)) void score_kernel(const gd_score_args a) {
@@ -2145,6 +2147,7 @@ hipError_t pick_tiling(const gd_score_args& a, hipStream_t s) {
     // (the 256-thread tilings take 2048 buckets: four workgroups then share a CU's LDS, and
     // their barrier-bound phases overlap)
     static_assert(4 * lds_bytes<256, 16, 11>() <= 160 * 1024, "four workgroups of the 16 384-rank tiling share a CU's LDS");
+    static_assert(5 * lds_bytes<256, 8, 11>() <= 160 * 1024, "five of those of up to 8 192 ranks");
     switch (a.R) {
         case 256: return launch<64, 1, 10>(a, n_cu, s);
         case 1024: return launch<64, 4, 10>(a, n_cu, s);

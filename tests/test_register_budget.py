@@ -75,3 +75,15 @@ x.hip:1:1: remark:     VGPRs Spill: 4 [-Rpass-analysis=kernel-resource-usage]
                  "Occupancy [waves/SIMD]": 3, "VGPRs Spill": 4}
     bad = hip_build.check_register_budget(res)
     assert len(bad) == 3, bad
+
+
+@pytest.mark.parametrize("kernel,needed", [
+    ("score_ragged_kernelILi256ELi8ELi11ELb0ELb0EEE", 5), ("score_ragged_kernelILi256ELi8ELi11ELb0ELb1EEE", 4),
+    ("score_ragged_kernelILi256ELi10ELi11ELb0ELb0EEE", 4), ("score_kernelILi256ELi4ELi11ELb1ELb0ELb0EEE", 5),
+    ("score_kernelILi256ELi4ELi11ELb1ELb0ELb1EEE", 4), ("score_kernelILi512ELi16ELi12ELb1ELb0ELb0EEE", 4)])
+def test_the_check_asks_for_the_waves_that_the_launcher_counts_on(kernel, needed):
+    name = f"_ZN1_1{kernel}v13gd_score_args"
+    for waves in (needed - 1, needed):
+        res = {name: {"VGPRs": 96, "AGPRs": 0, "ScratchSize [bytes/lane]": 0, "Occupancy [waves/SIMD]": waves,
+                      "VGPRs Spill": 0, "Dynamic Stack": False}}
+        assert len(hip_build.check_register_budget(res)) == (1 if waves < needed else 0)
