@@ -577,16 +577,13 @@ __device__ __forceinline__ void count_blocks(const gd_ledger_args& a, uint32_t w
 }
 
 // A workgroup takes a tile (of ranks, of nodes, of nodes once more for the default rule) and a
-// stretch.  Workgroups that start one behind another take neighbouring tiles of the same stretch:
-// they read neighbouring pieces of the same rows (65 536 ranks x 4 096 steps, the whole update and
-// its read-outs: 117.5 us with the stretches of a tile one behind another, 114.9 so).  Dynamic
-// LDS: planes of every slot -- a block of the stretch or one of the few before it -- and word.
+// stretch: tiles along x and stretches along y where side_by_side, the other way round otherwise.
+// Dynamic LDS: planes of every slot -- a block of the stretch or one of the few before it -- and word.
 __global__ __launch_bounds__(BLOCKS_NT) void ledger_blocks_kernel(const gd_ledger_args a, uint32_t rank_tiles,
-                                                                  uint32_t node_tiles, uint32_t stretch) {
+                                                                  uint32_t node_tiles, uint32_t stretch, bool side_by_side) {
     extern __shared__ uint32_t lds[];
     __shared__ uint32_t final_planes[GD_COUNT_PLANES][TILE];
-    const uint32_t id = blockIdx.y * gridDim.x + blockIdx.x;          // (stretches by tiles: below 2^32, up to 320 tiles)
-    const uint32_t y = id % gridDim.y, run = id / gridDim.y;
+    const uint32_t y = side_by_side ? blockIdx.x : blockIdx.y, run = side_by_side ? blockIdx.y : blockIdx.x;
     if (y < rank_tiles) count_blocks<RANK_METRICS>(a, y * TILE, run, stretch, lds, final_planes);
     else if (y < rank_tiles + node_tiles) count_blocks<NODE_METRICS>(a, (y - rank_tiles) * TILE, run, stretch, lds, final_planes);
     else count_blocks<NODE_RULE>(a, (y - rank_tiles - node_tiles) * TILE, run, stretch, lds, final_planes);
@@ -807,8 +804,15 @@ hipError_t gd_launch_ledger(const gd_ledger_args& a, hipStream_t s) {
         static std::atomic<uint64_t> granted{0};
         const hipError_t e = gd_grant_lds(granted, reinterpret_cast<const void*>(ledger_blocks_kernel), most);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(ledger_blocks_kernel, dim3(stretches, tiles), dim3(nt), lds, s, a, rank_tiles, node_tiles,
-                           stretch);
+        // Workgroups that start one behind another take neighbouring tiles of the same stretch, that is
+        // neighbouring pieces of the same rows, where there are many of both.  An update, stretches of a tile
+        // one behind another / tiles side by side, window 256: 65 536 ranks x 4 096 steps 102 / 103 us, x 2 000
+        // 80 / 65, x 512 43 / 39; 32 768 x 4 096 69 / 56; 16 384 x 1 024 31.0 / 26.1 (320 workgroups), x 512
+        // 21.3 / 21.7 (160), x 10 000 67.5 / 68.6; few tiles find less in the caches: 1 000 ranks (6 tiles) x
+        // 10 000 21.4 / 22.9, window 1 024 45.6 / 48.0.
+        const bool side_by_side = tiles >= 16 && (uint64_t)stretches * tiles > 256 && stretches <= 65535u;
+        hipLaunchKernelGGL(ledger_blocks_kernel, side_by_side ? dim3(tiles, stretches) : dim3(stretches, tiles), dim3(nt),
+                           lds, s, a, rank_tiles, node_tiles, stretch, side_by_side);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
