@@ -1185,7 +1185,9 @@ __device__ __forceinline__ void score_row_fast(const float (&x)[4], float med, f
         zs[i] = TWO_SIDED ? fabsf(q2) : q2;
     }
     // (finite numbers and a threshold that is not -0, which less a score of +0 would be negative: a
-    // score exceeds iff thr less it is negative, denormals being kept)
+    // score exceeds iff thr less it is negative, denormals being kept.  Compared value by value / so,
+    // 1 024 steps x 8: two-sided metrics 40 000 ranks 386 / 382 us, 65 536 541 / 539; one-sided ones,
+    // of which only the primary comes here, the same within 0.5 %)
     *e = (sign_bytes(__float_as_uint(thr - zs[0]), __float_as_uint(thr - zs[1]), __float_as_uint(thr - zs[2]),
                      __float_as_uint(thr - zs[3])) >> 7) & 0x01010101u;
     const float half = (zs[0] + zs[1]) + (zs[2] + zs[3]);
@@ -1250,8 +1252,10 @@ __device__ __forceinline__ gd_args_ptr args_here() {
 // there, and from the count to the scores the memory has nothing to do.  Measured: ten rows, 40 000
 // ranks x 1 024 steps x 8: none 399 us, three 391, five 383, six 382, seven 390; twelve, 48 000 x
 // 2 048 x 4: none 471, two 471, three 465, four 460, five 456; fourteen, 56 000 x 2 048 x 4: none
-// 532, two 538, three 532.  With fewer threads other workgroups of the CU fill the gap (up to eight
-// rows kept this way: 5 000 to 24 000 ranks within 1 %).
+// 532, two 538, three 532.  The six and the five hold over their whole tilings: 33 000, 36 000 and 40 952
+// ranks x 1 024 steps x 8 without / with them 364 / 355, 364 / 353 and 389 / 368 us, 41 000, 44 000 and 49 144
+// 415 / 393, 419 / 399 and 444 / 417 (2 048 x 4 and 1 500 x 2: 3 to 7 %).  With fewer threads other
+// workgroups of the CU fill the gap (up to eight rows kept this way: 5 000 to 24 000 ranks within 1 %).
 constexpr int rows_ahead(int nt, int rows) {
     return nt < 1024 ? 0 : rows == 10 ? 6 : rows == 12 ? 5 : 0;
 }
