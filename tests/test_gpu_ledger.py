@@ -124,6 +124,13 @@ def test_ledger_on_synthetic_histories(R, M, W, k, T, batches, horizon, limit):
     det.close()
 
 
+# Either side of the lines from which tiles lie side by side: 16 tiles, more than 256 workgroups (a tile
+# is 256 ranks or 256 nodes, nodes counted twice; 4 blocks of 64 steps a workgroup here), ragged last ones.
+@pytest.mark.parametrize("R,T", [(2816, 4400), (3072, 4096), (3072, 4097), (3072, 4359), (3320, 4096), (3328, 3900)])
+def test_ledger_where_the_order_of_tiles_changes(R, T):
+    test_ledger_on_synthetic_histories(R, 2, 16, 12, T, None, 500, 3)
+
+
 def _random_ledger_case(seed):
     rng = np.random.default_rng(5000 + seed)
     R = 8 * int(np.exp(rng.uniform(0, np.log(700))))
