@@ -15,9 +15,9 @@
 //      gathers that bucket's few values into LDS where they are ranked exactly;
 //      a bracket that misses, or a bucket that is too full (ties), falls back
 //      to wider or narrower ranges until the answer is exact;
-//   3. gets the MAD from the same histogram (pairs of bucket edges around the
-//      median bound the wanted distances; one pass counts and gathers), or by a
-//      second selection on |x - med| when that does not apply;
+//   3. gets the MAD from the same histogram (bucket edges on either side of the median bound the
+//      wanted distances, and the values there are gathered in the same pass or in one of their
+//      own), or by a second selection on |x - med| when that does not apply;
 //   4. computes z, the exceedance bits and the node scores from the registers.
 // After the M columns the per-rank mask bytes, anomaly bits and node outputs
 // are written.  HBM traffic is the 4 bytes per sample read plus ~1.8 bytes per
@@ -69,7 +69,34 @@ struct alignas(16) ScoreParams {
     float s, ss, rs;           // scale, its signed form and the reciprocal of that
     float cc, kk, margin, sthr;    // node estimate of the decision-only route
     uint32_t xcut, route, exact_recip;
+    float med, mad;
+    uint32_t settled;              // the gathered candidates gave median and MAD
 };
+// What the first wave works these out from: the same for all columns.
+struct alignas(16) ScoreRules {
+    float thr, node_scale, rel_floor, abs_floor;
+    float inv_node_scale;
+    uint32_t agg;
+};
+
+// What the hinted selection gathers (worked out by one wave).  Buckets are of its counting pass.
+struct alignas(16) GatherPlan {
+    // the MAD's buckets, lb0 .. li - 1 left of the median and rb0 .. rx - 1 right of it: what lies
+    // between them is nearer to `center` than `inner`, or in them; n_in values there, n_out with theirs
+    float inner;
+    uint32_t li, rb0, n_in;
+    float outer;                   // what lies beyond them is farther from `center`
+    uint32_t lb0, rx, n_out;
+    float center, reach;           // |x - center| <= reach: in one of the median's buckets,
+    uint32_t mid, status;          // the first in the low half, further ones in the high half; PLAN_*
+    uint32_t lo, shift;            // bucket b starts at the key lo + (b << shift)
+    uint32_t skip, n_mid;          // values before the median's buckets and in them
+};
+constexpr uint32_t PLAN_NONE = 0, PLAN_LOCATED = 1, PLAN_GATHER = 2;
+// Gathered at the most.  sh.cand holds the ones, the others and a wave's worth of room for the last
+// of them; these words are CAND_NONE (above every key, and a NaN) between columns.
+constexpr uint32_t MOST_MID = 64, MOST_DIST = 256, CAND_REST = MOST_MID + MOST_DIST + WAVE, CAND_NONE = 0x7FFFFFFFu;
+static_assert(CAND_REST <= (uint32_t)CAND_CAP, "the gathered candidates fit their list");
 
 template <int NT, int LOG_NB, int MAX_NODES>
 struct Shared {
@@ -94,6 +121,8 @@ struct Shared {
     uint32_t hok[8];
     uint32_t hfast[8];         // the hinted selection below has not failed for this metric yet
     ScoreParams par;
+    ScoreRules rules;
+    GatherPlan plan;
     alignas(8) uint8_t nodeb[MAX_NODES];        // the step's node mask bytes, read eight at a time
     uint64_t ranka[MAX_NODES / 8 > 0 ? MAX_NODES / 8 : 1];     // the step's rank anomaly words (zero between steps)
 };
@@ -758,33 +787,41 @@ __device__ __forceinline__ bool mad_from_histogram(SH& sh, const float (&v)[ROWS
 }
 
 // Hinted selection: median and MAD of a sign-free column whose predecessor (the same
-// metric one step earlier) left a bracket [hint_lo, hint_hi] around its median that
-// reaches past median -+ MAD, and its MAD.  Three passes over the registers instead of
-// the four of the general route, each with less work per value:
+// metric one step earlier) left a bracket around its median that reaches past median -+ MAD,
+// and its MAD.  Two passes over the registers instead of the four of the general route:
 //   1. counting: every key adds one to a counter -- its bucket inside the bracket, or a
 //      lane-private word under / over it (no test, no branch: the bucket index is clamped);
 //      the pass also finds the largest bit pattern of the column.
-//   2. the median's bucket(s) are gathered and ranked as in the general route.
-//   3. MAD: with the exact median, the threads search the prefix sums for the right edge
-//      e and the left edge f with  #[f, e) <= k0 < #[f', e + 1) -- the wanted distances
-//      end inside the few buckets around those edges.  One pass gathers the values whose
-//      distance lies between the distances of those buckets' edges (a few dozen); the
-//      values strictly between the two bucket ranges are known from the prefix sums, so
-//      nothing is counted per value.  The gathered values are then classified exactly:
-//        inner: all values of the buckets between the ranges, distance <= DI;
-//        outer: all values beyond the ranges, distance >= DO;
-//      a gathered value with distance < DI counts with the inner ones, those in
-//      [DI, DO] are ranked, and the wanted ranks must fall among them -- else the
-//      function reports failure and the caller selects in the general way.
-// found = 2: median and MAD; 1: the median alone (MAD by the general route); 0: neither
-// (the work area is at rest in every case, the column is never modified).  umax is
-// valid in every case.
+//   2. gathering.  The prefix sums give the median to a bucket or two, and with them the buckets
+//      on either side that the middle distances may end in (plan_gather); one pass lists the
+//      register rows that hold a value of any of these, and the waves sort out which.
+// Then one wave takes the median from its bucket's values, classifies the others by their exact
+// distances and takes the MAD (finish_gather); the values between the two ranges of the MAD's buckets
+// are known from the prefix sums, so nothing is counted per value.  Where that fails -- crowded
+// buckets, a list that is too short, a hint of the MAD that is far off -- the median's bucket is
+// gathered and ranked by itself, the edges are searched for with the exact median and a third
+// pass gathers what lies about them (hinted_rest).
+// What bounds it: 16 waves of one workgroup a CU wait for the chain between the passes, in which a
+// lone wave starts an instruction every eight cycles; so as few steps, and instructions, as can be.
+// One gathering pass instead of two, and one wave instead of all for what comes after: 65 536 ranks x
+// 4 096 x 8 a pass 1 974 -> 1 919 us (19.7 -> 17.9 vector and 8.8 -> 6.7 scalar instructions a
+// sample), 40 000 x 1 024 x 8 381 -> 371, 32 768 x 512 x 8 with z 249 -> 245, one step of 32 768 x 8
+// 27.8 -> 27.4; 16 384 x 10 000 x 4, four workgroups a CU, the same.  (With the candidates sorted by
+// lane exchanges and kept unnarrowed that wave took 4 900 cycles a column instead of 3 800, and the
+// gain was 0.2 %.)
+// The result of either is exact: what lies between the buckets is nearer than DI, what lies beyond
+// them farther than DO, and what is ranked in [DI, DO] must hold the ranks asked for.  The work
+// area is at rest in every case, the column is never modified.
 struct HintedResult {
-    int found;                  // 2: median and MAD, 1: median alone, 0: neither
-    uint32_t umax;              // largest raw bit pattern of the column
+    int found;                  // 2: median and MAD, 1: median alone
     uint32_t m0, m1;            // the two middle keys
     uint32_t q0, q1;            // the two middle distances (bit patterns), or, of `listed` ones in
     uint32_t listed;            // sh.cand (at most 64), their ranks: for the first wave to sort
+};
+struct GatherResult {
+    uint32_t status;            // PLAN_*
+    uint32_t umax;              // largest raw bit pattern of the column, of the samples that arrived
+                                // where the median's buckets were found
     uint32_t present;           // samples that arrived, where some did not (0: all did)
 };
 
@@ -819,24 +856,208 @@ __device__ __forceinline__ void count_present(SH& sh, const float (&v)[ROWS][4],
     if (tid == 0) { sh.ncand = 0; sh.smax = 0; }
 }
 
+// What the hinted selection gathers, worked out by one wave from the prefix sums of the counting
+// pass.  The median is known to its buckets ba..bb alone, ml <= median < mh, and so are the MAD's.
+// Candidate e is a right edge (a bucket's lower edge, e > bb + 1); its distance from the median
+// mirrored to the left gives an edge f, the first one above the mirror point, and F = #[f, e) never
+// decreases with e.  It is taken for both ends of the median's range: Fl >= F >= Fh.  With the
+// last e of Fl <= k0 at most k0 values are nearer than any value from f on outwards, with the first
+// of Fh > k1 more than k1 are no farther; the wanted distances end in between.  The candidates looked
+// at are the 64 edges around the one that the hint points at, one a lane; should they not hold the
+// answer, every sixteenth of the 1 024 about them and then the 64 where those point (a hint that
+// is 17 % off).  A wave that runs alone starts an instruction every eight cycles, of whatever kind
+// (measured), so that the number of instructions counts here: what is not the lanes' is left to
+// those who read the plan.
+template <int LOG_NB, typename SH>
+__device__ __forceinline__ void plan_gather(SH& sh, uint32_t lane, uint32_t lo, int shift, float mad_hint,
+                                            uint32_t below, uint32_t k0, uint32_t k1) {
+    constexpr uint32_t bmax = (1u << LOG_NB) - 1u;
+    const uint32_t ba = rfl(sh.res[0]), pa = rfl(sh.res[1]);
+    const uint32_t bb = rfl(sh.res[2]), pb = rfl(sh.res[3]);
+    auto edge = [&](uint32_t e) { return __uint_as_float(lo + (e << shift)); };
+    const float ml = edge(ba), mh = edge(bb + 1u), center = 0.5f * (ml + mh);
+    GatherPlan& plan = sh.plan;
+    if (lane == 0) {
+        plan.center = center;
+        plan.reach = fmaxf(center - ml, mh - center);
+        plan.mid = ba | (bb - ba) << 16;
+        // crowded (ties): the general route narrows
+        plan.status = pb - pa > (uint32_t)CAND_CAP / 2 || bb - ba > 1u ? PLAN_NONE : PLAN_LOCATED;
+        plan.lo = lo; plan.shift = (uint32_t)shift; plan.skip = below + pa; plan.n_mid = pb - pa;
+    }
+    if (pb - pa > MOST_MID || bb - ba > 1u || !(mad_hint > 0.0f)) return;
+    // the first lane's edge (mod 2^32; a hint beyond the bracket points at its end)
+    uint32_t e0 = rfl(min((__float_as_uint(center + mad_hint) - lo) >> shift, bmax)) - 32u;
+    uint32_t step = 1;
+    for (int round = 0; round < 3; ++round) {
+        const uint32_t e = e0 + lane * step;
+        const float x = edge(e);
+        const uint32_t ql = (__float_as_uint(ml - (x - ml)) - lo) >> shift;      // (under the bracket: beyond bmax)
+        const uint32_t qh = (__float_as_uint(mh - (x - mh)) - lo) >> shift;
+        const float inner = fminf(center - edge(qh + 1u), edge(e - 1u) - center), outer = fmaxf(center - edge(ql), x - center);
+        uint32_t pe = 0, pl1 = 0, ph = 0, pb1 = 0, cl = 0xFFFFFFFFu, ch = 0;
+        if (e - (bb + 2u) < bmax - bb && ql <= bmax && qh < ba) {          // (e in bb + 2 .. bmax + 1)
+            pe = sh.pref[e]; ph = sh.pref[qh + 1u]; pl1 = sh.pref[ql]; pb1 = sh.pref[e - 1u];
+            cl = pe - sh.pref[ql + 1u];
+            ch = pe - ph;
+        }
+        const uint64_t under = gd_ballot(cl <= k0), over = gd_ballot(ch > k1);
+        if (round == 1) {                                          // the fine look, about where the coarse one points
+            if (over == 0ull || under == 0ull) break;
+            e0 += 16u * (63u - (uint32_t)__builtin_clzll(under)) - 24u;
+            step = 1;
+            continue;
+        }
+        if (over == 0ull || under == 0ull) {                       // not here: every sixteenth edge, 512 to either side
+            e0 -= 32u * 15u;
+            step = 16;
+            continue;
+        }
+        // At most as many values as are asked for are closer than f, the edge that the last `under` gives
+        // on the left.  Buckets grow wider with their values, so that f's own mirror image lies in the
+        // bucket before the right edge.  (A bucket further in on both sides has twice as many distances
+        // to rank where the left ones are narrow: exponential values, 56 000 ranks x 1 024 143 us, so 112.)
+        if (lane == 63u - (uint32_t)__builtin_clzll(under)) {
+            plan.inner = inner; plan.li = qh + 1u; plan.rb0 = e - 1u; plan.n_in = pb1 - ph;
+            plan.status = inner > 0.0f ? PLAN_GATHER : PLAN_LOCATED;
+        }
+        if (lane == (uint32_t)__builtin_ctzll(over)) {
+            plan.outer = outer; plan.lb0 = ql; plan.rx = e; plan.n_out = pe - pl1;
+        }
+        break;
+    }
+}
+
+// The rank of one of N keys (N = 16, 32 or 64; no two of them alike but for the CAND_NONE that
+// follow the last), by one wave: lane l ranks key l mod N, the lanes that rank the same one compare
+// it with their share of the others each.  Two instructions a comparison, 28 in all for sixteen
+// keys, 48 for thirty-two (a sort by lane exchanges takes seven for each of its ten to
+// twenty-one steps).
+template <int N>
+__device__ __forceinline__ uint32_t rank_key(const uint32_t* list, uint32_t mine, uint32_t lane) {
+    constexpr int SHARE = N * N / WAVE;
+    const uint4* others = reinterpret_cast<const uint4*>(list + lane / N * SHARE);
+    uint32_t r = 0;
+#pragma unroll 1
+    for (int at = 0; at < SHARE / 4; at += 2) {                  // (eight at a time: registers)
+        uint32_t bits = 0;
+#pragma unroll
+        for (int i = 0; i < (SHARE < 8 ? SHARE / 4 : 2); ++i) {
+            const uint4 q = others[at + i];
+            auto smaller = [&](uint32_t other) { bits = __builtin_amdgcn_alignbit(bits, other - mine, 31); };      // (the difference's sign follows)
+            smaller(q.x); smaller(q.y); smaller(q.z); smaller(q.w);
+        }
+        r += (uint32_t)__popc(bits);
+    }
+    if constexpr (N <= 32) {
+        const auto h = __builtin_amdgcn_permlane32_swap(r, r, false, false);
+        r = h[0] + h[1];
+    }
+    if constexpr (N <= 16) {
+        const auto h = __builtin_amdgcn_permlane16_swap(r, r, false, false);
+        r = h[0] + h[1];
+    }
+    return r;
+}
+// The keys of rank ka and kb among a list's first n, by one wave.
+__device__ __forceinline__ void pick_ranks(const uint32_t* list, uint32_t n, uint32_t lane, uint32_t ka, uint32_t kb, uint32_t* a, uint32_t* b) {
+    uint32_t mine, r;
+    if (n <= 16) { mine = list[lane & 15]; r = rank_key<16>(list, mine, lane); }
+    else if (n <= 32) { mine = list[lane & 31]; r = rank_key<32>(list, mine, lane); }
+    else { mine = list[lane]; r = rank_key<64>(list, mine, lane); }
+    *a = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)(__builtin_ctzll(gd_ballot(r == ka)) & (WAVE - 1)));
+    *b = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)(__builtin_ctzll(gd_ballot(r == kb)) & (WAVE - 1)));
+}
+
+// Median and MAD from what was gathered, by one wave: false where a wave's list was too short, or the
+// ranks asked for are not among the candidates.  A candidate's distance is compared with the bounds
+// inside which every value between the MAD's buckets lies and beyond which every value further out
+// does, so that what is ranked is exact whatever the plan was.
+template <typename SH>
+__device__ __forceinline__ bool finish_gather(SH& sh, uint32_t lane, uint32_t k0, uint32_t k1, float* med_out, float* mad_out) {
+    constexpr uint32_t CHUNKS = MOST_DIST / WAVE;
+    static_assert(CHUNKS == 4, "two chunks, and two more");
+    const GatherPlan plan = sh.plan;
+    const uint32_t got = sh.ncand;
+    uint32_t* const dist = sh.cand + MOST_MID;
+    float d[CHUNKS];
+#pragma unroll
+    for (uint32_t c = 0; c < CHUNKS; ++c) d[c] = __uint_as_float(dist[c * WAVE + lane]);      // (none: a NaN)
+    const uint32_t n_mid = rfl(plan.n_mid), n_in = rfl(plan.n_in), n_dist = rfl(plan.n_out) - n_in, skip = rfl(plan.skip);
+    const uint32_t lo = rfl(plan.lo), shift = rfl(plan.shift);
+    const bool whole = rfl(got) == (n_mid << 16 | n_dist), many = n_dist > 2 * WAVE;
+    auto edge = [&](uint32_t e) { return __uint_as_float(lo + (e << shift)); };
+    uint32_t s0, s1;
+    pick_ranks(sh.cand, n_mid, lane, k0 - skip, k1 - skip, &s0, &s1);
+    const uint32_t none = opaque_v(CAND_NONE), first = lo + ((rfl(plan.mid) & 0xFFFFu) << shift);
+    sh.cand[lane] = none; dist[lane] = none; dist[WAVE + lane] = none;
+    if (many) { dist[2 * WAVE + lane] = none; dist[3 * WAVE + lane] = none; }
+    if (lane == 0) sh.ncand = opaque_v(0u);
+    if (!whole) return false;
+    const float med = 0.5f * (__uint_as_float(first + (s0 >> 6)) + __uint_as_float(first + (s1 >> 6)));
+    float from = uniform(fmaxf(med - edge(plan.li), edge(plan.rb0) - med)), to = uniform(fminf(med - edge(plan.lb0), edge(plan.rx) - med));
+#pragma unroll
+    for (uint32_t c = 0; c < CHUNKS; ++c) d[c] = fabsf(d[c] - med);
+    uint32_t nearer = 0, upto = 0;              // candidates nearer than `from`, and not beyond `to`
+    auto count = [&](float x) {
+        nearer += (uint32_t)__popcll(gd_ballot(x < from));
+        upto += (uint32_t)__popcll(gd_ballot(x <= to));
+    };
+    auto classify = [&]() {
+        nearer = 0; upto = 0;
+        count(d[0]); count(d[1]);
+        if (many) { count(d[2]); count(d[3]); }
+    };
+    classify();
+    if (upto - nearer > 32u) {
+        // the candidates taken as evenly spread: the wanted rank's place, and 13 ranks to either side (the
+        // one wanted among 64 is off by four, one standard deviation, at the most)
+        const float per = (to - from) * __builtin_amdgcn_rcpf((float)(upto - nearer)), at = from + (float)(int)(k0 - n_in - nearer) * per;
+        from = uniform(fmaxf(from, at - 13.0f * per)); to = uniform(fminf(to, at + 13.0f * per));
+        classify();
+    }
+    const uint32_t c_in = n_in + nearer, kept = upto - nearer, base = __float_as_uint(from);
+    // (also where `from` is beyond `to`; keys of 25 bits and the place)
+    if (c_in > k0 || k1 >= c_in + kept || kept > (uint32_t)WAVE || __float_as_uint(to) - base >= 1u << 25) return false;
+    uint32_t* const slots = dist + MOST_DIST;
+    uint32_t pos = 0;
+    auto keep = [&](float x) {
+        const uint32_t off = __float_as_uint(x) - base;
+        const bool hit = off <= __float_as_uint(to) - base;
+        const uint64_t mask = gd_ballot(hit);
+        const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, pos));
+        if (hit) slots[at] = off << 6 | at;
+        pos += (uint32_t)__popcll(mask);
+    };
+    keep(d[0]); keep(d[1]);
+    if (many) { keep(d[2]); keep(d[3]); }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    uint32_t d0, d1;
+    pick_ranks(slots, kept, lane, k0 - c_in, k1 - c_in, &d0, &d1);
+    slots[lane] = none;
+    *med_out = med;
+    const float m0 = __uint_as_float(base + (d0 >> 6)), m1 = __uint_as_float(base + (d1 >> 6));
+    *mad_out = k0 == k1 ? m0 : 0.5f * (m0 + m1);
+    return true;
+}
+
 // Padding lanes (of the last rows of a ragged rank count) hold another lane's value until
 // `set_padding(j)` makes them NaN patterns: over the bracket in the count, never within a
 // distance in the gather.
 // `counted` is called by every wave as it is done with the counting pass.
 template <int NT, int ROWS, int LOG_NB, typename SH, typename Pad, typename Counted>
-__device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[ROWS][4], Pad set_padding, Counted counted,
+__device__ __forceinline__ GatherResult hinted_gather(SH& sh, const float (&v)[ROWS][4], Pad set_padding, Counted counted,
                                                       uint32_t hint_lo, uint32_t hint_hi, float mad_hint,
                                                       uint32_t k0, uint32_t k1, uint32_t* umax_slot) {
-    HintedResult out = {0, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+    GatherResult out = {PLAN_NONE, 0u, 0u};
     constexpr int NB = 1 << LOG_NB;
     constexpr uint32_t KEY_LIMIT = 0x7D000000u;    // beyond it the signed bucket arithmetic could wrap
     const uint32_t span0 = hint_hi - hint_lo;
     const int shift = shift_for<LOG_NB>(span0);
     // the bracket is widened to all NB buckets (less than twice the hint's span; the caller
     // has checked that this stays below KEY_LIMIT) and starts on a bucket boundary
-    constexpr uint32_t bmax = (uint32_t)NB - 1u;
     const uint32_t lo = hint_lo & ~((1u << shift) - 1u);
-    const uint32_t hi = lo + ((uint32_t)NB << shift) - 1u;
     uint32_t* const cnt = sh.dlo;                  // 64 + NB + 64 counters
     // ---- pass 1: count.  lo is a multiple of 2^shift, so a key's bucket is its own bits
     // shifted down, less lo's: the clamp works on the shifted bits and the subtraction
@@ -899,9 +1120,71 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
     uint32_t below;
     const bool bracketed = locate<NT, LOG_NB, true, true>(sh, tid, k0, k1, &below);
     if (top > KEY_LIMIT || !bracketed || shift < 2) return out;
+    if (w == 0) plan_gather<LOG_NB>(sh, lane, lo, shift, mad_hint, below, k0, k1);
+    __syncthreads();
+    // (all of it at once: read where it is used it is a chain of LDS latencies)
+    const GatherPlan plan = sh.plan;
+    const float center = uniform(plan.center), inner = uniform(plan.inner), reach = uniform(plan.reach);
+    const uint32_t wspan = rfl(__float_as_uint(plan.outer - plan.inner));
+    const uint32_t lb0 = rfl(plan.lb0), lspan = rfl(plan.li - plan.lb0), rb0 = rfl(plan.rb0), rspan = rfl(plan.rx - plan.rb0);
+    const uint32_t mid_p = rfl(plan.mid), ba = mid_p & 0xFFFFu, cspan = mid_p >> 16, n_dist = rfl(plan.n_out - plan.n_in);
+    out.status = rfl(plan.status);
+    if (out.status == PLAN_GATHER && n_dist > MOST_DIST) out.status = PLAN_LOCATED;
+    out.umax = out.status == PLAN_NONE ? umax : top;
+    if (__builtin_expect(out.status != PLAN_GATHER, 0)) return out;
+    // ---- gather the rows that hold a value of the median's buckets or of the MAD's
+    RowList<SH> rows(sh, w);
+    {
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int j = 0; j < ROWS; ++j) {
+            const float c = uniform(center), e = uniform(inner);
+            float y[4];
+            uint32_t off[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                y[i] = v[j][i] - c;
+                off[i] = __float_as_uint(fabsf(y[i]) - e);           // (negative: a large pattern)
+            }
+            const float near = fminf(fminf(fabsf(y[0]), fabsf(y[1])), fminf(fabsf(y[2]), fabsf(y[3])));
+            const uint32_t far = min(min(off[0], off[1]), min(off[2], off[3]));
+            rows.add(near <= reach || far <= wspan, v[j]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __builtin_amdgcn_s_setprio(3);
+        rows.drain(lane, [&](uint32_t x, bool valid) {
+            // (values under the bracket wrap round: (x - lo) >> shift is beyond every bucket)
+            const uint32_t b = (x - lo) >> shift;
+            const bool mid = valid && b - ba <= cspan, dist = valid && (b - lb0 < lspan || b - rb0 < rspan);
+            const uint64_t mids = gd_ballot(mid), dists = gd_ballot(dist);
+            if ((mids | dists) == 0ull) return;
+            uint32_t base = 0;            // both counts in one word
+            if (lane == 0) base = atomicAdd(&sh.ncand, (uint32_t)__popcll(mids) << 16 | (uint32_t)__popcll(dists));
+            base = rfl(base);
+            const uint64_t of = mid ? mids : dists;
+            const uint32_t to = __builtin_amdgcn_mbcnt_hi((uint32_t)(of >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)of, mid ? base >> 16 : base & 0xFFFFu));
+            // (the median's as keys of their own each: the offset in their buckets, then the place)
+            if (mid && to < MOST_MID) sh.cand[to] = (x - (lo + (ba << shift))) << 6 | to;
+            if (dist && to < MOST_DIST) sh.cand[MOST_MID + to] = x;
+        });
+    }
+    __syncthreads();
+    return out;
+}
+
+// The rest of the hinted selection where the gathered candidates did not settle it, or would have
+// been too many: the median's bucket(s), located by hinted_gather, first, and then the MAD's.
+template <int NT, int ROWS, int LOG_NB, typename SH>
+__device__ __forceinline__ HintedResult hinted_rest(SH& sh, const float (&v)[ROWS][4], float mad_hint, uint32_t k0, uint32_t k1) {
+    HintedResult out = {1, 0u, 0u, 0u, 0u, 0u};
+    constexpr int NB = 1 << LOG_NB;
+    constexpr uint32_t bmax = (uint32_t)NB - 1u;
+    const uint32_t tid = opaque_v(threadIdx.x), lane = tid & (WAVE - 1), w = rfl(tid >> 6);
+    const uint32_t lo = rfl(sh.plan.lo);
+    const int shift = (int)rfl(sh.plan.shift);
+    const uint32_t hi = lo + ((uint32_t)NB << shift) - 1u;
     const uint32_t ba = rfl(sh.res[0]), pa = rfl(sh.res[1]);
-    const uint32_t bb = rfl(sh.res[2]), pb = rfl(sh.res[3]);
-    if (pb - pa > (uint32_t)CAND_CAP / 2 || bb - ba > 1u) return out;      // crowded (ties): the general route narrows
+    const uint32_t bb = rfl(sh.res[2]), pb = rfl(sh.res[3]), below = rfl(sh.plan.skip) - pa;
     // ---- pass 2: the median's bucket(s)
     RowList<SH> rows(sh, w);
     {
@@ -930,8 +1213,6 @@ __device__ __forceinline__ HintedResult hinted_select(SH& sh, const float (&v)[R
     if (tid == 0) sh.ncand = 0;
     const uint32_t s0 = rfl(sh.res[4]), s1 = rfl(sh.res[5]);
     out.m0 = s0; out.m1 = s1;
-    out.found = 1;
-    out.umax = top;
     const float med = 0.5f * (__uint_as_float(s0) + __uint_as_float(s1));
     if (!(mad_hint > 0.0f)) return out;
     // ---- MAD: search the prefix sums.  Candidate e is a right edge (a bucket's lower
@@ -1306,10 +1587,13 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     // the selection's work area starts in its rest state (see the LDS protocol)
     for (int i = tid; i < SH::NB + 128; i += NT) sh.dlo[i] = 0;      // dlo, hist, dhi
     for (int i = tid; i < (MAX_NODES / 8 > 0 ? MAX_NODES / 8 : 1); i += NT) sh.ranka[i] = 0;
+    for (int i = tid; i < (int)CAND_REST; i += NT) sh.cand[i] = CAND_NONE;
     if (tid == 0) {
         sh.umax[0] = 0; sh.umax[1] = 0; sh.ncand = 0; sh.below = 0; sh.nkept = 0; sh.nnear = 0;
         sh.smin = 0xFFFFFFFFu; sh.smax = 0; sh.d1 = 0; sh.d2 = 0xFFFFFFFFu;
         for (int m = 0; m < 8; ++m) { sh.hok[m] = 0; sh.hfast[m] = 1; }
+        // (the reciprocal is only used where node_scale > 0)
+        sh.rules = {a.thr, a.node_scale, a.rel_floor, a.abs_floor, 1.0f / a.node_scale, a.node_agg};
         // A one-step call may be told the medians and MADs of a recent step (usually the
         // previous call's outputs).  They take the place of the hints a run of steps builds
         // up for itself; like those they are only trusted as far as the counting pass
@@ -1327,7 +1611,6 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     }
     __syncthreads();
     constexpr uint32_t nsample = NT;          // (row 0, the column's sample, holds ranks throughout)
-    const float inv_node_scale = uniform(1.0f / a.node_scale);      // (only used where node_scale > 0)
     uint32_t dir_codes = 0;          // direction + 1 of metric i in bits 2i, 2i + 1
 #pragma unroll
     for (int i = 0; i < 8; ++i) dir_codes |= (uint32_t)(a.dir[i] + 1) << (2 * i);
@@ -1420,122 +1703,13 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
             hinted = xl >= 0.0f && xh > xl && hint_hi < 0x7F800000u;
         }
         uint32_t* const umax_slot = &sh.umax[colpar];
-        uint32_t umax = 0;
-        uint32_t s0 = 0, s1 = 0;
-        float med = 0.0f;
-        bool have_mad = false;
-        uint32_t missing = 0;                   // the samples that arrived, where some did not (hinted selection)
-        // The hinted selection (sign-free column, a predecessor's bracket and MAD): median and
-        // MAD in three light passes.  Whatever it does not settle goes
-        // through the general route below.
-        int hsel = 0;
-        uint32_t listed = 0;                    // distances still to be sorted by the first wave
-        bool tried_fast = false;
-        if (hinted && rfl(sh.hfast[m]) != 0 && hint_hi < 0x7D000000u - 2u * (hint_hi - hint_lo) &&
-            hint_hi - hint_lo < 0x20000000u) {
-            tried_fast = true;
-            const HintedResult hr = hinted_select<NT, ROWS, LOG_NB>(
-                sh, v, [&](int j) { set_padding(j, tl); }, [&]() { load_ahead(next_col); }, hint_lo, hint_hi, sh.hmad[m], k0_all, k1_all, umax_slot);
-            hsel = hr.found;
-            umax = hr.umax;
-            if (hsel == 0) {
-                hinted = false;                 // (and this metric goes the general way from now on,
-                                                // unless the hint was only a sample's)
-                if (tid == 0 && !boot) sh.hfast[m] = 0;
-            } else {
-                med = 0.5f * (__uint_as_float(hr.m0) + __uint_as_float(hr.m1));
-                have_mad = hsel == 2;
-                s0 = hr.q0; s1 = hr.q1;
-                if (have_mad) listed = hr.listed;
-                missing = hr.present;
-                if (tid == 0) sh.hmed[m] = med;
-            }
-        }
-        // Largest raw bit pattern of the column: >= 0x80000000 iff some value carries
-        // a sign bit (negative or -0); otherwise it is the bit pattern of the maximum.
-        // With a hint the column is taken to be sign-free like its predecessor and the
-        // maximum is found by the median's counting pass itself, which starts on the
-        // register rows as they arrive; otherwise it takes a pass of its own.
-        const bool fused_umax = FULL && hinted && !tried_fast;
-        if (__builtin_expect(!fused_umax && !tried_fast, 0)) {
-            uint32_t um = 0;
-#pragma unroll
-            for (int j = 0; j < ROWS; ++j) {
-                um = max(um, max(__float_as_uint(v[j][0]), __float_as_uint(v[j][1])));
-                um = max(um, max(__float_as_uint(v[j][2]), __float_as_uint(v[j][3])));
-                set_padding(j, tl);
-            }
-            um = wave_max_to_last(um);
-            if (lane == WAVE - 1) atomicMax(umax_slot, um);
-            __syncthreads();
-            umax = rfl(*umax_slot);
-        }
-        if (!tried_fast) load_ahead(next_col);
-        // special: some value carries a sign bit or is a NaN.  The raw bits are then no
-        // keys to select by, and a NaN is a missing sample that the ranks must not count.
-        bool special = umax > 0x7F800000u;
-        uint32_t k0 = k0_all, k1 = k1_all;
-
-        if (hsel == 0 && !special) {
-            uint32_t hlo = 0, hhi = 0;
-            int hshift = 0;
-            const bool one_round = block_select<NT, ROWS, LOG_NB, true>(
-                sh, XKeys<ROWS, true>{v}, __float_as_uint(v[0][0]), true, nsample, k0_all, k1_all, &s0,
-                &s1, &hlo, &hhi, &hshift, hinted, hint_lo, hint_hi, fused_umax ? umax_slot : nullptr, &umax);
-            special = umax > 0x7F800000u;      // (only the fused pass can find this out here)
-        if (!special) {
-            med = 0.5f * (__uint_as_float(s0) + __uint_as_float(s1));
-            if (one_round)
-                have_mad = mad_from_histogram<NT, ROWS, LOG_NB>(sh, v, med, hlo, hhi, hshift, k0_all, k1_all,
-                                                                hinted ? sh.hmad[m] : 0.0f, &s0, &s1);
-            if (tid == 0) {
-                if (have_mad) {                 // keep the reach, follow the median
-                    if (!hinted) {
-                        // the reach kept for the coming steps: median -+ 1.25 MAD (the edge
-                        // pairing looks up to 1.125 MAD away) rather than the sample's wider
-                        // bracket -- fewer keys to count, finer buckets, fewer candidates
-                        const float madv = 0.5f * (__uint_as_float(s0) + __uint_as_float(s1));
-                        sh.hwl[m] = fminf(med - __uint_as_float(hlo), 1.25f * madv);
-                        sh.hwh[m] = fminf(__uint_as_float(hhi) - med, 1.25f * madv);
-                    }
-                    sh.hmed[m] = med;
-                    sh.hmad[m] = 0.5f * (__uint_as_float(s0) + __uint_as_float(s1));
-                    sh.hok[m] = 1;
-                } else {
-                    sh.hok[m] = 0;
-                }
-            }
-        }
-        }
         // the other slot is free again: every thread read it a column ago
         if (tid == 0) sh.umax[colpar ^ 1u] = 0;
         colpar ^= 1u;
-        uint32_t present = R;
-        if (__builtin_expect(missing != 0, 0)) { present = missing; k0 = (present - 1) / 2; k1 = present / 2; }
-        if (__builtin_expect(special, 0)) {
-            if (tid == 0) sh.hok[m] = 0;
-            __syncthreads();    // (a counting pass given up above has just reset its counters)
-            // median and MAD are taken over the samples present alone (padding lanes hold NaNs
-            // too): the middle one(s) of `present`
-            uint32_t top;
-            count_present(sh, v, &present, &top);
-            __syncthreads();
-            if (umax < 0x80000000u) { umax = top; missing = present; }      // (no signs)
-            k0 = present ? (present - 1) / 2 : 0u;
-            k1 = present / 2;
-            if (present) {
-                const bool sv = v[0][0] == v[0][0];
-                block_select<NT, ROWS, LOG_NB, false>(sh, XKeys<ROWS, false>{v}, key_of(v[0][0] + 0.0f),
-                                                      sv, nsample, k0, k1, &s0, &s1);
-                // (an odd count has one middle value: no sum that could overflow)
-                med = k0 == k1 ? float_of_key(s0) : 0.5f * (float_of_key(s0) + float_of_key(s1));
-            }
-        }
-        if (__builtin_expect(!have_mad && present, 0))
-            block_select<NT, ROWS, LOG_NB, false>(sh, DKeys<ROWS>{v, med},
-                                                  __float_as_uint(fabsf(v[0][0] - med)),
-                                                  v[0][0] == v[0][0], nsample, k0, k1, &s0, &s1);
-        if (!present) med = __uint_as_float(opaque_s(0x7FC00000u));  // nothing to take a median of
+        uint32_t umax = 0;
+        float med = 0.0f;
+        uint32_t missing = 0;                   // the samples that arrived, where some did not
+        bool special = false;                   // not scored by the fast routes: signs, or missing samples that stay
         // (all eight directions in one scalar word: indexing the argument array by m
         // would be a load from memory, and a wait for it, in every column)
         const int dir = (int)((dir_codes >> (2u * m)) & 3u) - 1;
@@ -1544,56 +1718,26 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         // that a missing sample counts with, and (with a threshold that is not negative) never
         // exceeds, so that the column is scored like any other.  Of a primary metric that
         // falls the zero would be negative; signs leave the fast routes anyway.
-        if (__builtin_expect(missing != 0, 0)) {
-          special = !(a.thr >= 0.0f && a.node_agg == 0 && (!prim || dir >= 0) && med < 3.0e38f);
-          if (!special) {
-            const uint32_t absm = opaque_s(0x7FFFFFFFu);
-#pragma unroll
-            for (int j = 0; j < ROWS; ++j) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[j][i] = (__float_as_uint(v[j][i]) & absm) <= 0x7F800000u ? v[j][i] : med;
-                __builtin_amdgcn_sched_barrier(0);
-            }
-          }
-        }
-        // The first wave alone sorts the last distances and works out the column's scoring
-        // parameters: done by every wave, the same hundred and thirty instructions kept all four
-        // waves of a SIMD busy one after another (2 100 of 41 000 cycles a column at 65 536 ranks),
-        // and the sort's result would cost one more barrier.
-        if (w == 0) {
-            const gd_args_ptr here = args_here();
-            const float thr = here->thr, node_scale = here->node_scale;
-            if (listed != 0) {
-                const uint32_t key = sh.cand[lane];
-                const uint32_t sorted = gd_sort64<true>((uint32_t)lane < listed ? key : 0xFFFFFFFFu);
-                s0 = (uint32_t)__builtin_amdgcn_readlane((int)sorted, (int)(s0 & (WAVE - 1)));
-                s1 = (uint32_t)__builtin_amdgcn_readlane((int)sorted, (int)(s1 & (WAVE - 1)));
-            }
-            float mad = k0 == k1 ? __uint_as_float(s0) : 0.5f * (__uint_as_float(s0) + __uint_as_float(s1));
-            if (!present) mad = __uint_as_float(opaque_s(0x7FC00000u));      // nothing to take a median of
-            if (tid == 0) {
-                here->med[t * M + m] = med;
-                here->mad[t * M + m] = mad;
-                if (hsel) sh.hmad[m] = mad;         // the hinted selection follows median and MAD step by step
-                // a column with missing samples, but no signs, leads the next step's selection too
-                if (hsel == 0 && missing != 0 && med > 0.0f && mad > 0.0f && med < 3.0e38f && mad < 3.0e38f) {
-                    sh.hmed[m] = med; sh.hmad[m] = mad;
-                    sh.hwl[m] = 1.25f * mad; sh.hwh[m] = 1.25f * mad;
-                    sh.hok[m] = 1;
-                }
-                // (from here on the reach is the exact MAD's, as after the general route)
-                if (boot && hsel == 2) { sh.hwl[m] = 1.25f * mad; sh.hwh[m] = 1.25f * mad; }
-            }
+        auto missing_stay = [&](float median) {
+            return !(a.thr >= 0.0f && a.node_agg == 0 && (!prim || dir >= 0) && median < 3.0e38f);
+        };
+        // The column's median and MAD go out, and what the score loop needs of them is worked out, by the
+        // first wave: done by every wave, the same hundred and thirty instructions kept all four
+        // waves of a SIMD busy one after another (2 100 of 41 000 cycles a column at 65 536 ranks).
+        auto work_out = [&](float med, float mad, bool special) {
+            const ScoreRules rules = sh.rules;
+            const float thr = uniform(rules.thr), node_scale = uniform(rules.node_scale), inv_node_scale = rules.inv_node_scale;
+            const uint32_t agg = rfl(rules.agg);
             float s = 1.4826f * mad;
-            s = fmaxf(s, here->rel_floor * fabsf(med));
-            s = fmaxf(s, here->abs_floor);
+            s = fmaxf(s, rules.rel_floor * fabsf(med));
+            s = fmaxf(s, rules.abs_floor);
 
             // The reciprocal route is exact while no intermediate can leave the normal
             // range: all x in [0, 2^59], 2^-34 <= med, 2^-60 <= s <= 2^60 (then every
             // non-zero |x - med| lies in [2^-59, 2^59]).
             const bool exact_recip = !special && umax <= 0x5D000000u && med >= 0x1p-34f && s >= 0x1p-60f &&
                                      s <= 0x1p60f;
-            const bool fast = exact_recip && here->node_agg == 0;
+            const bool fast = exact_recip && agg == 0;
             // Decision-only route for supporting one-sided metrics: find the exact boundary
             // xstar of "this rank exceeds" by probing 64 consecutive floats around
             // med +- thr*s with the defining operations (IEEE subtract and divide).
@@ -1648,18 +1792,196 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
             // 0/1 decision-only (higher / lower is worse), 2/3 exact by reciprocal
             // (one- / two-sided), 4/5 IEEE division (scaled sum / max)
             const uint32_t route = fast ? (decide ? (dir > 0 ? 0u : 1u) : (dir != 0 ? 2u : 3u))
-                                        : (here->node_agg == 0 ? 4u : 5u);
+                                        : (agg == 0 ? 4u : 5u);
             if (lane == 0) {
                 ScoreParams& p = sh.par;
                 p.s = s; p.ss = ss; p.rs = rs; p.cc = cc;
                 p.kk = kk; p.margin = margin; p.sthr = sthr; p.xcut = xcut;
                 p.route = route; p.exact_recip = exact_recip ? 1u : 0u;
+                p.med = med; p.mad = mad; p.settled = 1;
             }
+        };
+        // The hinted selection (sign-free column, a predecessor's bracket and MAD): one pass counts, one
+        // gathers what may be the median or the MAD, and the first wave alone takes these from the few
+        // dozen candidates and works out the column's scoring parameters.  Whatever that does not
+        // settle goes through the general route below.
+        bool tried_fast = false, settled = false;
+        uint32_t located = PLAN_NONE;
+        if (hinted && rfl(sh.hfast[m]) != 0 && hint_hi < 0x7D000000u - 2u * (hint_hi - hint_lo) &&
+            hint_hi - hint_lo < 0x20000000u) {
+            tried_fast = true;
+            const GatherResult gr = hinted_gather<NT, ROWS, LOG_NB>(
+                sh, v, [&](int j) { set_padding(j, tl); }, [&]() { load_ahead(next_col); }, hint_lo, hint_hi, sh.hmad[m], k0_all, k1_all, umax_slot);
+            umax = gr.umax;
+            located = gr.status;
+            if (located != PLAN_NONE) missing = gr.present;
+            if (located == PLAN_GATHER) {
+                if (w == 0) {
+                    float mad = 0.0f;
+                    const uint32_t k0 = missing ? (missing - 1) / 2 : k0_all, k1 = missing ? missing / 2 : k1_all;
+                    if (finish_gather(sh, lane, k0, k1, &med, &mad)) {
+                        if (tid == 0) {             // follow median and MAD step by step
+                            sh.hmed[m] = med;
+                            sh.hmad[m] = mad;
+                            if (boot) { sh.hwl[m] = 1.25f * mad; sh.hwh[m] = 1.25f * mad; }
+                        }
+                        work_out(med, mad, missing != 0 && missing_stay(med));
+                    } else if (lane == 0) {
+                        sh.par.settled = 0;
+                    }
+                }
+                __syncthreads();
+                settled = rfl(sh.par.settled) != 0;
+                med = uniform(sh.par.med);
+                special = missing != 0 && missing_stay(med);
+            }
+        }
+        if (__builtin_expect(!settled, 0)) {
+        uint32_t s0 = 0, s1 = 0;
+        bool have_mad = false;
+        int hsel = 0;
+        uint32_t listed = 0;                    // distances still to be sorted by the first wave
+        if (tried_fast && located == PLAN_NONE) {
+            hinted = false;                     // (and this metric goes the general way from now on,
+                                                // unless the hint was only a sample's)
+            if (tid == 0 && !boot) sh.hfast[m] = 0;
+        } else if (tried_fast) {
+            const uint32_t k0 = missing ? (missing - 1) / 2 : k0_all, k1 = missing ? missing / 2 : k1_all;
+            const HintedResult hr = hinted_rest<NT, ROWS, LOG_NB>(sh, v, sh.hmad[m], k0, k1);
+            hsel = hr.found;
+            med = 0.5f * (__uint_as_float(hr.m0) + __uint_as_float(hr.m1));
+            have_mad = hsel == 2;
+            s0 = hr.q0; s1 = hr.q1;
+            if (have_mad) listed = hr.listed;
+            if (tid == 0) sh.hmed[m] = med;
+        }
+        // Largest raw bit pattern of the column: >= 0x80000000 iff some value carries
+        // a sign bit (negative or -0); otherwise it is the bit pattern of the maximum.
+        // With a hint the column is taken to be sign-free like its predecessor and the
+        // maximum is found by the median's counting pass itself, which starts on the
+        // register rows as they arrive; otherwise it takes a pass of its own.
+        const bool fused_umax = FULL && hinted && !tried_fast;
+        if (__builtin_expect(!fused_umax && !tried_fast, 0)) {
+            uint32_t um = 0;
+#pragma unroll
+            for (int j = 0; j < ROWS; ++j) {
+                um = max(um, max(__float_as_uint(v[j][0]), __float_as_uint(v[j][1])));
+                um = max(um, max(__float_as_uint(v[j][2]), __float_as_uint(v[j][3])));
+                set_padding(j, tl);
+            }
+            um = wave_max_to_last(um);
+            if (lane == WAVE - 1) atomicMax(umax_slot, um);
+            __syncthreads();
+            umax = rfl(*umax_slot);
+        }
+        // special: some value carries a sign bit or is a NaN.  The raw bits are then no
+        // keys to select by, and a NaN is a missing sample that the ranks must not count.
+        special = umax > 0x7F800000u;
+        uint32_t k0 = k0_all, k1 = k1_all;
+
+        if (hsel == 0 && !special) {
+            uint32_t hlo = 0, hhi = 0;
+            int hshift = 0;
+            const bool one_round = block_select<NT, ROWS, LOG_NB, true>(
+                sh, XKeys<ROWS, true>{v}, __float_as_uint(v[0][0]), true, nsample, k0_all, k1_all, &s0,
+                &s1, &hlo, &hhi, &hshift, hinted, hint_lo, hint_hi, fused_umax ? umax_slot : nullptr, &umax);
+            special = umax > 0x7F800000u;      // (only the fused pass can find this out here)
+        if (!special) {
+            med = 0.5f * (__uint_as_float(s0) + __uint_as_float(s1));
+            if (one_round)
+                have_mad = mad_from_histogram<NT, ROWS, LOG_NB>(sh, v, med, hlo, hhi, hshift, k0_all, k1_all,
+                                                                hinted ? sh.hmad[m] : 0.0f, &s0, &s1);
+            if (tid == 0) {
+                if (have_mad) {                 // keep the reach, follow the median
+                    if (!hinted) {
+                        // the reach kept for the coming steps: median -+ 1.25 MAD (the edge
+                        // pairing looks up to 1.125 MAD away) rather than the sample's wider
+                        // bracket -- fewer keys to count, finer buckets, fewer candidates
+                        const float madv = 0.5f * (__uint_as_float(s0) + __uint_as_float(s1));
+                        sh.hwl[m] = fminf(med - __uint_as_float(hlo), 1.25f * madv);
+                        sh.hwh[m] = fminf(__uint_as_float(hhi) - med, 1.25f * madv);
+                    }
+                    sh.hmed[m] = med;
+                    sh.hmad[m] = 0.5f * (__uint_as_float(s0) + __uint_as_float(s1));
+                    sh.hok[m] = 1;
+                } else {
+                    sh.hok[m] = 0;
+                }
+            }
+        }
+        }
+        uint32_t present = R;
+        if (__builtin_expect(missing != 0, 0)) { present = missing; k0 = (present - 1) / 2; k1 = present / 2; }
+        if (__builtin_expect(special, 0)) {
+            if (tid == 0) sh.hok[m] = 0;
+            __syncthreads();    // (a counting pass given up above has just reset its counters)
+            // median and MAD are taken over the samples present alone (padding lanes hold NaNs
+            // too): the middle one(s) of `present`
+            uint32_t top;
+            count_present(sh, v, &present, &top);
+            __syncthreads();
+            if (umax < 0x80000000u) { umax = top; missing = present; }      // (no signs)
+            k0 = present ? (present - 1) / 2 : 0u;
+            k1 = present / 2;
+            if (present) {
+                const bool sv = v[0][0] == v[0][0];
+                block_select<NT, ROWS, LOG_NB, false>(sh, XKeys<ROWS, false>{v}, key_of(v[0][0] + 0.0f),
+                                                      sv, nsample, k0, k1, &s0, &s1);
+                // (an odd count has one middle value: no sum that could overflow)
+                med = k0 == k1 ? float_of_key(s0) : 0.5f * (float_of_key(s0) + float_of_key(s1));
+            }
+        }
+        if (__builtin_expect(!have_mad && present, 0))
+            block_select<NT, ROWS, LOG_NB, false>(sh, DKeys<ROWS>{v, med},
+                                                  __float_as_uint(fabsf(v[0][0] - med)),
+                                                  v[0][0] == v[0][0], nsample, k0, k1, &s0, &s1);
+        if (!present) med = __uint_as_float(opaque_s(0x7FC00000u));  // nothing to take a median of
+        if (__builtin_expect(missing != 0, 0)) special = missing_stay(med);
+        if (w == 0) {
+            if (listed != 0) {
+                const uint32_t key = sh.cand[lane];
+                const uint32_t sorted = gd_sort64<true>((uint32_t)lane < listed ? key : 0xFFFFFFFFu);
+                s0 = (uint32_t)__builtin_amdgcn_readlane((int)sorted, (int)(s0 & (WAVE - 1)));
+                s1 = (uint32_t)__builtin_amdgcn_readlane((int)sorted, (int)(s1 & (WAVE - 1)));
+            }
+            float mad = k0 == k1 ? __uint_as_float(s0) : 0.5f * (__uint_as_float(s0) + __uint_as_float(s1));
+            if (!present) mad = __uint_as_float(opaque_s(0x7FC00000u));      // nothing to take a median of
+            if (tid == 0) {
+                if (hsel) sh.hmad[m] = mad;         // the hinted selection follows median and MAD step by step
+                // a column with missing samples, but no signs, leads the next step's selection too
+                if (hsel == 0 && missing != 0 && med > 0.0f && mad > 0.0f && med < 3.0e38f && mad < 3.0e38f) {
+                    sh.hmed[m] = med; sh.hmad[m] = mad;
+                    sh.hwl[m] = 1.25f * mad; sh.hwh[m] = 1.25f * mad;
+                    sh.hok[m] = 1;
+                }
+                // (from here on the reach is the exact MAD's, as after the general route)
+                if (boot && hsel == 2) { sh.hwl[m] = 1.25f * mad; sh.hwh[m] = 1.25f * mad; }
+            }
+            work_out(med, mad, special);
         }
         __syncthreads();
         if (tid == 0) {          // (a zero made here: kept in registers for the whole kernel it ends up spilled)
             const uint32_t zero = opaque_v(0u);
             sh.nkept = zero; sh.nnear = zero;
+        }
+        for (uint32_t i = opaque_v((uint32_t)tid); i < CAND_REST; i += NT) sh.cand[i] = CAND_NONE;
+        load_ahead(next_col);       // (again, where the hinted selection asked for these rows: they are not kept on this way)
+        }
+        if (__builtin_expect(missing != 0, 0)) {
+          if (!special) {
+            const uint32_t absm = opaque_s(0x7FFFFFFFu);
+#pragma unroll
+            for (int j = 0; j < ROWS; ++j) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[j][i] = (__float_as_uint(v[j][i]) & absm) <= 0x7F800000u ? v[j][i] : med;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+          }
+        }
+        if (tid == 0) {
+            const gd_args_ptr here = args_here();
+            here->med[t * M + m] = sh.par.med;
+            here->mad[t * M + m] = sh.par.mad;
         }
         // z, exceedance and node scores
         const uint32_t tz = fresh_tid4();

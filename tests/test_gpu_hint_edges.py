@@ -93,3 +93,39 @@ def test_buckets_too_crowded_for_the_lists(R, T, threads, signs):
         x -= np.float32(1.0)
     p = oracle_params(R=R, M=1, W=8, k=4, directions=(1,), min_signals=1)
     run_and_compare(p, torch.from_numpy(x), topk_k=8, label=f"crowded buckets R{R}", want_z=False)
+
+
+# (values on a grid of 1/q of the MAD: about 0.27 R / q of them alike in the middle, so that the gathered
+# candidates and those ranked at last go from a few to beyond what one wave takes)
+GRIDS = [None, 4000, 1000, 400, 250, 120, 60, 30]
+
+
+@pytest.mark.parametrize("missing", [0, 1, 64])
+@pytest.mark.parametrize("R", [4104, 8192, 16384, 24000, 40960, 57344, 65536])
+def test_gathered_candidates_up_to_their_limits(R, missing):
+    """Few and many alike values in the buckets of the median and of the MAD, odd and even numbers of
+    samples: 16, 32 and 64 candidates and more, one step hinted and runs of steps."""
+    print(f"case candidates R={R} missing={missing}", flush=True)
+    rng = np.random.default_rng(R + missing)
+    M, T = len(GRIDS), 3
+    z = rng.standard_normal((T, M, R))
+    for m, q in enumerate(GRIDS):
+        if q:
+            z[:, m] = np.round(z[:, m] * q) / q
+    x = (1.0 + 0.02 * z).astype(np.float32)
+    for t in range(T):
+        for m in range(M):
+            x[t, m, rng.permutation(R)[:missing * t]] = np.nan
+    x = torch.from_numpy(x)
+    p = oracle_params(R=R, M=M, W=4, k=2, directions=(1, -1, 1, 0, -1, 1, 0, 1), min_signals=2)
+    o = oracle.score(p, x.numpy(), want_z=False)
+    det = detector_for(p)
+    out = det.alloc_outputs(1)
+    for t in range(1, T):                                    # one step per call, hinted by the one before
+        det.set_streaming_hints(torch.from_numpy(o.med[t - 1].copy()).cuda(), torch.from_numpy(o.mad[t - 1].copy()).cuda())
+        det.score_batch(x[t:t + 1].cuda(), out)
+        torch.cuda.synchronize()
+        compare_scores(oracle.score(p, x[t:t + 1].numpy(), want_z=False), out, f"R={R} step {t}")
+    det.set_streaming_hints(None, None)
+    det.close()
+    run_and_compare(p, x.repeat(400, 1, 1)[:max(6, 2200 * 4096 // R)], topk_k=8, label=f"candidates R{R}", want_z=False)
