@@ -67,8 +67,9 @@ constexpr uint32_t PLANE_RANKS = 2048;
 // What the score loop needs to know of a column (worked out by one wave).
 struct alignas(16) ScoreParams {
     float s, ss, rs;           // scale, its signed form and the reciprocal of that
-    float cc, kk, margin, sthr;    // node estimate of the decision-only route
-    uint32_t xcut, route, exact_recip;
+    float cc, kk, margin;          // node estimate of the decision-only route
+    uint32_t scut, xcut;           // and its bounds, for `decided`
+    uint32_t route, exact_recip;
     float med, mad;
     uint32_t settled;              // the gathered candidates gave median and MAD
 };
@@ -201,10 +202,8 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t tid, ui
 // bytes, and the columns of one wave, are no faster with them; the ledger's reads are slower, 118 and
 // 122 us: it finds part of the masks in the last cache.)
 typedef float gd_f4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void load_once(const float* p, float (&row)[4]) {
-    const gd_f4 q = __builtin_nontemporal_load(reinterpret_cast<const gd_f4*>(p));
-    row[0] = q.x; row[1] = q.y; row[2] = q.z; row[3] = q.w;
-}
+typedef uint32_t gd_u4 __attribute__((ext_vector_type(4)));
+constexpr int NONTEMPORAL = 2;            // (of a buffer load's cache policy)
 __device__ __forceinline__ void store_once(float* p, float x, float y, float z, float w) {
     const gd_f4 q = {x, y, z, w};
     __builtin_nontemporal_store(q, reinterpret_cast<gd_f4*>(p));
@@ -1065,7 +1064,9 @@ __device__ __forceinline__ GatherResult hinted_gather(SH& sh, const float (&v)[R
     {
         const uint32_t tid = opaque_v(threadIdx.x), lane = tid & (WAVE - 1);
         const int ql = (int)(lo >> shift);                       // (below 2^30: shift < 2 gives the result up anyway)
-        const int cl = ql - 1 - (int)lane, ch = ql + NB + (int)lane;
+        // (as floats; below 0, of a bracket that begins at a bucket under 64, `cl` is a NaN, and the
+        // median of three is then the least of the others: at least 0, counter 64 - ql)
+        const float cl = __uint_as_float((uint32_t)(ql - 1 - (int)lane)), ch = __uint_as_float((uint32_t)(ql + NB + (int)lane));
         const uint32_t kb = opaque_s((uint32_t)(64 - ql) * 4u);  // counter 64 is bucket 0 (bytes, mod 2^32)
         const uint32_t sh_s = opaque_s((uint32_t)shift);
         uint32_t um = 0;
@@ -1079,11 +1080,12 @@ __device__ __forceinline__ GatherResult hinted_gather(SH& sh, const float (&v)[R
             set_padding(j);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int q = (int)(__float_as_uint(row[i]) >> sh_s);
-                int c;          // q clamped to [cl, ch] (cl < ch): the median of the three
-                asm("v_med3_i32 %0, %1, %2, %3" : "=v"(c) : "v"(q), "v"(cl), "v"(ch));
+                const uint32_t q = __float_as_uint(row[i]) >> sh_s;
+                // q clamped to [cl, ch] (cl < ch): the median of the three, as floats, whose order theirs
+                // is too (positive ones, subnormals among them, and no NaNs: the keys are shifted)
+                const uint32_t c = __float_as_uint(__builtin_amdgcn_fmed3f(__uint_as_float(q), cl, ch));
                 // counter c - ql + 64, in [63 - lane, 64 + NB + lane]
-                atomicAdd(reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(cnt) + (((uint32_t)c << 2) + kb)), 1u);
+                atomicAdd(reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(cnt) + ((c << 2) + kb)), 1u);
             }
             asm volatile("" : "+v"(um));
             __builtin_amdgcn_sched_barrier(0);
@@ -1480,7 +1482,7 @@ __device__ __forceinline__ void score_row_fast(const float (&x)[4], float med, f
 // only the decisions are needed, not the scores, so no division is done.
 //   * A rank exceeds iff x >= xstar (higher is worse) or x <= xstar (lower is
 //     worse): sub and divide are monotone, and xstar is the exact boundary found
-//     by the caller with the very operations the definition uses.
+//     with the very operations the definition uses.
 //   * The node score scale*sum(z') is estimated as cc*sum(x) - kk with
 //     cc ~ +-scale/s and kk ~ 8*med*cc.  All roundings of the exact chain and of
 //     the estimate together stay below `margin` (see the caller), so the estimate
@@ -1490,21 +1492,13 @@ __device__ __forceinline__ void score_row_fast(const float (&x)[4], float med, f
 //     node cannot exceed nor come near.  *cand is set for the lanes on the near side;
 //     the caller then forms the estimate and, within `margin` of the threshold, the
 //     exact score.
-template <bool LOWER_IS_WORSE>
-__device__ __forceinline__ void score_row_decide(const float (&x)[4], uint32_t xcut, uint32_t shift_m,
-                                                 uint32_t mask_m, float sthr, uint32_t* e, bool* cand) {
-    // Values and boundary are positive floats, which order like their bit patterns: with
-    // xcut = bits(xstar) - 1 (higher is worse) or bits(xstar) + 1 (lower is worse) the sign of
-    // one integer difference per value is the decision.  The four sign bytes are brought
-    // together by byte permutes and land, shifted, on bit m of the four mask bytes.
-    uint32_t d[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        d[i] = LOWER_IS_WORSE ? __float_as_uint(x[i]) - xcut : xcut - __float_as_uint(x[i]);
-    *e = (sign_bytes(d[0], d[1], d[2], d[3]) >> shift_m) & mask_m;      // (already in place for metric m)
-    const float half = (x[0] + x[1]) + (x[2] + x[3]);
-    const float sum = half + lane_xor1(half);
-    *cand = LOWER_IS_WORSE ? sum <= sthr : sum >= sthr;
+//
+// Values, sums and their bounds are not negative, and such floats order like their bit patterns.
+// Of the bound b, `flip` is all ones and `cut` is b where higher is worse, `flip` is 0 and `cut` is
+// ~b where lower is: the sign of (x ^ flip) + cut, b - 1 - x or x - b - 1, is the decision, in one
+// instruction and the same code for both directions.
+__device__ __forceinline__ uint32_t decided(float x, uint32_t flip, uint32_t cut) {
+    return (__float_as_uint(x) ^ flip) + cut;
 }
 
 // FULL: R == NT*4*ROWS exactly, so no lane is padding and no bounds are checked.  A ragged
@@ -1631,17 +1625,15 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     // ranks once more (a load under a condition would be waited for on the spot) and become
     // NaNs, whose key lies above every real key, when the column is first looked at.
     auto load_row_to = [&](float (&row)[4], int j, const float* col, uint32_t tid4) {
-        // (a uniform row pointer plus the lane's 32-bit offset: one address mode, no vector
-        // arithmetic per row)
-        // (offsets in bytes, 32 bits wide: widened before the shift they are 64-bit sums)
-        const char* p = j < TAIL ? reinterpret_cast<const char*>(col + block_of(j) * BLK) + tid4 * 4u
-                                 : reinterpret_cast<const char*>(col) + min((uint32_t)j * BLK + tid4, R - 4) * 4u;
+        // (a buffer's base, a scalar and the lane's 32-bit offset: one address mode, no vector arithmetic
+        // per row; of a column, whose bytes bound it)
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(col), 0, (int)(R * 4u), 0x00020000);
+        const int from = j < TAIL ? (int)(block_of(j) * BLK * 4u) : 0;
+        const int lane_at = (int)(j < TAIL ? tid4 * 4u : min((uint32_t)j * BLK + tid4, R - 4) * 4u);
         // (a single step, just arrived, may still lie in the caches)
-        if (!SPLIT) load_once(reinterpret_cast<const float*>(p), row);
-        else {
-            const float4 q = *reinterpret_cast<const float4*>(p);
-            row[0] = q.x; row[1] = q.y; row[2] = q.z; row[3] = q.w;
-        }
+        const gd_u4 q = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_at, from, SPLIT ? 0 : NONTEMPORAL);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) row[i] = __uint_as_float(q[i]);
     };
     auto load_row = [&](int j, const float* col, uint32_t tid4) { load_row_to(v[j], j, col, tid4); };
     auto load_ahead = [&](const float* col) {
@@ -1788,7 +1780,8 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
                 const float sb = dir > 0 ? s0 - slack : s0 + slack;
                 if (__builtin_fmaf(sb, cc, -kk) < tl) sthr = sb;
             }
-            const uint32_t xcut = dir > 0 ? __float_as_uint(xstar) - 1u : __float_as_uint(xstar) + 1u;
+            const uint32_t shi = sthr >= 0.0f ? __float_as_uint(sthr + 0.0f) : (dir > 0 ? 0u : 0xFFFFFFFFu);
+            const uint32_t xcut = dir > 0 ? __float_as_uint(xstar) : ~__float_as_uint(xstar), scut = dir > 0 ? shi : ~shi;
             // 0/1 decision-only (higher / lower is worse), 2/3 exact by reciprocal
             // (one- / two-sided), 4/5 IEEE division (scaled sum / max)
             const uint32_t route = fast ? (decide ? (dir > 0 ? 0u : 1u) : (dir != 0 ? 2u : 3u))
@@ -1796,7 +1789,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
             if (lane == 0) {
                 ScoreParams& p = sh.par;
                 p.s = s; p.ss = ss; p.rs = rs; p.cc = cc;
-                p.kk = kk; p.margin = margin; p.sthr = sthr; p.xcut = xcut;
+                p.kk = kk; p.margin = margin; p.scut = scut; p.xcut = xcut;
                 p.route = route; p.exact_recip = exact_recip ? 1u : 0u;
                 p.med = med; p.mad = mad; p.settled = 1;
             }
@@ -2035,46 +2028,13 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         float* nzrow = here->node_z + t * N;
         const ScoreParams& par = sh.par;
         const float s = uniform(par.s), ss = uniform(par.ss), rs = uniform(par.rs);
-        const float cc = uniform(par.cc), kk = uniform(par.kk), margin = uniform(par.margin), sthr = uniform(par.sthr);
-        const uint32_t xcut = rfl(par.xcut), route = rfl(par.route);
+        const float cc = uniform(par.cc), kk = uniform(par.kk), margin = uniform(par.margin);
+        const uint32_t route = rfl(par.route);
         const uint32_t shift_m = 7u - m, mask_m = 0x01010101u << m;
-        const uint32_t absmask = dir == 0 ? 0x7FFFFFFFu : 0xFFFFFFFFu;
-        const uint32_t sgnmask = dir < 0 ? 0x80000000u : 0u;
         __builtin_amdgcn_s_setprio(0);
         uint32_t* const emask_lane = emask + opaque_v((uint32_t)tid);      // (row j: a constant offset from here)
-#pragma unroll
-        for (int j = 0; j < ROWS; ++j) {
-            const uint32_t rt = opaque_s(route);
-            uint32_t e, eplaced;
-            float nz;
-            if (rt <= 1u) {
-                bool cand;
-                if (rt == 0u) score_row_decide<false>(v[j], xcut, shift_m, mask_m, sthr, &e, &cand);
-                else score_row_decide<true>(v[j], xcut, shift_m, mask_m, sthr, &e, &cand);
-                eplaced = e;                                // (its bits are on metric m already)
-                nz = thr;                                   // (not above the threshold: no node bit)
-                if (__builtin_expect(gd_ballot(cand) != 0, 0)) {       // some node may exceed: the estimate decides,
-                    const float half = (v[j][0] + v[j][1]) + (v[j][2] + v[j][3]);     // or, too close, the exact chain
-                    nz = __builtin_fmaf(half + lane_xor1(half), cc, -kk);
-                    if (__builtin_expect(gd_ballot(fabsf(nz - thr) <= margin) != 0, 0)) {
-                        uint32_t e2;
-                        score_row_fast<false>(v[j], med, ss, rs, thr, node_scale, &e2, &nz);
-                    }
-                    NE[j / 4] |= (nz > thr ? 1u : 0u) << (8 * (j & 3) + m);
-                }
-            } else {
-                if (rt == 2u) {
-                    score_row_fast<false>(v[j], med, ss, rs, thr, node_scale, &e, &nz);
-                } else if (rt == 3u) {
-                    score_row_fast<true>(v[j], med, ss, rs, thr, node_scale, &e, &nz);
-                } else {
-                    score_row(rt - 4u, v[j], med, s, absmask, sgnmask, thr, node_scale, &e, &nz);
-                }
-                NE[j / 4] |= (nz > thr ? 1u : 0u) << (8 * (j & 3) + m);
-                eplaced = e << m;
-            }
+        auto done_with = [&](int j, uint32_t eplaced) {
             __hip_atomic_fetch_or(&emask_lane[j * NT], eplaced, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (prim && holds(j, tz) && !(tz & 4)) nzrow[rbase(j, tz) / 8] = nz;
             // the row is done: refill it with the next column
             if (j < AHEAD) {
 #pragma unroll
@@ -2083,6 +2043,46 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
             // pin the row's results here, or its scores stay live until the loop ends
             asm volatile("" : "+v"(NE[j / 4]));
             __builtin_amdgcn_sched_barrier(0);
+        };
+        const uint32_t flip = route == 0u ? 0xFFFFFFFFu : 0u;
+        const uint32_t xcut = opaque_v(par.xcut), scut = opaque_v(par.scut);      // (vector registers: an instruction takes one scalar)
+        const uint32_t absmask = dir == 0 ? 0x7FFFFFFFu : 0xFFFFFFFFu;
+        const uint32_t sgnmask = dir < 0 ? 0x80000000u : 0u;
+#pragma unroll
+        for (int j = 0; j < ROWS; ++j) {
+            const uint32_t rt = opaque_s(route);
+            uint32_t eplaced;
+            if (rt <= 1u) {
+                const float half = (v[j][0] + v[j][1]) + (v[j][2] + v[j][3]);
+                const float sum = half + lane_xor1(half);
+                if (__builtin_expect(gd_ballot((int32_t)decided(sum, flip, scut) < 0) != 0, 0)) {
+                    // some node may exceed: the estimate decides, or, too close, the exact chain
+                    float nz = __builtin_fmaf(sum, cc, -kk);
+                    if (__builtin_expect(gd_ballot(fabsf(nz - thr) <= margin) != 0, 0)) {
+                        uint32_t e2;
+                        score_row_fast<false>(v[j], med, ss, rs, thr, node_scale, &e2, &nz);
+                    }
+                    NE[j / 4] |= (nz > thr ? 1u : 0u) << (8 * (j & 3) + m);
+                }
+                // the four sign bytes, brought together by byte permutes, land on bit m of the four mask bytes
+                const uint32_t e = sign_bytes(decided(v[j][0], flip, xcut), decided(v[j][1], flip, xcut),
+                                              decided(v[j][2], flip, xcut), decided(v[j][3], flip, xcut));
+                eplaced = (e >> shift_m) & mask_m;
+            } else {
+                uint32_t e;
+                float nz;
+                if (rt == 2u) {
+                    score_row_fast<false>(v[j], med, ss, rs, thr, node_scale, &e, &nz);
+                } else if (rt == 3u) {
+                    score_row_fast<true>(v[j], med, ss, rs, thr, node_scale, &e, &nz);
+                } else {
+                    score_row(rt - 4u, v[j], med, s, absmask, sgnmask, thr, node_scale, &e, &nz);
+                }
+                NE[j / 4] |= (nz > thr ? 1u : 0u) << (8 * (j & 3) + m);
+                if (prim && holds(j, tz) && !(tz & 4)) nzrow[rbase(j, tz) / 8] = nz;
+                eplaced = e << m;
+            }
+            done_with(j, eplaced);
         }
 #pragma unroll
         for (int j = EARLY; j < ROWS; ++j) load_row(j, next_col, tz);
