@@ -98,6 +98,12 @@ constexpr uint32_t PLAN_NONE = 0, PLAN_LOCATED = 1, PLAN_GATHER = 2;
 // of them; these words are CAND_NONE (above every key, and a NaN) between columns.
 constexpr uint32_t MOST_MID = 64, MOST_DIST = 256, CAND_REST = MOST_MID + MOST_DIST + WAVE, CAND_NONE = 0x7FFFFFFFu;
 static_assert(CAND_REST <= (uint32_t)CAND_CAP, "the gathered candidates fit their list");
+// Buckets from the one that holds the lower middle rank to the upper one's: the two are neighbours, so
+// that nothing lies in those between.  (One in twenty columns of 5 000 ranks, where a bucket holds
+// a value or two, has them further apart than one, and a batch is done when its slowest column
+// is: 5 000 x 1 000 x 2 41 us a launch where these went the general way, 29.5 so, 8 000 x 1 000 x 4
+// 81 and 52, 16 384 x 10 000 x 4 661 and 608.)
+constexpr uint32_t MOST_APART = 63;
 
 template <int NT, int LOG_NB, int MAX_NODES>
 struct Shared {
@@ -881,10 +887,10 @@ __device__ __forceinline__ void plan_gather(SH& sh, uint32_t lane, uint32_t lo, 
         plan.reach = fmaxf(center - ml, mh - center);
         plan.mid = ba | (bb - ba) << 16;
         // crowded (ties): the general route narrows
-        plan.status = pb - pa > (uint32_t)CAND_CAP / 2 || bb - ba > 1u ? PLAN_NONE : PLAN_LOCATED;
+        plan.status = pb - pa > (uint32_t)CAND_CAP / 2 || bb - ba > MOST_APART ? PLAN_NONE : PLAN_LOCATED;
         plan.lo = lo; plan.shift = (uint32_t)shift; plan.skip = below + pa; plan.n_mid = pb - pa;
     }
-    if (pb - pa > MOST_MID || bb - ba > 1u || !(mad_hint > 0.0f)) return;
+    if (pb - pa > MOST_MID || bb - ba > MOST_APART || !(mad_hint > 0.0f)) return;
     // the first lane's edge (mod 2^32; a hint beyond the bracket points at its end)
     uint32_t e0 = rfl(min((__float_as_uint(center + mad_hint) - lo) >> shift, bmax)) - 32u;
     uint32_t step = 1;
@@ -1008,12 +1014,22 @@ __device__ __forceinline__ bool finish_gather(SH& sh, uint32_t lane, uint32_t k0
         if (many) { count(d[2]); count(d[3]); }
     };
     classify();
-    if (upto - nearer > 32u) {
+    for (int round = 0; upto - nearer > 32u && round < 4; ++round) {
         // the candidates taken as evenly spread: the wanted rank's place, and 13 ranks to either side (the
-        // one wanted among 64 is off by four, one standard deviation, at the most)
+        // one wanted among 64 is off by four, one standard deviation, at the most).  Beside that, the
+        // search goes on with what lies on the rank's side.
         const float per = (to - from) * __builtin_amdgcn_rcpf((float)(upto - nearer)), at = from + (float)(int)(k0 - n_in - nearer) * per;
+        const float first_from = from, first_to = to;
+        const uint32_t first_nearer = nearer, first_upto = upto;
         from = uniform(fmaxf(from, at - 13.0f * per)); to = uniform(fminf(to, at + 13.0f * per));
         classify();
+        if (__builtin_expect(n_in + nearer > k0, 0)) {
+            to = __uint_as_float(__float_as_uint(from) - 1u); upto = nearer;
+            from = first_from; nearer = first_nearer;
+        } else if (__builtin_expect(k1 >= n_in + upto, 0)) {
+            from = __uint_as_float(__float_as_uint(to) + 1u); nearer = upto;
+            to = first_to; upto = first_upto;
+        }
     }
     const uint32_t c_in = n_in + nearer, kept = upto - nearer, base = __float_as_uint(from);
     // (also where `from` is beyond `to`; keys of 25 bits and the place)

@@ -129,3 +129,28 @@ def test_gathered_candidates_up_to_their_limits(R, missing):
     det.set_streaming_hints(None, None)
     det.close()
     run_and_compare(p, x.repeat(400, 1, 1)[:max(6, 2200 * 4096 // R)], topk_k=8, label=f"candidates R{R}", want_z=False)
+
+
+# (the gap between the two middle values, in thousandths of the MAD, of which a bucket is one to two:
+# neighbours in one bucket, in two, a few and up to 63 apart, and beyond)
+GAPS = [0, 1, 2, 3, 8, 30, 60, 75, 100, 140, 160, 400]
+
+
+@pytest.mark.parametrize("R,T", [(4104, 2600), (5000, 2600), (8192, 2600), (16384, 2060), (24000, 1030), (65536, 520),
+                                 (16384, 24), (65536, 24)])
+def test_middle_ranks_in_buckets_apart(R, T):
+    """The two middle ranks far apart, in runs of steps and (T = 24) one or a few steps a workgroup; in
+    every second step the distances about the MAD are unevenly spread besides, so that the place
+    that an even spread gives to the wanted one is off by up to all of them."""
+    print(f"case middle ranks apart R={R} T={T}", flush=True)
+    rng = np.random.default_rng(R + T)
+    d = np.abs(rng.standard_normal((T, 1, R)))                  # distances from the middle, in standard deviations
+    for t in range(1, T, 2):
+        n = 2 * int(rng.integers(10, 120))
+        at = rng.permutation(R)[:n]
+        d[t, 0, at] = 0.6745 * (1.0 + 2e-3 * rng.random(n) ** float(rng.integers(2, 12)) * rng.choice([-1.0, 1.0]))
+    gap = 0.6745e-3 * np.array([GAPS[t % len(GAPS)] for t in range(T)])[:, None, None]
+    side = np.where(rng.permuted(np.tile(np.arange(R) % 2, (T, 1, 1)), axis=2), 1.0, -1.0)
+    x = torch.from_numpy((1.0 + 0.02 * side * (d + 0.5 * gap)).astype(np.float32))
+    p = oracle_params(R=R, M=1, W=8, k=4, directions=(1,), min_signals=1)
+    run_and_compare(p, x, topk_k=8, label=f"middle ranks apart R{R}", want_z=False, chunks=[T] if T > 24 else [4] * 6)
