@@ -1424,11 +1424,15 @@ __device__ __forceinline__ void sample_hints(SH& sh, const float (&row)[4], uint
     __syncthreads();
 }
 
-// The top bytes of four words, in order.
-__device__ __forceinline__ uint32_t sign_bytes(uint32_t d0, uint32_t d1, uint32_t d2, uint32_t d3) {
-    const uint32_t lo2 = __builtin_amdgcn_perm(d1, d0, 0x0C0C0703u);         // bytes: d0.b3, d1.b3, 0, 0
-    const uint32_t hi2 = __builtin_amdgcn_perm(d3, d2, 0x07030C0Cu);         // bytes: 0, 0, d2.b3, d3.b3
-    return lo2 | hi2;
+// The signs of four words, byte by byte in order: those bits of `bits` are set whose byte's word is
+// negative.  (A permute's selectors 9 and 11 fill a byte with the sign of a word, so that what
+// remains is one operation of three inputs; with the words' top bytes brought together, shifted
+// and masked it was five instructions a row instead of three: launch, 5 000 ranks x 10 000 x 2 157 us,
+// so 155, 16 384 x 10 000 x 4 609 and 605, 65 536 x 4 096 x 8 1 839 and 1 835.)
+__device__ __forceinline__ uint32_t sign_bytes(uint32_t d0, uint32_t d1, uint32_t d2, uint32_t d3, uint32_t bits) {
+    const uint32_t lo2 = __builtin_amdgcn_perm(d1, d0, 0x0C0C0B09u);
+    const uint32_t hi2 = __builtin_amdgcn_perm(d3, d2, 0x0B090C0Cu);
+    return (lo2 | hi2) & bits;
 }
 
 // Signed score and node score of one register row, dividing with the IEEE
@@ -1469,9 +1473,10 @@ __device__ __forceinline__ void score_row(uint32_t agg, const float (&x)[4], flo
 // (Markstein's division theorem), provided nothing under- or overflows --
 // the caller checks the column's magnitudes for that.  ss is +s or -s (a
 // lower-is-worse metric scores -z), TWO_SIDED scores |z|.
+// The exceed bits are those of `bits` (one in each byte).
 template <bool TWO_SIDED>
-__device__ __forceinline__ void score_row_fast(const float (&x)[4], float med, float ss, float rs,
-                                               float thr, float node_scale, uint32_t* e, float* nz) {
+__device__ __forceinline__ void score_row_fast(const float (&x)[4], float med, float ss, float rs, float thr,
+                                               float node_scale, uint32_t bits, uint32_t* e, float* nz) {
     float zs[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -1487,8 +1492,8 @@ __device__ __forceinline__ void score_row_fast(const float (&x)[4], float med, f
     // score exceeds iff thr less it is negative, denormals being kept.  Compared value by value / so,
     // 1 024 steps x 8: two-sided metrics 40 000 ranks 386 / 382 us, 65 536 541 / 539; one-sided ones,
     // of which only the primary comes here, the same within 0.5 %)
-    *e = (sign_bytes(__float_as_uint(thr - zs[0]), __float_as_uint(thr - zs[1]), __float_as_uint(thr - zs[2]),
-                     __float_as_uint(thr - zs[3])) >> 7) & 0x01010101u;
+    *e = sign_bytes(__float_as_uint(thr - zs[0]), __float_as_uint(thr - zs[1]), __float_as_uint(thr - zs[2]),
+                    __float_as_uint(thr - zs[3]), bits);
     const float half = (zs[0] + zs[1]) + (zs[2] + zs[3]);
     const float other = lane_xor1(half);
     *nz = node_scale * (half + other);
@@ -2046,7 +2051,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         const float s = uniform(par.s), ss = uniform(par.ss), rs = uniform(par.rs);
         const float cc = uniform(par.cc), kk = uniform(par.kk), margin = uniform(par.margin);
         const uint32_t route = rfl(par.route);
-        const uint32_t shift_m = 7u - m, mask_m = 0x01010101u << m;
+        const uint32_t mask_m = 0x01010101u << m;
         __builtin_amdgcn_s_setprio(0);
         uint32_t* const emask_lane = emask + opaque_v((uint32_t)tid);      // (row j: a constant offset from here)
         auto done_with = [&](int j, uint32_t eplaced) {
@@ -2076,27 +2081,25 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
                     float nz = __builtin_fmaf(sum, cc, -kk);
                     if (__builtin_expect(gd_ballot(fabsf(nz - thr) <= margin) != 0, 0)) {
                         uint32_t e2;
-                        score_row_fast<false>(v[j], med, ss, rs, thr, node_scale, &e2, &nz);
+                        score_row_fast<false>(v[j], med, ss, rs, thr, node_scale, mask_m, &e2, &nz);
                     }
                     NE[j / 4] |= (nz > thr ? 1u : 0u) << (8 * (j & 3) + m);
                 }
-                // the four sign bytes, brought together by byte permutes, land on bit m of the four mask bytes
-                const uint32_t e = sign_bytes(decided(v[j][0], flip, xcut), decided(v[j][1], flip, xcut),
-                                              decided(v[j][2], flip, xcut), decided(v[j][3], flip, xcut));
-                eplaced = (e >> shift_m) & mask_m;
+                eplaced = sign_bytes(decided(v[j][0], flip, xcut), decided(v[j][1], flip, xcut),
+                                     decided(v[j][2], flip, xcut), decided(v[j][3], flip, xcut), mask_m);
             } else {
-                uint32_t e;
                 float nz;
                 if (rt == 2u) {
-                    score_row_fast<false>(v[j], med, ss, rs, thr, node_scale, &e, &nz);
+                    score_row_fast<false>(v[j], med, ss, rs, thr, node_scale, mask_m, &eplaced, &nz);
                 } else if (rt == 3u) {
-                    score_row_fast<true>(v[j], med, ss, rs, thr, node_scale, &e, &nz);
+                    score_row_fast<true>(v[j], med, ss, rs, thr, node_scale, mask_m, &eplaced, &nz);
                 } else {
+                    uint32_t e;
                     score_row(rt - 4u, v[j], med, s, absmask, sgnmask, thr, node_scale, &e, &nz);
+                    eplaced = e << m;
                 }
                 NE[j / 4] |= (nz > thr ? 1u : 0u) << (8 * (j & 3) + m);
                 if (prim && holds(j, tz) && !(tz & 4)) nzrow[rbase(j, tz) / 8] = nz;
-                eplaced = e << m;
             }
             done_with(j, eplaced);
         }

@@ -300,8 +300,8 @@ __device__ __forceinline__ void score_small(const gd_score_args& a) {
     for (int j = 0; j < ROWS; ++j) {
         uint32_t e;
         float nz;
-        if (fast && dir != 0) score_row_fast<false>(v[j], med, ss, rs, thr, a.node_scale, &e, &nz);
-        else if (fast) score_row_fast<true>(v[j], med, ss, rs, thr, a.node_scale, &e, &nz);
+        if (fast && dir != 0) score_row_fast<false>(v[j], med, ss, rs, thr, a.node_scale, 0x01010101u, &e, &nz);
+        else if (fast) score_row_fast<true>(v[j], med, ss, rs, thr, a.node_scale, 0x01010101u, &e, &nz);
         else score_row(a.node_agg, v[j], med, s, absmask, sgnmask, thr, a.node_scale, &e, &nz);
         lds.exceed[m * SmallLds<ROWS>::WORDS + j * WAVE + lane] = e;
         const uint64_t nb = gd_ballot(nz > thr);
