@@ -326,9 +326,9 @@ __device__ __forceinline__ bool locate(SH& sh, uint32_t tid, uint32_t ka, uint32
 // then instead of narrowed, and to rank a few hundred candidates takes longer (16 384 ranks x 2 048 x
 // 2, 400 equal values about the median: 189 us; 866 with a second walk, which costs plain columns
 // 1 to 2 % too).
-template <typename SH>
+template <typename SH, uint32_t MOST_ROWS = 64>
 struct RowList {
-    static constexpr uint32_t MOST = 64;           // rows of a wave
+    static constexpr uint32_t MOST = MOST_ROWS;    // rows of a wave
     static_assert(MOST * 4 * SH::WAVES <= SH::NB, "the waves' lists lie in the counters");
     uint32_t* const words;
     uint32_t n = 0;                                // (wave-uniform)
@@ -1168,7 +1168,7 @@ __device__ __forceinline__ GatherResult hinted_gather(SH& sh, const float (&v)[R
     out.umax = out.status == PLAN_NONE ? umax : top;
     if (__builtin_expect(out.status != PLAN_GATHER, 0)) return out;
     // ---- gather the rows that hold a value of the median's buckets or of the MAD's
-    RowList<SH> rows(sh, w);
+    RowList<SH, SH::NB / (4 * SH::WAVES) < 128 ? 64 : 128> rows(sh, w);
     {
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
@@ -1364,15 +1364,81 @@ __device__ __forceinline__ HintedResult hinted_rest(SH& sh, const float (&v)[ROW
     return out;
 }
 
-// Hints for a column that has no predecessor to take them from (the first step of a
-// workgroup's run): median and quartiles of a sample -- the four values of register row 0
-// of every thread, which cover the whole rank range -- read off a histogram over the
-// sample's own range.  Half the interquartile distance stands in for the MAD (equal to it
-// for a symmetric spread).  Like all hints they are only trusted as far as the counting
-// pass of the hinted selection confirms them, so raw bit patterns serve as keys whatever
-// the column holds.  Thread 0 writes the hints of metric m; ends with a barrier, the work
-// area at rest.
-// (missing samples are left out)
+// Hints for columns that have no predecessor to take them from (the first step of a workgroup's
+// run): median and quartiles of a sample.  Like all hints they are only trusted as far as the
+// counting pass of the hinted selection confirms them, whatever the column holds.
+// All columns of the step are sampled at once, ahead of everything else and while the first column
+// is on its way: a wave takes 256 values of one column, sorts them as four lots of 64 by lane
+// exchanges and averages the lots' quartiles; up to four waves share a column.  (A sample of every
+// column in its turn, four values of every thread by way of a histogram, took five barriers and 4 000
+// to 6 000 cycles a column: launch, 5 000 ranks x 1 000 x 2 29.2 us, so 26.4, 20 000 x 512 x 3 48 and 43, 40 000 x
+// 256 x 8 102 and 92.5, x 1 024 336 and 326, 65 536 x 512 x 8 279 and 258, x 4 096 1 836 and 1 815, 32 768 x 512 x 8
+// with z 224 and 216.)
+
+// Four lots of 64 keys, into ascending order each: a lane keeps the smaller or the larger key of a
+// stage by way of the median of the two and of 0 or ~0.
+template <int J, int S>
+__device__ __forceinline__ void exchange_lots(uint32_t (&v)[4]) {
+    const uint32_t bound = gd_lane_in<gd_keeps_smaller<J, S>(), true>() ? 0u : 0xFFFFFFFFu;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t o;
+        if constexpr (J == 16) {
+            const auto r = __builtin_amdgcn_permlane16_swap(v[i], v[i], false, false);
+            o = gd_lane_in<gd_lanes_with<16>(), true>() ? r[0] : r[1];
+        } else if constexpr (J == 32) {
+            const auto r = __builtin_amdgcn_permlane32_swap(v[i], v[i], false, false);
+            o = gd_lane_in<gd_lanes_with<32>(), true>() ? r[0] : r[1];
+        } else {
+            o = gd_lane_xor<J>(v[i], 0);
+        }
+        v[i] = max(min(v[i], o), min(max(v[i], o), bound));
+    }
+}
+template <int S>
+__device__ __forceinline__ void merge_lots(uint32_t (&v)[4]) {
+    if constexpr (S > 32) exchange_lots<32, S>(v);
+    if constexpr (S > 16) exchange_lots<16, S>(v);
+    if constexpr (S > 8) exchange_lots<8, S>(v);
+    if constexpr (S > 4) exchange_lots<4, S>(v);
+    if constexpr (S > 2) exchange_lots<2, S>(v);
+    exchange_lots<1, S>(v);
+}
+
+// Quartiles of a wave's 256 values (missing samples, NaNs, are left out): the middle one is a NaN
+// where the sample says that hints would not hold -- signs, too few values, or few distinct ones (an
+// eighth of a lot alike about its middle, in two lots or more), whose buckets the hinted
+// selection would find crowded and give up after its counting pass.
+__device__ __forceinline__ void sample_quartiles(uint32_t (&k)[4], float* q25, float* q50, float* q75) {
+    uint32_t top = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) top = max(top, k[i]);
+    const bool signs = gd_ballot(top >= 0x80000000u) != 0ull;
+    merge_lots<2>(k); merge_lots<4>(k); merge_lots<8>(k);
+    merge_lots<16>(k); merge_lots<32>(k); merge_lots<64>(k);
+    float s25 = 0.0f, s50 = 0.0f, s75 = 0.0f;
+    uint32_t lots = 0, alike = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t n = (uint32_t)__popcll(gd_ballot(k[i] <= 0x7F800000u));
+        auto at = [&](uint32_t rank) { return (uint32_t)__builtin_amdgcn_readlane((int)k[i], (int)(rank & (WAVE - 1))); };
+        if (n >= 16u) {
+            s25 += __uint_as_float(at(n / 4)); s50 += __uint_as_float(at(n / 2)); s75 += __uint_as_float(at(n - 1u - n / 4));
+            alike += at(n / 2 - n / 16u) == at(n / 2 + n / 16u) ? 1u : 0u;
+            ++lots;
+        }
+    }
+    const float share = lots == 4u ? 0.25f : lots == 3u ? 1.0f / 3.0f : lots == 2u ? 0.5f : 1.0f;
+    const bool none = signs || lots == 0u || alike >= 2u;
+    *q25 = s25 * share;
+    *q50 = none ? __uint_as_float(0x7FC00000u) : s50 * share;
+    *q75 = s75 * share;
+}
+
+// The same for a column whose first register row has come: a sample of four values of every thread (row 0, which covers the whole
+// rank range), its median and quartiles read off a histogram over the sample's own range (one step
+// of 20 000 ranks x 4, no hints: 17.0 us; 18.2 by sorted lots).  Thread 0 writes the hints of metric m;
+// ends with a barrier, the work area at rest.  (missing samples are left out)
 template <int NT, int LOG_NB, typename SH>
 __device__ __forceinline__ void sample_hints(SH& sh, const float (&row)[4], uint32_t m) {
     constexpr int BPT = (1 << LOG_NB) / NT;
@@ -1579,6 +1645,14 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     constexpr int BLK = NT * 4;               // ranks per register row
     constexpr int MAX_NODES = BLK * ROWS / 8;
     constexpr int NWAVES = NT / WAVE;
+    // Where the first step's columns are sampled all at once (see sample_quartiles), and where one by
+    // one: with one column in a workgroup, in the exact fits of 256 threads (4 096 x 256 x 1 11.25 us,
+    // all at once 11.55; 16 384 x 10 000 x 4 609 and 613) and in sixteen rows of them (15 000 x 1 024 x 4
+    // 73.5 and 74.8; 12 000 x 1 000 x 4 61.5 and 56.2).  (A batch's ragged tiling of up to four
+    // rows is through the general route sooner: 4 000 ranks x 256 steps, one metric, 16.7 us that way,
+    // 19.5 with a sample's hints.)
+    constexpr bool SAMPLES = !SPLIT && (NT > 256 || (!FULL && ROWS > 4 && ROWS < 16));
+    constexpr bool SAMPLES_SINGLY = SPLIT || (NT <= 256 && (FULL || ROWS == 16));
     using SH = Shared<NT, LOG_NB, MAX_NODES>;
     // Dynamic LDS: the selection's work area, then one word of exceed-mask bytes
     // per (row, thread) -- kept in LDS, not registers, across the M columns.
@@ -1615,41 +1689,27 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     auto holds = [&](int j, uint32_t tid4) -> bool { return j < TAIL || rbase(j, tid4) < R; };
     auto fresh_tid4 = [&]() -> uint32_t { return opaque_v((uint32_t)tid * 4); };
 
-    uint32_t NE[(ROWS + 3) / 4]; // node mask byte per row, packed
-    // the selection's work area starts in its rest state (see the LDS protocol)
-    for (int i = tid; i < SH::NB + 128; i += NT) sh.dlo[i] = 0;      // dlo, hist, dhi
-    for (int i = tid; i < (MAX_NODES / 8 > 0 ? MAX_NODES / 8 : 1); i += NT) sh.ranka[i] = 0;
-    for (int i = tid; i < (int)CAND_REST; i += NT) sh.cand[i] = CAND_NONE;
-    if (tid == 0) {
-        sh.umax[0] = 0; sh.umax[1] = 0; sh.ncand = 0; sh.below = 0; sh.nkept = 0; sh.nnear = 0;
-        sh.smin = 0xFFFFFFFFu; sh.smax = 0; sh.d1 = 0; sh.d2 = 0xFFFFFFFFu;
-        for (int m = 0; m < 8; ++m) { sh.hok[m] = 0; sh.hfast[m] = 1; }
-        // (the reciprocal is only used where node_scale > 0)
-        sh.rules = {a.thr, a.node_scale, a.rel_floor, a.abs_floor, 1.0f / a.node_scale, a.node_agg};
-        // A one-step call may be told the medians and MADs of a recent step (usually the
-        // previous call's outputs).  They take the place of the hints a run of steps builds
-        // up for itself; like those they are only trusted as far as the counting pass
-        // confirms them, so any content is safe.
-        if (SPLIT && a.hint_med && a.hint_mad && a.T == 1) {
-            const float hm = a.hint_med[m_begin], hd = a.hint_mad[m_begin];
-            if (hm > 0.0f && hd > 0.0f && hm < 3.0e38f && hd < 3.0e38f) {      // (false for NaNs)
-                sh.hmed[m_begin] = hm;
-                sh.hwl[m_begin] = 1.25f * hd;
-                sh.hwh[m_begin] = 1.25f * hd;
-                sh.hmad[m_begin] = hd;
-                sh.hok[m_begin] = 1;
-            }
-        }
-    }
-    __syncthreads();
-    constexpr uint32_t nsample = NT;          // (row 0, the column's sample, holds ranks throughout)
-    uint32_t dir_codes = 0;          // direction + 1 of metric i in bits 2i, 2i + 1
+    // The first step's samples (see sample_quartiles): wave w takes part w mod 2^SL of column w >> SL, or,
+    // with fewer waves than columns, columns w, w + NWAVES, ..., and asks for them ahead of the first
+    // column.  The values, sixteen neighbours at a time (64 bytes), are spread over the ranks by
+    // multiples of the golden ratio, a step that no structure of the job shares.
+    constexpr int LOTS = (8 + NWAVES - 1) / NWAVES;
+    const uint32_t columns = m_end - m_begin;
+    const bool crowded = LOTS > 1 && columns > (uint32_t)NWAVES;
+    const uint32_t sl = 4u * columns <= (uint32_t)NWAVES ? 2u : 2u * columns <= (uint32_t)NWAVES ? 1u : 0u;
+    auto column_of = [&](int p) -> uint32_t { return crowded ? (uint32_t)(w + p * NWAVES) : p == 0 ? (uint32_t)w >> sl : columns; };
+    uint32_t lot[LOTS][4];
+    if (SAMPLES) {
+        const uint32_t pos = ((uint32_t)w & ((1u << sl) - 1u)) * WAVE + (uint32_t)lane;
+        const uint32_t from = min(__umulhi((pos / 4u) * 0x9E3779B9u, R / 16u) * 16u + (pos & 3u) * 4u, R - 4u);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) dir_codes |= (uint32_t)(a.dir[i] + 1) << (2 * i);
-    dir_codes = rfl(dir_codes);
-    const uint32_t k0_all = R / 2 - 1, k1_all = R / 2;   // the middle ranks when nothing is missing (R is even)
-    uint32_t colpar = 0;                          // parity of the column count: which umax slot is in use
-
+        for (int p = 0; p < LOTS; ++p) {
+            const float* col = a.x + ((size_t)t_begin * M + min(column_of(p), columns - 1u)) * R;
+            const uint4 q = *reinterpret_cast<const uint4*>(col + from);
+            lot[p][0] = q.x; lot[p][1] = q.y; lot[p][2] = q.z; lot[p][3] = q.w;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
     // Rows of the next column that the score loop asks for as it is done with each; the others
     // follow behind the loop.  Asked for row by row to the end, the loads fill the memory
     // pipeline and the loop's last rows wait for room in it (launch, 65 536 ranks x 4 096 x 8:
@@ -1687,7 +1747,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[j][i] = pad ? __uint_as_float(0x7FFFFFFFu) : v[j][i];
     };
-    {
+    auto load_first = [&]() {
         const uint32_t tl = fresh_tid4();
         const float* col = a.x + ((size_t)t_begin * M + m_begin) * R;
         // issued in row order, like the refills of the score loop: the waits of the
@@ -1697,7 +1757,82 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
             load_row(j, col, tl);
             __builtin_amdgcn_sched_barrier(0);
         }
+    };
+    if (!SPLIT) load_first();
+
+    uint32_t NE[(ROWS + 3) / 4]; // node mask byte per row, packed
+    // the selection's work area starts in its rest state (see the LDS protocol)
+    for (int i = tid; i < SH::NB + 128; i += NT) sh.dlo[i] = 0;      // dlo, hist, dhi
+    for (int i = tid; i < (MAX_NODES / 8 > 0 ? MAX_NODES / 8 : 1); i += NT) sh.ranka[i] = 0;
+    for (int i = tid; i < (int)CAND_REST; i += NT) sh.cand[i] = CAND_NONE;
+    if (tid == 0) {
+        sh.umax[0] = 0; sh.umax[1] = 0; sh.ncand = 0; sh.below = 0; sh.nkept = 0; sh.nnear = 0;
+        sh.smin = 0xFFFFFFFFu; sh.smax = 0; sh.d1 = 0; sh.d2 = 0xFFFFFFFFu;
+        for (int m = 0; m < 8; ++m) { sh.hok[m] = 0; sh.hfast[m] = 1; }
+        // (the reciprocal is only used where node_scale > 0)
+        sh.rules = {a.thr, a.node_scale, a.rel_floor, a.abs_floor, 1.0f / a.node_scale, a.node_agg};
+        // A one-step call may be told the medians and MADs of a recent step (usually the
+        // previous call's outputs).  They take the place of the hints a run of steps builds
+        // up for itself; like those they are only trusted as far as the counting pass
+        // confirms them, so any content is safe.
+        if (SPLIT && a.hint_med && a.hint_mad && a.T == 1) {
+            const float hm = a.hint_med[m_begin], hd = a.hint_mad[m_begin];
+            if (hm > 0.0f && hd > 0.0f && hm < 3.0e38f && hd < 3.0e38f) {      // (false for NaNs)
+                sh.hmed[m_begin] = hm;
+                sh.hwl[m_begin] = 1.25f * hd;
+                sh.hwh[m_begin] = 1.25f * hd;
+                sh.hmad[m_begin] = hd;
+                sh.hok[m_begin] = 1;
+            }
+        }
     }
+    if (SAMPLES) {
+        float* const found = reinterpret_cast<float*>(sh.pref);      // (not in use yet: three words a wave or column)
+#pragma unroll
+        for (int p = 0; p < LOTS; ++p) {
+            const uint32_t c = column_of(p);
+            if (c < columns) {
+                float q25, q50, q75;
+                sample_quartiles(lot[p], &q25, &q50, &q75);
+                if (lane == 0) {
+                    float* const to = found + 3u * (crowded ? c : (uint32_t)w);
+                    to[0] = q25; to[1] = q50; to[2] = q75;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    if (SPLIT) load_first();
+    if (SAMPLES) {
+        if ((uint32_t)tid < columns) {
+            const float* const found = reinterpret_cast<const float*>(sh.pref) + 3u * ((uint32_t)tid << sl);
+            float q25 = 0.0f, q50 = 0.0f, q75 = 0.0f;
+            for (uint32_t i = 0; i < 1u << sl; ++i) { q25 += found[3 * i]; q50 += found[3 * i + 1]; q75 += found[3 * i + 2]; }
+            const float share = 1.0f / (float)(1u << sl);
+            const float mid = q50 * share, hd = 0.5f * (q75 - q25) * share;      // (half the interquartile distance in place of the MAD)
+            // the reach that a run keeps from step to step, and as much more as a small sample is off
+            const float reach = (sl >= 2u ? 1.25f : sl == 1u ? 1.375f : 1.5f) * hd, low = mid - reach;
+            if (low > 0.0f && hd > 0.0f && mid < 3.0e38f && hd < 3.0e38f) {      // (false for NaNs)
+                // The histogram covers up to twice what it must, above the bracket: half of the rest is
+                // better below it.
+                const uint32_t klo = __float_as_uint(low), span = __float_as_uint(mid + reach) - klo;
+                const uint32_t rest = (1u << (LOG_NB + shift_for<LOG_NB>(span))) - span;
+                const uint32_t c = m_begin + (uint32_t)tid;
+                sh.hmed[c] = mid; sh.hmad[c] = hd;
+                sh.hwl[c] = mid - __uint_as_float(klo - min(rest / 2u, klo));
+                sh.hwh[c] = reach;
+                sh.hok[c] = 1;
+            }
+        }
+        __syncthreads();
+    }
+    constexpr uint32_t nsample = NT;          // (row 0, the column's sample, holds ranks throughout)
+    uint32_t dir_codes = 0;          // direction + 1 of metric i in bits 2i, 2i + 1
+#pragma unroll
+    for (int i = 0; i < 8; ++i) dir_codes |= (uint32_t)(a.dir[i] + 1) << (2 * i);
+    dir_codes = rfl(dir_codes);
+    const uint32_t k0_all = R / 2 - 1, k1_all = R / 2;   // the middle ranks when nothing is missing (R is even)
+    uint32_t colpar = 0;                          // parity of the column count: which umax slot is in use
 
     for (size_t t = t_begin; t < t_end; ++t) {
 #pragma unroll
@@ -1717,10 +1852,8 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         // reach its histogram had, brackets this step's counting pass without
         // sampling.  A bracket that misses is noticed and replaced by the sample's.
         // (the first step of a run has no predecessor: a sample of the column stands in)
-        // (a batch's ragged tiling of up to four rows is through the general route sooner: 4 000
-        // ranks x 256 steps, one metric, 16.7 us that way, 19.5 with the sample's hints)
-        bool boot = false;
-        if ((FULL || SPLIT || ROWS > 4) && t == t_begin && rfl(sh.hok[m]) == 0) {
+        bool boot = SAMPLES && t == t_begin;
+        if (SAMPLES_SINGLY && t == t_begin && rfl(sh.hok[m]) == 0) {
             sample_hints<NT, LOG_NB>(sh, v[0], m);
             boot = true;
         }
