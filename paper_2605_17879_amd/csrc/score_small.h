@@ -90,9 +90,10 @@ __device__ __forceinline__ uint32_t small_sample(const Keys& keys) {
 // (the others, padding and missing samples, are END or above).  Throughout, clo keys lie
 // under lo and chi under hi, with clo <= k0 and k1 < chi.  Ends for any contents: a round
 // narrows [lo, hi) to a part of it, from the fourth on to a half.
-template <int ROWS, typename Keys>
+// sort(sample): the sample's keys in ascending order (where n is more than a wave's).
+template <int ROWS, typename Keys, typename Sort>
 __device__ __forceinline__ void wave_select(const Keys& keys, uint32_t n, uint32_t k0, uint32_t k1, uint32_t lane,
-                                            uint32_t* slots, uint32_t* s0, uint32_t* s1) {
+                                            uint32_t* slots, uint32_t* s0, uint32_t* s1, Sort sort) {
     constexpr int V = ROWS * 4;
     uint32_t lo = 0, hi = Keys::END, clo = 0, chi = n;
     // two pivots, p <= q; true when one of them parts the two statistics (k0 < p <= k1)
@@ -137,7 +138,7 @@ __device__ __forceinline__ void wave_select(const Keys& keys, uint32_t n, uint32
         const uint32_t sample = small_sample<ROWS>(keys);
         const uint32_t ns = (uint32_t)__popcll(gd_ballot(sample < Keys::END));
         if (ns >= 16) {
-            const uint32_t sorted = gd_sort64(sample);
+            const uint32_t sorted = sort(sample);
             const uint32_t reach = 4u + ns / 16u;
             const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)sorted, (int)(ns / 2 - reach));
             const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)sorted, (int)min(ns / 2 + reach, ns - 1)) + 1u;
@@ -177,9 +178,9 @@ __device__ __forceinline__ void wave_select(const Keys& keys, uint32_t n, uint32
         const bool hit = k - lo < width;
         const uint64_t mask = gd_ballot(hit);
         if (mask != 0ull) {
-            const uint32_t to = pos + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-            if (hit && to < (uint32_t)WAVE) slots[to] = k;
+            // (chi - clo of them by the counts, so that every place is one of the wave's 64)
+            const uint32_t to = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, pos));
+            if (hit) slots[to] = k;
             pos += (uint32_t)__popcll(mask);
         }
     }
@@ -248,18 +249,34 @@ __device__ __forceinline__ void score_small(const gd_score_args& a) {
         const uint32_t k0 = (present - 1) / 2, k1 = present / 2;
         uint32_t* const slots = lds.slots + m * WAVE;
         uint32_t s0, s1;
+        float rising = 0.0f;                    // the median's sample in ascending order
         // (an odd count has one middle value: no sum that could overflow)
         if (!signs) {
             const PlainKeys<ROWS> keys{v};
-            wave_select<ROWS>(keys, present, k0, k1, lane, slots, &s0, &s1);
+            wave_select<ROWS>(keys, present, k0, k1, lane, slots, &s0, &s1, [&](uint32_t sample) {
+                const uint32_t sorted = gd_sort64(sample);
+                rising = keys.value(sorted);
+                return sorted;
+            });
             med = k0 == k1 ? keys.value(s0) : 0.5f * (keys.value(s0) + keys.value(s1));
         } else {
             const MappedKeys<ROWS> keys{v};
-            wave_select<ROWS>(keys, present, k0, k1, lane, slots, &s0, &s1);
+            wave_select<ROWS>(keys, present, k0, k1, lane, slots, &s0, &s1, [&](uint32_t sample) {
+                const uint32_t sorted = gd_sort64(sample);
+                rising = keys.value(sorted);
+                return sorted;
+            });
             med = k0 == k1 ? keys.value(s0) : 0.5f * (keys.value(s0) + keys.value(s1));
         }
+        // The MAD's sample holds the same values: in their order their distances fall and then rise (missing
+        // ones at the end, made alike), and the last six of a sort's 21 stages are what remains of it
+        // (with that, and three instructions less for each candidate's place, 1 024 ranks x 2 000 x 4
+        // 30.0 -> 29.0 us, one step of 1 000 x 4 10.35 -> 9.93).
         const DistanceKeys<ROWS> keys{v, med};
-        wave_select<ROWS>(keys, present, k0, k1, lane, slots, &s0, &s1);
+        wave_select<ROWS>(keys, present, k0, k1, lane, slots, &s0, &s1, [&](uint32_t) {
+            const float d = fabsf(rising - med);
+            return gd_merge<64, false>(d == d ? __float_as_uint(d) : 0xFFFFFFFFu);
+        });
         mad = k0 == k1 ? keys.value(s0) : 0.5f * (keys.value(s0) + keys.value(s1));
     }
     if (lane == 0) { a.med[column] = med; a.mad[column] = mad; }
