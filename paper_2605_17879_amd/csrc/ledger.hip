@@ -791,13 +791,31 @@ hipError_t gd_launch_ledger(const gd_ledger_args& a, hipStream_t s) {
         const uint32_t q = a.W / 64, r = a.W % 64, hist = q + (r ? 1 : 0), blocks = (a.T + 63) / 64;
         // Long stretches load less twice (hist blocks each), short ones fill the chip: two
         // blocks per wave of a 16-wave workgroup, less while there are not two workgroups per
-        // CU to run side by side.
-        uint32_t stretch = MAX_SLOTS - 1 - hist;
+        // CU to run side by side -- or as many as let two of eight waves share a CU by LDS, where
+        // windows with a tail take twice the planes and there are few blocks to load twice.
+        constexpr size_t slot_bytes = GD_BLOCK_PLANES * TILE * 4, tail_bytes = (GD_BLOCK_PLANES - 1) * TILE * 4;
+        constexpr uint32_t TAIL_SLOTS = 22;
+        static_assert(2 * (MAX_SLOTS * slot_bytes + 1024 + sizeof(uint32_t) * GD_COUNT_PLANES * TILE) <= 160 * 1024 &&
+                      2 * (TAIL_SLOTS * (slot_bytes + tail_bytes) + 1024 + sizeof(uint32_t) * GD_COUNT_PLANES * TILE) <= 160 * 1024,
+                      "two workgroups of eight waves share a CU's LDS");
+        const bool tail_pairs = r && hist <= 4;
+        uint32_t stretch = (tail_pairs ? TAIL_SLOTS : MAX_SLOTS) - 1 - hist;
         if (stretch > blocks) stretch = blocks;
         while (stretch > 4 && (uint64_t)((blocks + stretch - 1) / stretch) * tiles < 512) --stretch;
         const uint32_t stretches = (blocks + stretch - 1) / stretch, slots = hist + stretch + 1;
         if (stretches > 0x7FFFFFFFu / 1024 || tiles > 65535u) return hipErrorInvalidValue;
-        const uint32_t nt = (slots < (uint32_t)BLOCKS_NT / WAVE ? slots : (uint32_t)BLOCKS_NT / WAVE) * WAVE;
+        // Sixteen waves (registers for as many a CU), or eight, two workgroups of which a CU holds: one
+        // loads while the other counts.  An update, sixteen / eight: 65 536 ranks x 4 096 steps, window 64
+        // 90.5 / 88, 100 100 / 85, 200 105 / 97.5, 256 102.4 / 94.0, 384 115 / 107, 512 123 / 115; 65 536 x
+        // 2 000, window 20 63 / 51, 256 66 / 64; 16 384 x 10 000, 128 68 / 60, 100 72 / 70.5; 8 192 x 10 000,
+        // 256 50.8 / 43.8; 32 768 x 4 096, 256 56 / 54.5.  Not where every wave has one block of sixteen or
+        // less to load (65 536 x 512, 256 39.0 / 39.8), nor where few workgroups have long windows before them
+        // (65 536 x 2 000, 512 77.7 / 83) or, with a tail, the many slots that these take leave room for
+        // one workgroup (40 000 x 3 000, 300 69 / 75).
+        const bool pairs = slots > (uint32_t)BLOCKS_NT / WAVE &&
+                           (r ? tail_pairs : q <= 6 || (uint64_t)stretches * tiles >= 768);
+        const uint32_t most_waves = (pairs ? BLOCKS_NT / 2 : BLOCKS_NT) / WAVE;
+        const uint32_t nt = (slots < most_waves ? slots : most_waves) * WAVE;
         const size_t lds = (size_t)(r ? 2 * GD_BLOCK_PLANES - 1 : GD_BLOCK_PLANES) * slots * TILE * 4;
         constexpr size_t most = (size_t)(2 * GD_BLOCK_PLANES - 1) * MAX_SLOTS * TILE * 4;
         static_assert(most + sizeof(uint32_t) * GD_COUNT_PLANES * TILE <= 160 * 1024, "LDS budget of one CU");

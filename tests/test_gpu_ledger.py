@@ -219,6 +219,31 @@ def test_ledger_behind_the_scoring_kernel():
     assert want["nodes"].flag.sum() >= 4
 
 
+@pytest.mark.parametrize("T,W,k", [(960, 64, 40), (1000, 64, 40), (896, 100, 70), (930, 100, 70), (1930, 250, 180),
+                                   (1500, 300, 200), (2000, 448, 300)])
+def test_ledger_where_the_width_of_workgroups_changes(T, W, k):
+    """65 536 ranks on either side of the lines between sixteen waves a workgroup and eight: 16 and 17
+    blocks loaded, windows with and without a tail, up to four blocks before a stretch and more."""
+    R, M = 65536, 2
+    N = R // 8
+    say(f"case ledger widths T={T} W={W}")
+    p = oracle_params(R=R, M=M, W=W, k=k, directions=(1,) * M)
+    exceed = exceed_history(T, T, R, M, 0.02, burst_items=2000, burst_len=(W // 2, 2 * W), gap_len=(5, W))
+    node_mask = exceed_history(T + 1, T, N, M, 0.02, burst_items=300, burst_len=(W // 2, 2 * W), gap_len=(5, W))
+    node_z = node_score_history(T, T, N, scale=2.0)
+    rng = np.random.default_rng(T)
+    ranks = np.unique(np.concatenate([[0, 255, 256, R - 1], rng.choice(R, 500, replace=False)]))
+    nodes = np.unique(np.concatenate([[0, N - 1], rng.choice(N, 250, replace=False)]))
+    want = oracle_ledger(p, exceed, node_mask, oracle.combine(node_mask, p.primary, p.min_signals), node_z, 64.0, 900, 2, 64,
+                         ranks=ranks, nodes=nodes)
+    det = detector_for(p)
+    det.alloc_ledger(T, recur_horizon=900, recur_limit=2)
+    feed(det, exceed, node_mask, node_z, [T])
+    compare_ledger(want, read_ledger(det, 64), f"widths T={T} W={W}", ranks=ranks, nodes=nodes)
+    assert (want["ranks"].first >= 0).any()
+    det.close()
+
+
 def test_ledger_at_the_benchmark_size():
     """65 536 ranks x 4 096 steps x 8 metrics in one call, the launch configuration the
     benchmark times.  The oracle re-sums every window, so it follows 2 048 sampled ranks
