@@ -1168,6 +1168,9 @@ __device__ __forceinline__ GatherResult hinted_gather(SH& sh, const float (&v)[R
     out.umax = out.status == PLAN_NONE ? umax : top;
     if (__builtin_expect(out.status != PLAN_GATHER, 0)) return out;
     // ---- gather the rows that hold a value of the median's buckets or of the MAD's
+    // (128 rows of a wave where the counters have room for them, up to 512 threads: a sample's wide
+    // bracket has up to twice the candidates, and with 64 rows one in twenty first columns of 16 384
+    // ranks overflowed a list of one of its four waves)
     RowList<SH, SH::NB / (4 * SH::WAVES) < 128 ? 64 : 128> rows(sh, w);
     {
         __builtin_amdgcn_s_setprio(1);
