@@ -24,6 +24,7 @@
 // rank and step of outputs.
 #include <type_traits>
 
+#include "gd_bracket.h"
 #include "gd_grant.h"
 #include "gd_internal.h"
 #include "gd_lanes.h"
@@ -456,12 +457,6 @@ __device__ __forceinline__ void rank_candidates(SH& sh, uint32_t tid, uint32_t c
         }
     }
     __syncthreads();
-}
-
-template <int LOG_NB>
-__device__ __forceinline__ int shift_for(uint32_t span) {
-    const int width = 32 - __builtin_clz(span | 1u);
-    return width > LOG_NB ? width - LOG_NB : 0;            // (span >> shift) < NB
 }
 
 // Exact selection of the order statistics k0 <= k1 (0-based, k1 - k0 <= 1) of
@@ -1084,23 +1079,17 @@ __device__ __forceinline__ GatherResult hinted_gather(SH& sh, const float (&v)[R
                                                       uint32_t k0, uint32_t k1, uint32_t* umax_slot) {
     GatherResult out = {PLAN_NONE, 0u, 0u};
     constexpr int NB = 1 << LOG_NB;
-    constexpr uint32_t KEY_LIMIT = 0x7D000000u;    // beyond it the signed bucket arithmetic could wrap
     const uint32_t span0 = hint_hi - hint_lo;
     const int shift = shift_for<LOG_NB>(span0);
-    // the bracket is widened to all NB buckets (less than twice the hint's span; the caller
-    // has checked that this stays below KEY_LIMIT) and starts on a bucket boundary
+    // the bracket (`bracket_counts` has let it pass) is widened to all NB buckets, less than twice the
+    // hint's span, and starts on a bucket boundary
     const uint32_t lo = hint_lo & ~((1u << shift) - 1u);
     uint32_t* const cnt = sh.dlo;                  // 64 + NB + 64 counters
-    // ---- pass 1: count.  lo is a multiple of 2^shift, so a key's bucket is its own bits
-    // shifted down, less lo's: the clamp works on the shifted bits and the subtraction
-    // moves into the counter's address (three vector instructions per value).
+    // ---- pass 1: count
     {
         const uint32_t tid = opaque_v(threadIdx.x), lane = tid & (WAVE - 1);
-        const int ql = (int)(lo >> shift);                       // (below 2^30: shift < 2 gives the result up anyway)
-        // (as floats; below 0, of a bracket that begins at a bucket under 64, `cl` is a NaN, and the
-        // median of three is then the least of the others: at least 0, counter 64 - ql)
-        const float cl = __uint_as_float((uint32_t)(ql - 1 - (int)lane)), ch = __uint_as_float((uint32_t)(ql + NB + (int)lane));
-        const uint32_t kb = opaque_s((uint32_t)(64 - ql) * 4u);  // counter 64 is bucket 0 (bytes, mod 2^32)
+        const BracketCounters<LOG_NB> counters(lo >> shift, lane);
+        const uint32_t kb = opaque_s(counters.base);
         const uint32_t sh_s = opaque_s((uint32_t)shift);
         uint32_t um = 0;
         __builtin_amdgcn_s_setprio(2);
@@ -1113,12 +1102,8 @@ __device__ __forceinline__ GatherResult hinted_gather(SH& sh, const float (&v)[R
             set_padding(j);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const uint32_t q = __float_as_uint(row[i]) >> sh_s;
-                // q clamped to [cl, ch] (cl < ch): the median of the three, as floats, whose order theirs
-                // is too (positive ones, subnormals among them, and no NaNs: the keys are shifted)
-                const uint32_t c = __float_as_uint(__builtin_amdgcn_fmed3f(__uint_as_float(q), cl, ch));
-                // counter c - ql + 64, in [63 - lane, 64 + NB + lane]
-                atomicAdd(reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(cnt) + ((c << 2) + kb)), 1u);
+                const uint32_t at = counters.at(__float_as_uint(row[i]) >> sh_s, kb, [](float x, float l, float h) { return __builtin_amdgcn_fmed3f(x, l, h); });
+                atomicAdd(reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(cnt) + at), 1u);
             }
             asm volatile("" : "+v"(um));
             __builtin_amdgcn_sched_barrier(0);
@@ -1154,7 +1139,7 @@ __device__ __forceinline__ GatherResult hinted_gather(SH& sh, const float (&v)[R
     if (w == 1u) cnt[64 + NB + lane] = 0;
     uint32_t below;
     const bool bracketed = locate<NT, LOG_NB, true, true>(sh, tid, k0, k1, &below);
-    if (top > KEY_LIMIT || !bracketed || shift < 2) return out;
+    if (top > BRACKET_KEY_LIMIT || !bracketed) return out;
     if (w == 0) plan_gather<LOG_NB>(sh, lane, lo, shift, mad_hint, below, k0, k1);
     __syncthreads();
     // (all of it at once: read where it is used it is a chain of LDS latencies)
@@ -1977,8 +1962,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
         // settle goes through the general route below.
         bool tried_fast = false, settled = false;
         uint32_t located = PLAN_NONE;
-        if (hinted && rfl(sh.hfast[m]) != 0 && hint_hi < 0x7D000000u - 2u * (hint_hi - hint_lo) &&
-            hint_hi - hint_lo < 0x20000000u) {
+        if (hinted && rfl(sh.hfast[m]) != 0 && bracket_counts<LOG_NB>(hint_lo, hint_hi)) {
             tried_fast = true;
             const GatherResult gr = hinted_gather<NT, ROWS, LOG_NB>(
                 sh, v, [&](int j) { set_padding(j, tl); }, [&]() { load_ahead(next_col); }, hint_lo, hint_hi, sh.hmad[m], k0_all, k1_all, umax_slot);

@@ -154,3 +154,64 @@ def test_middle_ranks_in_buckets_apart(R, T):
     x = torch.from_numpy((1.0 + 0.02 * side * (d + 0.5 * gap)).astype(np.float32))
     p = oracle_params(R=R, M=1, W=8, k=4, directions=(1,), min_signals=1)
     run_and_compare(p, x, topk_k=8, label=f"middle ranks apart R{R}", want_z=False, chunks=[T] if T > 24 else [4] * 6)
+
+
+def _negative_and_tiny(R, kind, seed):
+    """Values that no shifted bits of a real column hold: -2.0 to -2.0095, whose bits are 0xC0000000 and
+    a little more, negative subnormals, -0 and plain negative numbers."""
+    rng = np.random.default_rng(seed)
+    if kind == "below_minus_two":
+        b = np.uint32(0xC0000000) + rng.integers(0, 40000, R).astype(np.uint32)
+    elif kind == "negative_subnormals":
+        b = np.uint32(0x80000000) + rng.integers(0, 40000, R).astype(np.uint32)
+    elif kind == "mixed":
+        b = (np.float32(1.0) + np.float32(0.02) * rng.standard_normal(R, dtype=np.float32)).view(np.uint32).copy()
+        at = rng.permutation(R)
+        b[at[: R // 8]] = np.uint32(0xC0000000) + rng.integers(0, 40000, R // 8).astype(np.uint32)
+        b[at[R // 8:R // 4]] = np.uint32(0x80000000)
+    elif kind == "subnormals":                              # (no signs: units about 44)
+        b = rng.integers(20, 69, R).astype(np.uint32)
+    elif kind == "wider_subnormals":                        # (a bracket wide enough to count in, from near 0 on)
+        b = rng.integers(1, 60000, R).astype(np.uint32)
+    else:
+        b = (-400.0 * np.exp(0.02 * rng.standard_normal(R))).astype(np.float32).view(np.uint32)
+    return b.astype(np.uint32).view(np.float32)
+
+
+TINY_KINDS = ["below_minus_two", "negative_subnormals", "mixed", "subnormals", "wider_subnormals", "negative"]
+# (median and MAD hinted, in units of the last place of zero)
+TINY_HINTS = [(50, 20), (44, 30), (64, 50), (65, 51), (200, 3), (3000, 1500), (30000, 15000), (1, 1)]
+
+
+@pytest.mark.parametrize("R", [4096, 4104, 8192, 16384, 20000, 40000, 65536])
+def test_hints_of_a_few_subnormal_units(R):
+    """Brackets that begin next to zero, narrower and wider than the counters, over columns with signs and
+    without: hints cost time, never results."""
+    print(f"case tiny hints R={R}", flush=True)
+    M = len(TINY_KINDS)
+    x = torch.from_numpy(np.stack([_negative_and_tiny(R, k, 7 * R + i) for i, k in enumerate(TINY_KINDS)])[None].copy())
+    p = oracle_params(R=R, M=M, W=4, k=2, directions=(1, -1, 1, 0, -1, 1), min_signals=2)
+    o = oracle.score(p, x.numpy(), want_z=True)
+    det = detector_for(p)
+    xd = x.cuda()
+    for med, mad in TINY_HINTS:
+        hints = [torch.from_numpy(np.full(M, v, dtype=np.uint32).view(np.float32)).cuda() for v in (med, mad)]
+        det.set_streaming_hints(*hints)
+        out = det.alloc_outputs(1, want_z=True)
+        for v in out.values():
+            v.view(torch.uint8).fill_(0xA5)
+        det.score_batch(xd, out)
+        torch.cuda.synchronize()
+        assert compare_scores(o, out, f"R={R} hints {med} {mad}")["z_bit_exact"]
+    det.set_streaming_hints(None, None)
+    det.close()
+
+
+@pytest.mark.parametrize("R,T", [(4104, 2600), (16384, 2060), (24000, 1030), (40000, 520), (65536, 520)])
+def test_steps_of_a_few_subnormal_units_before_negative_ones(R, T):
+    """The same from step to step: a column of subnormal values leaves its hints to one with signs."""
+    print(f"case tiny steps R={R} T={T}", flush=True)
+    order = ["subnormals", "subnormals", "below_minus_two", "wider_subnormals", "mixed", "subnormals", "negative_subnormals"]
+    x = torch.from_numpy(np.stack([_negative_and_tiny(R, order[t % len(order)], 11 * R + t % 21) for t in range(T)])[:, None].copy())
+    p = oracle_params(R=R, M=1, W=8, k=4, directions=(1,), min_signals=1)
+    run_and_compare(p, x, topk_k=8, label=f"tiny steps R{R}", want_z=False)
