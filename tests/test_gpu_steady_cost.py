@@ -237,3 +237,25 @@ def test_scoring_of_a_crowd_at_the_edge_of_the_mad(R, T):
     det.close()
     print(f"crowd at the MAD's edge, {R} ranks: {us[0]:.1f} us plain, {us[1]:.1f} us", flush=True)
     assert us[1] < 1.6 * us[0]
+
+
+@pytest.mark.parametrize("R,T,M", [(5000, 1000, 2), (7000, 1000, 8), (8000, 1000, 4), (12000, 1000, 4), (24000, 512, 8), (32768, 512, 8)])
+@pytest.mark.parametrize("kind", ["exponential", "log-normal of sigma 1"])
+def test_scoring_of_skewed_columns_in_runs_of_one_step_or_two(kind, R, T, M):
+    """Columns whose quartiles lie unevenly about the median, and whose first hints are a sample's.  Measured,
+    plain / exponential / log-normal, us: 8 000 ranks x 1 000 steps x 4 45 / 90 / 88 with half the interquartile
+    distance in place of the MAD, 45 / 50 / 49 with the sides' unevenness taken into account; 24 000 x 512 x 8 102 /
+    182 / 172 and 103 / 110 / 110; 5 000 x 1 000 x 2 26 / 46 / 44 and 26 / 27 / 27.  The bound lies half way between
+    1.1 and 1.6."""
+    us = []
+    det = detector_for(oracle_params(R=R, M=M, W=4, k=2, min_signals=1, directions=(1,) * M))
+    g = torch.Generator(device="cuda").manual_seed(11)
+    x = torch.randn((T, M, R), device="cuda", generator=g)
+    skewed = torch.exp(x) if kind != "exponential" else torch.empty_like(x).exponential_(generator=g) + 1e-6
+    x = torch.exp(0.02 * x)
+    out = det.alloc_outputs(T)
+    for v in (x, skewed):
+        us.append(device_us(lambda: None, lambda: [det.score_batch(v, out) for _ in range(10)]) / 10)
+    det.close()
+    print(f"{kind}, {R} ranks x {T} x {M}: {us[0]:.1f} us plain, {us[1]:.1f} us", flush=True)
+    assert us[1] < 1.35 * us[0]
