@@ -1426,6 +1426,20 @@ __device__ __forceinline__ void sample_quartiles(uint32_t (&k)[4], float* q25, f
     *q75 = s75 * share;
 }
 
+// The MAD of a sample whose quartiles lie `left` and `right` of its median, `half` their mean: that, and
+// less of it where one side is the wider one.  Of exponential, log-normal and gamma distributed values it
+// is `half` times the fourth power of the sides' geometric mean over `half`, to 3 %; where that would be
+// less than a half of it, the column is no skewed heap but several.  (`half` alone, launch, exponential
+// values / log-normal ones of sigma 1: sampled all at once, with a reach that then went below zero and
+// left the column without hints, 8 000 ranks x 1 000 x 4 90 / 88 us, so 50 / 49, 12 000 x 1 000 x 4 105 / 104 and
+// 62 / 63, 32 768 x 512 x 8 209 / 203 and 126 / 126; one by one, 16 384 x 1 024 x 4 115 / 95 and 73 / 75, 4 096 x 256 x 1
+// 20.3 / 19.6 and 12.2 / 12.2, one step of 20 000 x 4 21.4 / 17.6 and 17.1 / 17.2.  Even columns and such in two
+// heaps the same within 1 %.)
+__device__ __forceinline__ float mad_of_quartiles(float left, float right, float half) {
+    const float per = __builtin_amdgcn_rcpf(half), even = (left * per) * (right * per), share = even * even;
+    return share >= 0.5f ? half * share : half;
+}
+
 // The same for a column whose first register row has come: a sample of four values of every thread (row 0, which covers the whole
 // rank range), its median and quartiles read off a histogram over the sample's own range (one step
 // of 20 000 ranks x 4, no hints: 17.0 us; 18.2 by sorted lots).  Thread 0 writes the hints of metric m;
@@ -1486,11 +1500,12 @@ __device__ __forceinline__ void sample_hints(SH& sh, const float (&row)[4], uint
         const float q25 = __uint_as_float(smin + (sh.res[0] << sshift) + half);
         const float q50 = __uint_as_float(smin + (sh.res[1] << sshift) + half);
         const float q75 = __uint_as_float(smin + (sh.res[2] << sshift) + half);
-        const float hd = 0.5f * (q75 - q25);
+        const float sides = 0.5f * (q75 - q25), hd = mad_of_quartiles(q50 - q25, q75 - q50, sides);
         if (q50 > 0.0f && hd > 0.0f && q50 < 3.0e38f && hd < 3.0e38f) {      // (false for NaNs)
             sh.hmed[m] = q50;
-            sh.hwl[m] = 1.25f * hd;          // (the reach a run keeps from step to step)
-            sh.hwh[m] = 1.25f * hd;
+            // (the reach a run keeps from step to step, on the left no further than half way from where the MAD ends to zero)
+            sh.hwl[m] = fminf(1.25f * sides, 0.5f * (q50 + hd));
+            sh.hwh[m] = 1.25f * sides;
             sh.hmad[m] = hd;
             sh.hok[m] = 1;
         }
@@ -1801,14 +1816,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
             for (uint32_t i = 0; i < 1u << sl; ++i) { q25 += found[3 * i]; q50 += found[3 * i + 1]; q75 += found[3 * i + 2]; }
             const float share = 1.0f / (float)(1u << sl);
             const float mid = q50 * share, left = mid - q25 * share, right = q75 * share - mid, half = 0.5f * (left + right);
-            // Half the interquartile distance stands in for the MAD, and less of it where one side is the
-            // wider: of exponential, log-normal and gamma distributed values the MAD is that times the fourth
-            // power of the sides' geometric mean over their mean, to 3 %.  (Half the distance alone, with a reach
-            // that then went below zero and left the column without hints, launch, exponential values / log-normal
-            // ones of sigma 1: 8 000 ranks x 1 000 x 4 90 / 88 us, so 50 / 49, 12 000 x 1 000 x 4 105 / 104 and 62 / 63,
-            // 32 768 x 512 x 8 209 / 203 and 126 / 126, 65 536 x 512 x 4 177 / 165 and 159 / 158; even columns and
-            // such in two heaps the same.)
-            const float even = left * right / (half * half), hd = half * fmaxf(even * even, 0.7f);
+            const float hd = mad_of_quartiles(left, right, half);
             // the reach that a run keeps from step to step, and as much more as a small sample is off; on
             // the left no further than half way from where the MAD ends to zero
             const float reach = (sl >= 2u ? 1.25f : sl == 1u ? 1.375f : 1.5f) * half, low = fmaxf(mid - reach, 0.5f * (mid - hd));

@@ -239,14 +239,16 @@ def test_scoring_of_a_crowd_at_the_edge_of_the_mad(R, T):
     assert us[1] < 1.6 * us[0]
 
 
-@pytest.mark.parametrize("R,T,M", [(5000, 1000, 2), (7000, 1000, 8), (8000, 1000, 4), (12000, 1000, 4), (24000, 512, 8), (32768, 512, 8)])
+@pytest.mark.parametrize("R,T,M", [(5000, 1000, 2), (7000, 1000, 8), (8000, 1000, 4), (12000, 1000, 4), (24000, 512, 8), (32768, 512, 8),
+                                   (4096, 256, 1), (16384, 200, 1), (15000, 1024, 4), (16384, 1024, 4)])
 @pytest.mark.parametrize("kind", ["exponential", "log-normal of sigma 1"])
 def test_scoring_of_skewed_columns_in_runs_of_one_step_or_two(kind, R, T, M):
     """Columns whose quartiles lie unevenly about the median, and whose first hints are a sample's.  Measured,
     plain / exponential / log-normal, us: 8 000 ranks x 1 000 steps x 4 45 / 90 / 88 with half the interquartile
     distance in place of the MAD, 45 / 50 / 49 with the sides' unevenness taken into account; 24 000 x 512 x 8 102 /
-    182 / 172 and 103 / 110 / 110; 5 000 x 1 000 x 2 26 / 46 / 44 and 26 / 27 / 27.  The bound lies half way between
-    1.1 and 1.6."""
+    182 / 172 and 103 / 110 / 110; 5 000 x 1 000 x 2 26 / 46 / 44 and 26 / 27 / 27; columns sampled one by one, 16 384 x
+    1 024 x 4 69 / 115 / 95 and 69 / 73 / 75, 4 096 x 256 x 1 12 / 20 / 20 and 12 / 12 / 12.  The bound lies half way
+    between 1.1 and 1.6."""
     us = []
     det = detector_for(oracle_params(R=R, M=M, W=4, k=2, min_signals=1, directions=(1,) * M))
     g = torch.Generator(device="cuda").manual_seed(11)
