@@ -28,6 +28,7 @@
 #include "gd_grant.h"
 #include "gd_internal.h"
 #include "gd_lanes.h"
+#include "gd_sample.h"
 
 // This file is compiled several times, side by side: as it is (every launch without the
 // optional z output, and the entry points), through score_z.hip with GD_SCORE_WANT_Z = 1
@@ -1697,17 +1698,15 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
 
     // The first step's samples (see sample_quartiles): wave w takes part w mod 2^SL of column w >> SL, or,
     // with fewer waves than columns, columns w, w + NWAVES, ..., and asks for them ahead of the first
-    // column.  The values, sixteen neighbours at a time (64 bytes), are spread over the ranks by
-    // multiples of the golden ratio, a step that no structure of the job shares.
+    // column.
     constexpr int LOTS = (8 + NWAVES - 1) / NWAVES;
     const uint32_t columns = m_end - m_begin;
     const bool crowded = LOTS > 1 && columns > (uint32_t)NWAVES;
-    const uint32_t sl = 4u * columns <= (uint32_t)NWAVES ? 2u : 2u * columns <= (uint32_t)NWAVES ? 1u : 0u;
+    const uint32_t sl = sample_parts_log(columns, NWAVES);
     auto column_of = [&](int p) -> uint32_t { return crowded ? (uint32_t)(w + p * NWAVES) : p == 0 ? (uint32_t)w >> sl : columns; };
     uint32_t lot[LOTS][4];
     if (SAMPLES) {
-        const uint32_t pos = ((uint32_t)w & ((1u << sl) - 1u)) * WAVE + (uint32_t)lane;
-        const uint32_t from = min(__umulhi((pos / 4u) * 0x9E3779B9u, R / 16u) * 16u + (pos & 3u) * 4u, R - 4u);
+        const uint32_t from = sample_rank(((uint32_t)w & ((1u << sl) - 1u)) * WAVE + (uint32_t)lane, R);
 #pragma unroll
         for (int p = 0; p < LOTS; ++p) {
             const float* col = a.x + ((size_t)t_begin * M + min(column_of(p), columns - 1u)) * R;
