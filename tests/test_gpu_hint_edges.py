@@ -215,3 +215,24 @@ def test_steps_of_a_few_subnormal_units_before_negative_ones(R, T):
     x = torch.from_numpy(np.stack([_negative_and_tiny(R, order[t % len(order)], 11 * R + t % 21) for t in range(T)])[:, None].copy())
     p = oracle_params(R=R, M=1, W=8, k=4, directions=(1,), min_signals=1)
     run_and_compare(p, x, topk_k=8, label=f"tiny steps R{R}", want_z=False)
+
+
+@pytest.mark.parametrize("R,T", [(4104, 2600), (8192, 2600), (16384, 2060), (24000, 1030), (40960, 520), (57344, 520), (65536, 520)])
+def test_gathered_candidates_from_step_to_step(R, T):
+    """The columns of the test above -- few and many alike values, odd and even numbers of samples -- in batches of
+    more than twice the steps that the chip takes at once, so that each workgroup's later steps are hinted by
+    its own earlier ones, over columns of another kind."""
+    print(f"case candidates from step to step R={R} T={T}", flush=True)
+    rng = np.random.default_rng(3 * R)
+    n = 3 * len(GRIDS)                                          # steps that differ, given again and again
+    x = np.empty((n, 2, R), np.float32)
+    for t in range(n):
+        for m in range(2):
+            z = rng.standard_normal(R)
+            q = GRIDS[(t + 3 * m * (t // len(GRIDS) + 1)) % len(GRIDS)]
+            z = np.round(z * q) / q if q else z
+            x[t, m] = 1.0 + 0.02 * z
+            x[t, m, rng.permutation(R)[:(0, 1, 64, 0)[(t + m) % 4]]] = np.nan
+    x = torch.from_numpy(x).repeat((T + n - 1) // n, 1, 1)[:T].contiguous()
+    p = oracle_params(R=R, M=2, W=4, k=2, directions=(1, -1), min_signals=2)
+    run_and_compare(p, x, topk_k=8, label=f"candidates from step to step R{R}", want_z=False)
