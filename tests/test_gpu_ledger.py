@@ -244,6 +244,12 @@ def test_ledger_where_the_width_of_workgroups_changes(T, W, k):
     det.close()
 
 
+def test_ledger_where_many_workgroups_have_long_windows_before_them():
+    """The line above six blocks before a stretch from the side of eight waves: 65 536 ranks, three stretches of a
+    window of eight blocks (960 workgroups, 768 being the line; 640 above)."""
+    test_ledger_where_the_width_of_workgroups_changes(4096, 512, 400)
+
+
 def test_ledger_at_the_benchmark_size():
     """65 536 ranks x 4 096 steps x 8 metrics in one call, the launch configuration the
     benchmark times.  The oracle re-sums every window, so it follows 2 048 sampled ranks
