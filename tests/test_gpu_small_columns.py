@@ -99,3 +99,51 @@ def test_infinite_medians_repeat(R):
         seen.add(bits32(out["med"].cpu()).tobytes() + bits32(out["mad"].cpu()).tobytes())
     det.close()
     assert len(seen) == 1
+
+
+def _so_many_between_the_pivots(R, n, rng):
+    """A column of which exactly n values lie between the pivots that its sample gives (a quarter of the sample's
+    64 about its middle, both ends included): 64 fill the wave's list of last candidates."""
+    at = sampled_ranks(R)
+    ns = len(at)
+    reach = 4 + ns // 16
+    lo, hi = ns // 2 - reach, ns // 2 + reach
+    sample = (1.0 + (np.arange(ns) - ns // 2) * 1e-3).astype(np.float32)
+    x = np.empty(R, np.float32)
+    x[at] = rng.permutation(sample)
+    rest = rng.permutation(np.setdiff1d(np.arange(R), at))
+    inside = n - (hi - lo + 1)
+    x[rest[:inside]] = rng.uniform(sample[lo] + 1e-5, sample[hi] - 1e-5, inside)
+    out = rest[inside:]
+    below = (R - n) // 2 - lo                                   # the median's ranks lie in the middle of the n
+    x[out[:below]] = 0.9 * (1.0 + 0.01 * rng.random(below))
+    x[out[below:]] = 1.1 * (1.0 + 0.01 * rng.random(len(out) - below))
+    assert ((x >= sample[lo]) & (x <= sample[hi])).sum() == n
+    return x
+
+
+@pytest.mark.parametrize("R,M", [(64, 8), (256, 8), (512, 8), (1000, 8), (1024, 4), (2048, 8), (3000, 4), (3072, 2), (4000, 8), (4096, 2)])
+def test_last_candidates_that_fill_their_list(R, M):
+    """62 to 66 candidates in every wave of a workgroup, whose lists lie one behind another; a column of
+    64 ranks is such a list by itself, also with values missing or of either sign."""
+    rng = np.random.default_rng(R)
+    counts = [62, 63, 64, 65, 66, 64]
+    x = np.empty((len(counts) * 4, M, R), np.float32)
+    for t in range(len(x)):
+        for m in range(M):
+            if R == 64:
+                col = (1.0 + 0.02 * rng.standard_normal(R)).astype(np.float32)
+                kind = (t + m) % 4
+                if kind == 1:
+                    col[rng.integers(R)] = np.nan
+                elif kind == 2:
+                    col[rng.permutation(R)[:20]] = 1.0
+                elif kind == 3:
+                    col = col - np.float32(1.0)
+            else:
+                col = _so_many_between_the_pivots(R, counts[(t + m) % len(counts)], rng)
+                if t % 4 == 3:
+                    col = -col
+            x[t, m] = col
+    p = oracle_params(R=R, M=M, W=4, k=2, directions=(1, -1, 0, 1, -1, 1, 0, 1)[:M], min_signals=min(2, M))
+    run_and_compare(p, torch.from_numpy(x), topk_k=min(8, R // 8), chunks=[len(x) - 1, 1], label=f"full lists R{R} M{M}")
