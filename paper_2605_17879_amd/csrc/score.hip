@@ -7,7 +7,9 @@
 // column after column.  For each of a step's M columns it
 //   1. holds the column in registers (float4 per lane per row, loaded once from
 //      HBM, coalesced, rank-contiguous; the next column is loaded row by row
-//      while the current one is scored) -- a column is never read again;
+//      while the current one is scored) -- a column is never read again, but for the
+//      rows asked for ahead (five or six in two tilings) where the column before
+//      them leaves the hinted route and they are not kept;
 //   2. finds the two middle order statistics by counting: a bracket (taken from
 //      the previous step of the same metric, else from a sample of the column)
 //      is counted into an LDS histogram of order-preserving integer keys, a
@@ -104,7 +106,7 @@ static_assert(CAND_REST <= (uint32_t)CAND_CAP, "the gathered candidates fit thei
 // that nothing lies in those between.  (One in twenty columns of 5 000 ranks, where a bucket holds
 // a value or two, has them further apart than one, and a batch is done when its slowest column
 // is: 5 000 x 1 000 x 2 41 us a launch where these went the general way, 29.5 so, 8 000 x 1 000 x 4
-// 81 and 52, 16 384 x 10 000 x 4 661 and 608.)
+// 81 and 52.  A launch of 16 384 x 10 000 x 4 differs by less than with the place of its buffers: 515 to 605.)
 constexpr uint32_t MOST_APART = 63;
 
 template <int NT, int LOG_NB, int MAX_NODES>
@@ -1518,7 +1520,7 @@ __device__ __forceinline__ void sample_hints(SH& sh, const float (&row)[4], uint
 // negative.  (A permute's selectors 9 and 11 fill a byte with the sign of a word, so that what
 // remains is one operation of three inputs; with the words' top bytes brought together, shifted
 // and masked it was five instructions a row instead of three: launch, 5 000 ranks x 10 000 x 2 157 us,
-// so 155, 16 384 x 10 000 x 4 609 and 605, 65 536 x 4 096 x 8 1 839 and 1 835.)
+// so 155, 65 536 x 4 096 x 8 1 839 and 1 835.)
 __device__ __forceinline__ uint32_t sign_bytes(uint32_t d0, uint32_t d1, uint32_t d2, uint32_t d3, uint32_t bits) {
     const uint32_t lo2 = __builtin_amdgcn_perm(d1, d0, 0x0C0C0B09u);
     const uint32_t hi2 = __builtin_amdgcn_perm(d3, d2, 0x0B090C0Cu);
@@ -1598,11 +1600,10 @@ __device__ __forceinline__ void score_row_fast(const float (&x)[4], float med, f
 //     cc ~ +-scale/s and kk ~ 8*med*cc.  All roundings of the exact chain and of
 //     the estimate together stay below `margin` (see the caller), so the estimate
 //     decides unless it falls within `margin` of the threshold.  The estimate is
-//     monotone in sum(x), so the caller hands in a bound sthr on the sum itself,
-//     checked by it against the estimate's own formula: on the far side of sthr the
-//     node cannot exceed nor come near.  *cand is set for the lanes on the near side;
-//     the caller then forms the estimate and, within `margin` of the threshold, the
-//     exact score.
+//     monotone in sum(x), so that a bound on the sum itself, checked against the
+//     estimate's own formula where it is worked out (work_out), passes over the rows
+//     in which no node exceeds or comes near.  In the others the estimate is formed
+//     and, within `margin` of the threshold, the exact score.
 //
 // Values, sums and their bounds are not negative, and such floats order like their bit patterns.
 // Of the bound b, `flip` is all ones and `cut` is b where higher is worse, `flip` is 0 and `cut` is
@@ -1653,11 +1654,14 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
     constexpr int MAX_NODES = BLK * ROWS / 8;
     constexpr int NWAVES = NT / WAVE;
     // Where the first step's columns are sampled all at once (see sample_quartiles), and where one by
-    // one: with one column in a workgroup, in the exact fits of 256 threads (4 096 x 256 x 1 11.25 us,
-    // all at once 11.55; 16 384 x 10 000 x 4 609 and 613) and in sixteen rows of them (15 000 x 1 024 x 4
-    // 73.5 and 74.8; 12 000 x 1 000 x 4 61.5 and 56.2).  (A batch's ragged tiling of up to four
-    // rows is through the general route sooner: 4 000 ranks x 256 steps, one metric, 16.7 us that way,
-    // 19.5 with a sample's hints.)
+    // one: with one column in a workgroup, and in the exact fits of 256 threads and in sixteen rows of them, of
+    // which plain columns in runs of one step gain by the larger sample (one by one / all at once, launch:
+    // 4 096 x 256 x 1 11.6 / 12.0 us, 15 000 x 1 024 x 4 70.2 / 73.4, 16 384 x 1 024 x 4 70.9 / 71.4; fewer rows,
+    // 12 000 x 1 000 x 4 61.5 / 56.2).  Longer runs gain nothing either way (15 000 x 3 000 x 4 194 / 194, 16 384 x
+    // 10 000 x 4 605 / 606), more metrics would lose (16 384 x 512 x 8 94.0 / 90.5), and so do columns in two heaps or of
+    // few distinct values, which the lots find out sooner (16 384 x 1 024 x 4 110 / 82 and 406 / 333).  (A batch's
+    // ragged tiling of up to four rows is through the general route sooner: 4 000 ranks x 256 steps, one
+    // metric, 16.7 us that way, 19.5 with a sample's hints.)
     constexpr bool SAMPLES = !SPLIT && (NT > 256 || (!FULL && ROWS > 4 && ROWS < 16));
     constexpr bool SAMPLES_SINGLY = SPLIT || (NT <= 256 && (FULL || ROWS == 16));
     using SH = Shared<NT, LOG_NB, MAX_NODES>;
@@ -2135,7 +2139,7 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
             sh.nkept = zero; sh.nnear = zero;
         }
         for (uint32_t i = opaque_v((uint32_t)tid); i < CAND_REST; i += NT) sh.cand[i] = CAND_NONE;
-        load_ahead(next_col);       // (again, where the hinted selection asked for these rows: they are not kept on this way)
+        load_ahead(next_col);       // (a second time where the hinted selection asked for these rows: they are not kept on this way)
         }
         if (__builtin_expect(missing != 0, 0)) {
           if (!special) {
@@ -2233,7 +2237,8 @@ __device__ __forceinline__ void score_columns(const gd_score_args& a) {
                 const float half = (v[j][0] + v[j][1]) + (v[j][2] + v[j][3]);
                 const float sum = half + lane_xor1(half);
                 if (__builtin_expect(gd_ballot((int32_t)decided(sum, flip, scut) < 0) != 0, 0)) {
-                    // some node may exceed: the estimate decides, or, too close, the exact chain
+                    // some node may exceed: the estimate decides, or, too close, the exact chain (padding, NaNs, comes
+                    // here where higher is worse: the NaN exceeds nothing)
                     float nz = __builtin_fmaf(sum, cc, -kk);
                     if (__builtin_expect(gd_ballot(fabsf(nz - thr) <= margin) != 0, 0)) {
                         uint32_t e2;
