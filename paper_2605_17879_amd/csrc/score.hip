@@ -1400,9 +1400,9 @@ __device__ __forceinline__ void merge_lots(uint32_t (&v)[4]) {
 // where the sample says that hints would not hold -- signs, too few values, or few distinct ones (three
 // alike in the middle of two lots or more), whose buckets the hinted selection would find crowded
 // and give up after its counting pass.  (Whole degrees, 65 536 ranks x 256 x 4 385 us where an eighth of
-// a lot had to be alike, so 308, 8 000 x 1 000 x 4 249 and 205.  The MAD by the lots' own distances
-// instead of the quartiles: exponential values 10 to 15 % sooner, but 12 000 x 1 000 x 4 56.0 and 57.7,
-// and values in two heaps 5 000 x 1 000 x 2 35 and 52.)
+// a lot had to be alike, so 308, 8 000 x 1 000 x 4 249 and 205.  The MAD comes of the quartiles, see
+// mad_of_quartiles: by the lots' own distances plain columns took longer, 12 000 x 1 000 x 4 56.0 and
+// 57.7, and values in two heaps, 5 000 x 1 000 x 2 35 and 52.)
 __device__ __forceinline__ void sample_quartiles(uint32_t (&k)[4], float* q25, float* q50, float* q75) {
     uint32_t top = 0;
 #pragma unroll
